@@ -2,6 +2,7 @@
 // argument validation, handle management, plan caching, kernel dispatch.  No arithmetic of
 // the method happens on the host.
 #include <limits.h>
+#include <string.h>
 
 #include <new>
 
@@ -59,6 +60,7 @@ void free_plan(SfPlan *p)
     if (!p) return;
     if (p->segptr) (void)hipFree(p->segptr);
     if (p->recs) (void)hipFree(p->recs);
+    if (p->packed) (void)hipFree(p->packed);
     for (auto &sc : p->split)
         if (sc.buf) (void)hipFree(sc.buf);
     delete p;
@@ -98,7 +100,8 @@ fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_
 }
 
 // Returns the plan of `variant` (>= 1) for this handle, building it on `st` when absent.
-// variant == -1 stands for the direct kernel (no device data besides the canonical CSR).
+// kDirectPlan stands for the direct kernel (no device data besides the canonical CSR), kContractPlan
+// for the contraction on the matrix cores (the bank as a dense array).
 fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan **out)
 {
     std::lock_guard<std::mutex> lock(f->mu);
@@ -110,8 +113,28 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
     SfPlan *p = new (std::nothrow) SfPlan();
     if (!p) return FSCNN_ERR_ALLOC;
     p->variant = variant;
-    if (variant == -1) {
+    if (variant == kDirectPlan) {
         p->direct = true;
+        f->plans.push_back(p);
+        *out = p;
+        return FSCNN_OK;
+    }
+    if (variant == kContractPlan) {
+        int dev;
+        fscnn_status_t ds = have_device(&dev);
+        if (ds == FSCNN_OK && dev != f->device) ds = FSCNN_ERR_MISMATCH;
+        if (ds != FSCNN_OK) {
+            delete p;
+            return ds;
+        }
+        hipError_t e = hipMalloc(&p->packed, sizeof(float) * (size_t)contract_packed_elems(f->K, f->C, f->R * f->S));
+        if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);   // the plan may be used from other streams
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            free_plan(p);
+            return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
+        }
         f->plans.push_back(p);
         *out = p;
         return FSCNN_OK;
@@ -196,6 +219,39 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
                      : 0;
     *resolved = v > 0 ? v : -1;
     return FSCNN_OK;
+}
+
+// Whether an automatic call is served by the contraction on the matrix cores instead of the resolved
+// gather configuration (or the direct kernel), by its estimated time against theirs.  The gather
+// kernels take 15 to 25 us plus the stored entries' multiply-adds at 40 TFLOP/s (measured: 512 -> 512
+// at 28x28, N = 8: 140 / 236 / 500 us at 10 / 20 / 50 % stored against 255 us contracted; 64 -> 64 at
+// 28x28, N = 1: 25 / 34 / 62 against 9), the direct kernel multiplies and adds at under 1 TFLOP/s.
+// Fewer than 16 input channels leave most of a slice idle (an RGB layer at 224x224, N = 1: 23 us gathered,
+// 50 contracted).  Plain NCHW calls only.  Call with the handle's lock not held.
+bool contracts(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int resolved, ContractPick *pick)
+{
+    const double macs = (double)f->nnz * Ho * Wo * N, dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
+    const double gather = resolved < 0 ? 4e-6 + 2 * macs / 1e12 : 15e-6 + 2 * macs / 40e12;
+    if (2 * dense / 150e12 + 4e-6 > gather || (resolved > 0 && f->C < 16)) return false;
+    const int key[7] = {N, H, W, sh, sw, Ho, Wo};
+    std::lock_guard<std::mutex> lock(f->mu);
+    for (const auto &c : f->choices)
+        if (memcmp(c.key, key, sizeof key) == 0) {
+            *pick = c.pick;
+            return c.use;
+        }
+    *pick = contract_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw);
+    fscnn_filter::Choice c;
+    memcpy(c.key, key, sizeof key);
+    c.pick = *pick;
+    c.use = pick->cfg >= 0 && pick->seconds < gather;
+    if (f->choices.size() < 8) {
+        f->choices.push_back(c);
+    } else {
+        f->choices[f->next_choice] = c;
+        f->next_choice = (f->next_choice + 1) % 8;
+    }
+    return c.use;
 }
 
 // Number of stored values of a compressed activation.  A handle made without a host synchronisation
@@ -361,6 +417,9 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if ((in4 || out4 || pool) && v < 0) return FSCNN_ERR_UNSUPPORTED;
     if (v > 0 && !sf_variant_has_layout(v, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
     SfPlan *p;
+    ContractPick pick;
+    if (variant == 0 && !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, v, &pick))
+        return get_plan(f, kContractPlan, (hipStream_t)stream, &p);
     s = get_plan(f, v, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p->direct) return s;
     // the same decisions as the convolution call takes
@@ -504,6 +563,14 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (dev != f->device) return FSCNN_ERR_MISMATCH;   // the handle's buffers live on another GPU
     hipStream_t st = (hipStream_t)stream;
     SfPlan *p;
+    ContractPick pick;
+    if (variant == 0 && !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, v, &pick)) {
+        s = get_plan(f, kContractPlan, st, &p);
+        if (s != FSCNN_OK) return s;
+        FSCNN_HIP(launch_contract_dense(x_dev, p->packed, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,
+                                        Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, pick, st));
+        return FSCNN_OK;
+    }
     s = get_plan(f, v, st, &p);
     if (s != FSCNN_OK) return s;
     if (p->direct) {
@@ -904,8 +971,15 @@ fscnn_status_t fscnn_dense_filter_prepare(const float *w_dev, int K, int C, int 
     d->device = dev;
     d->K = K; d->C = C; d->R = R; d->S = S; d->Kpad = Kpad;
     d->wT = nullptr;
-    hipError_t e = hipMalloc(&d->wT, sizeof(float) * (size_t)Kpad * C * R * S);
-    if (e == hipSuccess) e = launch_dense_transpose(w_dev, K, C, R * S, Kpad, d->wT, (hipStream_t)stream);
+    const size_t words = (size_t)Kpad * C * R * S;
+    const bool pack = R == 3 && S == 3;   // what the prepared calls serve
+    const size_t packed = pack ? (size_t)Kpad * ((C + 15) / 16 * 16) * 9 : 0;
+    hipError_t e = hipMalloc(&d->wT, sizeof(float) * (words + packed) + 256);
+    d->packed = pack ? d->wT + words : nullptr;
+    d->flag = pack ? reinterpret_cast<int *>(d->packed + packed) : nullptr;
+    if (e == hipSuccess)
+        e = pack ? launch_pack_dense(w_dev, K, C, Kpad, d->packed, d->wT, d->flag, (hipStream_t)stream)
+                 : launch_dense_transpose(w_dev, K, C, R * S, Kpad, d->wT, (hipStream_t)stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         if (d->wT) (void)hipFree(d->wT);

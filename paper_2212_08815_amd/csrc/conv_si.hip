@@ -435,6 +435,17 @@ conv_si_direct_kernel(const int *__restrict__ cptr, int NCP, const uint32_t *__r
 
 }  // namespace
 
+// Whether the contraction on the matrix cores is the faster form of a 3x3 / stride-1 call: its
+// estimated time against the stored pairs' multiply-adds at the rate the gather kernel reaches.  The
+// number of stored pairs of a handle that a convolution emitted is not known here without waiting
+// for the device: half of the entries, as after a ReLU.
+static bool si_contracts(const fscnn_input *in, int K, int Ho, int Wo, double gather_rate, ContractPick *pick)
+{
+    *pick = contract_pick(in->N, in->C, K, in->H, in->W, 3, 3, Ho, Wo, 1, 1);
+    const double stored = in->nnz >= 0 ? (double)in->nnz : 0.5 * in->N * in->C * (double)in->H * in->W;
+    return pick->cfg >= 0 && in->CC == kSiCC && pick->seconds < 2.0 * 9 * stored * K / gather_rate + 20e-6;
+}
+
 bool si_tiled_supported(int K, int C, int R, int S, int sh, int sw)
 {
     (void)K; (void)C;
@@ -446,6 +457,9 @@ hipError_t launch_conv_si(const fscnn_input *in, const float *w, int K, int R, i
                           hipStream_t st)
 {
     const int NKT = (K + 63) / 64;
+    ContractPick pick;
+    if (si_tiled_supported(K, in->C, R, S, sh, sw) && si_contracts(in, K, Ho, Wo, 7.5e12, &pick))
+        return launch_contract_lists(in, w, nullptr, K, Ho, Wo, ph, pw, bias, relu, y, pick, st);
     if (si_tiled_supported(K, in->C, R, S, sh, sw) && in->CC == kSiCC) {
         using G = SiCfg<4, 4, 4>;
         const int tiles_x = (Wo + G::TPW * G::WAVES - 1) / (G::TPW * G::WAVES);
@@ -505,6 +519,9 @@ hipError_t launch_conv_si_prepared(const fscnn_input *in, const fscnn_dense *d, 
         // automatic: 16-byte weight vectors and 16-wave groups once there are enough patches to
         // fill the chip with them (measured on 28x28, C = K = 512: N = 32 yes, N = 8 no)
         const long long patches = (long long)in->N * ((Ho + 3) / 4) * ((Wo + 3) / 4) * (d->Kpad / 256);
+        ContractPick pick;
+        if (si_contracts(in, d->K, Ho, Wo, patches >= 2048 ? 32e12 : 15e12, &pick))
+            return launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, pick, st);
         variant = patches >= 2048 ? 4 : 1;
     }
     switch (variant) {

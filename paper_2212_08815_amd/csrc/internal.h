@@ -75,6 +75,16 @@ struct SfPlan {
         size_t bytes;
     };
     std::vector<SplitScratch> split;
+    // The plan of the contraction on the matrix cores (variant kContractPlan): the bank as a dense
+    // packed array (contract_packed_index), zeros where nothing is stored.
+    float *packed = nullptr;
+};
+constexpr int kDirectPlan = -1, kContractPlan = -2;
+
+// How a call of the contraction on the matrix cores would be launched (cfg < 0: it is not served) and an estimate of its time.  Host only.
+struct ContractPick {
+    int cfg = -1, npan = 1, lds = 0, SW = 0, pitch = 0, PL = 0, buf = 0;
+    double seconds = 0;
 };
 
 struct SiGeom {
@@ -99,6 +109,15 @@ struct fscnn_filter {
     float *val;     // device [nnz]
     std::mutex mu;
     std::vector<fscnn::SfPlan *> plans;
+    // whether calls of a geometry are served by the contraction, and how (see contracts() in api.hip):
+    // the last few geometries asked for
+    struct Choice {
+        int key[7];
+        bool use;
+        fscnn::ContractPick pick;
+    };
+    std::vector<Choice> choices;
+    size_t next_choice = 0;
 };
 
 struct fscnn_input {
@@ -131,7 +150,9 @@ struct fscnn_dense {
     uint64_t magic;
     int device;
     int K, C, R, S, Kpad;
-    float *wT;       // device [C*R*S*Kpad]
+    float *wT;       // device [C*R*S*Kpad]; the arrays below follow it in the same allocation
+    float *packed;   // 3x3: the bank in the order of the contraction's A operands; else NULL
+    int *flag;       // 3x3: non-zero if the bank holds an Inf or NaN
 };
 
 namespace fscnn {
@@ -189,6 +210,31 @@ hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const f
                                  const float *x, int N, int C, int H, int W, int K, int R, int S,
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,
                                  int relu, float *y, hipStream_t st);
+
+// ---- contract.hip: convolution as a dense contraction on the matrix cores
+ContractPick contract_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw);
+// Packed banks: position of w[k][c][tap], and the number of floats (rows padded to 64 by zeros)
+__host__ __device__ inline long long contract_packed_index(int k, int c, int rs, int RS, int nslice)
+{
+    return (((long long)(k >> 4) * nslice + (c >> 4)) * RS + rs) * 256 + ((c >> 2) & 3) * 64 + (k & 15) * 4 + (c & 3);
+}
+inline long long contract_packed_elems(int K, int C, int RS)
+{
+    return (long long)((K + 63) / 64 * 4) * ((C + 15) / 16) * RS * 256;
+}
+hipError_t launch_pack_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS,
+                            float *packed, hipStream_t st);
+// both copies of a dense K x C x 3 x 3 bank (Kpad a multiple of 64) and its non-finite flag (16 bytes are cleared)
+hipError_t launch_pack_dense(const float *w, int K, int C, int Kpad, float *packed, float *wT, int *flag, hipStream_t st);
+hipError_t launch_contract_dense(const float *x, const float *packed, const int *rowptr, const uint32_t *idx,
+                                 const float *val, int N, int C, int H, int W, int K, int R, int S, int Ho, int Wo,
+                                 int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
+                                 const ContractPick &p, hipStream_t st);
+// compressed activation, 3x3 at stride 1; with wflag: w is packed and wflag its non-finite flag,
+// without: w is K x C x 3 x 3
+hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,
+                                 int Wo, int ph, int pw, const float *bias, int relu, float *y,
+                                 const ContractPick &p, hipStream_t st);
 
 // ---- transpose.hip
 long long reorder_workspace_bytes(long long n_buckets, long long nnz);  // -1: too large
