@@ -1,4 +1,5 @@
 """Builds libfscnn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree, and beside it
+_fscnn_call.so, the native half of the binding (a CPython module, host code only), and
 libfscnn_bench_probe.so, the measurement helper that only bench.py loads.
 
     python -m paper_2212_08815_amd.build [--force] [--sanitize-host]
@@ -14,6 +15,7 @@ import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -23,6 +25,9 @@ LIB = os.path.join(HERE, "libfscnn.so")
 SOURCES = ["api.hip", "compress.hip", "conv_sf.hip", "conv_si.hip", "contract.hip", "transpose.hip"]
 PROBE_LIB = os.path.join(HERE, "libfscnn_bench_probe.so")
 PROBE_SRC = os.path.join(CSRC, "bench_probe.hip")
+CALL_LIB = os.path.join(HERE, "_fscnn_call.so")
+CALL_SRC = os.path.join(CSRC, "pycall.c")
+CC = os.environ.get("CC", "gcc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          # packed-fp32 forms are switched off for every device function of the library
@@ -94,6 +99,12 @@ def build(force=False, extra_flags=(), verbose=True):
         tmp = LIB + ".tmp%d" % os.getpid()
         subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
         os.replace(tmp, LIB)
+    if force or not _newer(CALL_LIB, [CALL_SRC] + headers):
+        tmp = CALL_LIB + ".tmp%d" % os.getpid()
+        subprocess.check_call([CC, "-O2", "-std=c11", "-D_GNU_SOURCE", "-Wall", "-Wno-unused-parameter", "-shared", "-fPIC",
+                               "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+                               "-o", tmp, CALL_SRC])
+        os.replace(tmp, CALL_LIB)
     if force or not _newer(PROBE_LIB, [PROBE_SRC, os.path.abspath(__file__)]):
         tmp = PROBE_LIB + ".tmp%d" % os.getpid()
         r = subprocess.run([HIPCC] + FLAGS + ["-shared", "-o", tmp, PROBE_SRC], capture_output=True, text=True)

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libfscnn.so (C ABI in include/fscnn.h).
+"""Thin binding of libfscnn.so (C ABI in include/fscnn.h): the calls of a program's inner loop
+through a native module (csrc/pycall.c), the rest through ctypes.
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  torch is used for device memory (`data_ptr()`) and the current
@@ -71,6 +72,23 @@ def lib():
     return _lib
 
 
+_nat = None
+
+
+def _native():
+    """The native half of the binding, bound to the loaded library; raises if it has not been built."""
+    global _nat
+    if _nat is None:
+        L = lib()
+        try:
+            from . import _fscnn_call as m
+        except ImportError as e:
+            raise RuntimeError("_fscnn_call.so is missing: run `python -m paper_2212_08815_amd.build`") from e
+        m.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
+        _nat = m
+    return _nat
+
+
 def _check(status, what):
     if status != OK:
         raise FscnnError(status, what)
@@ -80,8 +98,19 @@ def _ptr(t):
     return ctypes.c_void_p(0 if t is None else t.data_ptr())
 
 
+def _addr(t):
+    """Address of a tensor (None: NULL)."""
+    return None if t is None else t.data_ptr()
+
+
+def _raw_stream():
+    """Handle of torch's current stream on the current device (torch.cuda.current_stream() without the
+    Stream object around it: 2.7 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _dev_f32(t, name):
@@ -97,6 +126,11 @@ def _i(v):
 
 
 def conv2d_out_shape(H, W, R, S, stride=(1, 1), pad=(0, 0)):
+    # valid arguments here (the same arithmetic), anything else through the library's checks
+    if H > 0 and W > 0 and R > 0 and S > 0 and stride[0] > 0 and stride[1] > 0 and pad[0] >= 0 and pad[1] >= 0:
+        dh, dw = H + 2 * pad[0] - R, W + 2 * pad[1] - S
+        if 0 <= dh < 1 << 30 and 0 <= dw < 1 << 30:
+            return dh // stride[0] + 1, dw // stride[1] + 1
     ho, wo = ctypes.c_int(), ctypes.c_int()
     _check(lib().fscnn_conv2d_out_shape(_i(H), _i(W), _i(R), _i(S), _i(stride[0]), _i(stride[1]),
                                         _i(pad[0]), _i(pad[1]), ctypes.byref(ho), ctypes.byref(wo)),
@@ -154,6 +188,10 @@ class SparseFilter:
             raise RuntimeError("filter handle already destroyed")
         return self._h
 
+    @property
+    def address(self):
+        return self.handle.value
+
 
 def filter_compress(w):
     """fscnn_filter_compress: dense K x C x R x S float32 CUDA tensor -> SparseFilter."""
@@ -161,12 +199,9 @@ def filter_compress(w):
     if w.dim() != 4:
         raise TypeError("w must be K x C x R x S")
     K, C, R, S = w.shape
-    h = ctypes.c_void_p()
-    _check(lib().fscnn_filter_compress(_ptr(w), _i(K), _i(C), _i(R), _i(S), _stream(), ctypes.byref(h)),
-           "fscnn_filter_compress")
-    nnz = ctypes.c_longlong()
-    _check(lib().fscnn_filter_info(h, None, None, None, None, ctypes.byref(nnz)), "fscnn_filter_info")
-    return SparseFilter(h, (K, C, R, S), nnz.value)
+    st, h, nnz = _native().compress(0, w.data_ptr(), K, C, R, S, _raw_stream())
+    _check(st, "fscnn_filter_compress")
+    return SparseFilter(ctypes.c_void_p(h), (K, C, R, S), nnz)
 
 
 def filter_export(f):
@@ -248,7 +283,7 @@ def conv2d_sparse_filter(f, x, stride=(1, 1), pad=(0, 0), bias=None, relu=False,
         Ho, Wo = Ho // 2, Wo // 2
     oshape = (N, K, Ho, Wo) if y_layout == NCHW else n4_shape(N, K, Ho, Wo)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=x.device)
+        out = x.new_empty(oshape)
     else:
         _dev_f32(out, "out")
         if tuple(out.shape) != oshape:
@@ -258,16 +293,14 @@ def conv2d_sparse_filter(f, x, stride=(1, 1), pad=(0, 0), bias=None, relu=False,
     if leaky is not None:
         if pool or relu:
             raise TypeError("leaky excludes relu and pool")
-        _check(lib().fscnn_conv2d_sparse_filter_leaky(
-            f.handle, _ptr(x), _i(N), _i(C), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
-            _ptr(bias), ctypes.c_float(float(leaky)), _ptr(out), _i(x_layout), _i(y_layout), _i(variant),
-            _stream()), "fscnn_conv2d_sparse_filter_leaky")
-        return out
-    fn = lib().fscnn_conv2d_sparse_filter_pool2x2 if pool else lib().fscnn_conv2d_sparse_filter_ex
-    _check(fn(f.handle, _ptr(x), _i(N), _i(C), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]),
-              _i(pad[1]), _ptr(bias), _i(bool(relu)), _ptr(out), _i(x_layout), _i(y_layout), _i(variant),
-              _stream()),
-           "fscnn_conv2d_sparse_filter_pool2x2" if pool else "fscnn_conv2d_sparse_filter_ex")
+        kind, act = 2, leaky
+    else:
+        kind, act = (1 if pool else 0), (1 if relu else 0)
+    st = _native().conv(kind, f.address, x.data_ptr(), N, C, H, W, stride[0], stride[1], pad[0], pad[1], _addr(bias), act,
+                        out.data_ptr(), x_layout, y_layout, variant, _raw_stream())
+    if st != OK:
+        raise FscnnError(st, ("fscnn_conv2d_sparse_filter_ex", "fscnn_conv2d_sparse_filter_pool2x2",
+                              "fscnn_conv2d_sparse_filter_leaky")[kind])
     return out
 
 
@@ -317,6 +350,10 @@ class SparseInput:
             raise RuntimeError("input handle already destroyed")
         return self._h
 
+    @property
+    def address(self):
+        return self.handle.value
+
 
 def input_compress(x):
     """fscnn_input_compress: dense N x C x H x W float32 CUDA tensor -> SparseInput."""
@@ -324,12 +361,9 @@ def input_compress(x):
     if x.dim() != 4:
         raise TypeError("x must be N x C x H x W")
     N, C, H, W = x.shape
-    h = ctypes.c_void_p()
-    _check(lib().fscnn_input_compress(_ptr(x), _i(N), _i(C), _i(H), _i(W), _stream(), ctypes.byref(h)),
-           "fscnn_input_compress")
-    nnz = ctypes.c_longlong()
-    _check(lib().fscnn_input_info(h, None, None, None, None, ctypes.byref(nnz)), "fscnn_input_info")
-    return SparseInput(h, (N, C, H, W), nnz.value)
+    st, h, nnz = _native().compress(1, x.data_ptr(), N, C, H, W, _raw_stream())
+    _check(st, "fscnn_input_compress")
+    return SparseInput(ctypes.c_void_p(h), (N, C, H, W), nnz)
 
 
 def conv2d_sparse_filter_emit(f, x, stride=(1, 1), pad=(0, 0), bias=None, relu=False, dense_out=None,
@@ -351,19 +385,14 @@ def conv2d_sparse_filter_emit(f, x, stride=(1, 1), pad=(0, 0), bias=None, relu=F
             raise TypeError("dense_out has the wrong shape")
     if bias is not None and bias.numel() != K:
         raise TypeError("bias must have K entries")
+    st, h = _native().emit(f.address, x.data_ptr(), N, C, H, W, stride[0], stride[1], pad[0], pad[1], _addr(bias),
+                           1 if relu else 0, _addr(dense_out), _raw_stream(), None if into is None else into.address)
     if into is not None:
-        _check(lib().fscnn_conv2d_sparse_filter_emit_into(
-            f.handle, _ptr(x), _i(N), _i(C), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
-            _ptr(bias), _i(bool(relu)), _ptr(dense_out), _stream(), into.handle),
-            "fscnn_conv2d_sparse_filter_emit_into")
+        _check(st, "fscnn_conv2d_sparse_filter_emit_into")
         into._nnz = None
         return into
-    h = ctypes.c_void_p()
-    _check(lib().fscnn_conv2d_sparse_filter_emit(
-        f.handle, _ptr(x), _i(N), _i(C), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
-        _ptr(bias), _i(bool(relu)), _ptr(dense_out), _stream(), ctypes.byref(h)),
-        "fscnn_conv2d_sparse_filter_emit")
-    return SparseInput(h, (N, K, Ho, Wo))
+    _check(st, "fscnn_conv2d_sparse_filter_emit")
+    return SparseInput(ctypes.c_void_p(h), (N, K, Ho, Wo))
 
 
 def input_export(s):
@@ -392,9 +421,8 @@ def conv2d_sparse_input(s, w, stride=(1, 1), pad=(0, 0), bias=None, relu=False, 
         raise TypeError("out has the wrong shape")
     if bias is not None and bias.numel() != K:
         raise TypeError("bias must have K entries")
-    _check(lib().fscnn_conv2d_sparse_input(s.handle, _ptr(w), _i(K), _i(R), _i(S), _i(stride[0]),
-                                           _i(stride[1]), _i(pad[0]), _i(pad[1]), _ptr(bias),
-                                           _i(bool(relu)), _ptr(_dev_f32(out, "out")), _stream()),
+    _check(_native().conv_si(s.address, w.data_ptr(), K, R, S, stride[0], stride[1], pad[0], pad[1], _addr(bias),
+                             1 if relu else 0, _dev_f32(out, "out").data_ptr(), _raw_stream()),
            "fscnn_conv2d_sparse_input")
     return out
 
@@ -423,6 +451,10 @@ class DenseFilter:
             raise RuntimeError("dense filter handle already destroyed")
         return self._h
 
+    @property
+    def address(self):
+        return self.handle.value
+
 
 def dense_filter_prepare(w):
     """fscnn_dense_filter_prepare: dense K x C x R x S CUDA tensor -> DenseFilter."""
@@ -448,9 +480,8 @@ def conv2d_sparse_input_prepared(s, d, stride=(1, 1), pad=(0, 0), bias=None, rel
     bias = _dev_f32(bias, "bias")
     if out is None:
         out = torch.empty((N, K, Ho, Wo), dtype=torch.float32, device="cuda")
-    _check(lib().fscnn_conv2d_sparse_input_prepared(s.handle, d.handle, _i(stride[0]), _i(stride[1]), _i(pad[0]),
-                                                    _i(pad[1]), _ptr(bias), _i(1 if relu else 0), _ptr(out),
-                                                    _i(variant), _stream()), "fscnn_conv2d_sparse_input_prepared")
+    _check(_native().conv_sip(s.address, d.address, stride[0], stride[1], pad[0], pad[1], _addr(bias), 1 if relu else 0,
+                              out.data_ptr(), variant, _raw_stream()), "fscnn_conv2d_sparse_input_prepared")
     return out
 
 
@@ -488,9 +519,9 @@ def _transpose(entry, rowptr, idx, val, dims, new_rows, workspace):
     tptr = torch.empty(new_rows + 1, dtype=torch.int32, device=rowptr.device)
     tidx = torch.empty(nnz, dtype=torch.int32, device=rowptr.device)
     tval = torch.empty(nnz, dtype=torch.float32, device=rowptr.device)
-    _check(getattr(lib(), entry)(_ptr(rowptr), _ptr(idx), _ptr(val), *[_i(d) for d in dims],
-                                 ctypes.c_longlong(nnz), _ptr(tptr), _ptr(tidx), _ptr(tval), _ptr(workspace),
-                                 ctypes.c_longlong(workspace.numel() * workspace.element_size()), _stream()), entry)
+    _check(_native().transpose(rowptr.data_ptr(), idx.data_ptr(), val.data_ptr(), dims, nnz, tptr.data_ptr(),
+                               tidx.data_ptr(), tval.data_ptr(), workspace.data_ptr(),
+                               workspace.numel() * workspace.element_size(), _raw_stream()), entry)
     return tptr, tidx, tval
 
 
