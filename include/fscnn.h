@@ -145,8 +145,10 @@ const char *fscnn_sf_variant_name(int variant);
 /* Which kernel configuration the automatic choice (variant 0) takes for this filter and
  * geometry: *variant_out receives its id (1..count), or -1 when the untiled direct kernel
  * serves the geometry.  `n4` is nonzero if the input or the output tensor is in the N4
- * layout, `pool` if the merged 2x2 max-pool epilogue is asked for.  Host-only: launches
- * nothing and needs no device. */
+ * layout, `pool` if the merged 2x2 max-pool epilogue is asked for.  (A plain NCHW call whose bank
+ * stores a large share of its entries, or of a geometry without a configuration, may be served by
+ * a dense contraction on the matrix cores instead, which is no configuration of this table.)
+ * Host-only: launches nothing and needs no device. */
 fscnn_status_t fscnn_sf_variant_choice(const fscnn_filter_t *f, int N, int H, int W,
                                        int stride_h, int stride_w, int n4, int pool,
                                        int *variant_out);
@@ -262,8 +264,8 @@ fscnn_status_t fscnn_input_destroy(fscnn_input_t *in);
  * N x K x Ho x Wo result is left there as well (caller-owned, must not alias x); with
  * y_dev NULL the dense result lives inside the handle's allocation.  The non-zero results are
  * counted in the convolution's own epilogue (per pixel and step of 8 output channels) where
- * the launch allows it -- small problems that run in the channel-split mode, and geometries
- * served by the direct kernel, count in a pass over the dense result instead -- then one scan and
+ * the launch allows it -- geometries served by the direct kernel or by the contraction on the
+ * matrix cores count in a pass over the dense result instead -- then one scan and
  * one pass that writes the pairs.  The call makes ONE device allocation, sized for the worst
  * case (every result non-zero: 8 bytes per result), and does not wait for the device: it is
  * asynchronous on `stream`, x_dev (and y_dev) must stay valid until the work queued on

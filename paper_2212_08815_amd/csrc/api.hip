@@ -55,6 +55,9 @@ bool live(const fscnn_filter_t *f) { return f && f->magic == kFilterMagic; }
 bool live(const fscnn_input_t *i) { return i && i->magic == kInputMagic; }
 bool live(const fscnn_dense_t *d) { return d && d->magic == kDenseMagic; }
 
+// Share of a bank's entries that are stored (1 exactly for a bank without zeros).
+double density(const fscnn_filter_t *f) { return (double)f->nnz / ((double)f->K * f->C * f->R * f->S); }
+
 void free_plan(SfPlan *p)
 {
     if (!p) return;
@@ -73,28 +76,29 @@ void free_plan(SfPlan *p)
 fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_t bytes, float **out)
 {
     std::lock_guard<std::mutex> lock(f->mu);
-    for (auto &sc : p->split)
-        if (sc.stream == st) {
-            if (sc.bytes < bytes) {
-                float *nb = nullptr;
-                if (hipMalloc(&nb, bytes) != hipSuccess) {
-                    (void)hipGetLastError();
-                    return FSCNN_ERR_ALLOC;
-                }
-                (void)hipStreamSynchronize(st);
-                (void)hipFree(sc.buf);
-                sc.buf = nb;
-                sc.bytes = bytes;
-            }
-            *out = sc.buf;
-            return FSCNN_OK;
-        }
+    SfPlan::SplitScratch *sc = nullptr;
+    for (auto &q : p->split)
+        if (q.stream == st) sc = &q;
+    if (sc && sc->bytes >= bytes) {
+        *out = sc->buf;
+        return FSCNN_OK;
+    }
     float *nb = nullptr;
-    if (hipMalloc(&nb, bytes) != hipSuccess) {
+    hipError_t e = hipMalloc(&nb, bytes);
+    if (e == hipSuccess) e = launch_split_clear(nb, st);
+    if (e != hipSuccess) {
         (void)hipGetLastError();
+        if (nb) (void)hipFree(nb);
         return FSCNN_ERR_ALLOC;
     }
-    p->split.push_back({st, nb, bytes});
+    if (sc) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(sc->buf);
+        sc->buf = nb;
+        sc->bytes = bytes;
+    } else {
+        p->split.push_back({st, nb, bytes});
+    }
     *out = nb;
     return FSCNN_OK;
 }
@@ -205,7 +209,6 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
     }
     // N4 tensors need four images per lane whatever the batch size; the choice goes by the
     // output's extent (about the input's divided by the stride)
-    const bool no_zeros = f->nnz == (long long)f->K * f->C * f->R * f->S;
     // one or two images through NCHW tensors: the four-image forms, their image slots filled with
     // bands of the image (sf_choose_bands), so the choice sees four slots of a quarter (half) the height
     int slots = n4 && N < 4 ? 4 : N, rows = (H + sh - 1) / sh;
@@ -215,23 +218,26 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
         slots = 4;
     }
     int v = tiled_ok ? sf_choose_variant(slots, f->C, f->K, rows, (W + sw - 1) / sw, f->R, f->S, sh, pool, n4,
-                                         no_zeros, banded)
+                                         density(f), banded)
                      : 0;
     *resolved = v > 0 ? v : -1;
     return FSCNN_OK;
 }
 
 // Whether an automatic call is served by the contraction on the matrix cores instead of the resolved
-// gather configuration (or the direct kernel), by its estimated time against theirs.  The gather
-// kernels take 15 to 25 us plus the stored entries' multiply-adds at 40 TFLOP/s (measured: 512 -> 512
-// at 28x28, N = 8: 140 / 236 / 500 us at 10 / 20 / 50 % stored against 255 us contracted; 64 -> 64 at
-// 28x28, N = 1: 25 / 34 / 62 against 9), the direct kernel multiplies and adds at under 1 TFLOP/s.
+// gather configuration (or the direct kernel), by its estimated time against theirs.  The small gather
+// configurations have a model of their own, the others take 15 to 25 us plus the stored entries'
+// multiply-adds at 40 TFLOP/s (measured: 512 -> 512 at 28x28, N = 8: 140 / 236 / 500 us at 10 / 20 /
+// 50 % stored against 255 us contracted), the direct kernel multiplies and adds at under 1 TFLOP/s.
 // Fewer than 16 input channels leave most of a slice idle (an RGB layer at 224x224, N = 1: 23 us gathered,
 // 50 contracted).  Plain NCHW calls only.  Call with the handle's lock not held.
 bool contracts(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int resolved, ContractPick *pick)
 {
     const double macs = (double)f->nnz * Ho * Wo * N, dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
-    const double gather = resolved < 0 ? 4e-6 + 2 * macs / 1e12 : 15e-6 + 2 * macs / 40e12;
+    int band_shift, band_h;
+    sf_choose_bands(resolved, N, Ho, false, false, &band_shift, &band_h);
+    const double small = sf_small_seconds(resolved, N << band_shift, f->C, f->K, band_h, Wo, density(f));
+    const double gather = resolved < 0 ? 4e-6 + 2 * macs / 1e12 : small > 0 ? small : 15e-6 + 2 * macs / 40e12;
     if (2 * dense / 150e12 + 4e-6 > gather || (resolved > 0 && f->C < 16)) return false;
     const int key[7] = {N, H, W, sh, sw, Ho, Wo};
     std::lock_guard<std::mutex> lock(f->mu);
@@ -244,7 +250,7 @@ bool contracts(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, i
     fscnn_filter::Choice c;
     memcpy(c.key, key, sizeof key);
     c.pick = *pick;
-    c.use = pick->cfg >= 0 && pick->seconds < gather;
+    c.use = pick->cfg >= 0 && pick->seconds < (resolved < 0 ? gather : 0.85 * gather);   // (the models are not better than that)
     if (f->choices.size() < 8) {
         f->choices.push_back(c);
     } else {
@@ -425,11 +431,10 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     // the same decisions as the convolution call takes
     int band_shift, band_h;
     sf_choose_bands(v, N, Ho, in4 || out4, pool != 0, &band_shift, &band_h);
-    const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->K, band_h, Wo, p->NCH) : 1;
+    const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->C, f->K, band_h, Wo, p->NCH, density(f)) : 1;
     if (csplit > 1) {
         float *parts;
-        s = split_scratch(f, p, (hipStream_t)stream,
-                          sizeof(float) * (size_t)csplit * (size_t)sf_split_elems(N, f->K, Ho, Wo, out4), &parts);
+        s = split_scratch(f, p, (hipStream_t)stream, sf_split_bytes(p->g, csplit, N << band_shift, f->K, band_h, Wo), &parts);
     }
     return s;
 }
@@ -580,14 +585,13 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
         // automatic choice only: an explicitly selected configuration runs as it is
         int band_shift, band_h;
         sf_choose_bands(v, N, Ho, in4 || out4, pool != 0, &band_shift, &band_h);
-        const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->K, band_h, Wo, p->NCH) : 1;
+        const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->C, f->K, band_h, Wo, p->NCH, density(f)) : 1;
         float *parts = nullptr;
         if (csplit > 1) {
-            s = split_scratch(f, p, st, sizeof(float) * (size_t)csplit * (size_t)sf_split_elems(N, f->K, Ho, Wo, out4),
-                              &parts);
+            s = split_scratch(f, p, st, sf_split_bytes(p->g, csplit, N << band_shift, f->K, band_h, Wo), &parts);
             if (s != FSCNN_OK) return s;
         }
-        int *cnt = (emit_cnt && csplit == 1 && !out4 && !pool) ? emit_cnt : nullptr;
+        int *cnt = (emit_cnt && !out4 && !pool) ? emit_cnt : nullptr;
         FSCNN_HIP(launch_conv_sf_tiled(*p, x_dev, N, C, H, W, f->K, Ho, Wo, ph, pw, bias_dev, relu,
                                        y_dev, in4, out4, pool, csplit, parts, cnt, band_shift, band_h, st));
         if (counted) *counted = cnt != nullptr;

@@ -35,7 +35,7 @@ namespace fscnn {
 namespace {
 
 template <int BV_, int LW_, int LHR_, int NV_, int SLOTS_, int WAVES_, int CC_, int U_, int NB_, int R_, int S_,
-          bool IN4_ = false, bool OUT4_ = false, bool POOL_ = false, int STRIDE_ = 1>
+          bool IN4_ = false, bool OUT4_ = false, bool POOL_ = false, int STRIDE_ = 1, bool REGST_ = false>
 struct Cfg {
     static constexpr int BV = BV_, LW = LW_, LHR = LHR_, NV = NV_, SLOTS = SLOTS_, WAVES = WAVES_;
     static constexpr int CC = CC_, U = U_, NB = NB_, R = R_, S = S_;
@@ -71,6 +71,9 @@ struct Cfg {
     static_assert(U != 0 || BV == 4, "the pipelined loop is written for four images per lane");
     static constexpr int IMGS = BV * IG;         // images per work-group
     static constexpr int P = NV * BV;            // accumulators per lane and channel
+    // the channel split is built for configurations with few accumulators, which are the ones small
+    // problems use (where there are many its code costs the others registers)
+    static constexpr bool SPLIT = P * SLOTS <= 32;
     static constexpr int TH = LHR * NV, TW = LW; // output tile
     static constexpr int IN_ROWS = TH + (R - 1) / STRIDE;   // rows of one plane
     // Bank conflicts of the 16-byte LDS reads, measured on gfx950 with per-lane offsets: a wave
@@ -100,6 +103,12 @@ struct Cfg {
     static constexpr int pick_ig_bytes() { return NI * LINE_BYTES; }
     static constexpr int IG_BYTES = pick_ig_bytes();
     static constexpr int BUF_BYTES = IG * IG_BYTES;
+    // REGST: NCHW input goes through registers (see stage_load in the kernel): a wave takes whole
+    // channels of the chunk, ST_IT rounds of 64 positions each
+    static constexpr bool REGST = REGST_;
+    static_assert(!REGST || (!IN4 && BV == 4 && IG == 1 && PL == 1 && U != 0 && U != 5 && NB == 2 && CC % WAVES == 0),
+                  "staging through registers: four image slots, NCHW, stride 1, two buffers");
+    static constexpr int ST_IT = (IN_ROWS * PITCH + 63) / 64, ST_CW = (CC + WAVES - 1) / WAVES;
     static constexpr int LDS_BYTES = NB * BUF_BYTES;
     static constexpr int D = NB - 1;                       // chunks whose loads run ahead
     static_assert(NB >= 2, "at least the chunk being read and the one being loaded");
@@ -118,7 +127,7 @@ struct Cfg {
     // registers of addressing (512 vector registers per SIMD lane, 4 SIMDs per CU).
     static constexpr int pick_wpe()
     {
-        const int need = P * SLOTS + (U == 0 || U == 5 ? 2 : U) * P + 24;
+        const int need = P * SLOTS + (U == 0 || U == 5 ? 2 : U) * P + 24 + (REGST ? ST_IT * (4 * ST_CW + 1) : 0);
         for (int g = 160 * 1024 / LDS_BYTES; g > 1; --g) {
             const int w = (g * WAVES + 3) / 4;
             if (w <= 8 && 512 / w >= need) return w;
@@ -183,7 +192,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
                      const float *__restrict__ bias, const Rec *__restrict__ recs,
                      const int *__restrict__ segptr, int N, int C, int H, int W, int K, int Ho,
                      int Wo, int ph, int pw, int relu, int NCH, int NG, int tiles_x,
-                     int tiles_per_img, int nblk, int csplit, long long part_stride,
+                     int tiles_per_img, int nblk, int csplit, float *__restrict__ parts, int *__restrict__ arrived,
                      int *__restrict__ emit_cnt, unsigned long long recs_addr, int band_shift,
                      int band_h)
 {
@@ -191,16 +200,15 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     extern __shared__ __align__(256) char ldsb[];
 
     // csplit > 1 (small problems): the input-channel chunks are divided among csplit
-    // work-groups per (tile, channel group); part cs stores its partial sums (no bias, no
-    // activation) into its own copy of the output, y + cs * part_stride, and a separate pass adds
-    // the copies up in the order of the parts: one writer per element, the same bits on every run
+    // work-groups per (tile, channel group); every part leaves its accumulators in its own slot of
+    // `parts`, and the one that arrives last adds the slots up in the order of the parts and goes on
+    // to the epilogue: one writer per output, the same bits on every run
     const int lid0 = xcd_remap(blockIdx.x, nblk);
     const int cs = lid0 % csplit;
     const int lid = lid0 / csplit;
     const int cper = (NCH + csplit - 1) / csplit;
     const int ci0 = cs * cper < NCH ? cs * cper : NCH;   // a part past the last chunk stores zeros
     const int ci1 = ci0 + cper < NCH ? ci0 + cper : NCH;
-    if (csplit > 1) y += (long long)cs * part_stride;
     const int kg = lid % NG;
     const int t = (lid / NG) % tiles_per_img;
     const int n0 = (lid / (NG * tiles_per_img)) * G::IMGS;
@@ -235,7 +243,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     // of a work-group's life on a small problem).
     const int HW = H * W;
     int goff[G::NIW];
-    {
+    if constexpr (!G::REGST) {
         constexpr int STEP = G::WAVES * 64 / (G::IN4 ? 1 : G::BV);
         constexpr int RP = G::IN_ROWS * G::PITCH;
         constexpr int S_CP = STEP / RP, S_ROW = (STEP % RP) / G::PITCH, S_COL = (STEP % RP) % G::PITCH;
@@ -310,6 +318,58 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         }
     };
 
+    // ---- staging through registers (NCHW input): lane l of a load takes position l of a row, so that a
+    // load touches whole lines (a direct-to-LDS load must deposit the four image slots of a pixel in
+    // adjacent dwords: four lines per four lanes, and the address unit takes them one by one), and one
+    // 16-byte LDS store puts the four slots of a position side by side.
+    typedef f4v StReg[G::REGST ? G::ST_CW : 1][G::REGST ? G::ST_IT : 1];
+    uint32_t soff[G::REGST ? G::ST_IT : 1];   // byte offset of the position in slot 0's channel plane
+    if constexpr (G::REGST) {
+#pragma unroll
+        for (int it = 0; it < G::ST_IT; ++it) {
+            const int e = it * 64 + lane, row = e / G::PITCH, col = e % G::PITCH;
+            const int gx = tx0 - pw + col;
+            // rows outside the image fall outside the plane's descriptor on either side (a negative
+            // offset is a huge one); columns are checked here (2^31 stays outside whatever is added)
+            const bool ok = row < G::IN_ROWS && gx >= 0 && gx < W;
+            soff[it] = ok ? (uint32_t)((ty0 - ph + row) * W + gx) * 4u : 0x80000000u;
+        }
+    }
+    auto stage_load = [&](int ci, StReg &r) {
+#pragma unroll
+        for (int cw = 0; cw < G::ST_CW; ++cw) {
+            const int c = ci * G::CC + cw * G::WAVES + wave;
+            const bool live = c < C && cw * G::WAVES + wave < G::CC;
+#pragma unroll
+            for (int b = 0; b < G::BV; ++b) {
+                const int slot = n0 + b, img = slot >> bsh_in, band = slot & ((1 << bsh_in) - 1);
+                const bool on = live && img < N;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float *>(x) + (on ? ((long long)img * C + c) * HW : 0), 0, on ? HW * 4 : 0, 0x00020000);
+                const uint32_t boff = (uint32_t)(band * band_h * W) * 4u;
+#pragma unroll
+                for (int it = 0; it < G::ST_IT; ++it)
+                    r[cw][it][b] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(soff[it] + boff), 0, 0));
+            }
+        }
+    };
+    auto stage_store = [&](int buf, const StReg &r) {
+#pragma unroll
+        for (int cw = 0; cw < G::ST_CW; ++cw) {
+            const int cl = cw * G::WAVES + wave;
+            if (G::CC % G::WAVES != 0 && cl >= G::CC) break;
+#pragma unroll
+            for (int it = 0; it < G::ST_IT; ++it) {
+                const int e = it * 64 + lane;
+                if ((it + 1) * 64 <= G::IN_ROWS * G::PITCH || e < G::IN_ROWS * G::PITCH)
+                    *reinterpret_cast<f4v *>(ldsb + buf * G::BUF_BYTES + (cl * (G::IN_ROWS * G::PITCH) + e) * 16) = r[cw][it];
+            }
+        }
+    };
+
+    StReg streg;
+    if constexpr (G::REGST) stage_load(ci0, streg);   // (an empty part: channels past the last one, zeros)
+
     float acc[G::SLOTS][G::P];
 #pragma unroll
     for (int j = 0; j < G::SLOTS; ++j)
@@ -362,7 +422,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     // run only three records ahead, and a stream that was last read a whole pass of the network
     // ago comes from HBM.  One load, lane l touching the 64-byte line l of the stream (lanes past
     // its end touch nothing); the data goes to ring slot D, which nobody reads or loads before the
-    // barrier below, and being the oldest load in flight it has landed by any wait further down.
+    // barrier below, and being older than any load waited for further down it has landed by then.
     // Only where few work-groups share a stream (one per tile and image group): with thousands
     // of them it is in the L2 anyway.
     if (nblk <= 128 * NG) {
@@ -375,10 +435,15 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         lds_dma_dword(rs, lds0 + (uint32_t)(G::D * G::BUF_BYTES + wave * 256), lane * 64);
     }
     // the first D chunks start loading; chunk 0 must have landed before anyone reads it
+    if constexpr (!G::REGST) {
 #pragma unroll
-    for (int d = 0; d < G::D; ++d)
-        if (ci0 + d < ci1) fetch(ci0 + d, d, 0, 1);
-    if (G::D <= ci1 - ci0) wait_vmcnt<G::WAITN>(); else wait_vmcnt<0>();
+        for (int d = 0; d < G::D; ++d)
+            if (ci0 + d < ci1) fetch(ci0 + d, d, 0, 1);
+        if (G::D <= ci1 - ci0) wait_vmcnt<G::WAITN>(); else wait_vmcnt<0>();
+    } else {
+        stage_store(0, streg);
+        wait_vmcnt<0>();   // (the line of records above, which the compiler does not count)
+    }
     __syncthreads();
 
     int rbuf = 0;         // ring slot of the chunk being computed
@@ -396,6 +461,8 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         const char *tile = ldsb + (lane_base + (uint32_t)(rbuf * G::BUF_BYTES));
         const uint32_t tile_lds = lds0 + lane_base + (uint32_t)(rbuf * G::BUF_BYTES);   // the same as an LDS address
         rbuf = rbuf + 1 == G::NB ? 0 : rbuf + 1;
+        if constexpr (G::REGST)
+            if (more) stage_load(ci + 1, streg);
 
         // ---- gather-FMA over this wave's records of the chunk (A5)
         if constexpr (G::U == 0) {
@@ -513,7 +580,8 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         } else
 #pragma unroll
         for (int j = 0; j < G::SLOTS; ++j) {
-            if (more) fetch(ci + G::D, wbuf, j, G::SLOTS);
+            if constexpr (!G::REGST)
+                if (more) fetch(ci + G::D, wbuf, j, G::SLOTS);
             const int end = bnd[j];
             // U records per trip.  The queue q[0..U-1] always holds the U records that start at
             // stream position i; a trip reads the taps of all U, refills the queue from where the
@@ -562,12 +630,58 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
             }
             i = end;  // boundaries never decrease, so the steps above always end exactly here
         }
+        if constexpr (G::REGST)
+            if (more) stage_store(wbuf, streg);
         wbuf = wbuf + 1 == G::NB ? 0 : wbuf + 1;
 #pragma unroll
         for (int j = 0; j < G::SLOTS; ++j) bnd[j] = nbnd[j];
         // the next chunk's lines of this wave must be in LDS before the barrier lets anyone read
-        if (ci + G::D < ci1) wait_vmcnt<G::WAITN>(); else wait_vmcnt<0>();
+        if constexpr (!G::REGST) {
+            if (ci + G::D < ci1) wait_vmcnt<G::WAITN>(); else wait_vmcnt<0>();
+        }
         __syncthreads();
+    }
+
+    if constexpr (G::SPLIT) if (csplit > 1) {
+        // The parts meet in memory that the XCDs' caches do not keep apart: agent-scope accesses go
+        // through to it.  A part's stores have reached it before its arrival is counted, so the
+        // last one to arrive (which has all other arrivals before its own) finds every slot whole.
+        constexpr int E = G::SLOTS * G::P / 2;   // pairs of accumulators per lane
+        static_assert(G::SLOTS * G::P % 2 == 0, "accumulators travel in pairs");
+        typedef unsigned long long u64;
+        auto slot = [&](int p) {
+            return reinterpret_cast<u64 *>(parts) + (((long long)lid * csplit + p) * G::WAVES + wave) * (E * 64) + lane;
+        };
+        float *af = &acc[0][0];
+        u64 *mine = slot(cs);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const u64 v = (u64)__float_as_uint(af[2 * e]) | ((u64)__float_as_uint(af[2 * e + 1]) << 32);
+            __hip_atomic_store(mine + e * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        wait_vmcnt<0>();
+        __syncthreads();
+        if (tid == 0) {
+            const int before = __hip_atomic_fetch_add(arrived + lid, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *reinterpret_cast<int *>(ldsb) = before;   // (the tile buffers are free)
+            if (before == csplit - 1) __hip_atomic_store(arrived + lid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (*reinterpret_cast<volatile int *>(ldsb) != csplit - 1) return;
+#pragma unroll
+        for (int e = 0; e < 2 * E; ++e) af[e] = 0.0f;
+        for (int p = 0; p < csplit; ++p) {
+            const u64 *src = slot(p);
+            u64 v[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] = __hip_atomic_load(src + e * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                af[2 * e] += __uint_as_float((uint32_t)v[e]);
+                af[2 * e + 1] += __uint_as_float((uint32_t)(v[e] >> 32));
+            }
+        }
+        __syncthreads();   // everyone has read the word before the epilogue may use the LDS
     }
 
     // ---- epilogue (A6): bias, ReLU, store (coalesced along x)
@@ -656,11 +770,6 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
             for (int v = 0; v < G::NV; ++v) {
                 const int oy = ty0 + lh * G::NV + v;
                 if (n < N && oy < Ho && ox < Wo) {
-                    if (csplit > 1) {  // partial sums of this channel range
-                        yk[(long long)oy * Wo + ox] =
-                            make_float4(acc[j][v * 4], acc[j][v * 4 + 1], acc[j][v * 4 + 2], acc[j][v * 4 + 3]);
-                        continue;
-                    }
                     float r[4];
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
@@ -681,10 +790,6 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
                     const int ly = ty0 + lh * G::NV + v;   // row of the band (of the image without bands)
                     const int oy = row0 + ly;
                     if (n < N && ly < band_h && oy < Ho && ox < Wo) {
-                        if (csplit > 1) {
-                            yk[(long long)oy * Wo + ox] = acc[j][v * G::BV + b];
-                            continue;
-                        }
                         float r = acc[j][v * G::BV + b] + bk;
                         r = act_apply(r, relu);
                         yk[(long long)oy * Wo + ox] = r;
@@ -704,7 +809,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     // (free by now), then one thread per (step, pixel) adds them and stores the sum.  One writer per
     // count, no atomics.
     if constexpr (!G::OUT4) {
-        if (emit_cnt != nullptr && csplit == 1) {
+        if (emit_cnt != nullptr) {
             static_assert(8 % G::SLOTS == 0 || G::SLOTS % 8 == 0, "channel steps of 8 align with the waves' slots");
             unsigned char *lc = reinterpret_cast<unsigned char *>(ldsb);   // [wave][pixel slot p][lane]
             static_assert(G::WAVES * G::P * 64 <= G::LDS_BYTES, "per-wave counts fit the tile's LDS");
@@ -785,58 +890,20 @@ conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict
     y[(((long long)n * K + k) * Ho + oy) * Wo + ox] = acc;
 }
 
-// Finishing pass of the channel-split mode: y = act(bias[k] + part 0 + part 1 + ...), the parts
-// added in their order.  Element i belongs to channel (i / (plane * inner)) % K, where inner is 1
-// for NCHW and 4 for the batch-interleaved layout.
-__global__ void __launch_bounds__(256) split_sum_kernel(const float *__restrict__ parts, int nparts,
-                                                        long long part_stride, const float *__restrict__ bias,
-                                                        int K, long long plane, int inner, int relu,
-                                                        long long n, float *__restrict__ y)
+__global__ void __launch_bounds__(256) clear_counters_kernel(int *p)
 {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float v = parts[i];
-    for (int p = 1; p < nparts; ++p) v += parts[(long long)p * part_stride + i];
-    if (bias) v += bias[(int)((i / (plane * inner)) % K)];
-    y[i] = act_apply(v, relu);
-}
-
-// The same with the merged 2x2 / stride-2 max-pool (Alg. 7): the parts hold full-size partial
-// sums, element i of the pooled result is the maximum over its window of the summed parts, then
-// bias and activation (they commute with the maximum, as in the merged epilogue of the kernel).
-__global__ void __launch_bounds__(256) split_sum_pool_kernel(const float *__restrict__ parts, int nparts,
-                                                             long long part_stride, const float *__restrict__ bias,
-                                                             int K, int Ho, int Wo, int inner, int relu,
-                                                             long long n, float *__restrict__ y)
-{
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int Hp = Ho / 2, Wp = Wo / 2;
-    const int b = (int)(i % inner);
-    const int px = (int)((i / inner) % Wp);
-    const int py = (int)((i / ((long long)inner * Wp)) % Hp);
-    const long long plane = i / ((long long)inner * Wp * Hp);
-    float m = 0.0f;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const long long src = ((plane * Ho + 2 * py + (d >> 1)) * Wo + 2 * px + (d & 1)) * inner + b;
-        float v = parts[src];
-        for (int p = 1; p < nparts; ++p) v += parts[(long long)p * part_stride + src];
-        m = d == 0 || v > m ? v : m;
-    }
-    if (bias) m += bias[(int)(plane % K)];
-    y[i] = act_apply(m, relu);
+    for (int i = threadIdx.x; i < kSplitGroups; i += 256) p[i] = 0;
 }
 
 // ---------------------------------------------------------------- variant table
 using LaunchFn = hipError_t (*)(const SfPlan &, const float *, int, int, int, int, int, int, int,
-                                int, int, const float *, int, float *, int, long long, int *, int, int,
+                                int, int, const float *, int, float *, int, float *, int *, int *, int, int,
                                 hipStream_t);
 
 template <class G>
 hipError_t launch_tiled(const SfPlan &p, const float *x, int N, int C, int H, int W, int K, int Ho,
                         int Wo, int ph, int pw, const float *bias, int relu, float *y, int csplit,
-                        long long part_stride, int *emit_cnt, int band_shift, int band_h, hipStream_t st)
+                        float *parts, int *arrived, int *emit_cnt, int band_shift, int band_h, hipStream_t st)
 {
     static_assert(G::LDS_BYTES <= 160 * 1024, "tile exceeds the 160 KB LDS of a gfx950 CU");
     if (G::LDS_BYTES > 64 * 1024) {
@@ -856,7 +923,7 @@ hipError_t launch_tiled(const SfPlan &p, const float *x, int N, int C, int H, in
     const int tiles_x = (Wo + G::TW - 1) / G::TW;
     const int tiles_y = (band_h + G::TH - 1) / G::TH;
     const int nbat = ((N << band_shift) + G::IMGS - 1) / G::IMGS;
-    if (csplit < 1 || (G::POOL && csplit != 1)) return hipErrorInvalidValue;
+    if (csplit < 1 || (csplit > 1 && (!G::SPLIT || !parts || !arrived))) return hipErrorInvalidValue;
     const long long nblk = (long long)p.NG * tiles_x * tiles_y * nbat * csplit;
     // (a dispatch counts its work-items in 32 bits)
     if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * G::NT > 0xffffffffLL) return hipErrorInvalidValue;
@@ -864,7 +931,7 @@ hipError_t launch_tiled(const SfPlan &p, const float *x, int N, int C, int H, in
     if (G::VREC && (p.nrec + kPlanSpare) * (long long)sizeof(Rec) >= 0x7ffffff0LL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(conv_sf_tiled_kernel<G>, dim3((unsigned)nblk), dim3(G::NT), G::LDS_BYTES, st,
                        x, y, bias, p.recs, p.segptr, N, C, H, W, K, Ho, Wo, ph, pw, relu, p.NCH,
-                       p.NG, tiles_x, tiles_x * tiles_y, (int)nblk, csplit, part_stride, emit_cnt,
+                       p.NG, tiles_x, tiles_x * tiles_y, (int)nblk, csplit, parts, arrived, emit_cnt,
                        (unsigned long long)(uintptr_t)p.recs, band_shift, band_h);
     return hipGetLastError();
 }
@@ -878,6 +945,7 @@ template <class G> SfGeom geom_of()
     g.STRIDE = G::STRIDE;
     g.DENSE = G::DENSE ? 1 : 0;
     g.lds_bytes = G::LDS_BYTES;
+    g.SPLIT = G::SPLIT ? 1 : 0;
     return g;
 }
 
@@ -931,6 +999,20 @@ struct Variant {
       {nullptr, nullptr}},                                                                    \
      {{&launch_tiled<FSCNN_CFGP(BV, LW, LHR, NV, SLOTS, WAVES, CC, U, NB, false, false)>, nullptr}, \
       {nullptr, nullptr}}}
+
+// NCHW tensors on both sides, staged through registers (small problems); without and with the pooled form
+#define FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, P) \
+    Cfg<4, LW, LHR, NV, SLOTS, WAVES, CC, U, 2, 3, 3, false, false, P, 1, true>
+#define FSCNN_VRN(LW, LHR, NV, SLOTS, WAVES, CC, U)                                           \
+    {FSCNN_NAME(4, LW, LHR, NV, SLOTS, WAVES, CC, U, 2) "_reg",                               \
+     geom_of<FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, false)>(),                          \
+     {{&launch_tiled<FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, false)>, nullptr}, {nullptr, nullptr}}, \
+     FSCNN_NOPOOL}
+#define FSCNN_VR(LW, LHR, NV, SLOTS, WAVES, CC, U)                                            \
+    {FSCNN_NAME(4, LW, LHR, NV, SLOTS, WAVES, CC, U, 2) "_reg",                               \
+     geom_of<FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, false)>(),                          \
+     {{&launch_tiled<FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, false)>, nullptr}, {nullptr, nullptr}}, \
+     {{&launch_tiled<FSCNN_CFGR(LW, LHR, NV, SLOTS, WAVES, CC, U, true)>, nullptr}, {nullptr, nullptr}}}
 
 // 3x3 filters at stride 2, four images per lane, all four layout combinations, no pooled form
 #define FSCNN_CFGS2(LW, LHR, NV, SLOTS, WAVES, CC, U, NB, I4, O4) \
@@ -995,6 +1077,16 @@ const Variant *variants(int *count)
         FSCNN_V4P(16, 4, 4, 2, 16, 15, 0, 2),  // 32  up to 16x16 images with many output channels: one 16x16 tile per image, pipelined
         FSCNN_V4P(16, 4, 2, 8, 8, 3, 5, 2),    // 33  banks without zeros over up to 3 input channels (an RGB first layer): taps outer, 8 channels per wave, 16x8 tiles (32x4: 4 % slower, 64x2: 20 %)
         FSCNN_V4P(16, 4, 2, 8, 4, 3, 5, 2),    // 34  the same with 32 channels per work-group (4 waves), for banks of 32, 96, ... channels
+        // small problems through NCHW tensors (choose_small)
+        FSCNN_VR(32, 2, 2, 1, 16, 16, 4),      // 35  32x4 tiles, one channel per wave
+        FSCNN_VR(32, 2, 2, 2, 16, 16, 4),      // 36  ... two
+        FSCNN_VR(32, 2, 2, 4, 16, 16, 4),      // 37  ... four
+        FSCNN_VR(16, 4, 2, 1, 16, 16, 4),      // 38  16x8 tiles, one channel per wave
+        FSCNN_VR(16, 4, 2, 2, 16, 16, 4),      // 39  ... two
+        FSCNN_VR(16, 4, 2, 4, 16, 16, 4),      // 40  ... four
+        FSCNN_VRN(16, 4, 1, 1, 16, 16, 4),      // 41  16x4 tiles, one channel per wave
+        FSCNN_VRN(16, 4, 1, 2, 16, 32, 4),      // 42  ... two, 32-channel chunks
+        FSCNN_VRN(32, 2, 1, 2, 16, 32, 4),      // 43  32x2 tiles, two channels per wave, 32-channel chunks
     };
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -1055,9 +1147,55 @@ static long long sf_blocks(const SfGeom &g, int N, int K, int Ho, int Wo)
 // 16x8 tiles with two channels per wave for 14x14, which keeps 256 groups of 16 waves in flight.  A configuration that
 // would launch too few work-groups to cover the 256 compute units, or that has no pooled form
 // when one is asked for, yields to the next one.
-int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
-                      bool no_zeros, bool banded)
+// Small problems (few work-groups, NCHW tensors): the configuration and the number of parts of the
+// channel split by a model of the launch's time in clocks, fitted to sweeps of one and two images over
+// the VGG16-shaped layers and a few ragged ones (it is 1 to 4 us low everywhere, and orders the
+// configurations within 3 % of the best).  A chunk costs its bytes through the 64 B/clk path from the
+// L2 -- with address work, LDS stores and what of that is not overlapped 1.6 times over --, a fixed part,
+// and its records: P multiply-adds each for four waves of a SIMD, a little more where a wave owns
+// several channels (a trip's last records, and chunks that are uneven between the waves).
+constexpr int kSmallFirst = 35, kSmallLast = 43;
+static double small_clocks(const SfGeom &g, int csplit, int N, int C, int K, int Ho, int Wo, double density)
 {
+    const long long groups = sf_blocks(g, N, K, Ho, Wo);
+    const int NCH = (C + g.CC - 1) / g.CC, chunks = (NCH + csplit - 1) / csplit;
+    const int P = g.NV * g.BV;
+    const double records = density * g.R * g.S * (C < g.CC ? C : g.CC) * g.SLOTS;
+    const double chunk = 1500 + 1.6 * g.lds_bytes / 2 / 64 + records * P * (22 + 4 * g.SLOTS);
+    const double parts = csplit > 1 ? 4000 + csplit * (double)g.WAVES * g.SLOTS * P * 4 : 0;
+    return 1000 + (double)((groups * csplit + 255) / 256) * (8000 + parts + chunks * chunk);   // 8000: first loads, stores
+}
+static int best_split(const SfGeom &g, int N, int C, int K, int Ho, int Wo, double density, double *clocks)
+{
+    const int NCH = (C + g.CC - 1) / g.CC;
+    int best = 1;
+    *clocks = small_clocks(g, 1, N, C, K, Ho, Wo, density);
+    for (int s = 2; s <= 8 && 2 * s <= NCH; s *= 2) {   // at least two chunks per part
+        if (sf_blocks(g, N, K, Ho, Wo) > kSplitGroups) break;
+        const double c = small_clocks(g, s, N, C, K, Ho, Wo, density);
+        if (c < *clocks) { *clocks = c; best = s; }
+    }
+    return best;
+}
+static int choose_small(int N, int C, int K, int Ho, int Wo, double density, bool pool)
+{
+    int n;
+    const Variant *t = variants(&n);
+    int best = kSmallFirst;
+    double best_clocks = 0;
+    for (int v = kSmallFirst; v <= kSmallLast; ++v) {
+        if (pool && !t[v - 1].pool[0][0]) continue;
+        double c;
+        best_split(t[v - 1].g, N, C, K, Ho, Wo, density, &c);
+        if (v == kSmallFirst || c < best_clocks) { best = v; best_clocks = c; }
+    }
+    return best;
+}
+
+int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
+                      double density, bool banded)
+{
+    const bool no_zeros = density >= 1.0;
     int n;
     const Variant *t = variants(&n);
     // a bank without zeros over at most 3 input channels (the first layer of a network fed RGB
@@ -1083,11 +1221,8 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
         return 20;
     }
     if (R != 3 || S != 3) return 0;
-    // One or two images in band mode (N counts the slots, H a band's rows): the work is small and
-    // what counts is the number of work-groups and how short each one's chain of chunks is, so the
-    // form with two channels per wave and the largest chunks, which the channel split then cuts
-    // into parts (measured on the VGG16-shaped stack at N = 1, every layer from 224x224 to 14x14)
-    if (banded && !(W > 64 && C <= 8)) return 3;
+    // One or two images in band mode (N counts the slots, H a band's rows)
+    if (banded) return choose_small(N, C, K, H, W, density, pool);
     int pref[4];
     // Fewer than four images: the one-image-per-lane forms only pay on the widest layers; from
     // 112x112 down they launch too few work-groups, and the four-image forms with idle image
@@ -1123,9 +1258,10 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
         const Variant &v = t[pref[i] - 1];
         if (pool && !v.pool[0][0]) continue;
         const long long b = sf_blocks(v.g, N, K, H, W);  // Ho, Wo ~ H, W for this purpose
-        if (b >= 192) return pref[i];
+        if (b >= 384 || (b >= 192 && (n4 || C < 16))) return pref[i];
         if (b > best_blocks) { best_blocks = b; best = pref[i]; }
     }
+    if (!n4 && C >= 16) return choose_small(N, C, K, H, W, density, pool);
     return best;
 }
 
@@ -1145,59 +1281,67 @@ void sf_choose_bands(int variant, int N, int Ho, bool n4, bool pool, int *shift,
     *band_h = h;
 }
 
-long long sf_split_elems(int N, int K, int Ho, int Wo, int out4)
+// Scratch of the channel-split mode: kSplitGroups arrival counters (always as many, so that launches of
+// different sizes can share a buffer), then every part's accumulators.
+size_t sf_split_bytes(const SfGeom &g, int csplit, int N, int K, int Ho, int Wo)
 {
-    return (out4 ? ((long long)N + 3) / 4 * 4 : (long long)N) * K * Ho * Wo;
+    return kSplitGroups * sizeof(int) +
+           (size_t)sf_blocks(g, N, K, Ho, Wo) * csplit * g.WAVES * 64 * g.SLOTS * g.NV * g.BV * sizeof(float);
+}
+hipError_t launch_split_clear(void *scratch, hipStream_t st)
+{
+    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(256), 0, st, static_cast<int *>(scratch));
+    return hipGetLastError();
 }
 
 hipError_t launch_conv_sf_tiled(const SfPlan &p, const float *x, int N, int C, int H, int W, int K,
                                 int Ho, int Wo, int ph, int pw, const float *bias, int relu,
-                                float *y, int in4, int out4, int pool, int csplit, float *parts,
+                                float *y, int in4, int out4, int pool, int csplit, void *scratch,
                                 int *emit_cnt, int band_shift, int band_h, hipStream_t st)
 {
     int n;
     const Variant *t = variants(&n);
     if (p.variant < 1 || p.variant > n) return hipErrorInvalidValue;
     const Variant &v = t[p.variant - 1];
-    // (the channel-split mode launches the form without the pool: its finishing pass pools)
-    LaunchFn fn = (pool && csplit == 1 ? v.pool : v.fn)[in4 ? 1 : 0][out4 ? 1 : 0];
-    if (!fn) return hipErrorInvalidValue;
+    LaunchFn fn = (pool ? v.pool : v.fn)[in4 ? 1 : 0][out4 ? 1 : 0];
+    if (!fn || (emit_cnt && (out4 || pool))) return hipErrorInvalidValue;
+    int *arrived = nullptr;
+    float *parts = nullptr;
     if (csplit > 1) {
-        // every part stores its partial sums into its own copy of the full-size output (parts:
-        // csplit * sf_split_elems floats of scratch), then one pass adds the copies, pools where
-        // asked to, and applies bias and activation
-        if (!parts) return hipErrorInvalidValue;
-        const long long total = sf_split_elems(N, K, Ho, Wo, out4);
-        if (emit_cnt) return hipErrorInvalidValue;   // the parts' sums are not final results
-        hipError_t e = fn(p, x, N, C, H, W, K, Ho, Wo, ph, pw, bias, relu, parts, csplit, total, nullptr,
-                          band_shift, band_h, st);
-        if (e != hipSuccess) return e;
-        if (pool) {
-            const long long pooled = sf_split_elems(N, K, Ho / 2, Wo / 2, out4);
-            hipLaunchKernelGGL(split_sum_pool_kernel, dim3((unsigned)((pooled + 255) / 256)), dim3(256), 0, st,
-                               parts, csplit, total, bias, K, Ho, Wo, out4 ? 4 : 1, relu, pooled, y);
-        } else {
-            hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, parts,
-                               csplit, total, bias, K, (long long)Ho * Wo, out4 ? 4 : 1, relu, total, y);
-        }
-        return hipGetLastError();
+        if (!scratch) return hipErrorInvalidValue;
+        if (sf_blocks(p.g, N << band_shift, K, band_h, Wo) > kSplitGroups) return hipErrorInvalidValue;
+        arrived = static_cast<int *>(scratch);
+        parts = static_cast<float *>(scratch) + kSplitGroups;
     }
-    if (emit_cnt && (out4 || pool)) return hipErrorInvalidValue;
-    return fn(p, x, N, C, H, W, K, Ho, Wo, ph, pw, bias, relu, y, 1, 0, emit_cnt, band_shift, band_h, st);
+    return fn(p, x, N, C, H, W, K, Ho, Wo, ph, pw, bias, relu, y, csplit, parts, arrived, emit_cnt, band_shift, band_h, st);
+}
+
+// Estimated time of an automatic launch of one of the small configurations, launch included; 0 for others.
+double sf_small_seconds(int variant, int N, int C, int K, int Ho, int Wo, double density)
+{
+    int n;
+    const Variant *t = variants(&n);
+    if (variant < kSmallFirst || variant > kSmallLast) return 0;
+    double c;
+    best_split(t[variant - 1].g, N, C, K, Ho, Wo, density, &c);
+    return c / 2.4e9 + 5e-6;
 }
 
 // How many ways the input channels are split for a launch: small problems (deep layers at small
 // batch) leave most of the 256 CUs idle and serialise hundreds of channels in a few groups;
-// splitting the chunk range restores parallelism at the price of one copy of the output per part
-// and a finishing pass that adds them up, which only pays while y is small (measured: 14x14 and
-// 28x28 at N <= 8 gain up to 3.7x, 56x56 and wider lose).
-int sf_choose_csplit(int variant, int N, int K, int Ho, int Wo, int NCH)
+// splitting the chunk range restores parallelism at the price of one copy of the accumulators per part
+// that the last part to arrive adds up.
+int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, int NCH, double density)
 {
     int n;
     const Variant *t = variants(&n);
     if (variant < 1 || variant > n) return 1;
+    if (variant >= kSmallFirst && variant <= kSmallLast) {
+        double c;
+        return best_split(t[variant - 1].g, N, C, K, Ho, Wo, density, &c);
+    }
     const long long b = sf_blocks(t[variant - 1].g, N, K, Ho, Wo);
-    if (b > 128 || NCH < 4) return 1;   // with more groups the extra passes cost more than they gain
+    if (b > 128 || NCH < 4 || !t[variant - 1].g.SPLIT) return 1;   // with more groups the extra passes cost more than they gain
     long long s = (256 + b - 1) / b;
     if (s > NCH / 2) s = NCH / 2;   // at least two chunks per part
     if (s > 8) s = 8;

@@ -32,6 +32,7 @@ struct SfGeom {
     int KG;                                 // output channels per work-group
     int STRIDE;                             // stride (both axes) the instance is built for
     int DENSE;                              // 1: the plan lists every tap of every chunk, SLOTS weights per tap
+    int SPLIT;                              // 1: built with the channel split
     int lds_bytes;
 };
 
@@ -189,23 +190,27 @@ const char *sf_variant_name(int variant);
 // false if the variant cannot serve RxS filters at this stride
 bool sf_variant_geom(int variant, int R, int S, int sh, int sw, SfGeom *g);
 int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
-                      bool no_zeros = false, bool banded = false);
+                      double density, bool banded = false);
 bool sf_variant_has_layout(int variant, int in4, int out4, int pool);
-// csplit > 1: `parts` is scratch of csplit * sf_split_elems(...) floats (one copy of y per part)
-long long sf_split_elems(int N, int K, int Ho, int Wo, int out4);
-// emit_cnt != nullptr (NCHW output, no pool, csplit == 1 only): the epilogue also stores, per output
+// csplit > 1: scratch of the launch (N and Ho: slots and rows per band, where the image is banded), and
+// the launch that clears its counters when it is new (a launch leaves them clear)
+size_t sf_split_bytes(const SfGeom &g, int csplit, int N, int K, int Ho, int Wo);
+constexpr int kSplitGroups = 256;   // (tile, channel group) pairs of a split launch, at most
+hipError_t launch_split_clear(void *scratch, hipStream_t st);
+// emit_cnt != nullptr (NCHW output, no pool only): the epilogue also stores, per output
 // pixel p = (n*Ho + oy)*Wo + ox and step j of 8 output channels, the number of non-zero results into
 // emit_cnt[p * ceil(K/8) + j] -- the counts the activation compressor scans
 hipError_t launch_conv_sf_tiled(const SfPlan &p, const float *x, int N, int C, int H, int W, int K,
                                 int Ho, int Wo, int ph, int pw, const float *bias, int relu,
-                                float *y, int in4, int out4, int pool, int csplit, float *parts,
+                                float *y, int in4, int out4, int pool, int csplit, void *scratch,
                                 int *emit_cnt, int band_shift, int band_h, hipStream_t st);
 // band_shift, band_h of a launch: 4 / N bands of band_h output rows per image where a four-image
 // configuration serves one or two images through NCHW tensors (then the work-groups of the launch,
 // and with them the channel split, go by N << band_shift slots of band_h rows); else 0 and Ho
 void sf_choose_bands(int variant, int N, int Ho, bool n4, bool pool, int *band_shift, int *band_h);
+double sf_small_seconds(int variant, int N, int C, int K, int Ho, int Wo, double density);
 // 1, or the number of parts the input-channel range is split into for a small problem
-int sf_choose_csplit(int variant, int N, int K, int Ho, int Wo, int NCH);
+int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, int NCH, double density);
 hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const float *val,
                                  const float *x, int N, int C, int H, int W, int K, int R, int S,
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,
