@@ -14,8 +14,22 @@
 //   4. every node of the scratch copy counts the nodes of its segment with a smaller key - its
 //      rank, since keys are unique inside a bucket - and lands at pointer[bucket] + rank.
 // The arbitrary order of step 3 never reaches the result.  Step 4 costs the sum of the squared
-// bucket sizes (a bucket is a column of the matrix / a pixel's channel list: tens to hundreds
-// of nodes).  Integer work only; values are copied bit for bit.
+// bucket sizes.  Integer work only; values are copied bit for bit.
+//
+// Those passes take up to 8 launches, binary searches over the row pointers per node, global atomics and
+// the rank's loop: at 28 x 28 x 512 with 31 % stored (124 000 nodes, 2.1 MB moved) 83 us, of them 27 + 29
+// in counting and dropping, 21 in ranking.  Where the scratch allows (use_tiles below) three launches over
+// tiles of the dense shape do it in 15, now launch latency mostly (112 x 112 x 512, 50 % stored: 693 -> 73;
+// a 1024 x 8192 matrix, 30 %: 324 -> 77, bound by its 4-byte stores; 64 x 64, 10 %: 26 -> 15):
+//   1. a work-group takes RG (up to 32) consecutive keys and a panel of up to kPanel buckets of one
+//      plane (a matrix is one plane, a tensor has one per h).  Its nodes set bit (key mod RG) of the
+//      bucket's word in LDS; the number of bits is the tile's count for the bucket;
+//   2. per bucket, the counts of the key groups become offsets inside the bucket, and the bucket
+//      totals are scanned per block of 256 buckets;
+//   3. the tile's words are built again and every node lands at (start of the bucket) + (offset of
+//      its key group) + (number of set bits below its own).
+#include <type_traits>
+
 #include "internal.h"
 
 namespace fscnn {
@@ -126,6 +140,161 @@ __global__ void __launch_bounds__(kBlock) reorder_place_kernel(const int *__rest
     tval[a + rank] = sval[p];
 }
 
+// ---- the tiled form
+constexpr int kPanel = 4096;        // buckets of a tile at most: 16 KB of words, 16 KB of starts
+constexpr int kMaxSums = 256;       // blocks of 256 buckets whose totals step 3 scans by itself
+
+// f(key mod RG, bucket of the plane relative to the panel, entry) for every node of the tile.  LPR lanes
+// share a row: about as many as an average row has nodes.
+template <class Fn>
+__device__ inline void for_tile_nodes(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx, int H, int C,
+                                      int h, int c0, int RG, int w0, int wn, int LPR, int nnz, Fn f)
+{
+    for (int r = (int)threadIdx.x / LPR; r < RG && c0 + r < C; r += kBlock / LPR) {
+        const int row = (c0 + r) * H + h;
+        int lo = rowptr[row], hi = rowptr[row + 1];
+        lo = lo < 0 ? 0 : lo;
+        hi = hi > nnz ? nnz : hi;
+        for (int e0 = lo + (int)threadIdx.x % LPR; e0 < hi; e0 += 4 * LPR) {
+            uint32_t w[4];   // four loads in flight
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = hi - e0 > u * LPR ? idx[e0 + u * LPR] : 0xffffffffu;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t q = w[u] - (uint32_t)w0;   // (an index outside the panel, or corrupt, wraps past it)
+                if (hi - e0 > u * LPR && q < (uint32_t)wn) f(r, (int)q, e0 + u * LPR);
+            }
+            if (hi - e0 <= 4 * LPR) break;
+        }
+    }
+}
+
+struct Tile {
+    int h, g, w0, wn;
+};
+__device__ inline Tile tile_of(int n_cols, int H, int panels, int pw)
+{
+    Tile t;
+    const int b = blockIdx.x;
+    t.w0 = (b % panels) * pw;
+    t.wn = n_cols - t.w0 < pw ? n_cols - t.w0 : pw;
+    t.h = (b / panels) % H;
+    t.g = b / panels / H;
+    return t;
+}
+
+// cnt[g * n_buckets + bucket], bucket = w * H + h
+__global__ void __launch_bounds__(kBlock) tile_count_kernel(const int *__restrict__ rowptr,
+                                                            const uint32_t *__restrict__ idx, int n_cols, int H, int C,
+                                                            int RG, int panels, int pw, int LPR, int nnz,
+                                                            long long n_buckets, unsigned short *__restrict__ cnt)
+{
+    extern __shared__ uint32_t word[];
+    const Tile t = tile_of(n_cols, H, panels, pw);
+    for (int w = threadIdx.x; w < t.wn; w += kBlock) word[w] = 0u;
+    __syncthreads();
+    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
+                   [&](int r, int w, int) { atomicOr(&word[w], 1u << r); });
+    __syncthreads();
+    for (int w = threadIdx.x; w < t.wn; w += kBlock)
+        cnt[t.g * n_buckets + (long long)(t.w0 + w) * H + t.h] = (unsigned short)__popc(word[w]);
+}
+
+// cnt -> offsets of the groups inside their bucket (in place); first[b] = start of bucket b inside its
+// block of 256 buckets; sums[block] = nodes of the block.  kParts threads share a bucket, each a run of
+// its groups: it adds them up, then writes their offsets; 16 loads in flight (one thread per bucket took
+// longer than the rest of the transpose where keys are many and buckets few).
+constexpr int kParts = 4;
+__global__ void __launch_bounds__(kBlock *kParts) tile_offsets_kernel(unsigned short *__restrict__ cnt, int n_buckets,
+                                                                      int G, int *__restrict__ first,
+                                                                      int *__restrict__ sums)
+{
+    __shared__ int part_sum[kParts][kBlock], wave_sum[kBlock / 64];
+    const int t = threadIdx.x % kBlock, part = threadIdx.x / kBlock;
+    const int b = blockIdx.x * kBlock + t, lane = threadIdx.x & 63, wave = t >> 6;
+    const int per = (G + kParts - 1) / kParts;
+    const int ga = part * per, gb = b < n_buckets ? (ga + per < G ? ga + per : G) : 0;
+    unsigned short *p = cnt + b;
+    auto walk = [&](int run, auto write) {
+        for (int g0 = ga; g0 < gb; g0 += 16) {
+            int v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = g0 + u < gb ? p[(long long)(g0 + u) * n_buckets] : 0;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                if (decltype(write)::value && g0 + u < gb) p[(long long)(g0 + u) * n_buckets] = (unsigned short)run;
+                run += v[u];
+            }
+        }
+        return run;
+    };
+    part_sum[part][t] = walk(0, std::false_type{});
+    __syncthreads();
+    int base = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) {
+        if (q < part) base += part_sum[q][t];
+        total += part_sum[q][t];
+    }
+    walk(base, std::true_type{});
+    int incl = total;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (part == 0 && lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int i = 0; i < wave; ++i) before += wave_sum[i];
+    if (part == 0 && b < n_buckets) first[b] = before + incl - total;
+    if (threadIdx.x == kBlock - 1) sums[blockIdx.x] = before + incl;
+}
+
+__global__ void __launch_bounds__(kBlock) tile_place_kernel(
+    const int *__restrict__ rowptr, const uint32_t *__restrict__ idx, const float *__restrict__ val, int n_cols, int H,
+    int C, int RG, int panels, int pw, int LPR, int nnz, long long n_buckets, const unsigned short *__restrict__ cnt,
+    const int *__restrict__ first, const int *__restrict__ sums, int nsums, int *__restrict__ tptr,
+    uint32_t *__restrict__ tidx, float *__restrict__ tval)
+{
+    extern __shared__ uint32_t word[];
+    int *start = reinterpret_cast<int *>(word + pw);
+    __shared__ int block_start[kMaxSums], wave_sum[kBlock / 64];
+    const Tile t = tile_of(n_cols, H, panels, pw);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int w = threadIdx.x; w < t.wn; w += kBlock) word[w] = 0u;
+    // starts of the blocks of buckets (kMaxSums == kBlock: one each)
+    const int mine = (int)threadIdx.x < nsums ? sums[threadIdx.x] : 0;
+    int incl = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int i = 0; i < wave; ++i) before += wave_sum[i];
+    block_start[threadIdx.x] = before + incl - mine;
+    if (blockIdx.x == 0 && threadIdx.x == kBlock - 1) tptr[n_buckets] = before + incl;
+    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
+                   [&](int r, int w, int) { atomicOr(&word[w], 1u << r); });
+    __syncthreads();
+    for (int w = threadIdx.x; w < t.wn; w += kBlock) {
+        const int b = (t.w0 + w) * H + t.h;
+        const int at = block_start[b / kBlock] + first[b];
+        if (t.g == 0) tptr[b] = at;
+        start[w] = at + cnt[t.g * n_buckets + b];
+    }
+    __syncthreads();
+    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz, [&](int r, int w, int e) {
+        const int p = start[w] + __popc(word[w] & ((1u << r) - 1u));
+        if (p < nnz) {   // (holds for every node of a valid pointer array)
+            tidx[p] = (uint32_t)(t.g * RG + r);
+            tval[p] = val[e];
+        }
+    });
+}
+static_assert(kMaxSums == kBlock, "step 3 scans one sum per thread");
+
 inline unsigned blocks_for(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 // scratch layout (32-bit words): cnt[n_buckets] | scan scratch | cursor[n_buckets] | skey[nnz] | sval[nnz]
@@ -142,6 +311,41 @@ inline Layout layout_of(long long n_buckets, long long nnz)
     l.sval = l.skey + nnz;
     l.words = l.sval + nnz;
     return l;
+}
+
+// How the tiled form would run.  Scratch, in 32-bit words: first[n_buckets] | sums[nsums] | cnt (16 bits each)
+struct TilePlan {
+    bool ok;
+    int RG, G, panels, pw, LPR, nsums;
+    long long blocks;
+};
+// The tiled form wants its counts (16 bits per bucket and key group) in the scratch that the callers bring
+// for the node-by-node form, which ties it to about 1 % stored nodes and more; step 3 scans at most 256
+// block totals (65536 buckets); a bucket's offsets fit 16 bits below 65536 keys.  As many keys per tile as
+// still give a work-group for every CU or leave it few nodes (more groups are more counts), 8 at least
+// (1024 x 64, 10 %: 37 us with 128 groups of 8, 15 with 32 of 32).
+TilePlan use_tiles(int n_cols, int H, int C, long long n_buckets, long long nnz)
+{
+    TilePlan t{};
+    t.nsums = (int)((n_buckets + kBlock - 1) / kBlock);
+    if (t.nsums > kMaxSums || C > 65535 || nnz <= 0) return t;
+    t.panels = (n_cols + kPanel - 1) / kPanel;
+    t.pw = (n_cols + t.panels - 1) / t.panels;
+    const long long room = layout_of(n_buckets, nnz).words;
+    for (int rg = 32; rg >= 8; rg /= 2) {
+        const long long G = (C + rg - 1) / rg, blocks = G * H * t.panels;
+        if (n_buckets + t.nsums + (G * n_buckets + 1) / 2 > room || blocks * kBlock > 0xffffffffLL) break;
+        if (blocks > 1024 && nnz < 16 * blocks) break;   // nearly empty tiles, each with its fixed part
+        t.ok = true;
+        t.RG = rg;
+        t.G = (int)G;
+        t.blocks = blocks;
+        if (blocks >= 256 || nnz <= 512 * blocks) break;
+    }
+    const long long avg = nnz / ((long long)C * H);
+    t.LPR = 4;
+    while (t.LPR < 64 && t.LPR < avg) t.LPR *= 2;
+    return t;
 }
 
 // Scratch of the entry point that allocates nothing: one copy per GPU, held until the process
@@ -183,8 +387,22 @@ hipError_t launch_reorder(bool tensor, const int *rowptr, const uint32_t *idx, c
                           int n_rows, int n_cols, int H, long long n_buckets, long long nnz,
                           int *tptr, uint32_t *tidx, float *tval, void *workspace, hipStream_t st)
 {
-    const Layout l = layout_of(n_buckets, nnz);
     int *ws = static_cast<int *>(workspace);
+    const int C = n_rows / H;   // keys (a matrix is one plane, H = 1)
+    const TilePlan tp = use_tiles(n_cols, H, C, n_buckets, nnz);
+    if (tp.ok) {
+        int *first = ws, *sums = ws + n_buckets;
+        unsigned short *groups = reinterpret_cast<unsigned short *>(sums + tp.nsums);
+        hipLaunchKernelGGL(tile_count_kernel, dim3((unsigned)tp.blocks), dim3(kBlock), tp.pw * 4, st, rowptr, idx,
+                           n_cols, H, C, tp.RG, tp.panels, tp.pw, tp.LPR, (int)nnz, n_buckets, groups);
+        hipLaunchKernelGGL(tile_offsets_kernel, dim3((unsigned)tp.nsums), dim3(kBlock * kParts), 0, st, groups, (int)n_buckets,
+                           tp.G, first, sums);
+        hipLaunchKernelGGL(tile_place_kernel, dim3((unsigned)tp.blocks), dim3(kBlock), tp.pw * 8, st, rowptr, idx, val,
+                           n_cols, H, C, tp.RG, tp.panels, tp.pw, tp.LPR, (int)nnz, n_buckets, groups, first, sums,
+                           tp.nsums, tptr, tidx, tval);
+        return hipGetLastError();
+    }
+    const Layout l = layout_of(n_buckets, nnz);
     int *cnt = ws + l.cnt, *cursor = ws + l.cursor;
     uint32_t *skey = reinterpret_cast<uint32_t *>(ws + l.skey);
     float *sval = reinterpret_cast<float *>(ws + l.sval);

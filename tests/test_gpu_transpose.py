@@ -124,3 +124,36 @@ def test_a_node_with_an_index_out_of_range_is_dropped(F):
                                                                     torch.from_numpy(val).cuda(), 2, 3))
     assert list(tptr) == [0, 1, 2, 4]
     assert list(tidx[:4]) == [0, 1, 0, 1] and list(tval[:4]) == [1.0, 4.0, 2.0, 5.0]
+
+
+@pytest.mark.parametrize("shape,keep", [
+    ((33, 4096), 0.5),      # one key past a group; a panel that is exactly full
+    ((31, 4097), 0.2),      # two panels
+    ((257, 8193), 0.1),     # three panels, 16-bit counts at an odd offset in the scratch
+    ((64, 65536), 0.05),    # the most buckets the tiles take
+    ((40, 65537), 0.05),    # one more: node by node
+    ((5000, 3), 0.4),       # many key groups per bucket
+    ((66000, 2), 0.5),      # more keys than 16 bits: node by node
+    ((2000, 90), 0.004),    # too few nodes for the counts
+    ((3, 300), 0.02),       # fewer nodes than one per bucket
+])
+def test_matrix_transpose_at_the_edges_of_its_tiles(F, shape, keep):
+    # ragged rows, one empty, one full
+    rng = np.random.default_rng(shape[0] * 7 + shape[1])
+    m = (rng.standard_normal(shape) * (rng.random(shape) < keep * rng.random((shape[0], 1)) * 2)).astype(np.float32)
+    m[shape[0] // 2] = 0.0
+    m[-1] = 1.0 + np.arange(shape[1], dtype=np.float32)
+    ptr, idx, val = csr_of(m)
+    got = F.sparse_transpose(dev_i32(ptr), dev_i32(idx), torch.from_numpy(val).cuda(), *shape)
+    same(got, oracle.sparse_transpose(ptr, idx, val, *shape))
+
+
+@pytest.mark.parametrize("W,H,C,keep", [(3, 70, 33, 0.5), (70, 3, 65, 0.2), (1, 600, 31, 0.6), (112, 112, 40, 0.1), (4100, 2, 9, 0.3)])
+def test_tensor_transpose_at_the_edges_of_its_tiles(F, W, H, C, keep):
+    rng = np.random.default_rng(W + H + C)
+    t = (rng.standard_normal((C, H, W)) * (rng.random((C, H, W)) < keep)).astype(np.float32)
+    t[:, 1, :] = 0.0
+    t[:, 2 % H, 0] = 2.0
+    ptr, widx, val = csr_of(t.reshape(C * H, W))
+    got = F.sparse_tensor_transpose(dev_i32(ptr), dev_i32(widx), torch.from_numpy(val).cuda(), W, H, C)
+    same(got, oracle.sparse_tensor_transpose(ptr, widx, val, W, H, C))
