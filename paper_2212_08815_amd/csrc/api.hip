@@ -61,8 +61,7 @@ double density(const fscnn_filter_t *f) { return (double)f->nnz / ((double)f->K 
 void free_plan(SfPlan *p)
 {
     if (!p) return;
-    if (p->segptr) (void)hipFree(p->segptr);
-    if (p->recs) (void)hipFree(p->recs);
+    if (p->recs) (void)hipFree(p->recs);   // with the pointers behind the records
     if (p->packed) (void)hipFree(p->packed);
     for (auto &sc : p->split)
         if (sc.buf) (void)hipFree(sc.buf);
@@ -166,21 +165,23 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
         delete p;
         return ds;
     }
+    // one allocation: the records, the pointers, and the counts the pointers are scanned from
+    const size_t nrecs = (size_t)(cap + kPlanSpare);
+    hipError_t e = hipMalloc(&p->recs, sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)));
     int *cnt = nullptr;
-    hipError_t e = hipMalloc(&cnt, sizeof(int) * (size_t)(nb + scan_tmp_elems(nb)));
-    if (e == hipSuccess) e = hipMalloc(&p->segptr, sizeof(int) * (size_t)(nb + 1));
-    if (e == hipSuccess) e = hipMalloc(&p->recs, sizeof(Rec) * (size_t)(cap + kPlanSpare));
-    if (e == hipSuccess)
+    if (e == hipSuccess) {
+        p->segptr = reinterpret_cast<int *>(p->recs + nrecs);
+        cnt = p->segptr + (nb + 1);
         e = launch_plan_count(f->rowptr, f->idx, f->K, f->R * f->S, g, p->NCH, p->NG, cnt, st);
+    }
     if (e == hipSuccess) e = launch_exclusive_scan(cnt, p->segptr, nb, cnt + nb, st);
     if (e == hipSuccess)
         e = g.DENSE ? launch_plan_fill_dense(f->rowptr, f->idx, f->val, f->K, f->C, f->R, f->S, g, p->NCH,
                                              p->NG, cap, p->recs, st)
-                    : launch_plan_fill(f->rowptr, f->idx, f->val, f->K, f->R, f->S, g, p->NCH, p->NG,
+                    : launch_plan_fill(f->rowptr, f->idx, f->val, f->K, f->R, f->S, g, p->NCH, p->NG, f->nnz,
                                        p->segptr, p->recs, st);
-    // The plan may be used from other streams and `cnt` is released here: wait for the build.
+    // The plan may be used from other streams: wait for the build.
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (cnt) (void)hipFree(cnt);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_plan(p);
@@ -347,8 +348,9 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     f->rowptr = nullptr; f->idx = nullptr; f->val = nullptr;
     int *cnt = nullptr;
     int total = 0;
-    hipError_t e = hipMalloc(&cnt, sizeof(int) * (size_t)(K + scan_tmp_elems(K)));
-    if (e == hipSuccess) e = hipMalloc(&f->rowptr, sizeof(int) * (size_t)(K + 1));
+    // two allocations: the pointers with the counts they are scanned from, and the nodes
+    hipError_t e = hipMalloc(&f->rowptr, sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)));
+    if (e == hipSuccess) cnt = f->rowptr + (K + 1);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, st);
     if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, st);
     if (e == hipSuccess)
@@ -357,17 +359,15 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     if (e == hipSuccess) {
         f->nnz = total;
         const size_t n = total > 0 ? (size_t)total : 1;
-        e = hipMalloc(&f->idx, sizeof(uint32_t) * n);
-        if (e == hipSuccess) e = hipMalloc(&f->val, sizeof(float) * n);
+        e = hipMalloc(&f->idx, (sizeof(uint32_t) + sizeof(float)) * n);
+        if (e == hipSuccess) f->val = reinterpret_cast<float *>(f->idx + n);
     }
     if (e == hipSuccess) e = launch_filter_pack(w_dev, K, row, f->rowptr, f->idx, f->val, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (cnt) (void)hipFree(cnt);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         if (f->rowptr) (void)hipFree(f->rowptr);
-        if (f->idx) (void)hipFree(f->idx);
-        if (f->val) (void)hipFree(f->val);
+        if (f->idx) (void)hipFree(f->idx);   // with the values behind the indices
         f->magic = 0;
         delete f;
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
@@ -506,7 +506,6 @@ fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f)
     f->plans.clear();
     if (f->rowptr) (void)hipFree(f->rowptr);
     if (f->idx) (void)hipFree(f->idx);
-    if (f->val) (void)hipFree(f->val);
     delete f;
     return FSCNN_OK;
 }

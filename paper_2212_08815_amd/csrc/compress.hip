@@ -16,29 +16,6 @@ constexpr int kBlock = 256;
 
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
-// Exclusive prefix of `flag` over the work-group in thread order, plus the group total.
-// Uses one ballot per wave and a small LDS array for the wave totals.
-__device__ inline int block_exclusive_count(bool flag, int *wave_tot /* LDS, >= blockDim/64 */,
-                                            int *total)
-{
-    const unsigned long long m = __ballot(flag);
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int nw = blockDim.x >> 6;
-    const int within = __popcll(m & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_tot[wave] = __popcll(m);
-    __syncthreads();
-    int before = 0, tot = 0;
-    for (int i = 0; i < nw; ++i) {
-        const int t = wave_tot[i];
-        if (i < wave) before += t;
-        tot += t;
-    }
-    __syncthreads();  // wave_tot may be reused by the caller's next round
-    *total = tot;
-    return before + within;
-}
-
 // ---- A1: per output channel, the number of entries with w != 0 ------------------------
 __global__ void __launch_bounds__(kBlock) filter_count_kernel(const float *__restrict__ w,
                                                               long long row, int *__restrict__ cnt)
@@ -58,33 +35,67 @@ __global__ void __launch_bounds__(kBlock) filter_count_kernel(const float *__res
 }
 
 // ---- exclusive scan of n ints into out[0..n] (out[n] = total); one work-group ---------
-constexpr int kScanThreads = 1024;
+// Latency is all there is to it (n is a few thousand): a round takes up to 16 elements per thread,
+// thread t the elements u*1024 + t, so that all its loads are coalesced and in flight together; every
+// (u, wave) row of 64 is scanned with lane shuffles, the 256 row totals by the first wave, two barriers
+// in all.  (A run of consecutive elements per thread and a scan of the 1024 sums with 20 barriers:
+// 6.8 us on average over the 26 scans of loading the 13-layer stack.)
+constexpr int kScanThreads = 1024, kScanPer = 16, kScanRows = kScanThreads / 64 * kScanPer;
+__device__ inline int wave_inclusive(int v)
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(v, o, 64);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
 __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int *__restrict__ in,
                                                                       int *__restrict__ out,
                                                                       long long n)
 {
-    __shared__ int sums[kScanThreads];
-    const long long per = (n + kScanThreads - 1) / kScanThreads;
-    const long long lo = (long long)threadIdx.x * per;
-    const long long hi = lo + per < n ? lo + per : n;
-    int s = 0;
-    for (long long i = lo; i < hi; ++i) s += in[i];
-    sums[threadIdx.x] = s;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over the 1024 partial sums
-    for (int o = 1; o < kScanThreads; o <<= 1) {
-        int v = (int)threadIdx.x >= o ? sums[threadIdx.x - o] : 0;
+    __shared__ int rows[kScanRows + 1];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    int carry = 0;
+    for (long long n0 = 0; n0 < n; n0 += kScanThreads * kScanPer) {
+        int v[kScanPer], incl[kScanPer];
+        const long long left = n - n0;
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) {
+            const int i = u * kScanThreads + (int)threadIdx.x;
+            v[u] = i < left ? in[n0 + i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) {
+            incl[u] = 0;
+            if ((long long)u * kScanThreads < left) incl[u] = wave_inclusive(v[u]);   // (the same for the whole group)
+            if (lane == 63) rows[u * (kScanThreads / 64) + wave] = incl[u];
+        }
         __syncthreads();
-        sums[threadIdx.x] += v;
+        if (wave == 0) {
+            constexpr int Q = kScanRows / 64;
+            int t[Q], s = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                t[q] = s;
+                s += rows[lane * Q + q];
+            }
+            const int end = wave_inclusive(s);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) rows[lane * Q + q] = end - s + t[q];
+            if (lane == 63) rows[kScanRows] = end;
+        }
         __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) {
+            const int i = u * kScanThreads + (int)threadIdx.x;
+            if (i < left) out[n0 + i] = carry + rows[u * (kScanThreads / 64) + wave] + incl[u] - v[u];
+        }
+        carry += rows[kScanRows];
+        __syncthreads();   // the next round writes `rows`
     }
-    int run = threadIdx.x == 0 ? 0 : sums[threadIdx.x - 1];
-    for (long long i = lo; i < hi; ++i) {
-        const int v = in[i];
-        out[i] = run;
-        run += v;
-    }
-    if (threadIdx.x == kScanThreads - 1) out[n] = sums[kScanThreads - 1];
+    if (threadIdx.x == 0) out[n] = carry;
 }
 
 // ---- the same for large n, three passes over tiles of kTile elements -------------------
@@ -159,28 +170,49 @@ __global__ void __launch_bounds__(kTileThreads) scan_tile_kernel(const int *__re
 }
 
 // ---- A2: ordered pack of row k into idx/val at rowptr[k] ------------------------------
+// A round takes kPackPer elements per thread, a wave 64 * kPackPer consecutive ones: all loads in flight
+// together, positions by ballots, one exchange of the wave totals (one element per thread and round, two
+// barriers each, spent its time in the 18 rounds of a 512 x 3 x 3 row).
+constexpr int kPackPer = 8;
 __global__ void __launch_bounds__(kBlock) filter_pack_kernel(const float *__restrict__ w,
                                                              long long row,
                                                              const int *__restrict__ rowptr,
                                                              uint32_t *__restrict__ idx,
                                                              float *__restrict__ val)
 {
-    __shared__ int wave_tot[kBlock / 64];
-    const int k = blockIdx.x;
+    __shared__ int wave_tot[2][kBlock / 64];
+    const int k = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
     const float *wk = w + (long long)k * row;
     long long base = rowptr[k];
-    for (long long f0 = 0; f0 < row; f0 += kBlock) {
-        const long long f = f0 + threadIdx.x;
-        float v = 0.0f;
-        if (f < row) v = wk[f];
-        const bool nz = (f < row) && (v != 0.0f);
-        int tot;
-        const int pos = block_exclusive_count(nz, wave_tot, &tot);
-        if (nz) {
-            idx[base + pos] = (uint32_t)f;
-            val[base + pos] = v;
+    int side = 0;
+    for (long long f0 = 0; f0 < row; f0 += kBlock * kPackPer) {
+        const long long first = f0 + wave * (64 * kPackPer) + lane;
+        float v[kPackPer];
+#pragma unroll
+        for (int u = 0; u < kPackPer; ++u) v[u] = first + u * 64 < row ? wk[first + u * 64] : 0.0f;
+        int pos[kPackPer], tot = 0;
+#pragma unroll
+        for (int u = 0; u < kPackPer; ++u) {
+            const unsigned long long m = __ballot(v[u] != 0.0f);
+            pos[u] = tot + __popcll(m & ((1ull << lane) - 1ull));
+            tot += __popcll(m);
         }
-        base += tot;
+        if (lane == 0) wave_tot[side][wave] = tot;
+        __syncthreads();
+        long long at = base;
+#pragma unroll
+        for (int i = 0; i < kBlock / 64; ++i) {
+            const int t = wave_tot[side][i];
+            if (i < wave) at += t;
+            base += t;
+        }
+        side ^= 1;   // the next round's totals go to the other set: one barrier per round is enough
+#pragma unroll
+        for (int u = 0; u < kPackPer; ++u)
+            if (v[u] != 0.0f) {
+                idx[at + pos[u]] = (uint32_t)(first + u * 64);
+                val[at + pos[u]] = v[u];
+            }
     }
 }
 
@@ -230,30 +262,35 @@ __global__ void plan_count_kernel(const int *__restrict__ rowptr, const uint32_t
     cnt[b] = c;
 }
 
+// LPB lanes (a power of two, 64 at most) share a bucket, about as many as it has entries: a thread per
+// bucket walked a dozen dependent loads and stores one by one (18 us a layer of the 13-layer stack).
 __global__ void plan_fill_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
                                  const float *__restrict__ val, int K, int R, int S, int CC,
                                  int SLOTS, int WAVES, int NCH, int NG, int IN_ROWS, int PITCH,
-                                 int BV, int STRIDE, const int *__restrict__ segptr,
+                                 int BV, int STRIDE, int LPB, const int *__restrict__ segptr,
                                  Rec *__restrict__ recs)
 {
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long b = t / LPB;
+    const int sub = (int)(t % LPB);
     const long long nb = (long long)NG * NCH * SLOTS * WAVES;
-    if (b < kPlanSpare) {  // spare records a prefetching reader may touch past the end
+    if (t < kPlanSpare) {  // spare records a prefetching reader may touch past the end
         const int last = segptr[nb];
         Rec z;
         z.off = 0u;
         z.val = 0.0f;
-        recs[last + b] = z;
+        recs[last + t] = z;
     }
     if (b >= nb) return;
     const Bucket q = decode_bucket(b, SLOTS, WAVES, NCH);
     if (q.k >= K) return;
     const int RS = R * S;
     const int lo = rowptr[q.k], hi = rowptr[q.k + 1];
+    const int o0 = segptr[b], count = segptr[b + 1] - o0;
+    if (count == 0) return;
     const int a = lower_bound_u32(idx, lo, hi, (uint32_t)q.ci * CC * RS);
-    const int e = lower_bound_u32(idx, lo, hi, (uint32_t)(q.ci + 1) * CC * RS);
-    int o = segptr[b];
-    for (int i = a; i < e; ++i, ++o) {
+    for (int d = sub; d < count; d += LPB) {
+        const int i = a + d, o = o0 + d;
         const uint32_t f = idx[i];
         const int c = (int)(f / RS) - q.ci * CC;
         const int rs = (int)(f % RS);
@@ -483,13 +520,16 @@ hipError_t launch_plan_count(const int *rowptr, const uint32_t *idx, int K, int 
 }
 
 hipError_t launch_plan_fill(const int *rowptr, const uint32_t *idx, const float *val, int K, int R,
-                            int S, const SfGeom &g, int NCH, int NG, const int *segptr, Rec *recs,
+                            int S, const SfGeom &g, int NCH, int NG, long long nnz, const int *segptr, Rec *recs,
                             hipStream_t st)
 {
     const long long nb = (long long)NG * NCH * g.KG;
-    hipLaunchKernelGGL(plan_fill_kernel, dim3(blocks_for(nb, kBlock)), dim3(kBlock), 0, st, rowptr,
+    int LPB = 1;
+    while (LPB < 64 && LPB * nb < nnz && 2 * LPB * nb < (1LL << 31)) LPB *= 2;
+    const long long threads = nb * LPB > kPlanSpare ? nb * LPB : kPlanSpare;
+    hipLaunchKernelGGL(plan_fill_kernel, dim3(blocks_for(threads, kBlock)), dim3(kBlock), 0, st, rowptr,
                        idx, val, K, R, S, g.CC, g.SLOTS, g.WAVES, NCH, NG, g.IN_ROWS, g.PITCH, g.BV, g.STRIDE,
-                       segptr, recs);
+                       LPB, segptr, recs);
     return hipGetLastError();
 }
 

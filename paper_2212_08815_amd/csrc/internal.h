@@ -66,8 +66,8 @@ struct SfPlan {
     SfGeom g{};
     int NCH = 0, NG = 0;
     long long nrec = 0;       // records (= nonzeros); the array carries kPlanSpare spare entries
-    int *segptr = nullptr;    // [NG*NCH*KG + 1], bucket order (group, wave, chunk, slot)
-    Rec *recs = nullptr;      // [nrec + kPlanSpare]
+    int *segptr = nullptr;    // [NG*NCH*KG + 1], bucket order (group, wave, chunk, slot); behind the records
+    Rec *recs = nullptr;      // [nrec + kPlanSpare]; owns the allocation
     // Scratch of the channel-split mode (small problems): one buffer per stream that has used the
     // plan in that mode, so that calls on different streams never share one.  Grown on demand.
     struct SplitScratch {
@@ -105,9 +105,9 @@ struct fscnn_filter {
     int device;
     int K, C, R, S;
     long long nnz;
-    int *rowptr;    // device [K+1]
-    uint32_t *idx;  // device [nnz]
-    float *val;     // device [nnz]
+    int *rowptr;    // device [K+1]; owns an allocation
+    uint32_t *idx;  // device [nnz]; owns an allocation
+    float *val;     // device [nnz], behind the indices
     std::mutex mu;
     std::vector<fscnn::SfPlan *> plans;
     // whether calls of a geometry are served by the contraction, and how (see contracts() in api.hip):
@@ -168,7 +168,7 @@ hipError_t launch_filter_pack(const float *w, int K, long long row, const int *r
 hipError_t launch_plan_count(const int *rowptr, const uint32_t *idx, int K, int RS, const SfGeom &g,
                              int NCH, int NG, int *cnt, hipStream_t st);
 hipError_t launch_plan_fill(const int *rowptr, const uint32_t *idx, const float *val, int K, int R,
-                            int S, const SfGeom &g, int NCH, int NG, const int *segptr, Rec *recs,
+                            int S, const SfGeom &g, int NCH, int NG, long long nnz, const int *segptr, Rec *recs,
                             hipStream_t st);
 // the taps-outer plan (SfGeom::DENSE): nrec = NG*WAVES*NCH*CC*R*S*SLOTS records plus the spare ones
 hipError_t launch_plan_fill_dense(const int *rowptr, const uint32_t *idx, const float *val, int K, int C,
