@@ -667,9 +667,13 @@ fscnn_status_t fscnn_conv2d_sparse_filter(fscnn_filter_t *f, const float *x_dev,
                                         0, stream);
 }
 
-// Dense N x C x H x W activations -> compressed handle.  Synchronises st once (the number of
-// stored values sizes the second buffer); the pass that fills the handle is still running on st
-// when this returns, and reads x.
+// Dense N x C x H x W activations -> compressed handle.  Synchronises st once, for the number of stored
+// values.  Up to kWholeBytes of indices and values, were every value stored, are allocated with the
+// pointers before anything runs, and the passes follow each other without the host; beyond that the
+// number of stored values sizes a second allocation (making and releasing one takes 50 us, more than
+// the passes of a 28x28 layer).  The pass that fills the handle may still be running on st when this
+// returns, and reads x.
+constexpr long long kWholeBytes = 256LL << 20;
 static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int H, int W,
                                            hipStream_t st, fscnn_input_t **out)
 {
@@ -693,31 +697,39 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     in->made_on = st; in->filled = nullptr;
     int total = 0;
     const long long nstep = npix * NCH;   // (pixel, channel step) pairs
-    // first allocation: the pointer array, then (256-byte aligned) the counts it is scanned from
-    // and the scan's scratch; the counts stay with the handle, so nothing is freed here
-    const size_t cnt_at = ((size_t)(nstep + 1) * sizeof(int) + 255) / 256 * 256;
-    hipError_t e = hipMalloc(&in->ptr_block, cnt_at + sizeof(int) * (size_t)(nstep + scan_tmp_elems(nstep)));
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    // first allocation: the pointer array, the scratch of the passes (it stays with the handle, so nothing
+    // is freed here), and the nodes if they are allocated for the worst case.  Spare entries: the
+    // sparse-input kernels fetch the next (channel, value) pairs of a pixel's list ahead, up to kSiSpare
+    // positions past the one in use
+    const size_t scratch_at = up((size_t)(nstep + 1) * sizeof(int));
+    const size_t nodes_at = scratch_at + up(sizeof(int) * (size_t)input_scratch_elems(npix, NCH));
+    auto val_at = [&](size_t n) { return up(n * sizeof(uint32_t)); };
+    const size_t most = (size_t)(npix * C) + kSiSpare;
+    const bool whole = npix * C * 8 <= kWholeBytes;
+    hipError_t e = hipMalloc(&in->ptr_block, nodes_at + (whole ? val_at(most) + most * sizeof(float) : 0));
+    int *scratch = nullptr;
+    auto fill = [&](void *nodes, size_t n) {
+        in->cidx = static_cast<uint32_t *>(nodes);
+        in->xval = reinterpret_cast<float *>(static_cast<char *>(nodes) + val_at(n));
+        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, st);
+    };
     if (e == hipSuccess) {
-        in->cptr = static_cast<int *>(in->ptr_block);
-        int *cnt = reinterpret_cast<int *>(static_cast<char *>(in->ptr_block) + cnt_at);
-        e = launch_input_count(x_dev, N, C, H, W, CC, NCH, cnt, st);
-        if (e == hipSuccess) e = launch_exclusive_scan(cnt, in->cptr, nstep, cnt + nstep, st);
+        char *base = static_cast<char *>(in->ptr_block);
+        in->cptr = reinterpret_cast<int *>(base);
+        scratch = reinterpret_cast<int *>(base + scratch_at);
+        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, st);
+        if (e == hipSuccess && whole) e = fill(base + nodes_at, most);
     }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(&total, in->cptr + nstep, sizeof(int), hipMemcpyDeviceToHost, st);
+        e = hipMemcpyAsync(&total, scratch + input_groups(npix, NCH), sizeof(int), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e == hipSuccess) {
         in->nnz = total;
-        // second allocation: indices, then (256-byte aligned) values.  Spare entries: the
-        // sparse-input kernels fetch the next (channel, value) pairs of a pixel's list ahead, up
-        // to kSiSpare positions past the one in use
-        const size_t n = (size_t)total + kSiSpare;
-        const size_t val_at = (n * sizeof(uint32_t) + 255) / 256 * 256;
-        e = hipMalloc(&in->node_block, val_at + n * sizeof(float));
-        if (e == hipSuccess) {
-            in->cidx = static_cast<uint32_t *>(in->node_block);
-            in->xval = reinterpret_cast<float *>(static_cast<char *>(in->node_block) + val_at);
-            e = launch_input_fill(x_dev, N, C, H, W, CC, NCH, in->cptr, in->cidx, in->xval, kSiSpare, st);
+        if (!whole) {
+            const size_t n = (size_t)total + kSiSpare;
+            e = hipMalloc(&in->node_block, val_at(n) + n * sizeof(float));
+            if (e == hipSuccess) e = fill(in->node_block, n);
         }
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&in->filled, hipEventDisableTiming);
@@ -746,10 +758,10 @@ fscnn_status_t fscnn_input_compress(const float *x_dev, int N, int C, int H, int
 namespace {
 
 // Where the parts of an emitted handle's one allocation start (256-byte aligned parts): pointer
-// array | counts + scan scratch | indices | values | the dense result when the caller takes none.
+// array | counts | scratch of the passes | indices | values | the dense result when the caller takes none.
 struct EmitLayout {
     long long nstep, dense;
-    size_t cnt_at, idx_at, val_at, y_at;
+    size_t cnt_at, sum_at, idx_at, val_at, y_at;
     size_t bytes(bool with_y) const { return y_at + (with_y ? sizeof(float) * (size_t)dense : 0); }
 };
 
@@ -760,7 +772,8 @@ EmitLayout emit_layout(long long npix, int K, int NCH)
     L.dense = npix * K;
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     L.cnt_at = up((size_t)(L.nstep + 1) * sizeof(int));
-    L.idx_at = L.cnt_at + up(sizeof(int) * (size_t)(L.nstep + scan_tmp_elems(L.nstep)));
+    L.sum_at = L.cnt_at + up(sizeof(int) * (size_t)L.nstep);
+    L.idx_at = L.sum_at + up(sizeof(int) * (size_t)input_scratch_elems(npix, NCH));
     L.val_at = L.idx_at + up(sizeof(uint32_t) * (size_t)(L.dense + kSiSpare));
     L.y_at = L.val_at + up(sizeof(float) * (size_t)(L.dense + kSiSpare));
     return L;
@@ -799,10 +812,9 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
                                       FSCNN_LAYOUT_NCHW, FSCNN_LAYOUT_NCHW, 0, 0, stream, cnt, &counted);
     if (s != FSCNN_OK) return s;
     hipError_t e = hipSuccess;
-    if (!counted) e = launch_input_count(y, N, K, Ho, Wo, in->CC, in->NCH, cnt, st);
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, in->cptr, L.nstep, cnt + L.nstep, st);
-    if (e == hipSuccess)
-        e = launch_input_fill(y, N, K, Ho, Wo, in->CC, in->NCH, in->cptr, in->cidx, in->xval, kSiSpare, st);
+    int *scratch = reinterpret_cast<int *>(base + L.sum_at);
+    e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, st);
+    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, st);
     if (e == hipSuccess) e = hipEventRecord(in->filled, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();

@@ -341,72 +341,147 @@ __global__ void plan_fill_dense_kernel(const int *__restrict__ rowptr, const uin
 }
 
 // ---- A7: compressed activation, rows = pixels, columns = channels ----------------------
-// One thread per (pixel, step of CC channels): threads of a work-group take consecutive pixels
-// of one step, so the reads of a channel plane are contiguous.  The exclusive scan of the counts
-// in (pixel, step) order is at once the position of every step's first entry (the chunk pointers
-// the convolution kernels read) and, at step 0, the start of the pixel's row.
-__global__ void __launch_bounds__(kBlock) input_count_kernel(const float *__restrict__ x, int C,
-                                                             long long HW, long long npix, int CC,
-                                                             int NCH, int *__restrict__ cnt)
-{
-    const long long p = (long long)blockIdx.x * kBlock + threadIdx.x;
-    const int j = blockIdx.y;
-    if (p >= npix) return;
-    const long long n = p / HW, q = p % HW;
-    const float *xp = x + n * C * HW + q;
-    const int c1 = (j + 1) * CC < C ? (j + 1) * CC : C;
-    int c = 0;
-    for (int ch = j * CC; ch < c1; ++ch) c += (xp[(long long)ch * HW] != 0.0f) ? 1 : 0;
-    cnt[p * NCH + j] = c;
-}
+// A work-group owns PX consecutive pixels (PX a power of two, at most 32), whose lists are adjacent in
+// memory.  (1) The stored values of every group are counted; (2) a scan of these few sums gives where a
+// group's lists start; (3) the group counts again per (pixel, step of CC channels), scans that in LDS --
+// the chunk pointers the convolution kernels read, at step 0 the start of the pixel's row -- and writes
+// pointers and lists.  The activation is read twice, from the last-level cache the second time; nothing
+// else goes through memory.  (Counts per (pixel, step) written out and scanned there, 401 000 of them for
+// 8 x 512 x 28 x 28, were four launches and 29 us in front of step 3.)
 
-// A work-group packs the lists of PX consecutive pixels (PX a power of two, at most 32): thread
-// (pixel px, step lane sj) walks the steps sj, sj + 256/PX, ... of its pixel, so the reads of a
-// channel plane cover PX adjacent floats, and drops its (channel, value) pairs into an LDS image
-// of the group's output range -- the lists of consecutive pixels are adjacent in memory -- which
-// is then copied out with fully coalesced stores.
-__global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restrict__ x, int C,
-                                                            long long HW, long long npix, int CC,
-                                                            int NCH, int PX,
-                                                            const int *__restrict__ cptr,
-                                                            uint32_t *__restrict__ cidx,
-                                                            float *__restrict__ xval, int spare)
+// with cnt: the counts per (pixel, step) are at hand (sparse output emission) and are only added up
+__global__ void __launch_bounds__(kBlock) input_sum_kernel(const float *__restrict__ x, const int *__restrict__ cnt,
+                                                           int C, long long HW, long long npix, int NCH, int PX,
+                                                           int *__restrict__ sums)
 {
-    extern __shared__ uint32_t stage[];   // [cap] channel indices, then [cap] value bit patterns
-    const int cap = PX * NCH * CC;
-    // the entries past the last stored one (readers fetch a few positions ahead); the number of
-    // stored entries is the pointer array's last element
-    if (blockIdx.x == 0 && (int)threadIdx.x < spare) {
-        const long long total = cptr[npix * NCH];
-        cidx[total + threadIdx.x] = 0u;
-        xval[total + threadIdx.x] = 0.0f;
-    }
-    const long long p0 = (long long)blockIdx.x * PX;
-    const long long p1 = p0 + PX < npix ? p0 + PX : npix;
-    const int base = cptr[p0 * NCH];
-    const int count = cptr[p1 * NCH] - base;      // <= cap: at most C entries per pixel
-    const int px = threadIdx.x % PX, sj = threadIdx.x / PX;
-    const long long p = p0 + px;
-    if (p < npix) {
-        const long long n = p / HW, q = p % HW;
-        const float *xp = x + n * C * HW + q;
-        for (int j = sj; j < NCH; j += kBlock / PX) {
-            const int c1 = (j + 1) * CC < C ? (j + 1) * CC : C;
-            int o = cptr[p * NCH + j] - base;
-            for (int ch = j * CC; ch < c1; ++ch) {
-                const float v = xp[(long long)ch * HW];
-                if (v != 0.0f) {
-                    stage[o] = (uint32_t)ch;
-                    stage[cap + o] = __float_as_uint(v);
-                    ++o;
-                }
+    __shared__ int part[kBlock / 64];
+    const long long p0 = (long long)blockIdx.x * PX, p1 = p0 + PX < npix ? p0 + PX : npix;
+    int c = 0;
+    if (cnt) {
+        const int m = (int)(p1 - p0) * NCH;
+        for (int i = threadIdx.x; i < m; i += kBlock) c += cnt[p0 * NCH + i];
+    } else {
+        const long long p = p0 + threadIdx.x % PX;
+        const int step = kBlock / PX;
+        if (p < npix) {
+            const float *xp = x + p / HW * C * HW + p % HW;
+            for (int ch = threadIdx.x / PX; ch < C; ch += 16 * step) {   // sixteen loads in flight
+                float v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = ch + u * step < C ? xp[(long long)(ch + u * step) * HW] : 0.0f;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) c += v[u] != 0.0f ? 1 : 0;
             }
         }
     }
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
+    if (lane_id() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
-    for (int t = threadIdx.x; t < count; t += kBlock) {
-        cidx[base + t] = stage[t];
-        xval[base + t] = __uint_as_float(stage[cap + t]);
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int i = 0; i < kBlock / 64; ++i) t += part[i];
+        sums[blockIdx.x] = t;
+    }
+}
+
+// Thread (pixel px, step lane sj) walks the steps sj, sj + 256/PX, ... of its pixel, so the reads of a
+// channel plane cover PX adjacent floats; the values of its first kKept steps stay in registers between
+// counting and placing.  The (channel, value) pairs meet in an LDS image of the group's output range,
+// copied out with fully coalesced stores.
+constexpr int kKept = 4;
+__global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restrict__ x, int C, long long HW,
+                                                            long long npix, int NCH, int PX,
+                                                            const int *__restrict__ start, int *__restrict__ cptr,
+                                                            uint32_t *__restrict__ cidx, float *__restrict__ xval,
+                                                            int spare)
+{
+    constexpr int CC = kSiCC;
+    extern __shared__ uint32_t stage[];   // [cap] value bit patterns, then in 16 bits [cap] channels, [PX * NCH] positions
+    __shared__ int wave_sum[kBlock / 64];
+    const int cap = PX * NCH * CC, M = PX * NCH;
+    unsigned short *chan = reinterpret_cast<unsigned short *>(stage + cap), *pos = chan + cap;   // (cap is below 10500)
+    const int base = start[blockIdx.x];
+    // the entries past the last stored one (readers fetch a few positions ahead) and the last pointer
+    if (blockIdx.x == 0 && (int)threadIdx.x <= spare) {
+        const int total = start[gridDim.x];
+        if ((int)threadIdx.x == spare) {
+            cptr[npix * NCH] = total;
+        } else {
+            cidx[total + threadIdx.x] = 0u;
+            xval[total + threadIdx.x] = 0.0f;
+        }
+    }
+    const long long p0 = (long long)blockIdx.x * PX;
+    const int px = threadIdx.x % PX, sj = threadIdx.x / PX, SJ = kBlock / PX;
+    const long long p = p0 + px;
+    const bool live = p < npix;
+    const float *xp = live ? x + p / HW * C * HW + p % HW : x;
+    auto load = [&](int j, float(&v)[CC]) {
+#pragma unroll
+        for (int u = 0; u < CC; ++u) {
+            const int ch = j * CC + u;
+            v[u] = live && j < NCH && ch < C ? xp[(long long)ch * HW] : 0.0f;
+        }
+    };
+    auto count = [&](int j, const float(&v)[CC]) {
+        int c = 0;
+#pragma unroll
+        for (int u = 0; u < CC; ++u) c += v[u] != 0.0f ? 1 : 0;
+        if (j < NCH) pos[px * NCH + j] = (unsigned short)c;
+    };
+    auto place = [&](int j, const float(&v)[CC]) {
+        int o = j < NCH ? pos[px * NCH + j] : 0;
+#pragma unroll
+        for (int u = 0; u < CC; ++u)
+            if (v[u] != 0.0f) {
+                chan[o] = (unsigned short)(j * CC + u);
+                stage[o] = __float_as_uint(v[u]);
+                ++o;
+            }
+    };
+    float kept[kKept][CC];
+#pragma unroll
+    for (int r = 0; r < kKept; ++r) load(sj + r * SJ, kept[r]);
+#pragma unroll
+    for (int r = 0; r < kKept; ++r) count(sj + r * SJ, kept[r]);
+    for (int j = sj + kKept * SJ; j < NCH; j += SJ) {
+        float v[CC];
+        load(j, v);
+        count(j, v);
+    }
+    __syncthreads();
+    // counts -> positions in the group's range: a run of them per thread
+    const int per = (M + kBlock - 1) / kBlock, a = (int)threadIdx.x * per, b = a + per < M ? a + per : M;
+    int s = 0;
+    for (int i = a; i < b; ++i) s += pos[i];
+    const int incl = wave_inclusive(s);
+    if (lane_id() == 63) wave_sum[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    int run = incl - s, total = 0;
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) {
+        if (i < (int)(threadIdx.x >> 6)) run += wave_sum[i];
+        total += wave_sum[i];
+    }
+    for (int i = a; i < b; ++i) {
+        const int c = pos[i];
+        pos[i] = (unsigned short)run;
+        run += c;
+    }
+    __syncthreads();
+    const int m = (int)((p0 + PX < npix ? p0 + PX : npix) - p0) * NCH;
+    for (int i = threadIdx.x; i < m; i += kBlock) cptr[p0 * NCH + i] = base + pos[i];
+#pragma unroll
+    for (int r = 0; r < kKept; ++r) place(sj + r * SJ, kept[r]);
+    for (int j = sj + kKept * SJ; j < NCH; j += SJ) {
+        float v[CC];
+        load(j, v);
+        place(j, v);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < total; t += kBlock) {
+        cidx[base + t] = chan[t];
+        xval[base + t] = __uint_as_float(stage[t]);
     }
 }
 
@@ -543,28 +618,47 @@ hipError_t launch_plan_fill_dense(const int *rowptr, const uint32_t *idx, const 
     return hipGetLastError();
 }
 
-hipError_t launch_input_count(const float *x, int N, int C, int H, int W, int CC, int NCH, int *cnt,
-                              hipStream_t st)
+// LDS bytes of the fill pass per pixel and step: 6 per possible entry, 2 for its position
+constexpr int kFillBytes = kSiCC * 6 + 2;
+// pixels per work-group: as many (up to 32) as fit 64 KB; 0: too many channels, not served
+static int input_pixels(int NCH)
 {
-    const long long HW = (long long)H * W, npix = (long long)N * HW;
-    hipLaunchKernelGGL(input_count_kernel, dim3(blocks_for(npix, kBlock), NCH), dim3(kBlock), 0, st, x, C,
-                       HW, npix, CC, NCH, cnt);
-    return hipGetLastError();
+    int PX = 32;
+    while (PX > 0 && (long long)PX * NCH * kFillBytes > 65536) PX /= 2;
+    return PX;
 }
 
-hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int CC, int NCH,
-                             const int *cptr, uint32_t *cidx, float *xval, int spare, hipStream_t st)
+long long input_groups(long long npix, int NCH)
 {
-    const long long HW = (long long)H * W, npix = (long long)N * HW;
-    if (spare > kBlock) return hipErrorInvalidValue;
-    // pixels per work-group: as many (up to 32) as keep the LDS image of their lists, 8 bytes per
-    // possible entry, within 64 KB
-    int PX = 32;
-    while (PX > 1 && (long long)PX * NCH * CC * 8 > 65536) PX /= 2;
-    const long long lds = (long long)PX * NCH * CC * 8;
-    if (lds > 65536) return hipErrorInvalidValue;   // more than 8192 channels: not served
-    hipLaunchKernelGGL(input_fill_kernel, dim3(blocks_for(npix, PX)), dim3(kBlock), (size_t)lds, st, x, C,
-                       HW, npix, CC, NCH, PX, cptr, cidx, xval, spare);
+    const int PX = input_pixels(NCH);
+    return PX ? (npix + PX - 1) / PX : 0;
+}
+
+long long input_scratch_elems(long long npix, int NCH)
+{
+    const long long g = input_groups(npix, NCH);
+    return 2 * g + 1 + scan_tmp_elems(g);
+}
+
+hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
+                             hipStream_t st)
+{
+    const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
+    if (g == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(input_sum_kernel, dim3((unsigned)g), dim3(kBlock), 0, st, x, cnt, C, HW, npix, NCH,
+                       input_pixels(NCH), scratch + g + 1);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, st);
+}
+
+hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
+                             uint32_t *cidx, float *xval, int spare, hipStream_t st)
+{
+    const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
+    if (g == 0 || spare >= kBlock) return hipErrorInvalidValue;
+    const int PX = input_pixels(NCH);
+    hipLaunchKernelGGL(input_fill_kernel, dim3((unsigned)g), dim3(kBlock), (size_t)PX * NCH * kFillBytes, st, x, C,
+                       HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare);
     return hipGetLastError();
 }
 

@@ -132,8 +132,8 @@ struct fscnn_input {
     float *xval;     // device [nnz]
     int *cptr;       // device [N*H*W*NCH + 1]: cptr[p*NCH + j] = first entry of pixel p with
                      // c >= j*CC; pixel p's row is [cptr[p*NCH], cptr[(p+1)*NCH])
-    // the two device allocations behind the arrays: pointers (and the counts they were scanned
-    // from), then indices and values
+    // the device allocations behind the arrays: pointers (and the scratch they are made from), then
+    // indices and values (null where they are part of the first: small or emitted activations)
     void *ptr_block, *node_block;
     // a handle made by an emitting convolution has ONE allocation (ptr_block) of emit_bytes, sized
     // for the worst case, with room for the dense result iff emit_has_y; 0 for other handles
@@ -174,11 +174,16 @@ hipError_t launch_plan_fill(const int *rowptr, const uint32_t *idx, const float 
 hipError_t launch_plan_fill_dense(const int *rowptr, const uint32_t *idx, const float *val, int K, int C,
                                   int R, int S, const SfGeom &g, int NCH, int NG, long long nrec, Rec *recs,
                                   hipStream_t st);
-hipError_t launch_input_count(const float *x, int N, int C, int H, int W, int CC, int NCH, int *cnt,
-                              hipStream_t st);
-// also zeroes the `spare` entries that follow the last stored one (cptr's last element says where)
-hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int CC, int NCH,
-                             const int *cptr, uint32_t *cidx, float *xval, int spare, hipStream_t st);
+// Activation compression: launch_input_sums leaves where the lists of every group of input_pixels(NCH)
+// pixels start in scratch[0 .. input_groups] (the last one is the number of stored values); with cnt, the
+// counts per (pixel, step) are added up instead of x.  launch_input_fill then writes pointers and lists, and
+// zeroes the `spare` entries that follow the last stored one.
+long long input_groups(long long npix, int NCH);
+long long input_scratch_elems(long long npix, int NCH);   // ints
+hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
+                             hipStream_t st);
+hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
+                             uint32_t *cidx, float *xval, int spare, hipStream_t st);
 hipError_t launch_maxpool2x2(const float *x, int N, int C, int H, int W, float *y, int n4,
                              hipStream_t st);
 hipError_t launch_layout_convert(const float *src, int N, int C, int H, int W, int src_n4, float *dst,
