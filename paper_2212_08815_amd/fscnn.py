@@ -126,11 +126,13 @@ def _i(v):
 
 
 def conv2d_out_shape(H, W, R, S, stride=(1, 1), pad=(0, 0)):
-    # valid arguments here (the same arithmetic), anything else through the library's checks
+    # valid ints here (the same arithmetic), anything else through the library's checks and int()
     if H > 0 and W > 0 and R > 0 and S > 0 and stride[0] > 0 and stride[1] > 0 and pad[0] >= 0 and pad[1] >= 0:
         dh, dw = H + 2 * pad[0] - R, W + 2 * pad[1] - S
         if 0 <= dh < 1 << 30 and 0 <= dw < 1 << 30:
-            return dh // stride[0] + 1, dw // stride[1] + 1
+            ho, wo = dh // stride[0] + 1, dw // stride[1] + 1
+            if type(ho) is int and type(wo) is int:
+                return ho, wo
     ho, wo = ctypes.c_int(), ctypes.c_int()
     _check(lib().fscnn_conv2d_out_shape(_i(H), _i(W), _i(R), _i(S), _i(stride[0]), _i(stride[1]),
                                         _i(pad[0]), _i(pad[1]), ctypes.byref(ho), ctypes.byref(wo)),

@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -33,6 +34,9 @@ def test_out_shape_and_status_strings(L):
     assert fscnn.conv2d_out_shape(224, 224, 3, 3, (1, 1), (1, 1)) == (224, 224)
     assert fscnn.conv2d_out_shape(7, 8, 3, 3, (2, 2), (0, 0)) == (3, 3)
     assert fscnn.conv2d_out_shape(5, 9, 5, 1, (1, 3), (0, 0)) == (1, 3)
+    # numbers that are no Python ints are taken by their integer value
+    got = fscnn.conv2d_out_shape(9, 9, 3, 3, (2.0, np.int64(2)), (1.0, 0))
+    assert got == (5, 4) and all(type(v) is int for v in got)
     for bad in [(0, 5, 3, 3, 1, 1, 0, 0), (5, 5, 3, 3, 0, 1, 0, 0), (5, 5, 3, 3, 1, 1, -1, 0),
                 (2, 5, 3, 3, 1, 1, 0, 0)]:
         ho, wo = ctypes.c_int(), ctypes.c_int()
