@@ -104,8 +104,8 @@ fscnn_status_t fscnn_filter_prepare(fscnn_filter_t *f, int N, int H, int W, int 
  * fscnn_conv2d_sparse_filter_ex / _pool2x2 / _leaky), to be issued on `stream`: builds the plan
  * of the configuration that call will resolve to and, when the call is small enough to run in
  * the channel-split mode (input channels divided over several work-groups, each storing its
- * partial sums into a scratch copy of the output that a finishing pass adds up in a fixed
- * order), that mode's scratch for `stream`.  Afterwards such calls on `stream` allocate nothing
+ * partial sums into scratch, which the last one to arrive adds up in a fixed order), that
+ * mode's scratch for `stream`.  Afterwards such calls on `stream` allocate nothing
  * and do not synchronise, which is what a caller that captures them into a HIP graph needs.
  * Without this call the first split-mode call of a handle on a stream allocates its scratch. */
 fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, int stride_h,
@@ -170,10 +170,10 @@ fscnn_status_t fscnn_sf_band_choice(int variant, int N, int Ho, int n4, int pool
  *                  (+ bias_dev[k] if bias_dev != NULL) (then max(.,0) if relu != 0).
  * x_dev: N x C x H x W, y_dev: N x K x Ho x Wo (must not alias x), bias_dev: K or NULL.
  * fp32 accumulation in an order fixed by the plan: results are run-to-run identical.  For small
- * problems (at most 128 work-groups with the automatic configuration) the input-channel range is
- * split over several work-groups; each stores its partial sums into a copy of its own (scratch
- * that belongs to the handle's plan, one buffer per stream) and a finishing pass adds the copies
- * in the order of the parts, so this mode is reproducible too, but its sums are grouped
+ * problems with the automatic configuration the input-channel range is split over several
+ * work-groups; each stores its partial sums into a copy of its own (scratch that belongs to the
+ * handle's plan, one buffer per stream) and the last one to arrive adds the copies in the order
+ * of the parts, so this mode is reproducible too, but its sums are grouped
  * differently from those of an explicitly selected configuration (fscnn_conv2d_sparse_filter_v /
  * _ex with variant > 0), which never splits.
  * The batch may be of any size that N, and the number of work-groups, hold as an int: images are
