@@ -130,7 +130,7 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
             delete p;
             return ds;
         }
-        hipError_t e = hipMalloc(&p->packed, sizeof(float) * (size_t)contract_packed_elems(f->K, f->C, f->R * f->S));
+        hipError_t e = hipMalloc(&p->packed, sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
         if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);   // the plan may be used from other streams
         if (e != hipSuccess) {
@@ -571,7 +571,9 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (variant == 0 && !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, v, &pick)) {
         s = get_plan(f, kContractPlan, st, &p);
         if (s != FSCNN_OK) return s;
-        FSCNN_HIP(launch_contract_dense(x_dev, p->packed, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,
+        // (the tiled gather kernels multiply entries outside the image by zeros as well)
+        const int *wflag = v < 0 ? reinterpret_cast<const int *>(p->packed + contract_packed_elems(f->K, f->C, f->R * f->S)) : nullptr;
+        FSCNN_HIP(launch_contract_dense(x_dev, p->packed, wflag, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,
                                         Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, pick, st));
         return FSCNN_OK;
     }

@@ -32,7 +32,8 @@
 // Non-finite operands: a gather never multiplies an entry that is not stored, so 0 * Inf cannot
 // appear there.  Dense tensors are checked while they are staged (a stripe that holds an Inf or NaN
 // makes the work-group recompute its tile the slow way, walking the stored entries); filter banks
-// that meet compressed activations likewise.
+// that meet compressed activations likewise, and those of calls that the direct kernel would serve: it
+// skips the entries that fall outside the image, which meet staged zeros here.
 #include <type_traits>
 
 #include "internal.h"
@@ -56,7 +57,7 @@ struct DcArgs {
     const uint32_t *cidx;
     const float *xval;
     const float *w;
-    const int *wflag;                    // kWPacked with lists: non-zero if the bank holds an Inf or NaN
+    const int *wflag;                    // kWPacked: non-zero if the bank holds an Inf or NaN; NULL: it does not matter
     const int *rowptr;                   // dense source: the stored entries, for the slow way
     const uint32_t *idx;
     const float *val;
@@ -457,7 +458,7 @@ __global__ void __launch_bounds__(G::NTH, G::WPE) contract_kernel(const DcArgs a
         }
     }
     bool bad = top >= 0x7f800000u;
-    if (G::SRC == kSrcLists && G::WSRC == kWPacked) bad = *a.wflag != 0;
+    if (G::WSRC == kWPacked && a.wflag) bad |= *a.wflag != 0;
     const bool slow = __syncthreads_or(bad ? 1 : 0) != 0;
     if (ks != 0) return;
 
@@ -480,16 +481,19 @@ __global__ void __launch_bounds__(G::NTH, G::WPE) contract_kernel(const DcArgs a
     }
 }
 
-// packed copy of a compressed bank (zero-filled before)
+// packed copy of a compressed bank (zero-filled before); *flag (likewise): set if an Inf or NaN is met
 __global__ void __launch_bounds__(256) pack_rows_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
                                                         const float *__restrict__ val, int RS, int nslice,
-                                                        float *__restrict__ packed)
+                                                        float *__restrict__ packed, int *__restrict__ flag)
 {
     const int k = blockIdx.x;
+    uint32_t top = 0;
     for (int i = rowptr[k] + (int)threadIdx.x; i < rowptr[k + 1]; i += 256) {
         const int c = (int)(idx[i] / (uint32_t)RS), rs = (int)(idx[i] % (uint32_t)RS);
+        see(top, val[i]);
         packed[contract_packed_index(k, c, rs, RS, nslice)] = val[i];
     }
+    if (top >= 0x7f800000u) *flag = 1;
 }
 
 // packed copy of a dense K x C x 3 x 3 bank, and the copy wT[c][tap][Kpad] the gather kernel reads: a
@@ -620,9 +624,10 @@ ContractPick contract_pick(int N, int C, int K, int H, int W, int R, int S, int 
 hipError_t launch_pack_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS,
                             float *packed, hipStream_t st)
 {
-    const long long n4 = contract_packed_elems(K, C, RS) / 4;
+    const long long n4 = contract_packed_elems(K, C, RS) / 4 + 1;   // with the flag behind it
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, reinterpret_cast<float4 *>(packed), n4);
-    hipLaunchKernelGGL(pack_rows_kernel, dim3(K), dim3(256), 0, st, rowptr, idx, val, RS, (C + 15) / 16, packed);
+    hipLaunchKernelGGL(pack_rows_kernel, dim3(K), dim3(256), 0, st, rowptr, idx, val, RS, (C + 15) / 16, packed,
+                       reinterpret_cast<int *>(packed + (n4 - 1) * 4));
     return hipGetLastError();
 }
 
@@ -635,14 +640,14 @@ hipError_t launch_pack_dense(const float *w, int K, int C, int Kpad, float *pack
     return hipGetLastError();
 }
 
-hipError_t launch_contract_dense(const float *x, const float *packed, const int *rowptr, const uint32_t *idx,
+hipError_t launch_contract_dense(const float *x, const float *packed, const int *wflag, const int *rowptr, const uint32_t *idx,
                                  const float *val, int N, int C, int H, int W, int K, int R, int S, int Ho, int Wo,
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st)
 {
     if (p.cfg < 0) return hipErrorInvalidValue;
     DcArgs a = {};
-    a.x = x; a.w = packed; a.nslice = (C + 15) / 16; a.rowptr = rowptr; a.idx = idx; a.val = val; a.bias = bias; a.y = y;
+    a.x = x; a.w = packed; a.wflag = wflag; a.nslice = (C + 15) / 16; a.rowptr = rowptr; a.idx = idx; a.val = val; a.bias = bias; a.y = y;
     a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.R = R; a.S = S; a.Ho = Ho; a.Wo = Wo;
     a.sh = sh; a.sw = sw; a.ph = ph; a.pw = pw; a.act = act;
     if (R == 3 && S == 3) return launch_any<kSrcDense, kWPacked, 9>(a, p, st);

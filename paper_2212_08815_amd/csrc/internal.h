@@ -77,7 +77,8 @@ struct SfPlan {
     };
     std::vector<SplitScratch> split;
     // The plan of the contraction on the matrix cores (variant kContractPlan): the bank as a dense
-    // packed array (contract_packed_index), zeros where nothing is stored.
+    // packed array (contract_packed_index), zeros where nothing is stored; behind it an int that is
+    // non-zero if a stored value is Inf or NaN (16 bytes).
     float *packed = nullptr;
 };
 constexpr int kDirectPlan = -1, kContractPlan = -2;
@@ -228,6 +229,7 @@ __host__ __device__ inline long long contract_packed_index(int k, int c, int rs,
 {
     return (((long long)(k >> 4) * nslice + (c >> 4)) * RS + rs) * 256 + ((c >> 2) & 3) * 64 + (k & 15) * 4 + (c & 3);
 }
+// (without the flag that follows a compressed bank's copy)
 inline long long contract_packed_elems(int K, int C, int RS)
 {
     return (long long)((K + 63) / 64 * 4) * ((C + 15) / 16) * RS * 256;
@@ -236,7 +238,8 @@ hipError_t launch_pack_rows(const int *rowptr, const uint32_t *idx, const float 
                             float *packed, hipStream_t st);
 // both copies of a dense K x C x 3 x 3 bank (Kpad a multiple of 64) and its non-finite flag (16 bytes are cleared)
 hipError_t launch_pack_dense(const float *w, int K, int C, int Kpad, float *packed, float *wT, int *flag, hipStream_t st);
-hipError_t launch_contract_dense(const float *x, const float *packed, const int *rowptr, const uint32_t *idx,
+// wflag: the packed bank's flag, if it is set every output is made entry by entry; NULL: not looked at
+hipError_t launch_contract_dense(const float *x, const float *packed, const int *wflag, const int *rowptr, const uint32_t *idx,
                                  const float *val, int N, int C, int H, int W, int K, int R, int S, int Ho, int Wo,
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st);

@@ -63,6 +63,15 @@ def test_only_stored_entries_meet_non_finite_values(F):
     got = F.conv2d_sparse_filter(F.filter_compress(dev(wt)), dev(x), (1, 1), (1, 1), dev(b), False).cpu().numpy()
     assert np.array_equal(np.isfinite(got), ~met) and np.array_equal(got[~met], want[~met])
     assert 0 < met.sum() < met.size
+    # an extent that only the direct kernel serves otherwise: entries outside the image meet nothing, so an
+    # Inf weight gives Inf or a finite sum there and no NaN
+    x, wt, b = inputs.random_layer(9, 2, c, k, 24, 19, 5, 5, 0.8, integer=True)
+    x = np.abs(x) + 1
+    wt[3, 7, 0, 0] = np.inf                                         # meets x at (oy - 2, ox - 2)
+    want = oracle.conv2d_dense(x, np.where(np.isinf(wt), 0, wt).astype(np.float32), (1, 1), (2, 2), b, False)
+    want[:, 3, 2:, 2:] = np.inf
+    got = F.conv2d_sparse_filter(F.filter_compress(dev(wt)), dev(x), (1, 1), (2, 2), dev(b), False).cpu().numpy()
+    assert np.array_equal(got, want)
     # compressed activation, Inf in the bank: outputs whose taps at that channel are all zero stay finite
     x, wt, b = inputs.random_layer(8, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)
     x[0, 11, :7] = 0.0
