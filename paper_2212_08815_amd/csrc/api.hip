@@ -58,13 +58,82 @@ bool live(const fscnn_dense_t *d) { return d && d->magic == kDenseMagic; }
 // Share of a bank's entries that are stored (1 exactly for a bank without zeros).
 double density(const fscnn_filter_t *f) { return (double)f->nnz / ((double)f->K * f->C * f->R * f->S); }
 
-void free_plan(SfPlan *p)
+// Buffers of the channel-split mode that destroyed handles leave behind, for the next handles: releasing an
+// allocation of some MB takes the runtime up to 290 us (small ones: 2 us), and a program that compresses
+// its banks for one pass makes a dozen (13-layer stack, N = 1, a load and a pass: at 160x160 2.66 ms
+// with them released, 1.29 kept; at 224x224 2.99 and 1.43).  At most kPoolBytes and kPoolBuffers
+// are held; all of it is given back when an allocation fails.  A buffer enters after its handle's records
+// were released, which waits for the device, so no launch still uses it; it leaves for one (plan, stream).
+constexpr size_t kPoolBytes = 64u << 20, kPoolBuffers = 64;
+struct SplitPool {
+    struct Entry {
+        int device;
+        float *buf;
+        size_t bytes;
+    };
+    std::mutex mu;
+    std::vector<Entry> free;
+    size_t held = 0;
+
+    // the smallest that is large enough, up to four times what is needed
+    bool take(int device, size_t bytes, float **buf, size_t *got)
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        size_t best = free.size();
+        for (size_t i = 0; i < free.size(); ++i)
+            if (free[i].device == device && free[i].bytes >= bytes && free[i].bytes / 4 <= bytes &&
+                (best == free.size() || free[i].bytes < free[best].bytes))
+                best = i;
+        if (best == free.size()) return false;
+        *buf = free[best].buf;
+        *got = free[best].bytes;
+        held -= free[best].bytes;
+        free[best] = free.back();
+        free.pop_back();
+        return true;
+    }
+    bool give(int device, float *buf, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (held + bytes > kPoolBytes || free.size() >= kPoolBuffers) return false;
+        free.push_back({device, buf, bytes});
+        held += bytes;
+        return true;
+    }
+    void trim()
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        for (auto &q : free) (void)hipFree(q.buf);
+        free.clear();
+        held = 0;
+    }
+};
+SplitPool &split_pool()
+{
+    static SplitPool *pool = new SplitPool();   // (never destroyed: handles may outlive static objects)
+    return *pool;
+}
+
+// hipMalloc that gives the pool back before it fails
+hipError_t device_alloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    split_pool().trim();
+    return hipMalloc(p, bytes);
+}
+
+// device: where the plan's buffers live
+void free_plan(SfPlan *p, int device)
 {
     if (!p) return;
-    if (p->recs) (void)hipFree(p->recs);   // with the pointers behind the records
+    const bool idle = p->recs && hipFree(p->recs) == hipSuccess;   // with the pointers behind the records; waits for the device
     if (p->packed) (void)hipFree(p->packed);
+    int dev = -1;
+    const bool keep = idle && hipGetDevice(&dev) == hipSuccess && dev == device;
     for (auto &sc : p->split)
-        if (sc.buf) (void)hipFree(sc.buf);
+        if (sc.buf && !(keep && split_pool().give(device, sc.buf, sc.bytes))) (void)hipFree(sc.buf);
     delete p;
 }
 
@@ -83,7 +152,8 @@ fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_
         return FSCNN_OK;
     }
     float *nb = nullptr;
-    hipError_t e = hipMalloc(&nb, bytes);
+    hipError_t e = hipSuccess;
+    if (!split_pool().take(f->device, bytes, &nb, &bytes)) e = device_alloc(reinterpret_cast<void **>(&nb), bytes);
     if (e == hipSuccess) e = launch_split_clear(nb, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -130,12 +200,12 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
             delete p;
             return ds;
         }
-        hipError_t e = hipMalloc(&p->packed, sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
+        hipError_t e = device_alloc(reinterpret_cast<void **>(&p->packed), sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
         if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);   // the plan may be used from other streams
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            free_plan(p);
+            free_plan(p, f->device);
             return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
         }
         f->plans.push_back(p);
@@ -167,7 +237,7 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
     }
     // one allocation: the records, the pointers, and the counts the pointers are scanned from
     const size_t nrecs = (size_t)(cap + kPlanSpare);
-    hipError_t e = hipMalloc(&p->recs, sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)));
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&p->recs), sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)));
     int *cnt = nullptr;
     if (e == hipSuccess) {
         p->segptr = reinterpret_cast<int *>(p->recs + nrecs);
@@ -184,7 +254,7 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_plan(p);
+        free_plan(p, f->device);
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
     }
     p->nrec = cap;
@@ -349,7 +419,7 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     int *cnt = nullptr;
     int total = 0;
     // two allocations: the pointers with the counts they are scanned from, and the nodes
-    hipError_t e = hipMalloc(&f->rowptr, sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)));
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&f->rowptr), sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)));
     if (e == hipSuccess) cnt = f->rowptr + (K + 1);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, st);
     if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, st);
@@ -359,7 +429,7 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     if (e == hipSuccess) {
         f->nnz = total;
         const size_t n = total > 0 ? (size_t)total : 1;
-        e = hipMalloc(&f->idx, (sizeof(uint32_t) + sizeof(float)) * n);
+        e = device_alloc(reinterpret_cast<void **>(&f->idx), (sizeof(uint32_t) + sizeof(float)) * n);
         if (e == hipSuccess) f->val = reinterpret_cast<float *>(f->idx + n);
     }
     if (e == hipSuccess) e = launch_filter_pack(w_dev, K, row, f->rowptr, f->idx, f->val, st);
@@ -502,7 +572,7 @@ fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f)
     if (!f) return FSCNN_ERR_NULL;
     if (!live(f)) return FSCNN_ERR_HANDLE;
     f->magic = 0;
-    for (SfPlan *p : f->plans) free_plan(p);
+    for (SfPlan *p : f->plans) free_plan(p, f->device);
     f->plans.clear();
     if (f->rowptr) (void)hipFree(f->rowptr);
     if (f->idx) (void)hipFree(f->idx);
@@ -709,7 +779,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     auto val_at = [&](size_t n) { return up(n * sizeof(uint32_t)); };
     const size_t most = (size_t)(npix * C) + kSiSpare;
     const bool whole = npix * C * 8 <= kWholeBytes;
-    hipError_t e = hipMalloc(&in->ptr_block, nodes_at + (whole ? val_at(most) + most * sizeof(float) : 0));
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at + (whole ? val_at(most) + most * sizeof(float) : 0));
     int *scratch = nullptr;
     auto fill = [&](void *nodes, size_t n) {
         in->cidx = static_cast<uint32_t *>(nodes);
@@ -730,7 +800,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         in->nnz = total;
         if (!whole) {
             const size_t n = (size_t)total + kSiSpare;
-            e = hipMalloc(&in->node_block, val_at(n) + n * sizeof(float));
+            e = device_alloc(reinterpret_cast<void **>(&in->node_block), val_at(n) + n * sizeof(float));
             if (e == hipSuccess) e = fill(in->node_block, n);
         }
     }
@@ -854,7 +924,7 @@ fscnn_status_t fscnn_conv2d_sparse_filter_emit(fscnn_filter_t *f, const float *x
     const EmitLayout L = emit_layout((long long)N * Ho * Wo, f->K, NCH);
     in->emit_bytes = L.bytes(y_dev == nullptr);
     in->emit_has_y = y_dev == nullptr;
-    hipError_t e = hipMalloc(&in->ptr_block, in->emit_bytes);
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), in->emit_bytes);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&in->filled, hipEventDisableTiming);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -991,7 +1061,7 @@ fscnn_status_t fscnn_dense_filter_prepare(const float *w_dev, int K, int C, int 
     const size_t words = (size_t)Kpad * C * R * S;
     const bool pack = R == 3 && S == 3;   // what the prepared calls serve
     const size_t packed = pack ? (size_t)Kpad * ((C + 15) / 16 * 16) * 9 : 0;
-    hipError_t e = hipMalloc(&d->wT, sizeof(float) * (words + packed) + 256);
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&d->wT), sizeof(float) * (words + packed) + 256);
     d->packed = pack ? d->wT + words : nullptr;
     d->flag = pack ? reinterpret_cast<int *>(d->packed + packed) : nullptr;
     if (e == hipSuccess)
