@@ -69,7 +69,7 @@ def build_host_sanitized(verbose=True):
             print(out)
         if rc != 0:
             raise RuntimeError("hipcc failed on %s" % src)
-    subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-fsanitize=address",
+    subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-sanitize", "-fsanitize=address",
                            "-fsanitize=undefined", "-shared-libsan", "-o", SAN_LIB] + objs)
     return SAN_LIB
 
