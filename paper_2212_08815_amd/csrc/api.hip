@@ -296,39 +296,51 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
 }
 
 // Whether an automatic call is served by the contraction on the matrix cores instead of the resolved
-// gather configuration (or the direct kernel), by its estimated time against theirs.  The small gather
-// configurations have a model of their own, the others take 15 to 25 us plus the stored entries'
-// multiply-adds at 40 TFLOP/s (measured: 512 -> 512 at 28x28, N = 8: 140 / 236 / 500 us at 10 / 20 /
-// 50 % stored against 255 us contracted), the direct kernel multiplies and adds at under 1 TFLOP/s.
+// gather configuration (or the direct kernel), which takes gather_us: by their estimated times (512 -> 512 at
+// 28x28, N = 8, measured: 126 / 217 / 320 / 500 us at 10 / 20 / 30 / 50 % stored against 250 us contracted).
 // Fewer than 16 input channels leave most of a slice idle (an RGB layer at 224x224, N = 1: 23 us gathered,
-// 50 contracted).  Plain NCHW calls only.  Call with the handle's lock not held.
-bool contracts(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int resolved, ContractPick *pick)
+// 50 contracted).  Plain NCHW calls only.
+bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int resolved, double gather_us,
+               ContractPick *pick)
 {
-    const double macs = (double)f->nnz * Ho * Wo * N, dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
-    int band_shift, band_h;
-    sf_choose_bands(resolved, N, Ho, false, false, &band_shift, &band_h);
-    const double small = sf_small_seconds(resolved, N << band_shift, f->C, f->K, band_h, Wo, density(f));
-    const double gather = resolved < 0 ? 4e-6 + 2 * macs / 1e12 : small > 0 ? small : 15e-6 + 2 * macs / 40e12;
+    const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N, gather = 1e-6 * gather_us;
     if (2 * dense / 150e12 + 4e-6 > gather || (resolved > 0 && f->C < 16)) return false;
-    const int key[7] = {N, H, W, sh, sw, Ho, Wo};
-    std::lock_guard<std::mutex> lock(f->mu);
-    for (const auto &c : f->choices)
-        if (memcmp(c.key, key, sizeof key) == 0) {
-            *pick = c.pick;
-            return c.use;
-        }
     *pick = contract_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw);
-    fscnn_filter::Choice c;
-    memcpy(c.key, key, sizeof key);
-    c.pick = *pick;
-    c.use = pick->cfg >= 0 && pick->seconds < (resolved < 0 ? gather : 0.85 * gather);   // (the models are not better than that)
-    if (f->choices.size() < 8) {
-        f->choices.push_back(c);
-    } else {
-        f->choices[f->next_choice] = c;
-        f->next_choice = (f->next_choice + 1) % 8;
+    return pick->cfg >= 0 && pick->seconds < (resolved < 0 ? gather : 0.85 * gather);   // (the models are not better than that)
+}
+
+// How a call is served.  An explicitly selected configuration runs as it is; the automatic choice is
+// remembered for the geometry (evaluating the models takes up to 3 us).  Call with the handle's lock not held.
+fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int in4, int out4, int pool,
+                          int variant, bool emit, SfRoute *r)
+{
+    const int key[8] = {N, H, W, sh, sw, Ho, Wo, (in4 ? 1 : 0) | (out4 ? 2 : 0) | (pool ? 4 : 0) | (emit ? 8 : 0)};
+    if (variant == 0) {
+        std::lock_guard<std::mutex> lock(f->mu);
+        for (const auto &c : f->routes)
+            if (memcmp(c.key, key, sizeof key) == 0) {
+                *r = c;
+                return FSCNN_OK;
+            }
     }
-    return c.use;
+    *r = SfRoute();
+    fscnn_status_t s = resolve_variant(f, N, H, W, sh, sw, variant, &r->variant, in4 || out4, pool != 0);
+    if (s != FSCNN_OK) return s;
+    sf_choose_bands(r->variant, N, Ho, in4 || out4, pool != 0, &r->band_shift, &r->band_h);
+    if (variant != 0) return FSCNN_OK;
+    memcpy(r->key, key, sizeof key);
+    double us = sf_direct_us(N, f->K, Ho, Wo, f->nnz);
+    if (r->variant > 0)
+        r->csplit = sf_choose_csplit(r->variant, N << r->band_shift, f->C, f->K, r->band_h, Wo, density(f), in4, emit, &us);
+    r->contract = !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, r->variant, us, &r->pick);
+    std::lock_guard<std::mutex> lock(f->mu);
+    if (f->routes.size() < 8) {
+        f->routes.push_back(*r);
+    } else {
+        f->routes[f->next_route] = *r;
+        f->next_route = (f->next_route + 1) % 8;
+    }
+    return FSCNN_OK;
 }
 
 // Number of stored values of a compressed activation.  A handle made without a host synchronisation
@@ -487,24 +499,18 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     fscnn_status_t s = out_shape(H, W, f->R, f->S, sh, sw, ph, pw, &Ho, &Wo);
     if (s != FSCNN_OK) return s;
     const int in4 = x_layout == FSCNN_LAYOUT_N4, out4 = y_layout == FSCNN_LAYOUT_N4;
-    int v;
-    s = resolve_variant(f, N, H, W, sh, sw, variant, &v, in4 || out4, pool != 0);
+    SfRoute r;
+    s = route_call(f, N, H, W, sh, sw, Ho, Wo, in4, out4, pool, variant, false, &r);
     if (s != FSCNN_OK) return s;
-    if ((in4 || out4 || pool) && v < 0) return FSCNN_ERR_UNSUPPORTED;
-    if (v > 0 && !sf_variant_has_layout(v, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
+    if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
+    if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
     SfPlan *p;
-    ContractPick pick;
-    if (variant == 0 && !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, v, &pick))
-        return get_plan(f, kContractPlan, (hipStream_t)stream, &p);
-    s = get_plan(f, v, (hipStream_t)stream, &p);
+    if (r.contract) return get_plan(f, kContractPlan, (hipStream_t)stream, &p);
+    s = get_plan(f, r.variant, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p->direct) return s;
-    // the same decisions as the convolution call takes
-    int band_shift, band_h;
-    sf_choose_bands(v, N, Ho, in4 || out4, pool != 0, &band_shift, &band_h);
-    const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->C, f->K, band_h, Wo, p->NCH, density(f)) : 1;
-    if (csplit > 1) {
+    if (r.csplit > 1) {
         float *parts;
-        s = split_scratch(f, p, (hipStream_t)stream, sf_split_bytes(p->g, csplit, N << band_shift, f->K, band_h, Wo), &parts);
+        s = split_scratch(f, p, (hipStream_t)stream, sf_split_bytes(p->g, r.csplit, N << r.band_shift, f->K, r.band_h, Wo), &parts);
     }
     return s;
 }
@@ -626,45 +632,40 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if ((in4 && !fits_int(4LL * C * H * W)) || (out4 && !fits_int(4LL * f->K * Ho * Wo)))
         return FSCNN_ERR_UNSUPPORTED;
     if (pool && (Ho < 2 || Wo < 2)) return FSCNN_ERR_SHAPE;   // empty pooled output
-    int v;
-    s = resolve_variant(f, N, H, W, sh, sw, variant, &v, in4 || out4, pool != 0);
+    SfRoute r;
+    s = route_call(f, N, H, W, sh, sw, Ho, Wo, in4, out4, pool, variant, emit_cnt != nullptr, &r);
     if (s != FSCNN_OK) return s;
-    if ((in4 || out4 || pool) && v < 0) return FSCNN_ERR_UNSUPPORTED;   // the direct kernel: NCHW, no pool
-    if (v > 0 && !sf_variant_has_layout(v, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
+    if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;   // the direct kernel: NCHW, no pool
+    if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
     int dev;
     s = have_device(&dev);
     if (s != FSCNN_OK) return s;
     if (dev != f->device) return FSCNN_ERR_MISMATCH;   // the handle's buffers live on another GPU
     hipStream_t st = (hipStream_t)stream;
     SfPlan *p;
-    ContractPick pick;
-    if (variant == 0 && !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, v, &pick)) {
+    if (r.contract) {
         s = get_plan(f, kContractPlan, st, &p);
         if (s != FSCNN_OK) return s;
         // (the tiled gather kernels multiply entries outside the image by zeros as well)
-        const int *wflag = v < 0 ? reinterpret_cast<const int *>(p->packed + contract_packed_elems(f->K, f->C, f->R * f->S)) : nullptr;
+        const int *wflag = r.variant < 0 ? reinterpret_cast<const int *>(p->packed + contract_packed_elems(f->K, f->C, f->R * f->S)) : nullptr;
         FSCNN_HIP(launch_contract_dense(x_dev, p->packed, wflag, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,
-                                        Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, pick, st));
+                                        Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, r.pick, st));
         return FSCNN_OK;
     }
-    s = get_plan(f, v, st, &p);
+    s = get_plan(f, r.variant, st, &p);
     if (s != FSCNN_OK) return s;
     if (p->direct) {
         FSCNN_HIP(launch_conv_sf_direct(f->rowptr, f->idx, f->val, x_dev, N, C, H, W, f->K, f->R,
                                         f->S, Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, st));
     } else {
-        // automatic choice only: an explicitly selected configuration runs as it is
-        int band_shift, band_h;
-        sf_choose_bands(v, N, Ho, in4 || out4, pool != 0, &band_shift, &band_h);
-        const int csplit = variant == 0 ? sf_choose_csplit(v, N << band_shift, f->C, f->K, band_h, Wo, p->NCH, density(f)) : 1;
         float *parts = nullptr;
-        if (csplit > 1) {
-            s = split_scratch(f, p, st, sf_split_bytes(p->g, csplit, N << band_shift, f->K, band_h, Wo), &parts);
+        if (r.csplit > 1) {
+            s = split_scratch(f, p, st, sf_split_bytes(p->g, r.csplit, N << r.band_shift, f->K, r.band_h, Wo), &parts);
             if (s != FSCNN_OK) return s;
         }
         int *cnt = (emit_cnt && !out4 && !pool) ? emit_cnt : nullptr;
         FSCNN_HIP(launch_conv_sf_tiled(*p, x_dev, N, C, H, W, f->K, Ho, Wo, ph, pw, bias_dev, relu,
-                                       y_dev, in4, out4, pool, csplit, parts, cnt, band_shift, band_h, st));
+                                       y_dev, in4, out4, pool, r.csplit, parts, cnt, r.band_shift, r.band_h, st));
         if (counted) *counted = cnt != nullptr;
     }
     return FSCNN_OK;

@@ -202,7 +202,8 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     // csplit > 1 (small problems): the input-channel chunks are divided among csplit
     // work-groups per (tile, channel group); every part leaves its accumulators in its own slot of
     // `parts`, and the one that arrives last adds the slots up in the order of the parts and goes on
-    // to the epilogue: one writer per output, the same bits on every run
+    // to the epilogue (without counters, a launch that follows does): one writer per output, the same bits
+    // on every run
     const int lid0 = xcd_remap(blockIdx.x, nblk);
     const int cs = lid0 % csplit;
     const int lid = lid0 / csplit;
@@ -659,6 +660,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
             const u64 v = (u64)__float_as_uint(af[2 * e]) | ((u64)__float_as_uint(af[2 * e + 1]) << 32);
             __hip_atomic_store(mine + e * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if (!arrived) return;   // split_finish_kernel adds the slots up
         wait_vmcnt<0>();
         __syncthreads();
         if (tid == 0) {
@@ -890,6 +892,73 @@ conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict
     y[(((long long)n * K + k) * Ho + oy) * Wo + ox] = acc;
 }
 
+// The sums of a channel split where a launch of its own is the faster way (split_by_launch): a wave adds up, in
+// the order of the parts, what the parts' waves of its number left, and stores the results as the
+// convolution kernel's epilogue does.
+template <class G>
+__global__ void __launch_bounds__(64)
+split_finish_kernel(const float *__restrict__ parts, int csplit, const float *__restrict__ bias, int N, int K, int Ho, int Wo,
+                    int relu, int NG, int tiles_x, int tiles_per_img, int band_shift, int band_h, float *__restrict__ y)
+{
+    static_assert(!G::POOL || G::NV % 2 == 0, "the merged pool pairs a lane's rows");
+    constexpr int E = G::SLOTS * G::P / 2;
+    const int lane = threadIdx.x, lid = blockIdx.x / G::WAVES, wave = blockIdx.x % G::WAVES;
+    float acc[G::SLOTS][G::P] = {};
+    float *af = &acc[0][0];
+    const float2 *src = reinterpret_cast<const float2 *>(parts) + ((long long)lid * csplit * G::WAVES + wave) * (E * 64) + lane;
+    for (int p = 0; p < csplit; ++p, src += G::WAVES * E * 64) {
+        float2 v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = src[e * 64];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            af[2 * e] += v[e].x;
+            af[2 * e + 1] += v[e].y;
+        }
+    }
+    const int t = (lid / NG) % tiles_per_img, n0 = (lid / (NG * tiles_per_img)) * G::IMGS;
+    const int ig = lane / (G::LW * G::LHR), lg = (lane / G::LW) % G::LHR;
+    const int lh = (G::LW == 16 && G::LHR == 4) ? (((lg & 1) << 1) | (lg >> 1)) : lg;
+    const int ox = (t % tiles_x) * G::TW + lane % G::LW, r0 = (t / tiles_x) * G::TH + lh * G::NV;   // row of the band
+    constexpr int D = G::POOL ? 2 : 1;
+    const int Hy = Ho / D, Wy = Wo / D, bh = band_h / D, px = ox / D;
+#pragma unroll
+    for (int j = 0; j < G::SLOTS; ++j) {
+        const int k = (lid % NG) * G::KG + wave * G::SLOTS + j;
+        if (k >= K) break;
+        const float bk = bias ? bias[k] : 0.0f;
+#pragma unroll
+        for (int v = 0; v < G::NV; v += D) {
+            const int py = (r0 + v) / D;
+            const bool ok = py < bh && px < Wy && ox % D == 0;
+            float r[G::BV];
+#pragma unroll
+            for (int b = 0; b < G::BV; ++b) {
+                float m = acc[j][v * G::BV + b];
+                if constexpr (G::POOL) {
+                    const float a = acc[j][(v + 1) * G::BV + b];
+                    m = a > m ? a : m;
+                    const float o = __shfl_xor(m, 1, 64);
+                    m = o > m ? o : m;
+                }
+                r[b] = act_apply(m + bk, relu);
+            }
+            if constexpr (G::OUT4) {
+                const int n = n0 + ig * 4;
+                if (ok && n < N)
+                    reinterpret_cast<float4 *>(y)[(((long long)(n / 4) * K + k) * Hy + py) * Wy + px] = make_float4(r[0], r[1], r[2], r[3]);
+            } else {
+#pragma unroll
+                for (int b = 0; b < G::BV; ++b) {
+                    const int slot = n0 + ig * G::BV + b, n = slot >> band_shift;
+                    const int oy = (slot & ((1 << band_shift) - 1)) * bh + py;
+                    if (ok && n < N && oy < Hy) y[(((long long)n * K + k) * Hy + oy) * Wy + px] = r[b];
+                }
+            }
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) clear_counters_kernel(int *p)
 {
     for (int i = threadIdx.x; i < kSplitGroups; i += 256) p[i] = 0;
@@ -923,7 +992,7 @@ hipError_t launch_tiled(const SfPlan &p, const float *x, int N, int C, int H, in
     const int tiles_x = (Wo + G::TW - 1) / G::TW;
     const int tiles_y = (band_h + G::TH - 1) / G::TH;
     const int nbat = ((N << band_shift) + G::IMGS - 1) / G::IMGS;
-    if (csplit < 1 || (csplit > 1 && (!G::SPLIT || !parts || !arrived))) return hipErrorInvalidValue;
+    if (csplit < 1 || (csplit > 1 && (!G::SPLIT || !parts)) || (emit_cnt && csplit > 1 && !arrived)) return hipErrorInvalidValue;
     const long long nblk = (long long)p.NG * tiles_x * tiles_y * nbat * csplit;
     // (a dispatch counts its work-items in 32 bits)
     if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * G::NT > 0xffffffffLL) return hipErrorInvalidValue;
@@ -933,6 +1002,11 @@ hipError_t launch_tiled(const SfPlan &p, const float *x, int N, int C, int H, in
                        x, y, bias, p.recs, p.segptr, N, C, H, W, K, Ho, Wo, ph, pw, relu, p.NCH,
                        p.NG, tiles_x, tiles_x * tiles_y, (int)nblk, csplit, parts, arrived, emit_cnt,
                        (unsigned long long)(uintptr_t)p.recs, band_shift, band_h);
+    if constexpr (G::SPLIT) {
+        if (csplit > 1 && !arrived)
+            hipLaunchKernelGGL(split_finish_kernel<G>, dim3((unsigned)(nblk / csplit * G::WAVES)), dim3(64), 0, st, parts, csplit, bias,
+                               N, K, Ho, Wo, relu, p.NG, tiles_x, tiles_x * tiles_y, band_shift, band_h, y);
+    }
     return hipGetLastError();
 }
 
@@ -946,6 +1020,7 @@ template <class G> SfGeom geom_of()
     g.DENSE = G::DENSE ? 1 : 0;
     g.lds_bytes = G::LDS_BYTES;
     g.SPLIT = G::SPLIT ? 1 : 0;
+    g.REGST = G::REGST ? 1 : 0;
     return g;
 }
 
@@ -1136,6 +1211,81 @@ static long long sf_blocks(const SfGeom &g, int N, int K, int Ho, int Wo)
     return tiles * ((K + g.KG - 1) / g.KG) * ((N + g.IMGS - 1) / g.IMGS);
 }
 
+// Estimated time of a launch, in microseconds, by a model fitted to sweeps over random geometries (N = 1..32,
+// 16..512 channels, 7..224 wide, 1 to 50 % stored).  A round of work-groups over the 256 CUs takes its first loads
+// and stores (F) and per chunk: a fixed part, its bytes through the path from the L2, and its records: P
+// multiply-adds each and a fetch.  Where two work-groups share a CU the second one of a round adds `second` of
+// it.  A split adds its parts' sums: see split_by_launch.  Standard deviation over the 11243 launches of the
+// register-staged configurations 12 %, over 4051 of the others through NCHW tensors 15 %, over 1235 through N4
+// tensors 13 %; among register-staged configurations and splits it picks one that takes 2 % more than
+// the best on average, 26 % at most.
+struct Cost {
+    double launch, F, chunk, kbyte, fma, fetch, second, last, finish, finish_mb;
+};
+constexpr Cost kCostReg = {3.01, 1.88, 0.238, 0.0248, 0.0069, 0.0271, 0.668, 1.41, 3.72, 0.264};
+constexpr Cost kCostNchw = {2.83, 5.51, 0.507, 0.0219, 0.0073, 0.0191, 0.744, 6.79, 2.58, 0.150};
+constexpr Cost kCostN4 = {2.02, 3.36, 0.501, 0.0089, 0.0040, 0.0411, 0.814, 3.98, 4.29, 0.143};
+constexpr int kSmallFirst = 35, kSmallLast = 43;   // the register-staged configurations
+static const Cost &cost_of(const SfGeom &g, bool in4) { return g.REGST ? kCostReg : in4 ? kCostN4 : kCostNchw; }
+
+// Bytes of accumulators of a work-group: what one part of a split leaves in memory.
+static double part_bytes(const SfGeom &g) { return 256.0 * g.WAVES * g.SLOTS * g.NV * g.BV; }
+
+// Whether the parts of a split are added up by a launch of their own: the last part to arrive reads them
+// at what one CU can take in (about 110 GB/s), a launch at what the chip can, but starts 2 us later.  Measured
+// over 1500 splits: up to 96 KB a work-group the last part is the faster by 0.2 us, at 128 KB the launch by
+// 1, at 512 KB by 3 to 4, at 1 MB by 9.
+static bool split_by_launch(const SfGeom &g, int csplit) { return csplit * part_bytes(g) >= 128 * 1024; }
+
+// groups: work-groups without a split; emit: the last part adds up, whatever there is (it counts the results)
+static double launch_us(const Cost &m, const SfGeom &g, int csplit, long long groups, int C, double density, bool emit)
+{
+    groups *= csplit;
+    const int NCH = (C + g.CC - 1) / g.CC, chunks = (NCH + csplit - 1) / csplit;
+    const double records = density * g.R * g.S * (C < g.CC ? C : g.CC) * g.SLOTS;
+    const double chunk = m.chunk + m.kbyte * g.lds_bytes / 2048 + records * (g.NV * g.BV * m.fma + m.fetch);
+    const bool pairs = 2 * g.lds_bytes <= 160 * 1024;
+    const long long full = groups / 512, rest = groups % 512;
+    const double rounds = !pairs ? (double)((groups + 255) / 256)
+                                 : full * (1 + m.second) + (rest > 256 ? 1 + m.second : rest > 0 ? 1 : 0);
+    double t = m.launch + rounds * (m.F + chunks * chunk);
+    if (csplit > 1)
+        t += split_by_launch(g, csplit) && !emit ? m.finish + m.finish_mb * groups * part_bytes(g) / (1 << 20)
+                                        : m.last * (1 + csplit * part_bytes(g) / 65536);
+    return t;
+}
+// The number of parts the input channels are split into (small problems: deep layers at small batch leave
+// most of the 256 CUs idle and serialise hundreds of channels in a few groups), and that launch's time.
+static int best_split(const Cost &m, const SfGeom &g, int N, int C, int K, int Ho, int Wo, double density, double *us,
+                      bool emit = false)
+{
+    const int NCH = (C + g.CC - 1) / g.CC;
+    int best = 1;
+    const long long groups = sf_blocks(g, N, K, Ho, Wo);
+    *us = launch_us(m, g, 1, groups, C, density, emit);
+    // (up to two rounds of work-groups, which bounds the scratch to 64 MB; the large tiles only where a round is far
+    // from full: 256 groups of configuration 4, 16 x 512 x 28 x 28 at 20 %, 388 us whole and 411 in halves)
+    const long long most = g.REGST ? kSplitGroups : 191;
+    for (int s = 2; g.SPLIT && groups <= most && s <= 8 && s <= NCH && groups * s <= 512; ++s) {
+        const double t = launch_us(m, g, s, groups, C, density, emit);
+        if (t < *us) { *us = t; best = s; }
+    }
+    return best;
+}
+static int choose_small(int N, int C, int K, int Ho, int Wo, double density, bool pool, double *us)
+{
+    int n;
+    const Variant *t = variants(&n);
+    int best = kSmallFirst;
+    for (int v = kSmallFirst; v <= kSmallLast; ++v) {
+        if (pool && !t[v - 1].pool[0][0]) continue;
+        double c;
+        best_split(kCostReg, t[v - 1].g, N, C, K, Ho, Wo, density, &c);
+        if (v == kSmallFirst || c < *us) { best = v; *us = c; }
+    }
+    return best;
+}
+
 // Automatic choice.  Batches of at least four images use the image-interleaved (b128)
 // configurations.  Preference order measured on VGG16-shaped layers (N = 32, 95 % sparse):
 // 8-wave groups with small chunks for the wide layers with a handful of input channels; from
@@ -1147,51 +1297,6 @@ static long long sf_blocks(const SfGeom &g, int N, int K, int Ho, int Wo)
 // 16x8 tiles with two channels per wave for 14x14, which keeps 256 groups of 16 waves in flight.  A configuration that
 // would launch too few work-groups to cover the 256 compute units, or that has no pooled form
 // when one is asked for, yields to the next one.
-// Small problems (few work-groups, NCHW tensors): the configuration and the number of parts of the
-// channel split by a model of the launch's time in clocks, fitted to sweeps of one and two images over
-// the VGG16-shaped layers and a few ragged ones (it is 1 to 4 us low everywhere, and orders the
-// configurations within 3 % of the best).  A chunk costs its bytes through the 64 B/clk path from the
-// L2 -- with address work, LDS stores and what of that is not overlapped 1.6 times over --, a fixed part,
-// and its records: P multiply-adds each for four waves of a SIMD, a little more where a wave owns
-// several channels (a trip's last records, and chunks that are uneven between the waves).
-constexpr int kSmallFirst = 35, kSmallLast = 43;
-static double small_clocks(const SfGeom &g, int csplit, int N, int C, int K, int Ho, int Wo, double density)
-{
-    const long long groups = sf_blocks(g, N, K, Ho, Wo);
-    const int NCH = (C + g.CC - 1) / g.CC, chunks = (NCH + csplit - 1) / csplit;
-    const int P = g.NV * g.BV;
-    const double records = density * g.R * g.S * (C < g.CC ? C : g.CC) * g.SLOTS;
-    const double chunk = 1500 + 1.6 * g.lds_bytes / 2 / 64 + records * P * (22 + 4 * g.SLOTS);
-    const double parts = csplit > 1 ? 4000 + csplit * (double)g.WAVES * g.SLOTS * P * 4 : 0;
-    return 1000 + (double)((groups * csplit + 255) / 256) * (8000 + parts + chunks * chunk);   // 8000: first loads, stores
-}
-static int best_split(const SfGeom &g, int N, int C, int K, int Ho, int Wo, double density, double *clocks)
-{
-    const int NCH = (C + g.CC - 1) / g.CC;
-    int best = 1;
-    *clocks = small_clocks(g, 1, N, C, K, Ho, Wo, density);
-    for (int s = 2; s <= 8 && 2 * s <= NCH; s *= 2) {   // at least two chunks per part
-        if (sf_blocks(g, N, K, Ho, Wo) > kSplitGroups) break;
-        const double c = small_clocks(g, s, N, C, K, Ho, Wo, density);
-        if (c < *clocks) { *clocks = c; best = s; }
-    }
-    return best;
-}
-static int choose_small(int N, int C, int K, int Ho, int Wo, double density, bool pool)
-{
-    int n;
-    const Variant *t = variants(&n);
-    int best = kSmallFirst;
-    double best_clocks = 0;
-    for (int v = kSmallFirst; v <= kSmallLast; ++v) {
-        if (pool && !t[v - 1].pool[0][0]) continue;
-        double c;
-        best_split(t[v - 1].g, N, C, K, Ho, Wo, density, &c);
-        if (v == kSmallFirst || c < best_clocks) { best = v; best_clocks = c; }
-    }
-    return best;
-}
-
 int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
                       double density, bool banded)
 {
@@ -1209,7 +1314,7 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
         if (R != 3 || S != 3 || pool) return 0;
         const int first = W > 64 ? 28 : W > 16 ? 27 : 24;   // measured on Darknet-53's down-sampling layers, N = 32
         if (sf_blocks(t[first - 1].g, N, K, H, W) >= 192) return first;
-        return sf_blocks(t[24 - 1].g, N, K, H, W) >= 192 ? 24 : 22;
+        return sf_blocks(t[24 - 1].g, N, K, H, W) >= 192 ? 24 : 25;
     }
     if (stride != 1) return 0;
     if (R == 1 && S == 1) {   // 1x1: four-image forms only, no pooled form
@@ -1222,7 +1327,8 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
     }
     if (R != 3 || S != 3) return 0;
     // One or two images in band mode (N counts the slots, H a band's rows)
-    if (banded) return choose_small(N, C, K, H, W, density, pool);
+    double small_us = 0;
+    if (banded) return choose_small(N, C, K, H, W, density, pool, &small_us);
     int pref[4];
     // Fewer than four images: the one-image-per-lane forms only pay on the widest layers; from
     // 112x112 down they launch too few work-groups, and the four-image forms with idle image
@@ -1258,10 +1364,18 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
         const Variant &v = t[pref[i] - 1];
         if (pool && !v.pool[0][0]) continue;
         const long long b = sf_blocks(v.g, N, K, H, W);  // Ho, Wo ~ H, W for this purpose
-        if (b >= 384 || (b >= 192 && (n4 || C < 16))) return pref[i];
+        if (b >= 192) {
+            // up to a round and a half through NCHW tensors: the register-staged forms where the model sees them ahead
+            // by 10 % (127 geometries there: 13 % faster than always this configuration, 4 % slower at worst; 512 ->
+            // 512 at 28x28, N = 8, 256 groups of configuration 3: 63 us against 53 at 1 % stored, 218 against 230
+            // at 20 %; N = 16, 256 groups of configuration 4: 111 against 81 at 1 %, 390 against 414 at 20 %)
+            if (b >= 384 || n4 || C < 16) return pref[i];
+            const int small = choose_small(N, C, K, H, W, density, pool, &small_us);
+            return 1.1 * small_us < launch_us(kCostNchw, v.g, 1, b, C, density, false) ? small : pref[i];
+        }
         if (b > best_blocks) { best_blocks = b; best = pref[i]; }
     }
-    if (!n4 && C >= 16) return choose_small(N, C, K, H, W, density, pool);
+    if (!n4 && C >= 16) return choose_small(N, C, K, H, W, density, pool, &small_us);
     return best;
 }
 
@@ -1310,47 +1424,30 @@ hipError_t launch_conv_sf_tiled(const SfPlan &p, const float *x, int N, int C, i
     if (csplit > 1) {
         if (!scratch) return hipErrorInvalidValue;
         if (sf_blocks(p.g, N << band_shift, K, band_h, Wo) > kSplitGroups) return hipErrorInvalidValue;
-        arrived = static_cast<int *>(scratch);
+        if (emit_cnt || !split_by_launch(p.g, csplit)) arrived = static_cast<int *>(scratch);
         parts = static_cast<float *>(scratch) + kSplitGroups;
     }
     return fn(p, x, N, C, H, W, K, Ho, Wo, ph, pw, bias, relu, y, csplit, parts, arrived, emit_cnt, band_shift, band_h, st);
 }
 
-// Estimated time of an automatic launch of one of the small configurations, launch included; 0 for others.
-double sf_small_seconds(int variant, int N, int C, int K, int Ho, int Wo, double density)
+int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, double density, int in4, bool emit, double *us)
 {
     int n;
     const Variant *t = variants(&n);
-    if (variant < kSmallFirst || variant > kSmallLast) return 0;
-    double c;
-    best_split(t[variant - 1].g, N, C, K, Ho, Wo, density, &c);
-    return c / 2.4e9 + 5e-6;
+    double c = 0;
+    const int s = variant < 1 || variant > n
+                      ? 1
+                      : best_split(cost_of(t[variant - 1].g, in4 != 0), t[variant - 1].g, N, C, K, Ho, Wo, density, &c, emit);
+    if (us) *us = c;
+    return s;
 }
 
-// How many ways the input channels are split for a launch: small problems (deep layers at small
-// batch) leave most of the 256 CUs idle and serialise hundreds of channels in a few groups;
-// splitting the chunk range restores parallelism at the price of one copy of the accumulators per part
-// that the last part to arrive adds up.
-int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, int NCH, double density)
+// A thread of the direct kernel walks its filter's entries, a wave 64 columns of a row: measured over 65 layers of 5x5
+// and 7x7 filters, 41 us to 10 ms, within 7 %.
+double sf_direct_us(int N, int K, int Ho, int Wo, long long nnz)
 {
-    int n;
-    const Variant *t = variants(&n);
-    if (variant < 1 || variant > n) return 1;
-    if (variant >= kSmallFirst && variant <= kSmallLast) {
-        double c;
-        return best_split(t[variant - 1].g, N, C, K, Ho, Wo, density, &c);
-    }
-    const long long b = sf_blocks(t[variant - 1].g, N, K, Ho, Wo);
-    if (b > 128 || NCH < 4 || !t[variant - 1].g.SPLIT) return 1;   // with more groups the extra passes cost more than they gain
-    long long s = (256 + b - 1) / b;
-    if (s > NCH / 2) s = NCH / 2;   // at least two chunks per part
-    // (1x1: chunks are short, and the last part adding eight takes longer than the chunks that four parts have
-    // more: 52-layer chain at 224x224, N = 6, N4 tensors: 992 us a pass with up to eight, 965 with up to four)
-    const int most = t[variant - 1].g.R == 1 ? 4 : 8;
-    if (s > most) s = most;
-    const long long outputs = (long long)N * K * Ho * Wo;
-    if (s * outputs > (4LL << 20)) s = (4LL << 20) / outputs;   // bound the scratch and its traffic
-    return s < 1 ? 1 : (int)s;
+    const double waves = (double)N * K * ((Wo + 63) / 64) * ((Ho + 3) / 4) * 4;
+    return 9.7 + (double)nnz / K * (0.132 + 7.48e-5 * waves);
 }
 
 hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const float *val,

@@ -33,6 +33,7 @@ struct SfGeom {
     int STRIDE;                             // stride (both axes) the instance is built for
     int DENSE;                              // 1: the plan lists every tap of every chunk, SLOTS weights per tap
     int SPLIT;                              // 1: built with the channel split
+    int REGST;                              // 1: NCHW input staged through registers
     int lds_bytes;
 };
 
@@ -89,6 +90,16 @@ struct ContractPick {
     double seconds = 0;
 };
 
+// How a sparse-filter call is served.
+struct SfRoute {
+    int key[8];
+    int variant = 0;                       // configuration, or kDirectPlan
+    int band_shift = 0, band_h = 0;        // sf_choose_bands
+    int csplit = 1;                        // sf_choose_csplit
+    bool contract = false;                 // by the contraction, as `pick` says, once its plan is there
+    ContractPick pick;
+};
+
 struct SiGeom {
     int CC;  // channels per chunk of the compressed activation's chunk pointers
 };
@@ -111,15 +122,9 @@ struct fscnn_filter {
     float *val;     // device [nnz], behind the indices
     std::mutex mu;
     std::vector<fscnn::SfPlan *> plans;
-    // whether calls of a geometry are served by the contraction, and how (see contracts() in api.hip):
-    // the last few geometries asked for
-    struct Choice {
-        int key[7];
-        bool use;
-        fscnn::ContractPick pick;
-    };
-    std::vector<Choice> choices;
-    size_t next_choice = 0;
+    // how automatic calls of a geometry are served (route_call in api.hip): the last few geometries asked for
+    std::vector<fscnn::SfRoute> routes;
+    size_t next_route = 0;
 };
 
 struct fscnn_input {
@@ -214,9 +219,10 @@ hipError_t launch_conv_sf_tiled(const SfPlan &p, const float *x, int N, int C, i
 // configuration serves one or two images through NCHW tensors (then the work-groups of the launch,
 // and with them the channel split, go by N << band_shift slots of band_h rows); else 0 and Ho
 void sf_choose_bands(int variant, int N, int Ho, bool n4, bool pool, int *band_shift, int *band_h);
-double sf_small_seconds(int variant, int N, int C, int K, int Ho, int Wo, double density);
-// 1, or the number of parts the input-channel range is split into for a small problem
-int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, int NCH, double density);
+// 1, or the number of parts the input-channel range is split into for a small problem; the estimated time of that
+// launch; emit: with emit_cnt below
+int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, double density, int in4, bool emit, double *us);
+double sf_direct_us(int N, int K, int Ho, int Wo, long long nnz);   // the direct kernel's
 hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const float *val,
                                  const float *x, int N, int C, int H, int W, int K, int R, int S,
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,

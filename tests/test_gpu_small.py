@@ -62,6 +62,42 @@ def test_small_problems_are_exact_on_integers(F, n, c, k, h, w, keep, pool):
         assert np.array_equal(rows, np.concatenate([[0], np.cumsum((flat != 0).sum(1))]))
 
 
+@pytest.mark.parametrize("n,c,k,h,w,r,stride,pool,n4", [
+    (1, 64, 40, 9, 9, 3, 1, False, False),     # parts of 16 KB: the last one to arrive adds them up
+    (1, 512, 70, 14, 14, 3, 1, True, False),   # parts of a work-group beyond 128 KB: a launch of its own, merged pool
+    (5, 120, 70, 17, 19, 3, 2, False, False),  # stride 2
+    (5, 120, 70, 17, 19, 3, 2, False, True),   # ... N4 tensors, three idle image slots
+    (6, 300, 70, 9, 11, 3, 1, True, True),     # N4, merged pool, odd rows
+    (6, 300, 33, 15, 8, 3, 1, False, True),
+    (4, 500, 40, 13, 13, 1, 1, False, True),   # 1x1
+    (3, 400, 37, 12, 20, 1, 1, False, False),
+])
+def test_both_ways_to_add_up_the_parts_of_a_split(F, n, c, k, h, w, r, stride, pool, n4):
+    x, wt, b = inputs.random_layer(n + c + k + h + w, n, c, k, h, w, r, r, 0.05, integer=True)
+    pad = (r // 2, r // 2)
+    want = oracle.conv2d_dense(x, wt, (stride, stride), pad, b, True)
+    if pool:
+        want = oracle.maxpool2x2(want)
+    f, xd, lay = F.filter_compress(dev(wt)), dev(x), F.NCHW
+    if n4:
+        xd, lay = F.layout_convert(xd, F.NCHW), F.N4
+    for _ in range(3):
+        y = F.conv2d_sparse_filter(f, xd, (stride, stride), pad, dev(b), True, x_layout=lay, y_layout=lay, n=n, pool=pool)
+        y = F.layout_convert(y, F.N4, n) if n4 else y
+        assert np.array_equal(y.cpu().numpy(), want)
+
+
+def test_choice_between_large_tiles_and_register_staging(F):
+    """192 to 383 work-groups of the large tiles: they stay where records outweigh chunks (16 images, or 10 % stored at
+    eight), the register-staged forms (35 and up) take nearly empty banks.  More groups: never."""
+    def choice(n, c, k, hw, keep):
+        _, wt, _ = inputs.random_layer(5, 1, c, k, 3, 3, 3, 3, keep)
+        return F.sf_variant_choice(F.filter_compress(dev(wt)), n, hw, hw)
+    assert choice(16, 512, 512, 28, 0.20) < 35
+    assert choice(8, 512, 512, 28, 0.01) >= 35
+    assert choice(32, 512, 512, 28, 0.01) < 35 and choice(4, 512, 512, 14, 0.10) >= 35
+
+
 @pytest.mark.parametrize("k,c,r", [(1, 1, 3), (3, 683, 3), (65, 228, 3), (2, 2048, 1), (17, 40, 5)])
 def test_bank_compression_at_the_edges_of_its_rounds(F, k, c, r):
     # rows of one element, of whole rounds of 2048, one short and one past them
