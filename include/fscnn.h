@@ -163,6 +163,14 @@ fscnn_status_t fscnn_sf_variant_choice(const fscnn_filter_t *f, int N, int H, in
 fscnn_status_t fscnn_sf_band_choice(int variant, int N, int Ho, int n4, int pool, int *bands_out,
                                     int *band_rows_out);
 
+/* How the automatic choice (variant 0, NCHW tensors, no pool) serves a call by the dense contraction on
+ * the matrix cores: *tile_out receives the number (0..7) of its tile, or -1 where the configuration of
+ * fscnn_sf_variant_choice (or the direct kernel) serves the call, *panels_out the panels the image's
+ * columns are divided into.  Host-only: launches nothing and needs no device. */
+fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h,
+                                        int stride_w, int pad_h, int pad_w, int *tile_out,
+                                        int *panels_out);
+
 /* Sparse-filter convolution (Alg. 6: every output element, all filters; inner product of
  * Alg. 2 over the stored nonzeros only; no kernel flip; padding as index shift):
  *   y[n,k,oy,ox] = sum over stored (c,r,s,v) of filter k of

@@ -305,8 +305,8 @@ bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int
 {
     const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N, gather = 1e-6 * gather_us;
     if (2 * dense / 150e12 + 4e-6 > gather || (resolved > 0 && f->C < 16)) return false;
-    *pick = contract_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw);
-    return pick->cfg >= 0 && pick->seconds < (resolved < 0 ? gather : 0.85 * gather);   // (the models are not better than that)
+    *pick = contract_pick(kContractDense, N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw);
+    return pick->cfg >= 0 && pick->seconds < gather;
 }
 
 // How a call is served.  An explicitly selected configuration runs as it is; the automatic choice is
@@ -607,6 +607,23 @@ fscnn_status_t fscnn_sf_band_choice(int variant, int N, int Ho, int n4, int pool
     int shift;
     sf_choose_bands(variant, N, Ho, n4 != 0, pool != 0, &shift, band_rows_out);
     *bands_out = 1 << shift;
+    return FSCNN_OK;
+}
+
+fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int ph, int pw,
+                                        int *tile_out, int *panels_out)
+{
+    if (!f || !tile_out || !panels_out) return FSCNN_ERR_NULL;
+    if (!live(f)) return FSCNN_ERR_HANDLE;
+    if (N <= 0) return FSCNN_ERR_SHAPE;
+    int Ho, Wo;
+    fscnn_status_t s = out_shape(H, W, f->R, f->S, sh, sw, ph, pw, &Ho, &Wo);
+    if (s != FSCNN_OK) return s;
+    SfRoute r;
+    s = route_call(f, N, H, W, sh, sw, Ho, Wo, 0, 0, 0, 0, false, &r);
+    if (s != FSCNN_OK) return s;
+    *tile_out = r.contract ? r.pick.cfg : -1;
+    *panels_out = r.contract ? r.pick.npan : 0;
     return FSCNN_OK;
 }
 

@@ -569,13 +569,23 @@ template <int SRC, int WSRC, int RS> hipError_t launch_any(const DcArgs &a, cons
 
 }  // namespace
 
-// The configuration of a launch, by a model of its time: rounds of work-groups over the 256 CUs, each
-// taking its MFMAs (32 clocks each on four SIMDs; an eighth on top for what the two waves of a SIMD do
-// not hide of each other) plus, per chunk, the staging instructions, plus a prologue of one memory
-// round trip; then launch and epilogue.  Measured against it, 3x3: 512 -> 512 at 28x28, N = 8: 245 us
-// estimated, 255 measured; 128 -> 128 at 56x56, N = 4: 39 / 43; 64 -> 64 at 28x28, N = 1: 9 / 9.
-ContractPick contract_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw)
+// The configuration of a launch, by a model of its time in clocks: rounds of work-groups over the 256 CUs, each
+// taking per chunk its MFMAs (32 clocks each on four SIMDs; an eighth on top for what the two waves of a SIMD do
+// not hide of each other), the staging and a fixed part, then a prologue of one memory round trip and the
+// epilogue's stores per 16-pixel column block; then the launch.  Fitted per form to what random geometries took
+// (the share that is stored does not matter): 3x3 dense source, strides 1 and 2, 480 launches, standard deviation 5 %;
+// other extents (1x1, 5x5, 7x7), 215, 6 %; lists with a packed bank, 350, 4 %; lists with a bank as the caller
+// holds it, 350, 5 %.
+struct ContractCost {
+    double mfma, stage, chunk, round, block, launch;
+};
+constexpr ContractCost kContractCost[] = {{0.971, 163, 987, 8615, 2747, 3606},     // kContractDense, 3x3
+                                          {1.132, 67, 2383, 7345, 2469, 3160},     // kContractDense, any other extent
+                                          {1.004, 169, 1378, 4311, 2864, 7213},    // kContractLists
+                                          {0.996, 248, 4071, 9309, 2361, 5412}};   // kContractListsRows
+ContractPick contract_pick(ContractForm form, int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw)
 {
+    const ContractCost &m = kContractCost[form != kContractDense ? form + 1 : R == 3 && S == 3 ? 0 : 1];
     ContractPick best;
     // weights and the images a stripe can touch are addressed with 32-bit byte offsets, pixels of a
     // panel numbered with ints
@@ -608,8 +618,8 @@ ContractPick contract_pick(int N, int C, int K, int H, int W, int R, int S, int 
             const long long nwg = (P + T - 1) / T * npan * ((K + 16 * q.MW - 1) / (16 * q.MW));
             const int nch = (C + 16 * q.KS - 1) / (16 * q.KS);
             const double mfma = 36.0 * q.MW * q.NT * q.KS * R * S;
-            const double stage = 128.0 * q.KS * (double)((npx + 63) / 64) + 300;
-            const double clocks = (double)((nwg + 255) / 256) * (nch * (mfma + stage) + 6000) + 8000;
+            const double chunk = m.mfma * mfma + m.stage * q.KS * (double)((npx + 63) / 64) + m.chunk;
+            const double clocks = (double)((nwg + 255) / 256) * (nch * chunk + m.round + m.block * q.NT) + m.launch;
             if (best.cfg < 0 || clocks < best_clocks) {
                 best_clocks = clocks;
                 best.cfg = g; best.npan = npan; best.lds = lds;

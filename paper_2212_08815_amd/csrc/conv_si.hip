@@ -441,7 +441,7 @@ conv_si_direct_kernel(const int *__restrict__ cptr, int NCP, const uint32_t *__r
 // for the device: half of the entries, as after a ReLU.
 static bool si_contracts(const fscnn_input *in, int K, int Ho, int Wo, double gather_rate, ContractPick *pick)
 {
-    *pick = contract_pick(in->N, in->C, K, in->H, in->W, 3, 3, Ho, Wo, 1, 1);
+    *pick = contract_pick(kContractLists, in->N, in->C, K, in->H, in->W, 3, 3, Ho, Wo, 1, 1);
     const double stored = in->nnz >= 0 ? (double)in->nnz : 0.5 * in->N * in->C * (double)in->H * in->W;
     return pick->cfg >= 0 && in->CC == kSiCC && pick->seconds < 2.0 * 9 * stored * K / gather_rate + 20e-6;
 }

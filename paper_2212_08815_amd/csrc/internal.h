@@ -229,7 +229,9 @@ hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const f
                                  int relu, float *y, hipStream_t st);
 
 // ---- contract.hip: convolution as a dense contraction on the matrix cores
-ContractPick contract_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw);
+// (sources and banks: dense tensor; lists with a packed bank; lists with a K x C x 3 x 3 bank)
+enum ContractForm { kContractDense, kContractLists, kContractListsRows };
+ContractPick contract_pick(ContractForm form, int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw);
 // Packed banks: position of w[k][c][tap], and the number of floats (rows padded to 64 by zeros)
 __host__ __device__ inline long long contract_packed_index(int k, int c, int rs, int RS, int nslice)
 {
@@ -254,7 +256,6 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
 hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,
                                  int Wo, int ph, int pw, const float *bias, int relu, float *y,
                                  const ContractPick &p, hipStream_t st);
-
 // ---- transpose.hip
 long long reorder_workspace_bytes(long long n_buckets, long long nnz);  // -1: too large
 // Size of the per-GPU static scratch of fscnn_sparse_transpose_noalloc, and its device address on

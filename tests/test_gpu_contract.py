@@ -1,7 +1,8 @@
 """The contraction on the matrix cores: dense-ish filter banks, filter extents without a gather
-configuration, compressed activations with dense banks.  Sizes at the edges of its tiles: one pixel,
-tiles that end inside a row, rows that cross images, panels of wide images, channel counts around the
-slices of 16 and the rows of 16, chunks that end early; Inf and NaN."""
+configuration, compressed activations with dense banks.  Every tile of it, for each source and form of
+bank, with what the choice says asserted; sizes at the edges: one pixel, tiles that end inside a row, rows that
+cross images, panels of wide images, channel counts around the slices of 16 and the rows of 16, chunks
+that end early; Inf and NaN.  Which calls it serves."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,46 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
+@pytest.mark.parametrize("tile,wide,n,c,k,h,w,r,s,stride", [
+    (0, False, 8, 75, 131, 46, 48, 3, 3, (1, 1)), (0, True, 6, 120, 91, 44, 91, 3, 3, (1, 1)),
+    (1, False, 8, 125, 65, 35, 51, 3, 3, (1, 1)), (1, False, 9, 56, 148, 48, 43, 3, 3, (2, 1)),
+    (2, False, 7, 58, 96, 28, 41, 3, 3, (1, 1)), (2, True, 4, 140, 34, 24, 122, 3, 3, (1, 1)),
+    (2, True, 9, 70, 111, 41, 61, 3, 3, (1, 3)), (3, False, 9, 120, 84, 43, 21, 3, 3, (1, 1)),
+    (4, False, 6, 118, 139, 25, 12, 3, 3, (1, 1)), (4, True, 2, 88, 33, 17, 139, 3, 3, (1, 1)),
+    (4, False, 6, 63, 148, 50, 18, 3, 3, (2, 1)), (5, True, 3, 94, 25, 3, 35, 3, 3, (1, 1)),
+    (6, False, 9, 113, 79, 25, 22, 3, 3, (1, 1)), (7, False, 3, 76, 129, 34, 16, 3, 3, (1, 1)),
+    (0, True, 4, 14, 104, 40, 128, 5, 5, (1, 1)), (1, False, 8, 14, 146, 37, 32, 5, 5, (1, 1)),
+    (2, False, 9, 21, 130, 49, 22, 5, 5, (2, 2)), (2, True, 5, 19, 103, 46, 118, 5, 5, (2, 2)),
+    (3, False, 8, 56, 144, 45, 10, 5, 5, (1, 1)), (4, False, 9, 134, 72, 29, 11, 5, 5, (1, 1)),
+    (6, False, 9, 42, 140, 29, 12, 5, 5, (1, 1)), (7, False, 6, 72, 141, 16, 17, 5, 5, (1, 1)),
+    (2, False, 1, 4, 41, 46, 16, 7, 3, (1, 3)), (4, True, 7, 42, 105, 21, 49, 7, 3, (2, 1)),
+    (7, False, 9, 20, 91, 50, 11, 7, 3, (2, 1)),     # uneven strides
+    (1, True, 7, 49, 42, 46, 147, 2, 4, (2, 1)), (4, True, 9, 28, 77, 25, 42, 2, 4, (1, 3)),
+    (5, True, 3, 2, 72, 32, 30, 2, 4, (2, 2)),       # ... filter no wider than the stride
+    (1, False, 8, 107, 82, 20, 89, 1, 1, (1, 1)), (2, True, 8, 12, 8, 27, 145, 1, 1, (2, 2)),
+])
+def test_every_tile_is_exact_on_integers(F, tile, wide, n, c, k, h, w, r, s, stride):
+    # integers: every partial sum is exact in fp32, so any order of summation gives the same bits
+    pad = (r // 2, s // 2)
+    x, wt, b = inputs.random_layer(n + c + k + h + w, n, c, k, h, w, r, s, 0.7, integer=True)
+    f = F.filter_compress(dev(wt))
+    assert F.sf_contract_choice(f, n, h, w, stride, pad)[0] == tile
+    assert (F.sf_contract_choice(f, n, h, w, stride, pad)[1] > 1) == wide
+    want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), stride, pad).relu_()
+    assert torch.equal(F.conv2d_sparse_filter(f, dev(x), stride, pad, dev(b), True).cpu(), want)
+
+
+@pytest.mark.parametrize("n,c,k,r,hw,keep", [
+    (31, 139, 369, 1, 12, 0.05), (15, 23, 62, 1, 79, 0.21), (9, 82, 50, 1, 102, 0.07),   # 1x1: 2 to 3 times as long contracted
+    (27, 29, 327, 3, 46, 0.35),
+    (8, 512, 512, 3, 28, 0.20),
+    (6, 40, 35, 5, 96, 0.02),       # the direct kernel
+])
+def test_layers_that_are_faster_gathered_are_not_contracted(F, n, c, k, r, hw, keep):
+    _, wt, _ = inputs.random_layer(4, 1, c, k, 3, 3, r, r, keep)
+    assert F.sf_contract_choice(F.filter_compress(dev(wt)), n, hw, hw, (1, 1), (r // 2, r // 2))[0] == -1
+
+
 @pytest.mark.parametrize("n,c,k,h,w,r,s,stride,pad", [
     (1, 1, 1, 1, 1, 3, 3, (1, 1), (1, 1)),        # one pixel, one channel
     (1, 16, 64, 14, 14, 3, 3, (1, 1), (1, 1)),    # whole slices and rows
@@ -33,8 +74,7 @@ def dev(a):
     (1, 70, 20, 9, 131, 3, 3, (1, 1), (1, 1)),    # panels, the last one narrower
     (7, 128, 130, 11, 11, 3, 3, (1, 1), (1, 1)),  # several chunks, ragged last rows
     (2, 40, 33, 12, 19, 5, 5, (1, 1), (2, 2)),    # an extent without a gather configuration
-    (3, 20, 40, 23, 9, 7, 3, (2, 1), (3, 0)),     # ... at uneven strides
-    (4, 9, 50, 10, 10, 2, 4, (1, 3), (0, 2)),     # ... filter narrower than the stride
+    (4, 9, 50, 10, 10, 2, 4, (1, 3), (0, 2)),     # ... that the direct kernel may serve
 ])
 def test_integer_data_is_exact(F, n, c, k, h, w, r, s, stride, pad):
     # integers: every partial sum is exact in fp32, so any order of summation gives the same bits
