@@ -171,6 +171,14 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
                                         int stride_w, int pad_h, int pad_w, int *tile_out,
                                         int *panels_out);
 
+/* The same for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
+ * values on the contraction serves the call (prepared: fscnn_conv2d_sparse_input_prepared, else
+ * fscnn_conv2d_sparse_input), below a gather kernel; *from_out > N*C*H*W: never (then *tile_out may be
+ * -1).  Host-only. */
+fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int pad_h, int pad_w,
+                                        int prepared, long long *from_out, int *tile_out,
+                                        int *panels_out);
+
 /* Sparse-filter convolution (Alg. 6: every output element, all filters; inner product of
  * Alg. 2 over the stored nonzeros only; no kernel flip; padding as index shift):
  *   y[n,k,oy,ox] = sum over stored (c,r,s,v) of filter k of

@@ -627,6 +627,23 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
     return FSCNN_OK;
 }
 
+fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int ph, int pw, int prepared, long long *from_out,
+                                        int *tile_out, int *panels_out)
+{
+    if (!from_out || !tile_out || !panels_out) return FSCNN_ERR_NULL;
+    if (N <= 0 || C <= 0 || K <= 0) return FSCNN_ERR_SHAPE;
+    int Ho, Wo;
+    fscnn_status_t s = out_shape(H, W, 3, 3, 1, 1, ph, pw, &Ho, &Wo);
+    if (s != FSCNN_OK) return s;
+    if (!fits_int((long long)N * C * H * W) || !fits_int((long long)N * K * Ho * Wo) || !fits_int((long long)K * C * 9))
+        return FSCNN_ERR_UNSUPPORTED;
+    const SiChoice c = si_choose(N, C, H, W, K, Ho, Wo, prepared != 0);
+    *from_out = c.from;
+    *tile_out = c.pick.cfg;
+    *panels_out = c.pick.cfg < 0 ? 0 : c.pick.npan;
+    return FSCNN_OK;
+}
+
 // emit_cnt / counted: sparse output emission.  When the launch that serves the call can count the
 // non-zero results per (pixel, step of 8 channels) in its epilogue it writes them to emit_cnt and
 // sets *counted; otherwise the caller counts in a pass of its own.

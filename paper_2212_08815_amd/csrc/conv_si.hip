@@ -167,8 +167,9 @@ conv_si_kq_kernel(const int *__restrict__ cptr, const uint32_t *__restrict__ cid
                   const float *__restrict__ xval, const float *__restrict__ wT,
                   const float *__restrict__ bias, float *__restrict__ y, int C, int H, int W, int K,
                   int Kpad, int Ho, int Wo, int ph, int pw, int relu, int NCP, int NKT,
-                  int tiles_x, int tiles_per_img)
+                  int tiles_x, int tiles_per_img, const int *__restrict__ gate, int gate_from)
 {
+    if (gate && *gate >= gate_from) return;   // the contraction serves this activation (launch_conv_si_prepared)
     typedef float wvec __attribute__((ext_vector_type(G::KQ)));
     extern __shared__ __align__(256) char ldsb[];
     const int NCH = (NCP + G::CM - 1) / G::CM;
@@ -435,15 +436,43 @@ conv_si_direct_kernel(const int *__restrict__ cptr, int NCP, const uint32_t *__r
 
 }  // namespace
 
-// Whether the contraction on the matrix cores is the faster form of a 3x3 / stride-1 call: its
-// estimated time against the stored pairs' multiply-adds at the rate the gather kernel reaches.  The
-// number of stored pairs of a handle that a convolution emitted is not known here without waiting
-// for the device: half of the entries, as after a ReLU.
-static bool si_contracts(const fscnn_input *in, int K, int Ho, int Wo, double gather_rate, ContractPick *pick)
+// How a 3x3 / stride-1 call is served: by the contraction on the matrix cores (as `pick` says) for activations
+// of `from` stored values and more, by a gather kernel below.  The bank as the caller holds it: always by the
+// contraction where it serves the sizes (64 -> 64 at 56x56 to 512 -> 512 at 28x28, N = 1 to 32, 1 % stored: the
+// gather takes 1.5 to 7 times as long).  A prepared bank: by the estimates of contract_pick and of the gather, which
+// takes a round of work-groups over the CUs its stores and, per step of 8 channels, the weights' way to LDS
+// and the stored pairs (fitted to 240 launches of configuration 1 and 110 of configuration 4 over random sizes,
+// standard deviation 11 and 14 %; 512 -> 512 at 28x28, N = 8: 265 us contracted, 157 / 263 / 490 gathered at 3 / 10 / 25 %
+// stored; N = 32: 1090, and 257 / 482 / 920).
+SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepared)
 {
-    *pick = contract_pick(kContractLists, in->N, in->C, K, in->H, in->W, 3, 3, Ho, Wo, 1, 1);
-    const double stored = in->nnz >= 0 ? (double)in->nnz : 0.5 * in->N * in->C * (double)in->H * in->W;
-    return pick->cfg >= 0 && in->CC == kSiCC && pick->seconds < 2.0 * 9 * stored * K / gather_rate + 20e-6;
+    SiChoice r;
+    const int Kpad = (K + 255) / 256 * 256;
+    // 16-byte weight vectors and 16-wave groups once there are enough patches to fill the chip with
+    // them (measured on 28x28, C = K = 512: N = 32 yes, N = 8 no)
+    const bool wide = (long long)N * ((Ho + 3) / 4) * ((Wo + 3) / 4) * (Kpad / 256) >= 2048;
+    r.variant = wide ? 4 : 1;
+    r.pick = contract_pick(prepared ? kContractLists : kContractListsRows, N, C, K, H, W, 3, 3, Ho, Wo, 1, 1);
+    const double all = (double)N * C * H * W, steps = (C + 7) / 8;
+    if (r.pick.cfg < 0) {
+        r.from = (long long)all + 1;
+    } else if (prepared) {
+        const int ty = wide ? 16 : 8, kt = wide ? 256 : 128;
+        const long long groups = (long long)N * ((Wo + 15) / 16) * ((Ho + ty - 1) / ty) * (Kpad / kt);
+        // us = 2 + rounds * (stores + steps * (weights + pairs * share stored)), solved for the share
+        double rounds = (double)((groups + 255) / 256), stores, weights, pairs;
+        if (wide) {
+            stores = 92.4 * ((double)N * K * Ho * Wo / ((double)groups * 256 * 256));   // (of what a full group stores)
+            weights = 1.84, pairs = 46.95;
+        } else {   // two work-groups share a CU
+            const long long full = groups / 512, rest = groups % 512;
+            rounds = 1.5 * full + (rest > 256 ? 1.5 : rest > 0 ? 1.0 : 0.0);
+            stores = 4.46, weights = 1.553, pairs = 22.57;
+        }
+        const double share = (((1e6 * r.pick.seconds - 2) / rounds - stores) / steps - weights) / pairs;
+        r.from = share <= 0 ? 0 : share >= 1 ? (long long)all + 1 : (long long)(share * all);
+    }
+    return r;
 }
 
 bool si_tiled_supported(int K, int C, int R, int S, int sh, int sw)
@@ -457,9 +486,10 @@ hipError_t launch_conv_si(const fscnn_input *in, const float *w, int K, int R, i
                           hipStream_t st)
 {
     const int NKT = (K + 63) / 64;
-    ContractPick pick;
-    if (si_tiled_supported(K, in->C, R, S, sh, sw) && si_contracts(in, K, Ho, Wo, 7.5e12, &pick))
-        return launch_contract_lists(in, w, nullptr, K, Ho, Wo, ph, pw, bias, relu, y, pick, st);
+    if (si_tiled_supported(K, in->C, R, S, sh, sw)) {
+        const SiChoice c = si_choose(in->N, in->C, in->H, in->W, K, Ho, Wo, false);
+        if (c.from == 0) return launch_contract_lists(in, w, nullptr, K, Ho, Wo, ph, pw, bias, relu, y, c.pick, nullptr, 0, st);
+    }
     if (si_tiled_supported(K, in->C, R, S, sh, sw) && in->CC == kSiCC) {
         using G = SiCfg<4, 4, 4>;
         const int tiles_x = (Wo + G::TPW * G::WAVES - 1) / (G::TPW * G::WAVES);
@@ -490,7 +520,8 @@ hipError_t launch_dense_transpose(const float *w, int K, int C, int RS, int Kpad
 
 template <class G>
 static hipError_t launch_si_kq(const fscnn_input *in, const fscnn_dense *d, int Ho, int Wo, int ph, int pw,
-                               const float *bias, int relu, float *y, hipStream_t st)
+                               const float *bias, int relu, float *y, hipStream_t st, const int *gate = nullptr,
+                               int gate_from = 0)
 {
     static_assert(G::LDS_BYTES <= 160 * 1024, "weight ring exceeds the LDS of a CU");
     if (d->Kpad % G::KT != 0 || in->CC != kSiCC) return hipErrorInvalidValue;
@@ -504,7 +535,7 @@ static hipError_t launch_si_kq(const fscnn_input *in, const fscnn_dense *d, int 
     if (nblk <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(conv_si_kq_kernel<G>, dim3((unsigned)nblk), dim3(G::NT), G::LDS_BYTES, st,
                        in->cptr, in->cidx, in->xval, d->wT, bias, y, in->C, in->H, in->W, d->K, d->Kpad,
-                       Ho, Wo, ph, pw, relu, in->NCH, NKT, tiles_x, tiles_x * tiles_y);
+                       Ho, Wo, ph, pw, relu, in->NCH, NKT, tiles_x, tiles_x * tiles_y, gate, gate_from);
     return hipGetLastError();
 }
 
@@ -515,24 +546,33 @@ hipError_t launch_conv_si_prepared(const fscnn_input *in, const fscnn_dense *d, 
                                    int pw, const float *bias, int relu, float *y, int variant,
                                    hipStream_t st)
 {
+    const int *gate = nullptr;
+    int gate_from = 0;
     if (variant == 0) {
-        // automatic: 16-byte weight vectors and 16-wave groups once there are enough patches to
-        // fill the chip with them (measured on 28x28, C = K = 512: N = 32 yes, N = 8 no)
-        const long long patches = (long long)in->N * ((Ho + 3) / 4) * ((Wo + 3) / 4) * (d->Kpad / 256);
-        ContractPick pick;
-        if (si_contracts(in, d->K, Ho, Wo, patches >= 2048 ? 32e12 : 15e12, &pick))
-            return launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, pick, st);
-        variant = patches >= 2048 ? 4 : 1;
+        const SiChoice c = si_choose(in->N, in->C, in->H, in->W, d->K, Ho, Wo, true);
+        const long long all = (long long)in->N * in->C * in->H * in->W;
+        // A handle that a convolution emitted may not have told the host its number of stored values: then both
+        // kernels are launched and the one that does not serve it ends at once (2 us), so that a call's kernel, and
+        // with it the order of its sums, goes by the activation alone.
+        if (in->nnz < 0 && c.from > 0 && c.from <= all) {
+            gate = in->cptr + (long long)in->N * in->H * in->W * in->NCH;
+            gate_from = (int)c.from;
+        }
+        if (gate || (in->nnz >= 0 ? in->nnz >= c.from : c.from == 0)) {
+            const hipError_t e = launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, c.pick, gate, gate_from, st);
+            if (!gate || e != hipSuccess) return e;
+        }
+        variant = c.variant;
     }
     switch (variant) {
     case 1:  // 2 channels per lane, 16x8 outputs and 128 channels per group, 74 KB of LDS: two groups per CU
-        return launch_si_kq<SiKqCfg<2, 4, 2, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st);
+        return launch_si_kq<SiKqCfg<2, 4, 2, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st, gate, gate_from);
     case 2:  // 16 waves, 16x16 outputs, 16-channel chunks
-        return launch_si_kq<SiKqCfg<2, 4, 4, 2>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st);
+        return launch_si_kq<SiKqCfg<2, 4, 4, 2>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st, gate, gate_from);
     case 3:  // 4 channels per lane (16-byte weight vectors), 256 channels per group, 8 waves
-        return launch_si_kq<SiKqCfg<4, 4, 2, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st);
+        return launch_si_kq<SiKqCfg<4, 4, 2, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st, gate, gate_from);
     case 4:  // the same with 16 waves
-        return launch_si_kq<SiKqCfg<4, 4, 4, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st);
+        return launch_si_kq<SiKqCfg<4, 4, 4, 1>>(in, d, Ho, Wo, ph, pw, bias, relu, y, st, gate, gate_from);
     default:
         return hipErrorInvalidValue;
     }

@@ -252,10 +252,18 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st);
 // compressed activation, 3x3 at stride 1; with wflag: w is packed and wflag its non-finite flag,
-// without: w is K x C x 3 x 3
+// without: w is K x C x 3 x 3.  gate (device, packed banks only) with fewer than gate_from: the launch does nothing; NULL: it runs
 hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,
                                  int Wo, int ph, int pw, const float *bias, int relu, float *y,
-                                 const ContractPick &p, hipStream_t st);
+                                 const ContractPick &p, const int *gate, int gate_from, hipStream_t st);
+// How a sparse-input call (3x3, stride 1) is served: by the contraction from `from` stored values on
+struct SiChoice {
+    ContractPick pick;
+    long long from = 0;
+    int variant = 1;   // prepared banks: the gather configuration below
+};
+SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepared);
+
 // ---- transpose.hip
 long long reorder_workspace_bytes(long long n_buckets, long long nnz);  // -1: too large
 // Size of the per-GPU static scratch of fscnn_sparse_transpose_noalloc, and its device address on

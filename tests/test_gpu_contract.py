@@ -89,6 +89,63 @@ def test_integer_data_is_exact(F, n, c, k, h, w, r, s, stride, pad):
             assert np.array_equal(y.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("tile,wide,n,c,k,h,w", [
+    (0, True, 8, 17, 65, 29, 78), (1, False, 7, 25, 68, 38, 53), (1, True, 6, 17, 65, 30, 46), (2, False, 7, 20, 33, 32, 73),
+    (2, True, 2, 17, 68, 34, 62), (3, False, 4, 37, 138, 40, 34), (3, True, 8, 35, 33, 19, 56), (4, False, 8, 17, 44, 40, 14),
+    (4, True, 6, 17, 34, 13, 54), (5, False, 2, 23, 35, 3, 4), (5, True, 1, 20, 41, 3, 10), (6, False, 5, 35, 132, 27, 22),
+    (6, True, 8, 36, 65, 9, 57), (7, False, 5, 18, 65, 34, 14), (7, True, 3, 17, 65, 12, 59),
+])
+def test_every_tile_is_exact_on_lists(F, tile, wide, n, c, k, h, w):
+    x, wt, b = inputs.random_layer(n + c + k + h + w, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)
+    xs = F.input_compress(dev(x))
+    want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), (1, 1), (1, 1)).relu_()
+    for prepared in (False, True):
+        start, t, panels = F.si_contract_choice(n, c, h, w, k, (1, 1), prepared)
+        assert start <= xs.nnz and t == tile and (panels > 1) == wide
+        y = (F.conv2d_sparse_input_prepared(xs, F.dense_filter_prepare(dev(wt)), (1, 1), (1, 1), dev(b), True) if prepared
+             else F.conv2d_sparse_input(xs, dev(wt), (1, 1), (1, 1), dev(b), True))
+        assert torch.equal(y.cpu(), want)
+
+
+@pytest.mark.parametrize("n,c,k,h,w", [(1, 4, 8, 2, 40001), (2, 21, 70, 1, 40003), (1, 17, 65, 40001, 2)])
+def test_sizes_the_contraction_does_not_serve_are_gathered(F, n, c, k, h, w):
+    # images beyond 40000 rows or columns; ragged channels, rows and columns of the gather kernels' tiles
+    x, wt, b = inputs.random_layer(n + c + k, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.7)
+    xs = F.input_compress(dev(x))
+    want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), (1, 1), (1, 1)).relu_()
+    for prepared in (False, True):
+        assert F.si_contract_choice(n, c, h, w, k, (1, 1), prepared)[0] > n * c * h * w
+        y = (F.conv2d_sparse_input_prepared(xs, F.dense_filter_prepare(dev(wt)), (1, 1), (1, 1), dev(b), True) if prepared
+             else F.conv2d_sparse_input(xs, dev(wt), (1, 1), (1, 1), dev(b), True))
+        assert torch.equal(y.cpu(), want)
+
+
+@pytest.mark.parametrize("n,c,k,h,w,shift", [
+    (8, 40, 256, 28, 28, -2.5), (8, 40, 256, 28, 28, 0.0),      # below and above the number from which it is contracted
+    (9, 33, 300, 53, 57, -2.5), (9, 33, 300, 53, 57, 0.0),      # ... 16-wave form of the gather
+    (8, 40, 256, 28, 28, -99.0),                                # nothing stored
+])
+def test_emitted_activations_go_by_what_they_store(F, n, c, k, h, w, shift):
+    """The kernel that serves an emitted activation goes by its stored values, whether or not the caller has asked for
+    their number: the same bits before and after, and those of the gather kernel exactly where that is to serve."""
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn(n, 8, h, w, generator=g).cuda()
+    f = F.filter_compress((torch.randn(c, 8, 3, 3, generator=g) / 8.5).cuda())
+    d = F.dense_filter_prepare(torch.randn(k, c, 3, 3, generator=g).cuda())
+    s = F.conv2d_sparse_filter_emit(f, x, (1, 1), (1, 1), torch.full((c,), shift).cuda(), True)
+    start = F.si_contract_choice(n, c, h, w, k, (1, 1), True)[0]
+    assert 0 < start < n * c * h * w
+    before = F.conv2d_sparse_input_prepared(s, d, (1, 1), (1, 1))
+    below = s.nnz < start
+    assert below == (shift < 0)
+    after = F.conv2d_sparse_input_prepared(s, d, (1, 1), (1, 1))
+    assert torch.equal(before, after)
+    patches = n * -(-h // 4) * -(-w // 4) * -(-k // 256)
+    gathered = F.conv2d_sparse_input_prepared(s, d, (1, 1), (1, 1), variant=4 if patches >= 2048 else 1)
+    assert torch.equal(before, gathered) == below
+    assert torch.allclose(before, gathered, rtol=1e-4, atol=1e-4)
+
+
 def test_only_stored_entries_meet_non_finite_values(F):
     """0 * Inf never appears: a filter without an entry at a tap does not see the Inf there, a zero
     activation does not meet an Inf weight."""
