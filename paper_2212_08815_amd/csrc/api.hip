@@ -124,6 +124,16 @@ hipError_t device_alloc(void **p, size_t bytes)
     return hipMalloc(p, bytes);
 }
 
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
 // device: where the plan's buffers live
 void free_plan(SfPlan *p, int device)
 {
@@ -132,15 +142,15 @@ void free_plan(SfPlan *p, int device)
     if (p->packed) (void)hipFree(p->packed);
     int dev = -1;
     const bool keep = idle && hipGetDevice(&dev) == hipSuccess && dev == device;
-    for (auto &sc : p->split)
-        if (sc.buf && !(keep && split_pool().give(device, sc.buf, sc.bytes))) (void)hipFree(sc.buf);
+    for (auto *list : {&p->split, &p->outgrown})
+        for (auto &sc : *list)
+            if (sc.buf && !(keep && split_pool().give(device, sc.buf, sc.bytes))) (void)hipFree(sc.buf);
     delete p;
 }
 
 // Scratch of the channel-split mode for a call on `st`: the buffer this stream used before if it is
-// large enough, else a new one (the first such call of a plan on a stream allocates; replacing a
-// buffer that is too small waits for the stream's earlier work on it).  One buffer per stream:
-// calls that share a handle on different streams never share scratch.
+// large enough, else a new one (the first such call of a plan on a stream allocates).  One buffer per
+// stream: calls that share a handle on different streams never share scratch.
 fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_t bytes, float **out)
 {
     std::lock_guard<std::mutex> lock(f->mu);
@@ -153,16 +163,27 @@ fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_
     }
     float *nb = nullptr;
     hipError_t e = hipSuccess;
-    if (!split_pool().take(f->device, bytes, &nb, &bytes)) e = device_alloc(reinterpret_cast<void **>(&nb), bytes);
-    if (e == hipSuccess) e = launch_split_clear(nb, st);
+    if (capturing(st)) {
+        // (a capture in relaxed mode; in the others the allocation is refused.)  The clear must run now: recorded, it
+        // would leave the counters as they are for calls that come before the first replay
+        hipStream_t own = nullptr;
+        e = device_alloc(reinterpret_cast<void **>(&nb), bytes);
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
+        if (e == hipSuccess) e = launch_split_clear(nb, own);
+        if (e == hipSuccess) e = hipStreamSynchronize(own);
+        if (own) (void)hipStreamDestroy(own);
+    } else {
+        if (!split_pool().take(f->device, bytes, &nb, &bytes)) e = device_alloc(reinterpret_cast<void **>(&nb), bytes);
+        if (e == hipSuccess) e = launch_split_clear(nb, st);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         if (nb) (void)hipFree(nb);
         return FSCNN_ERR_ALLOC;
     }
     if (sc) {
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(sc->buf);
+        // launches in flight and graphs captured so far use the smaller one: it stays with the plan
+        p->outgrown.push_back({sc->stream, sc->buf, sc->bytes});
         sc->buf = nb;
         sc->bytes = bytes;
     } else {

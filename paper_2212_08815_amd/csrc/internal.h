@@ -76,7 +76,7 @@ struct SfPlan {
         float *buf;
         size_t bytes;
     };
-    std::vector<SplitScratch> split;
+    std::vector<SplitScratch> split, outgrown;
     // The plan of the contraction on the matrix cores (variant kContractPlan): the bank as a dense
     // packed array (contract_packed_index), zeros where nothing is stored; behind it an int that is
     // non-zero if a stored value is Inf or NaN (16 bytes).

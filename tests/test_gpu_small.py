@@ -62,6 +62,57 @@ def test_small_problems_are_exact_on_integers(F, n, c, k, h, w, keep, pool):
         assert np.array_equal(rows, np.concatenate([[0], np.cumsum((flat != 0).sum(1))]))
 
 
+def test_split_scratch_made_under_capture_is_clear_before_the_first_replay(F):
+    """A call of the channel split that was prepared on another stream only, captured (relaxed mode): its counters are
+    clear for eager calls on that stream that come before the first replay, and after."""
+    x, wt, b = inputs.random_layer(11, 1, 130, 26, 8, 8, 3, 3, 0.1, integer=True)
+    want = oracle.conv2d_dense(x, wt, (1, 1), (1, 1), b, True)
+    f, xd, bd = F.filter_compress(dev(wt)), dev(x), dev(b)
+    run = lambda out=None: F.conv2d_sparse_filter(f, xd, (1, 1), (1, 1), bd, True, out=out)
+    assert np.array_equal(run().cpu().numpy(), want)
+    side, graph, y = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.zeros(want.shape, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        run(y)
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            eager = run(torch.zeros_like(y))
+        torch.cuda.synchronize()
+        assert np.array_equal(eager.cpu().numpy(), want)
+        y.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), want)
+
+
+def test_graph_outlives_larger_calls_on_its_stream(F):
+    """A captured call keeps its scratch when a later call on the same stream needs more."""
+    side = torch.cuda.Stream()
+    layers = {h: inputs.random_layer(12, 1, 130, 26, h, 8, 3, 3, 0.1, integer=True) for h in (8, 30)}
+    wt, b = layers[8][1], layers[8][2]
+    f, bd = F.filter_compress(dev(wt)), dev(b)
+    x = {h: dev(layers[h][0]) for h in layers}
+    want = {h: oracle.conv2d_dense(layers[h][0], wt, (1, 1), (1, 1), b, True) for h in layers}
+    run = lambda h, out: F.conv2d_sparse_filter(f, x[h], (1, 1), (1, 1), bd, True, out=out)
+    y = {h: torch.zeros(want[h].shape, device="cuda") for h in layers}
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        run(8, y[8])
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        run(8, y[8])
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            run(30, y[30])
+        y[8].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(np.array_equal(y[h].cpu().numpy(), want[h]) for h in y)
+
+
 @pytest.mark.parametrize("n,c,k,h,w,r,stride,pool,n4", [
     (1, 64, 40, 9, 9, 3, 1, False, False),     # parts of 16 KB: the last one to arrive adds them up
     (1, 512, 70, 14, 14, 3, 1, True, False),   # parts of a work-group beyond 128 KB: a launch of its own, merged pool
