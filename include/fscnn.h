@@ -107,6 +107,11 @@ fscnn_status_t fscnn_filter_prepare(fscnn_filter_t *f, int N, int H, int W, int 
  * partial sums into scratch, which the last one to arrive adds up in a fixed order), that
  * mode's scratch for `stream`.  Afterwards such calls on `stream` allocate nothing
  * and do not synchronise, which is what a caller that captures them into a HIP graph needs.
+ * A call that the dense contraction on the matrix cores is to serve (fscnn_sf_contract_choice) needs a
+ * dense copy of the bank (4 bytes per entry, rows and channels padded to 64 and 16, below 2 GiB),
+ * which the first such call or this one makes and the handle keeps.  Where there is no room for it, or
+ * on a capturing stream before it is made, the call is served by the gather kernels as if there were
+ * no contraction (with sums in another order).
  * Without this call the first split-mode call of a handle on a stream allocates its scratch. */
 fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, int stride_h,
                                        int stride_w, int pad_h, int pad_w, fscnn_layout_t x_layout,

@@ -330,6 +330,26 @@ bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int
     return pick->cfg >= 0 && pick->seconds < gather;
 }
 
+// The contraction's plan of an automatic call that it is to serve, NULL where it cannot be made now: no room for
+// the bank as a dense array, or a capture on the stream (building it allocates and waits).  The call then goes to
+// the gather configuration or the direct kernel, which need none of that or fail for reasons of their own.
+fscnn_status_t contract_plan(fscnn_filter_t *f, hipStream_t st, SfPlan **out)
+{
+    *out = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(f->mu);
+        for (SfPlan *p : f->plans)
+            if (p->variant == kContractPlan) {
+                *out = p;
+                return FSCNN_OK;
+            }
+    }
+    if (capturing(st)) return FSCNN_OK;
+    const fscnn_status_t s = get_plan(f, kContractPlan, st, out);
+    if (s != FSCNN_OK) *out = nullptr;
+    return s == FSCNN_ERR_ALLOC ? FSCNN_OK : s;
+}
+
 // How a call is served.  An explicitly selected configuration runs as it is; the automatic choice is
 // remembered for the geometry (evaluating the models takes up to 3 us).  Call with the handle's lock not held.
 fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int in4, int out4, int pool,
@@ -525,8 +545,9 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (s != FSCNN_OK) return s;
     if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
     if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
-    SfPlan *p;
-    if (r.contract) return get_plan(f, kContractPlan, (hipStream_t)stream, &p);
+    SfPlan *p = nullptr;
+    if (r.contract) s = contract_plan(f, (hipStream_t)stream, &p);
+    if (s != FSCNN_OK || p) return s;
     s = get_plan(f, r.variant, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p->direct) return s;
     if (r.csplit > 1) {
@@ -697,10 +718,10 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (s != FSCNN_OK) return s;
     if (dev != f->device) return FSCNN_ERR_MISMATCH;   // the handle's buffers live on another GPU
     hipStream_t st = (hipStream_t)stream;
-    SfPlan *p;
-    if (r.contract) {
-        s = get_plan(f, kContractPlan, st, &p);
-        if (s != FSCNN_OK) return s;
+    SfPlan *p = nullptr;
+    if (r.contract) s = contract_plan(f, st, &p);
+    if (s != FSCNN_OK) return s;
+    if (p) {
         // (the tiled gather kernels multiply entries outside the image by zeros as well)
         const int *wflag = r.variant < 0 ? reinterpret_cast<const int *>(p->packed + contract_packed_elems(f->K, f->C, f->R * f->S)) : nullptr;
         FSCNN_HIP(launch_contract_dense(x_dev, p->packed, wflag, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,

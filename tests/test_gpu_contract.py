@@ -146,6 +146,54 @@ def test_emitted_activations_go_by_what_they_store(F, n, c, k, h, w, shift):
     assert torch.allclose(before, gathered, rtol=1e-4, atol=1e-4)
 
 
+def test_contracted_layers_can_be_captured_unprepared(F):
+    """A layer without a gather configuration needs no device data of its own under capture: the direct kernel."""
+    x, wt, b = inputs.random_layer(21, 2, 24, 40, 20, 17, 5, 5, 0.5, integer=True)
+    want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), (1, 1), (2, 2)).relu_()
+    f, xd, bd, y = F.filter_compress(dev(wt)), dev(x), dev(b), torch.zeros(want.shape, device="cuda")
+    assert F.sf_contract_choice(f, 2, 20, 17, (1, 1), (2, 2))[0] >= 0
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        F.conv2d_sparse_filter(f, xd, (1, 1), (2, 2), bd, True, out=y)
+    for _ in range(3):
+        y.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.cpu(), want)
+        assert torch.equal(F.conv2d_sparse_filter(f, xd, (1, 1), (2, 2), bd, True).cpu(), want)   # eager: contracted
+
+
+def test_no_room_for_the_dense_copy_of_a_bank(F):
+    """A sparse bank of a large extent on a nearly full card: its dense copy (679 MB) does not fit, the direct kernel
+    serves the call, and fscnn_filter_prepare does not fail either."""
+    k, c, r = 1024, 2048, 9
+    wt = torch.zeros(k, c, r, r, device="cuda")
+    wt.view(-1)[::47] = 1.0
+    f = F.filter_compress(wt)
+    x = (torch.arange(c * 49, device="cuda") % 5 - 2).float().view(1, c, 7, 7)
+    want = torch.nn.functional.conv2d(x.cpu(), wt.cpu(), None, 1, 4)
+    assert F.sf_contract_choice(f, 1, 7, 7, (1, 1), (4, 4))[0] >= 0
+    del wt
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    try:
+        while (free := torch.cuda.mem_get_info()[0]) > (600 << 20):
+            held.append(torch.empty(min(free - (512 << 20), 64 << 30), dtype=torch.uint8, device="cuda"))
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(679 << 20, dtype=torch.uint8, device="cuda")
+        F.filter_prepare(f, 1, 7, 7, (1, 1), (4, 4))
+        got = F.conv2d_sparse_filter(f, x, (1, 1), (4, 4))
+        torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert torch.equal(got.cpu(), want)
+    assert torch.equal(F.conv2d_sparse_filter(f, x, (1, 1), (4, 4)).cpu(), want)     # room again
+
+
 def test_only_stored_entries_meet_non_finite_values(F):
     """0 * Inf never appears: a filter without an entry at a tap does not see the Inf there, a zero
     activation does not meet an Inf weight."""
