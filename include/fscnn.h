@@ -263,7 +263,8 @@ fscnn_status_t fscnn_layout_convert(const float *src_dev, int N, int C, int H, i
  * innermost list): one row per pixel in (n, iy, ix) raster order holding the (channel,
  * value) pairs with x != 0.0f, channel ascending.  C up to 8192 (beyond:
  * FSCNN_ERR_UNSUPPORTED).  Allocates the handle's buffers (room for every value up to 256 MB of
- * pairs, beyond that for the stored ones) and synchronises `stream` once, for the number of stored
+ * pairs, but no more than 1 GB beyond what all live handles store; beyond that, or if there is no such room, for
+ * the stored ones) and synchronises `stream` once, for the number of stored
  * values.  The pass that writes the pairs may still be queued on `stream` when the call returns: x_dev must stay valid until
  * the work queued on `stream` so far has run (stream order suffices), and the library
  * orders every later use of the handle, on any stream, behind that pass. */

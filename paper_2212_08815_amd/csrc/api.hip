@@ -4,6 +4,7 @@
 #include <limits.h>
 #include <string.h>
 
+#include <atomic>
 #include <new>
 
 #include "internal.h"
@@ -820,9 +821,11 @@ fscnn_status_t fscnn_conv2d_sparse_filter(fscnn_filter_t *f, const float *x_dev,
 // values.  Up to kWholeBytes of indices and values, were every value stored, are allocated with the
 // pointers before anything runs, and the passes follow each other without the host; beyond that the
 // number of stored values sizes a second allocation (making and releasing one takes 50 us, more than
-// the passes of a 28x28 layer).  The pass that fills the handle may still be running on st when this
+// the passes of a 28x28 layer), and also where the live handles already hold kUnusedBytes more than they store
+// or the allocation fails.  The pass that fills the handle may still be running on st when this
 // returns, and reads x.
-constexpr long long kWholeBytes = 256LL << 20;
+constexpr long long kWholeBytes = 256LL << 20, kUnusedBytes = 1LL << 30;
+std::atomic<long long> unused_bytes{0};
 static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int H, int W,
                                            hipStream_t st, fscnn_input_t **out)
 {
@@ -855,8 +858,16 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     const size_t nodes_at = scratch_at + up(sizeof(int) * (size_t)input_scratch_elems(npix, NCH));
     auto val_at = [&](size_t n) { return up(n * sizeof(uint32_t)); };
     const size_t most = (size_t)(npix * C) + kSiSpare;
-    const bool whole = npix * C * 8 <= kWholeBytes;
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at + (whole ? val_at(most) + most * sizeof(float) : 0));
+    bool whole = npix * C * 8 <= kWholeBytes && unused_bytes.load() + npix * C * 8 <= kUnusedBytes;
+    hipError_t e = hipErrorOutOfMemory;
+    if (whole) {
+        e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at + val_at(most) + most * sizeof(float));
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            whole = false;
+        }
+    }
+    if (!whole) e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at);
     int *scratch = nullptr;
     auto fill = [&](void *nodes, size_t n) {
         in->cidx = static_cast<uint32_t *>(nodes);
@@ -875,7 +886,10 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e == hipSuccess) {
         in->nnz = total;
-        if (!whole) {
+        if (whole) {
+            in->unused = 8 * (npix * C - total);
+            unused_bytes += in->unused;
+        } else {
             const size_t n = (size_t)total + kSiSpare;
             e = device_alloc(reinterpret_cast<void **>(&in->node_block), val_at(n) + n * sizeof(float));
             if (e == hipSuccess) e = fill(in->node_block, n);
@@ -889,6 +903,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         if (in->filled) (void)hipEventDestroy(in->filled);
         if (in->ptr_block) (void)hipFree(in->ptr_block);
         if (in->node_block) (void)hipFree(in->node_block);
+        unused_bytes -= in->unused;
         in->magic = 0;
         delete in;
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
@@ -1093,6 +1108,7 @@ fscnn_status_t fscnn_input_destroy(fscnn_input_t *in)
     (void)hipEventDestroy(in->filled);
     if (in->ptr_block) (void)hipFree(in->ptr_block);
     if (in->node_block) (void)hipFree(in->node_block);
+    unused_bytes -= in->unused;
     delete in;
     return FSCNN_OK;
 }
@@ -1136,9 +1152,14 @@ fscnn_status_t fscnn_dense_filter_prepare(const float *w_dev, int K, int C, int 
     d->K = K; d->C = C; d->R = R; d->S = S; d->Kpad = Kpad;
     d->wT = nullptr;
     const size_t words = (size_t)Kpad * C * R * S;
-    const bool pack = R == 3 && S == 3;   // what the prepared calls serve
+    bool pack = R == 3 && S == 3;   // what the prepared calls serve
     const size_t packed = pack ? (size_t)Kpad * ((C + 15) / 16 * 16) * 9 : 0;
     hipError_t e = device_alloc(reinterpret_cast<void **>(&d->wT), sizeof(float) * (words + packed) + 256);
+    if (e == hipErrorOutOfMemory && pack) {   // without the second copy: the gather kernels serve every call
+        (void)hipGetLastError();
+        pack = false;
+        e = device_alloc(reinterpret_cast<void **>(&d->wT), sizeof(float) * words);
+    }
     d->packed = pack ? d->wT + words : nullptr;
     d->flag = pack ? reinterpret_cast<int *>(d->packed + packed) : nullptr;
     if (e == hipSuccess)

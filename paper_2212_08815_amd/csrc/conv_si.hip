@@ -554,11 +554,11 @@ hipError_t launch_conv_si_prepared(const fscnn_input *in, const fscnn_dense *d, 
         // A handle that a convolution emitted may not have told the host its number of stored values: then both
         // kernels are launched and the one that does not serve it ends at once (2 us), so that a call's kernel, and
         // with it the order of its sums, goes by the activation alone.
-        if (in->nnz < 0 && c.from > 0 && c.from <= all) {
+        if (d->packed && in->nnz < 0 && c.from > 0 && c.from <= all) {
             gate = in->cptr + (long long)in->N * in->H * in->W * in->NCH;
             gate_from = (int)c.from;
         }
-        if (gate || (in->nnz >= 0 ? in->nnz >= c.from : c.from == 0)) {
+        if (gate || (d->packed && (in->nnz >= 0 ? in->nnz >= c.from : c.from == 0))) {
             const hipError_t e = launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, c.pick, gate, gate_from, st);
             if (!gate || e != hipSuccess) return e;
         }

@@ -141,6 +141,7 @@ struct fscnn_input {
     // the device allocations behind the arrays: pointers (and the scratch they are made from), then
     // indices and values (null where they are part of the first: small or emitted activations)
     void *ptr_block, *node_block;
+    long long unused = 0;   // bytes of indices and values allocated ahead and not stored
     // a handle made by an emitting convolution has ONE allocation (ptr_block) of emit_bytes, sized
     // for the worst case, with room for the dense result iff emit_has_y; 0 for other handles
     size_t emit_bytes = 0;
@@ -158,7 +159,7 @@ struct fscnn_dense {
     int device;
     int K, C, R, S, Kpad;
     float *wT;       // device [C*R*S*Kpad]; the arrays below follow it in the same allocation
-    float *packed;   // 3x3: the bank in the order of the contraction's A operands; else NULL
+    float *packed;   // 3x3: the bank in the order of the contraction's A operands; else, or where there was no room for it, NULL
     int *flag;       // 3x3: non-zero if the bank holds an Inf or NaN
 };
 

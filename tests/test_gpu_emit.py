@@ -179,3 +179,48 @@ def test_emit_rejects_bad_arguments(F):
     with pytest.raises(F.FscnnError) as e:
         F.conv2d_sparse_filter_emit(f, xd, (1, 1), (1, 1), dense_out=xd)     # dense copy on top of x
     assert e.value.status == 4
+
+
+def test_activation_handles_hold_little_more_than_they_store(F):
+    """Sixteen nearly empty activations with room for 134 MB of pairs each: at most 1 GB is held ahead over all of them."""
+    x = torch.zeros(8, 512, 64, 64, device="cuda")
+    x.view(-1)[::1009] = 2.0
+    torch.cuda.synchronize()
+    F.input_compress(x)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    handles = [F.input_compress(x) for _ in range(16)]
+    held = before - torch.cuda.mem_get_info()[0]
+    assert held < (1 << 30) + 16 * (16 << 20)     # the pointers and scratch of one take 9 MB
+    flat = x.permute(0, 2, 3, 1).reshape(-1, 512).cpu().numpy()
+    p, ch = np.nonzero(flat)
+    for s in (handles[0], handles[-1]):
+        rows, idx, val = F.input_export(s)
+        assert np.array_equal(idx, ch) and np.array_equal(val, flat[p, ch])
+
+
+def test_no_room_ahead_on_a_nearly_full_card(F):
+    """Less than the 201 MB of pairs ahead, less than two copies of a bank of 113 MB: activations are compressed with room
+    for what they store, the bank is kept once and the gather kernel serves its calls."""
+    x = torch.zeros(8, 1536, 32, 64, device="cuda")
+    x.view(-1)[::11] = 1.0
+    w = (torch.arange(2048 * 1536 * 9, device="cuda") % 3 - 1).float().view(2048, 1536, 3, 3)
+    y = torch.empty(8, 2048, 32, 64, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    try:
+        while (free := torch.cuda.mem_get_info()[0]) > (176 << 20):
+            held.append(torch.empty(min(free - (160 << 20), 64 << 30), dtype=torch.uint8, device="cuda"))
+        s = F.input_compress(x)
+        nnz = s.nnz
+        s.destroy()
+        xs = torch.ones(1, 1536, 3, 3, device="cuda")
+        d = F.dense_filter_prepare(w)
+        one = F.conv2d_sparse_input_prepared(F.input_compress(xs), d, (1, 1), (1, 1), out=y.view(-1)[:2048 * 9].view(1, 2048, 3, 3))
+        torch.cuda.synchronize()
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert nnz == int((x != 0).sum())
+    assert torch.equal(one.cpu(), torch.nn.functional.conv2d(xs.cpu(), w.cpu(), None, 1, 1))
