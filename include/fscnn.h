@@ -142,6 +142,10 @@ fscnn_status_t fscnn_filter_plan_export(fscnn_filter_t *f, int N, int H, int W, 
 
 fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f);
 
+/* Scratch of the channel-split mode that destroyed filter handles leave is kept for the next handles, up to
+ * 64 MB in all.  This call releases it, for other allocators to use. */
+fscnn_status_t fscnn_pool_trim(void);
+
 /* Number of selectable kernel configurations of the sparse-filter convolution and a short
  * description of each (variant ids are 1..count; 0 = automatic). */
 int fscnn_sf_variant_count(void);

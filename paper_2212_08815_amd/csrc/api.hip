@@ -63,7 +63,7 @@ double density(const fscnn_filter_t *f) { return (double)f->nnz / ((double)f->K 
 // allocation of some MB takes the runtime up to 290 us (small ones: 2 us), and a program that compresses
 // its banks for one pass makes a dozen (13-layer stack, N = 1, a load and a pass: at 160x160 2.66 ms
 // with them released, 1.29 kept; at 224x224 2.99 and 1.43).  At most kPoolBytes and kPoolBuffers
-// are held; all of it is given back when an allocation fails.  A buffer enters after its handle's records
+// are held; all of it is given back when an allocation of the library fails, and by fscnn_pool_trim.  A buffer enters after its handle's records
 // were released, which waits for the device, so no launch still uses it; it leaves for one (plan, stream).
 constexpr size_t kPoolBytes = 64u << 20, kPoolBuffers = 64;
 struct SplitPool {
@@ -626,6 +626,12 @@ fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f)
     if (f->rowptr) (void)hipFree(f->rowptr);
     if (f->idx) (void)hipFree(f->idx);
     delete f;
+    return FSCNN_OK;
+}
+
+fscnn_status_t fscnn_pool_trim(void)
+{
+    split_pool().trim();
     return FSCNN_OK;
 }
 

@@ -35,7 +35,7 @@ EXPORTS = [
     "fscnn_sparse_transpose", "fscnn_sparse_tensor_transpose", "fscnn_sparse_transpose_workspace",
     "fscnn_dense_filter_prepare", "fscnn_dense_filter_destroy", "fscnn_conv2d_sparse_input_prepared",
     "fscnn_si_variant_count", "fscnn_conv2d_sparse_filter_leaky", "fscnn_sparse_transpose_noalloc",
-    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_si_contract_choice",
+    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_si_contract_choice", "fscnn_pool_trim",
 ]
 
 NCHW, N4 = 0, 1      # fscnn_layout_t
@@ -138,6 +138,11 @@ def conv2d_out_shape(H, W, R, S, stride=(1, 1), pad=(0, 0)):
                                         _i(pad[0]), _i(pad[1]), ctypes.byref(ho), ctypes.byref(wo)),
            "fscnn_conv2d_out_shape")
     return ho.value, wo.value
+
+
+def pool_trim():
+    """fscnn_pool_trim: release the scratch that destroyed filter handles left for the next ones."""
+    _check(lib().fscnn_pool_trim(), "fscnn_pool_trim")
 
 
 def sf_variant_count():

@@ -113,6 +113,26 @@ def test_graph_outlives_larger_calls_on_its_stream(F):
         assert all(np.array_equal(y[h].cpu().numpy(), want[h]) for h in y)
 
 
+def test_pool_of_scratch_is_bounded_and_given_back(F):
+    _, wt, _ = inputs.random_layer(13, 1, 512, 512, 3, 3, 3, 3, 0.05)
+    w, x, y = dev(wt), torch.randn(6, 512, 28, 28, device="cuda"), torch.empty(6, 512, 28, 28, device="cuda")
+    F.pool_trim()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    handles = [F.filter_compress(w) for _ in range(4)]
+    for f in handles:
+        F.conv2d_sparse_filter(f, x, (1, 1), (1, 1), out=y)
+    torch.cuda.synchronize()
+    scratch = before - torch.cuda.mem_get_info()[0]
+    assert scratch > 4 * (16 << 20)               # a split launch: its parts are 16 MB and more
+    for f in handles:
+        f.destroy()
+    kept = before - torch.cuda.mem_get_info()[0]
+    assert 0 < kept <= 66 << 20
+    F.pool_trim()
+    assert before - torch.cuda.mem_get_info()[0] <= 2 << 20
+
+
 @pytest.mark.parametrize("n,c,k,h,w,r,stride,pool,n4", [
     (1, 64, 40, 9, 9, 3, 1, False, False),     # parts of 16 KB: the last one to arrive adds them up
     (1, 512, 70, 14, 14, 3, 1, True, False),   # parts of a work-group beyond 128 KB: a launch of its own, merged pool
