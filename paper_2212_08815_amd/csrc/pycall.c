@@ -37,8 +37,14 @@ _Static_assert(sizeof(L) == kEntries * sizeof(void *), "one name per entry point
 /* Argument readers: a failed conversion sets *bad and leaves the Python error for the caller. */
 static int geti(PyObject *o, int *bad)
 {
-    if (PyFloat_Check(o)) return (int)PyFloat_AS_DOUBLE(o);
-    const long v = PyLong_AsLong(o);
+    long v;
+    if (PyLong_Check(o)) {
+        v = PyLong_AsLong(o);
+    } else {   /* any other number by its integer value, as int() takes it (which refuses infinities and NaN) */
+        PyObject *n = PyNumber_Long(o);
+        v = n ? PyLong_AsLong(n) : -1;
+        Py_XDECREF(n);
+    }
     if (v == -1 && PyErr_Occurred()) *bad = 1;
     else if (v != (int)v) {
         PyErr_SetString(PyExc_OverflowError, "argument does not fit an int");

@@ -170,6 +170,26 @@ def test_band_choice_is_host_arithmetic():
         assert fscnn.sf_band_choice(v, 1, 56) == (1, 56)
 
 
+def test_native_calls_take_numbers_by_their_integer_value(L):
+    """Sizes through the native half of the binding: any number whose int() fits, in a call whose status (not a live
+    handle: 7) is decided before any device work."""
+    import decimal
+    import torch
+    from paper_2212_08815_amd import fscnn
+    m = fscnn._native()
+    junk = (ctypes.c_ubyte * 1024)()
+    h = ctypes.addressof(junk)
+    conv = lambda v: m.conv(0, h, 256, v, 1, 4, 4, 1, 1, 0, 0, None, 0, 256, 0, 0, 0, 0)
+    for v in (1, True, 1.0, 2.9, np.int32(1), np.float32(2), np.float64(1.5), np.uint8(1), torch.tensor(2), torch.tensor(1.5),
+              decimal.Decimal("1.5"), "3"):
+        assert conv(v) == 7
+    for v, err in ((float("inf"), OverflowError), (float("-inf"), OverflowError), (float("nan"), ValueError), (1e30, OverflowError),
+                   (1 << 31, OverflowError), (-(1 << 31) - 1, OverflowError), (1 << 70, OverflowError), (np.float32("inf"), OverflowError),
+                   ("x", ValueError), (None, TypeError), (object(), TypeError)):
+        with pytest.raises(err):
+            conv(v)
+
+
 def test_no_cpu_fallback_without_a_device(L):
     import torch
     if torch.cuda.is_available():
