@@ -104,7 +104,7 @@ fscnn_status_t fscnn_filter_prepare(fscnn_filter_t *f, int N, int H, int W, int 
  * fscnn_conv2d_sparse_filter_ex / _pool2x2 / _leaky), to be issued on `stream`: builds the plan
  * of the configuration that call will resolve to and, when the call is small enough to run in
  * the channel-split mode (input channels divided over several work-groups, each storing its
- * partial sums into scratch, which the last one to arrive adds up in a fixed order), that
+ * partial sums into scratch, which the last one to arrive, or a second launch, adds up in a fixed order), that
  * mode's scratch for `stream`.  Afterwards such calls on `stream` allocate nothing
  * and do not synchronise, which is what a caller that captures them into a HIP graph needs.
  * A call that the dense contraction on the matrix cores is to serve (fscnn_sf_contract_choice) needs a
@@ -197,7 +197,7 @@ fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int p
  * fp32 accumulation in an order fixed by the plan: results are run-to-run identical.  For small
  * problems with the automatic configuration the input-channel range is split over several
  * work-groups; each stores its partial sums into a copy of its own (scratch that belongs to the
- * handle's plan, one buffer per stream) and the last one to arrive adds the copies in the order
+ * handle's plan, one buffer per stream) and the last one to arrive, or a second launch, adds the copies in the order
  * of the parts, so this mode is reproducible too, but its sums are grouped
  * differently from those of an explicitly selected configuration (fscnn_conv2d_sparse_filter_v /
  * _ex with variant > 0), which never splits.

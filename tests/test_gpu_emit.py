@@ -52,7 +52,7 @@ CASES = [
     (1, 33, 20, 9, 12, 1, 1, (1, 1), (0, 0)),       # 1x1 filters
     (1, 7, 66, 10, 9, 5, 2, (1, 2), (2, 0)),        # direct kernel
     (16, 72, 96, 56, 56, 3, 3, (1, 1), (1, 1)),     # many chunks and enough work-groups not to split: epilogue counts
-    (1, 128, 40, 14, 14, 3, 3, (1, 1), (1, 1)),     # small and deep: channel-split mode, counted in a separate pass
+    (1, 128, 40, 14, 14, 3, 3, (1, 1), (1, 1)),     # small and deep: channel-split mode, counted by the part that finishes
 ]
 
 

@@ -90,6 +90,7 @@ def test_filter_compress_special_values_and_empty_rows(F):
 
 # ------------------------------------------------------------------ A3: regrouped plan
 def test_variant_choice_names_the_kernel_that_runs(F):
+    """(Where the contraction does not serve the call, which fscnn_sf_contract_choice says.)"""
     _, w, _ = inputs.random_layer(5, 1, 24, 40, 4, 4, 3, 3, keep=0.2)
     f = F.filter_compress(dev(w))
     n = F.sf_variant_count()
@@ -97,6 +98,7 @@ def test_variant_choice_names_the_kernel_that_runs(F):
         v = F.sf_variant_choice(f, N, hw, hw)
         assert 1 <= v <= n
         assert F.filter_plan_export(f, N, hw, hw, (1, 1), (1, 1))["variant"] == v
+        assert (F.sf_contract_choice(f, N, hw, hw, (1, 1), (1, 1))[0] == -1) == (N > 2)   # (small and a fifth stored: contracted)
         vp = F.sf_variant_choice(f, N, hw, hw, n4=True, pool=True)
         assert 1 <= vp <= n and not F.sf_variant_name(vp).endswith("_n4only")
     assert F.sf_variant_choice(f, 4, 56, 56, stride=(3, 3)) == -1      # stride 3: the direct kernel
@@ -332,7 +334,7 @@ def test_conv_n4_layouts_match_oracle(F, case):
 def test_small_problems_split_the_channel_range(F, case):
     """Few work-groups and many input channels: the automatic configuration splits the channel
     chunks over several groups (a copy of the partial sums per part, added up in the order of the
-    parts with bias + ReLU by a finishing pass; with one or two images the groups work on bands)."""
+    parts by the last one to arrive or by a launch; with one or two images the groups work on bands)."""
     n, c, k, h, w_, keep, use_b, relu = case
     x, w, b = inputs.random_layer(sum(case[:5]), n, c, k, h, w_, 3, 3, keep, bias=use_b)
     csr = oracle.filter_compress(w)
@@ -867,9 +869,9 @@ def test_first_layer_form_for_banks_without_zeros(F):
 
 def test_channel_split_mode_is_bit_reproducible_and_matches_the_oracle(F):
     """Small problems (few work-groups) divide the input channels over several work-groups; every
-    part stores its partial sums into its own copy of the output and a finishing pass adds the
-    copies in the order of the parts, so two runs give the same bits (one writer per element, no
-    atomics).  Config 3's deep layers at N=1 take this mode."""
+    part stores its partial sums into its own copy and the last part to arrive, or a launch that
+    follows, adds the copies in the order of the parts, so two runs give the same bits (one writer per
+    element).  Config 3's deep layers at N=1 take this mode."""
     for (n, c, k, hw, lay) in [(1, 512, 512, 14, "nchw"), (1, 256, 512, 28, "nchw"), (2, 300, 70, 14, "n4"),
                                (8, 512, 512, 14, "n4")]:
         x, w, b = inputs.random_layer(400 + c + hw, n, c, k, hw, hw, 3, 3, 0.1)
@@ -888,7 +890,7 @@ def test_channel_split_mode_is_bit_reproducible_and_matches_the_oracle(F):
 
 def test_channel_split_mode_with_the_merged_pool(F):
     """The same mode where the 2x2 max-pool is merged into the call: the parts hold full-size partial
-    sums and the finishing pass pools.  Against the oracle's convolution followed by its plain
+    sums, and whoever adds them up pools.  Against the oracle's convolution followed by its plain
     max-pool (odd sizes: the last row and column drop out), twice for the same bits."""
     for (n, c, k, h, w_, lay) in [(1, 512, 512, 28, 28, "nchw"), (1, 256, 96, 15, 17, "nchw"), (3, 300, 70, 14, 14, "n4"),
                                   (8, 512, 512, 14, 14, "n4")]:

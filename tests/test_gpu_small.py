@@ -181,9 +181,22 @@ def test_bank_compression_at_the_edges_of_its_rounds(F, k, c, r):
     assert np.array_equal(rp, want[0]) and np.array_equal(ix, want[1]) and np.array_equal(vl.view(np.uint32), want[2].view(np.uint32))
 
 
-@pytest.mark.parametrize("n,c,h,w", [(1, 8, 1, 1), (1, 8, 31, 33), (1, 8, 32, 32), (1, 128, 32, 32), (1, 9, 89, 92), (1, 17, 75, 73)])
-def test_scan_at_the_edges_of_its_rounds(F, n, c, h, w):
-    # (pixel, step of 8 channels) counts: 1, 1023, 1024, 16384 (the single work-group's last), 16376, 16425
+@pytest.mark.parametrize("k", [1, 1023, 1024, 1025, 16383, 16384, 16385, 20481])
+def test_scan_at_the_edges_of_its_rounds(F, k):
+    # one count per filter is scanned: rows of 1024, and from 16385 on tiles of 4096 instead of one work-group
+    rng = np.random.default_rng(k)
+    w = (rng.standard_normal((k, 3, 1, 1)) * (rng.random((k, 3, 1, 1)) < 0.4)).astype(np.float32)
+    want = oracle.filter_compress(w)
+    rp, ix, vl = F.filter_export(F.filter_compress(dev(w)))
+    assert np.array_equal(rp, want[0]) and np.array_equal(ix, want[1]) and np.array_equal(vl.view(np.uint32), want[2].view(np.uint32))
+
+
+@pytest.mark.parametrize("n,c,h,w", [
+    (1, 8, 1, 1), (1, 8, 31, 33), (1, 8, 32, 32), (1, 128, 32, 32), (1, 9, 89, 92), (1, 17, 75, 73),
+    # sums of groups of 32 pixels that are scanned: 1023, 1024, 1025; 16384, 16385
+    (1, 3, 31, 1056), (1, 3, 32, 1024), (1, 3, 41, 800), (1, 1, 512, 1024), (1, 1, 3, 174763),
+])
+def test_activation_compression_at_the_edges_of_its_groups(F, n, c, h, w):
     rng = np.random.default_rng(c * h)
     x = (rng.standard_normal((n, c, h, w)) * (rng.random((n, c, h, w)) < 0.4)).astype(np.float32)
     rows, idx, val = F.input_export(F.input_compress(dev(x)))
