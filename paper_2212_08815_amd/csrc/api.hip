@@ -288,7 +288,8 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
 // Which variant serves this geometry: `variant` > 0 is taken as is (checked), 0 = automatic,
 // anything the tiled kernel cannot do goes to the direct kernel (-1).
 fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw,
-                               int variant, int *resolved, bool n4 = false, bool pool = false)
+                               int variant, int *resolved, bool n4 = false, bool pool = false,
+                               bool emit = false)
 {
     // the tiled kernel serves strides 1 and 2 (equal on both axes) and addresses up to four
     // images' channels with 32-bit byte offsets
@@ -311,7 +312,7 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
         slots = 4;
     }
     int v = tiled_ok ? sf_choose_variant(slots, f->C, f->K, rows, (W + sw - 1) / sw, f->R, f->S, sh, pool, n4,
-                                         density(f), banded)
+                                         density(f), banded, emit)
                      : 0;
     *resolved = v > 0 ? v : -1;
     return FSCNN_OK;
@@ -366,7 +367,7 @@ fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw
             }
     }
     *r = SfRoute();
-    fscnn_status_t s = resolve_variant(f, N, H, W, sh, sw, variant, &r->variant, in4 || out4, pool != 0);
+    fscnn_status_t s = resolve_variant(f, N, H, W, sh, sw, variant, &r->variant, in4 || out4, pool != 0, emit);
     if (s != FSCNN_OK) return s;
     sf_choose_bands(r->variant, N, Ho, in4 || out4, pool != 0, &r->band_shift, &r->band_h);
     if (variant != 0) return FSCNN_OK;

@@ -1272,7 +1272,7 @@ static int best_split(const Cost &m, const SfGeom &g, int N, int C, int K, int H
     }
     return best;
 }
-static int choose_small(int N, int C, int K, int Ho, int Wo, double density, bool pool, double *us)
+static int choose_small(int N, int C, int K, int Ho, int Wo, double density, bool pool, bool emit, double *us)
 {
     int n;
     const Variant *t = variants(&n);
@@ -1280,7 +1280,7 @@ static int choose_small(int N, int C, int K, int Ho, int Wo, double density, boo
     for (int v = kSmallFirst; v <= kSmallLast; ++v) {
         if (pool && !t[v - 1].pool[0][0]) continue;
         double c;
-        best_split(kCostReg, t[v - 1].g, N, C, K, Ho, Wo, density, &c);
+        best_split(kCostReg, t[v - 1].g, N, C, K, Ho, Wo, density, &c, emit);
         if (v == kSmallFirst || c < *us) { best = v; *us = c; }
     }
     return best;
@@ -1298,7 +1298,7 @@ static int choose_small(int N, int C, int K, int Ho, int Wo, double density, boo
 // would launch too few work-groups to cover the 256 compute units, or that has no pooled form
 // when one is asked for, yields to the next one.
 int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
-                      double density, bool banded)
+                      double density, bool banded, bool emit)
 {
     const bool no_zeros = density >= 1.0;
     int n;
@@ -1328,7 +1328,7 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
     if (R != 3 || S != 3) return 0;
     // One or two images in band mode (N counts the slots, H a band's rows)
     double small_us = 0;
-    if (banded) return choose_small(N, C, K, H, W, density, pool, &small_us);
+    if (banded) return choose_small(N, C, K, H, W, density, pool, emit, &small_us);
     int pref[4];
     // Fewer than four images: the one-image-per-lane forms only pay on the widest layers; from
     // 112x112 down they launch too few work-groups, and the four-image forms with idle image
@@ -1370,12 +1370,12 @@ int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int strid
             // 512 at 28x28, N = 8, 256 groups of configuration 3: 63 us against 53 at 1 % stored, 218 against 230
             // at 20 %; N = 16, 256 groups of configuration 4: 111 against 81 at 1 %, 390 against 414 at 20 %)
             if (b >= 384 || n4 || C < 16) return pref[i];
-            const int small = choose_small(N, C, K, H, W, density, pool, &small_us);
+            const int small = choose_small(N, C, K, H, W, density, pool, emit, &small_us);
             return 1.1 * small_us < launch_us(kCostNchw, v.g, 1, b, C, density, false) ? small : pref[i];
         }
         if (b > best_blocks) { best_blocks = b; best = pref[i]; }
     }
-    if (!n4 && C >= 16) return choose_small(N, C, K, H, W, density, pool, &small_us);
+    if (!n4 && C >= 16) return choose_small(N, C, K, H, W, density, pool, emit, &small_us);
     return best;
 }
 

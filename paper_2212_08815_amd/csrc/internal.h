@@ -202,7 +202,7 @@ const char *sf_variant_name(int variant);
 // false if the variant cannot serve RxS filters at this stride
 bool sf_variant_geom(int variant, int R, int S, int sh, int sw, SfGeom *g);
 int sf_choose_variant(int N, int C, int K, int H, int W, int R, int S, int stride, bool pool, bool n4,
-                      double density, bool banded = false);
+                      double density, bool banded = false, bool emit = false);
 bool sf_variant_has_layout(int variant, int in4, int out4, int pool);
 // csplit > 1: scratch of the launch (N and Ho: slots and rows per band, where the image is banded), and
 // the launch that clears its counters when it is new (a launch leaves them clear)
