@@ -1216,7 +1216,7 @@ static long long sf_blocks(const SfGeom &g, int N, int K, int Ho, int Wo)
 // and stores (F) and per chunk: a fixed part, its bytes through the path from the L2, and its records: P
 // multiply-adds each and a fetch.  Where two work-groups share a CU the second one of a round adds `second` of
 // it.  A split adds its parts' sums: see split_by_launch.  Standard deviation over the 11243 launches of the
-// register-staged configurations 12 %, over 4051 of the others through NCHW tensors 15 %, over 1235 through N4
+// register-staged configurations 12 %, over 4051 of the others through NCHW tensors 15 %, over 2506 through N4
 // tensors 13 %; among register-staged configurations and splits it picks one that takes 2 % more than
 // the best on average, 26 % at most.
 struct Cost {
@@ -1224,7 +1224,7 @@ struct Cost {
 };
 constexpr Cost kCostReg = {3.01, 1.88, 0.238, 0.0248, 0.0069, 0.0271, 0.668, 1.41, 3.72, 0.264};
 constexpr Cost kCostNchw = {2.83, 5.51, 0.507, 0.0219, 0.0073, 0.0191, 0.744, 6.79, 2.58, 0.150};
-constexpr Cost kCostN4 = {2.02, 3.36, 0.501, 0.0089, 0.0040, 0.0411, 0.814, 3.98, 4.29, 0.143};
+constexpr Cost kCostN4 = {2.00, 3.05, 0.641, 0.0058, 0.0043, 0.0404, 0.840, 1.20, 3.60, 0.226};
 constexpr int kSmallFirst = 35, kSmallLast = 43;   // the register-staged configurations
 static const Cost &cost_of(const SfGeom &g, bool in4) { return g.REGST ? kCostReg : in4 ? kCostN4 : kCostNchw; }
 
@@ -1232,14 +1232,21 @@ static const Cost &cost_of(const SfGeom &g, bool in4) { return g.REGST ? kCostRe
 static double part_bytes(const SfGeom &g) { return 256.0 * g.WAVES * g.SLOTS * g.NV * g.BV; }
 
 // Whether the parts of a split are added up by a launch of their own: the last part to arrive reads them
-// at what one CU can take in (about 110 GB/s), a launch at what the chip can, but starts 2 us later.  Measured
+// at what one CU can take in (about 110 GB/s), a launch at what the chip can, in 5 to 7 us.  Measured
 // over 1500 splits: up to 96 KB a work-group the last part is the faster by 0.2 us, at 128 KB the launch by
-// 1, at 512 KB by 3 to 4, at 1 MB by 9.
-static bool split_by_launch(const SfGeom &g, int csplit) { return csplit * part_bytes(g) >= 128 * 1024; }
+// 1, at 512 KB by 3 to 4, at 1 MB by 9; into N4 tensors, which the last parts store four times as fast, the
+// launch is the slower by 1 to 4 where it adds up more than 8 MB in pieces below 384 KB.
+// groups: work-groups without the split
+static bool split_by_launch(const SfGeom &g, int csplit, long long groups, bool out4)
+{
+    const double bytes = csplit * part_bytes(g);
+    return bytes >= 128 * 1024 && (!out4 || bytes >= 384 * 1024 || bytes * groups <= 8 << 20);
+}
 
 // groups: work-groups without a split; emit: the last part adds up, whatever there is (it counts the results)
 static double launch_us(const Cost &m, const SfGeom &g, int csplit, long long groups, int C, double density, bool emit)
 {
+    const bool by_launch = !emit && split_by_launch(g, csplit, groups, &m == &kCostN4);
     groups *= csplit;
     const int NCH = (C + g.CC - 1) / g.CC, chunks = (NCH + csplit - 1) / csplit;
     const double records = density * g.R * g.S * (C < g.CC ? C : g.CC) * g.SLOTS;
@@ -1250,7 +1257,7 @@ static double launch_us(const Cost &m, const SfGeom &g, int csplit, long long gr
                                  : full * (1 + m.second) + (rest > 256 ? 1 + m.second : rest > 0 ? 1 : 0);
     double t = m.launch + rounds * (m.F + chunks * chunk);
     if (csplit > 1)
-        t += split_by_launch(g, csplit) && !emit ? m.finish + m.finish_mb * groups * part_bytes(g) / (1 << 20)
+        t += by_launch ? m.finish + m.finish_mb * groups * part_bytes(g) / (1 << 20)
                                         : m.last * (1 + csplit * part_bytes(g) / 65536);
     return t;
 }
@@ -1424,8 +1431,9 @@ hipError_t launch_conv_sf_tiled(const SfPlan &p, const float *x, int N, int C, i
     float *parts = nullptr;
     if (csplit > 1) {
         if (!scratch) return hipErrorInvalidValue;
-        if (sf_blocks(p.g, N << band_shift, K, band_h, Wo) > kSplitGroups) return hipErrorInvalidValue;
-        if (emit_cnt || !split_by_launch(p.g, csplit)) arrived = static_cast<int *>(scratch);
+        const long long groups = sf_blocks(p.g, N << band_shift, K, band_h, Wo);
+        if (groups > kSplitGroups) return hipErrorInvalidValue;
+        if (emit_cnt || !split_by_launch(p.g, csplit, groups, out4 != 0)) arrived = static_cast<int *>(scratch);
         parts = static_cast<float *>(scratch) + kSplitGroups;
     }
     return fn(p, x, N, C, H, W, K, Ho, Wo, ph, pw, bias, relu, y, csplit, parts, arrived, emit_cnt, band_shift, band_h, st);
