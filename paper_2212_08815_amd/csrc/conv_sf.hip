@@ -73,7 +73,9 @@ struct Cfg {
     static constexpr int P = NV * BV;            // accumulators per lane and channel
     // the channel split is built for configurations with few accumulators, which are the ones small
     // problems use (where there are many its code costs the others registers)
-    static constexpr bool SPLIT = P * SLOTS <= 32;
+    // (not for 32x8 tiles with two channels a wave: a launch with few of them takes the 16x8 ones, and the code for it
+    // cost their pooled form a quarter: 64 -> 64 at 112x112, N = 32, N4: 80 us with it, 60 without)
+    static constexpr bool SPLIT = P * SLOTS <= 32 && !(LW == 32 && NV == 4 && SLOTS == 2);
     static constexpr int TH = LHR * NV, TW = LW; // output tile
     static constexpr int IN_ROWS = TH + (R - 1) / STRIDE;   // rows of one plane
     // Bank conflicts of the 16-byte LDS reads, measured on gfx950 with per-lane offsets: a wave
