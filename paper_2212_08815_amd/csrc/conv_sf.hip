@@ -188,6 +188,17 @@ __device__ inline int xcd_remap(int bid, int nblk)
     return xcd < rem ? xcd * (q + 1) + slot : rem * (q + 1) + (xcd - rem) * q + slot;
 }
 
+// Whether any of a lane's accumulators becomes a result: its column and the first of its rows lie in the image (or
+// band), the first of its images and its wave's first channel exist.  n0, ty0, tx0, k0: of the tile and the wave.
+template <class G>
+__device__ __forceinline__ bool lane_has_output(int lane, int n0, int ty0, int tx0, int k0, int N, int K, int Wo, int band_shift,
+                                                int band_h)
+{
+    const int lg = (lane / G::LW) % G::LHR, lh = (G::LW == 16 && G::LHR == 4) ? (((lg & 1) << 1) | (lg >> 1)) : lg;
+    const int n = (n0 + lane / (G::LW * G::LHR) * G::BV) >> band_shift;
+    return k0 < K && n < N && ty0 + lh * G::NV < band_h && tx0 + lane % G::LW < Wo;
+}
+
 template <class G>
 __global__ void __launch_bounds__(G::NT, G::WPE)
 conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
@@ -657,10 +668,15 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         };
         float *af = &acc[0][0];
         u64 *mine = slot(cs);
+        // (lanes without an output leave nothing and find zeros: three quarters of a 16x16 tile on a 7x7 image; 171 ->
+        // 393 there, N = 4, N4: 18.8 us with them, 15.0 without)
+        const bool live = lane_has_output<G>(lane, n0, ty0, tx0, kg * G::KG + wave * G::SLOTS, N, K, Wo, bsh_out, band_h);
+        if (live) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const u64 v = (u64)__float_as_uint(af[2 * e]) | ((u64)__float_as_uint(af[2 * e + 1]) << 32);
-            __hip_atomic_store(mine + e * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int e = 0; e < E; ++e) {
+                const u64 v = (u64)__float_as_uint(af[2 * e]) | ((u64)__float_as_uint(af[2 * e + 1]) << 32);
+                __hip_atomic_store(mine + e * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         if (!arrived) return;   // split_finish_kernel adds the slots up
         wait_vmcnt<0>();
@@ -674,7 +690,7 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         if (*reinterpret_cast<volatile int *>(ldsb) != csplit - 1) return;
 #pragma unroll
         for (int e = 0; e < 2 * E; ++e) af[e] = 0.0f;
-        for (int p = 0; p < csplit; ++p) {
+        for (int p = 0; p < csplit && live; ++p) {
             const u64 *src = slot(p);
             u64 v[E];
 #pragma unroll
@@ -907,8 +923,11 @@ split_finish_kernel(const float *__restrict__ parts, int csplit, const float *__
     const int lane = threadIdx.x, lid = blockIdx.x / G::WAVES, wave = blockIdx.x % G::WAVES;
     float acc[G::SLOTS][G::P] = {};
     float *af = &acc[0][0];
+    const int t = (lid / NG) % tiles_per_img, n0 = (lid / (NG * tiles_per_img)) * G::IMGS;
+    const bool live = lane_has_output<G>(lane, n0, (t / tiles_x) * G::TH, (t % tiles_x) * G::TW,
+                                         (lid % NG) * G::KG + wave * G::SLOTS, N, K, Wo, G::OUT4 ? 0 : band_shift, band_h);
     const float2 *src = reinterpret_cast<const float2 *>(parts) + ((long long)lid * csplit * G::WAVES + wave) * (E * 64) + lane;
-    for (int p = 0; p < csplit; ++p, src += G::WAVES * E * 64) {
+    for (int p = 0; p < csplit && live; ++p, src += G::WAVES * E * 64) {
         float2 v[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) v[e] = src[e * 64];
@@ -918,7 +937,6 @@ split_finish_kernel(const float *__restrict__ parts, int csplit, const float *__
             af[2 * e + 1] += v[e].y;
         }
     }
-    const int t = (lid / NG) % tiles_per_img, n0 = (lid / (NG * tiles_per_img)) * G::IMGS;
     const int ig = lane / (G::LW * G::LHR), lg = (lane / G::LW) % G::LHR;
     const int lh = (G::LW == 16 && G::LHR == 4) ? (((lg & 1) << 1) | (lg >> 1)) : lg;
     const int ox = (t % tiles_x) * G::TW + lane % G::LW, r0 = (t / tiles_x) * G::TH + lh * G::NV;   // row of the band
@@ -1237,12 +1255,13 @@ static double part_bytes(const SfGeom &g) { return 256.0 * g.WAVES * g.SLOTS * g
 // at what one CU can take in (about 110 GB/s), a launch at what the chip can, in 5 to 7 us.  Measured
 // over 1500 splits: up to 96 KB a work-group the last part is the faster by 0.2 us, at 128 KB the launch by
 // 1, at 512 KB by 3 to 4, at 1 MB by 9; into N4 tensors, which the last parts store four times as fast, the
-// launch is the slower by 1 to 4 where it adds up more than 8 MB in pieces below 384 KB.
+// launch is the slower by 1 to 7 where it adds up more than 12 MB in pieces below 768 KB (256 -> 256 at 8x8, N = 32,
+// pooled, 3 parts of 384 KB together, 24 MB: 32 us by a launch, 24 by the last part).
 // groups: work-groups without the split
 static bool split_by_launch(const SfGeom &g, int csplit, long long groups, bool out4)
 {
     const double bytes = csplit * part_bytes(g);
-    return bytes >= 128 * 1024 && (!out4 || bytes >= 384 * 1024 || bytes * groups <= 8 << 20);
+    return bytes >= 128 * 1024 && (!out4 || bytes >= 768 * 1024 || bytes * groups <= 12 << 20);
 }
 
 // groups: work-groups without a split; emit: the last part adds up, whatever there is (it counts the results)

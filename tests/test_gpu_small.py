@@ -140,6 +140,10 @@ def test_pool_of_scratch_is_bounded_and_given_back(F):
     (5, 120, 70, 17, 19, 3, 2, False, True),   # ... N4 tensors, three idle image slots
     (6, 300, 70, 9, 11, 3, 1, True, True),     # N4, merged pool, odd rows
     (6, 300, 33, 15, 8, 3, 1, False, True),
+    (4, 171, 393, 7, 7, 3, 1, False, True),    # tiles that are mostly padding, whose lanes leave and read nothing
+    (5, 120, 35, 3, 5, 3, 1, False, True),     # ... three idle image slots, waves without a channel
+    (7, 130, 70, 5, 7, 3, 1, True, True),      # ... merged pool: the odd row and column have no result
+    (32, 256, 130, 8, 8, 3, 1, True, True),    # many parts into N4 tensors: the last one to arrive
     (4, 500, 40, 13, 13, 1, 1, False, True),   # 1x1
     (3, 400, 37, 12, 20, 1, 1, False, False),
 ])
