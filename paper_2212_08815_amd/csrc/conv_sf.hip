@@ -1235,16 +1235,17 @@ static long long sf_blocks(const SfGeom &g, int N, int K, int Ho, int Wo)
 // 16..512 channels, 7..224 wide, 1 to 50 % stored).  A round of work-groups over the 256 CUs takes its first loads
 // and stores (F) and per chunk: a fixed part, its bytes through the path from the L2, and its records: P
 // multiply-adds each and a fetch.  Where two work-groups share a CU the second one of a round adds `second` of
-// it.  A split adds its parts' sums: see split_by_launch.  Standard deviation over the 11243 launches of the
+// it.  A split adds its parts' sums: see split_by_launch (register-staged with finish_part: 256 -> 512 at 28x28, N = 1,
+// 10 %, went from 8 parts, 25 us, to 4, 21).  Standard deviation over the 11243 launches of the
 // register-staged configurations 12 %, over 4051 of the others through NCHW tensors 15 %, over 2506 through N4
 // tensors 13 %; among register-staged configurations and splits it picks one that takes 2 % more than
 // the best on average, 26 % at most.
 struct Cost {
-    double launch, F, chunk, kbyte, fma, fetch, second, last, finish, finish_mb;
+    double launch, F, chunk, kbyte, fma, fetch, second, last, finish, finish_part, finish_mb;
 };
-constexpr Cost kCostReg = {3.01, 1.88, 0.238, 0.0248, 0.0069, 0.0271, 0.668, 1.41, 3.72, 0.264};
-constexpr Cost kCostNchw = {2.83, 5.51, 0.507, 0.0219, 0.0073, 0.0191, 0.744, 6.79, 2.58, 0.150};
-constexpr Cost kCostN4 = {2.00, 3.05, 0.641, 0.0058, 0.0043, 0.0404, 0.840, 1.20, 3.60, 0.226};
+constexpr Cost kCostReg = {3.01, 1.88, 0.238, 0.0248, 0.0069, 0.0271, 0.668, 1.75, 3.72, 0.1, 0.314};
+constexpr Cost kCostNchw = {2.83, 5.51, 0.507, 0.0219, 0.0073, 0.0191, 0.744, 6.79, 2.58, 0, 0.150};
+constexpr Cost kCostN4 = {2.00, 3.05, 0.641, 0.0058, 0.0043, 0.0404, 0.840, 1.20, 3.60, 0, 0.226};
 constexpr int kSmallFirst = 35, kSmallLast = 43;   // the register-staged configurations
 static const Cost &cost_of(const SfGeom &g, bool in4) { return g.REGST ? kCostReg : in4 ? kCostN4 : kCostNchw; }
 
@@ -1278,7 +1279,7 @@ static double launch_us(const Cost &m, const SfGeom &g, int csplit, long long gr
                                  : full * (1 + m.second) + (rest > 256 ? 1 + m.second : rest > 0 ? 1 : 0);
     double t = m.launch + rounds * (m.F + chunks * chunk);
     if (csplit > 1)
-        t += by_launch ? m.finish + m.finish_mb * groups * part_bytes(g) / (1 << 20)
+        t += by_launch ? m.finish + m.finish_part * csplit + m.finish_mb * groups * part_bytes(g) / (1 << 20)
                                         : m.last * (1 + csplit * part_bytes(g) / 65536);
     return t;
 }
