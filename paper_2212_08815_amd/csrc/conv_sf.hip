@@ -670,7 +670,10 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
         u64 *mine = slot(cs);
         // (lanes without an output leave nothing and find zeros: three quarters of a 16x16 tile on a 7x7 image; 171 ->
         // 393 there, N = 4, N4: 18.8 us with them, 15.0 without)
-        const bool live = lane_has_output<G>(lane, n0, ty0, tx0, kg * G::KG + wave * G::SLOTS, N, K, Wo, bsh_out, band_h);
+        // (not the register-staged forms, whose bands leave little padding: 13 layers at N = 1 took 303 us with the question,
+        // 298 without)
+        const bool live =
+            G::REGST || lane_has_output<G>(lane, n0, ty0, tx0, kg * G::KG + wave * G::SLOTS, N, K, Wo, bsh_out, band_h);
         if (live) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
