@@ -107,8 +107,8 @@ fscnn_status_t fscnn_filter_prepare(fscnn_filter_t *f, int N, int H, int W, int 
  * partial sums into scratch, which the last one to arrive, or a second launch, adds up in a fixed order), that
  * mode's scratch for `stream`.  Afterwards such calls on `stream` allocate nothing
  * and do not synchronise, which is what a caller that captures them into a HIP graph needs.
- * A call that the dense contraction on the matrix cores is to serve (fscnn_sf_contract_choice) needs a
- * dense copy of the bank (4 bytes per entry, rows and channels padded to 64 and 16, below 2 GiB),
+ * A call that a dense contraction on the matrix cores is to serve (fscnn_sf_contract_choice, fscnn_sf_split_choice) needs a
+ * dense copy of the bank (4 or 6 bytes per entry, rows and channels padded to 64 or 32 and 16, below 2 GiB),
  * which the first such call or this one makes and the handle keeps.  Where there is no room for it, or
  * on a capturing stream before it is made, the call is served by the gather kernels as if there were
  * no contraction (with sums in another order).
@@ -173,14 +173,20 @@ fscnn_status_t fscnn_sf_band_choice(int variant, int N, int Ho, int n4, int pool
                                     int *band_rows_out);
 
 /* How the automatic choice (variant 0, NCHW tensors, no pool) serves a call by the dense contraction on
- * the matrix cores: *tile_out receives the number (0..7) of its tile, or -1 where the configuration of
- * fscnn_sf_variant_choice (or the direct kernel) serves the call, *panels_out the panels the image's
+ * the matrix cores, where fscnn_sf_split_choice below says -1: *tile_out receives the number (0..7) of its tile, or -1 where the
+ * configuration of fscnn_sf_variant_choice (or the direct kernel) serves the call, *panels_out the panels the image's
  * columns are divided into.  Host-only: launches nothing and needs no device. */
 fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h,
                                         int stride_w, int pad_h, int pad_w, int *tile_out,
                                         int *panels_out);
 
-/* The same for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
+/* The same for the contraction with its operands taken apart into bfloat16 parts (3x3 and 5x5; products and sums
+ * as precise as in fp32): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
+ * does.  Host-only. */
+fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h, int stride_w,
+                                     int pad_h, int pad_w, int *tile_out, int *panels_out);
+
+/* The same as fscnn_sf_contract_choice for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
  * values on the contraction serves the call (prepared: fscnn_conv2d_sparse_input_prepared, else
  * fscnn_conv2d_sparse_input), below a gather kernel; *from_out > N*C*H*W: never (then *tile_out may be
  * -1).  Host-only. */

@@ -141,6 +141,7 @@ void free_plan(SfPlan *p, int device)
     if (!p) return;
     const bool idle = p->recs && hipFree(p->recs) == hipSuccess;   // with the pointers behind the records; waits for the device
     if (p->packed) (void)hipFree(p->packed);
+    if (p->parts) (void)hipFree(p->parts);
     int dev = -1;
     const bool keep = idle && hipGetDevice(&dev) == hipSuccess && dev == device;
     for (auto *list : {&p->split, &p->outgrown})
@@ -214,7 +215,7 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
         *out = p;
         return FSCNN_OK;
     }
-    if (variant == kContractPlan) {
+    if (variant == kContractPlan || variant == kSplitPlan) {
         int dev;
         fscnn_status_t ds = have_device(&dev);
         if (ds == FSCNN_OK && dev != f->device) ds = FSCNN_ERR_MISMATCH;
@@ -222,8 +223,14 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
             delete p;
             return ds;
         }
-        hipError_t e = device_alloc(reinterpret_cast<void **>(&p->packed), sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
-        if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
+        hipError_t e;
+        if (variant == kSplitPlan) {
+            e = device_alloc(&p->parts, (size_t)split_packed_bytes(f->K, f->C, f->R * f->S));
+            if (e == hipSuccess) e = launch_split_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->parts, st);
+        } else {
+            e = device_alloc(reinterpret_cast<void **>(&p->packed), sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
+            if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(st);   // the plan may be used from other streams
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -332,32 +339,46 @@ bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int
     return pick->cfg >= 0 && pick->seconds < gather;
 }
 
-// The contraction's plan of an automatic call that it is to serve, NULL where it cannot be made now: no room for
+// Whether such a call is served by the contraction in bfloat16 parts, where what it would go to otherwise takes
+// `other` seconds (512 -> 512 at 28x28, N = 8, any share stored: 250 us contracted in fp32, 132 in parts; gathered 126
+// at 10 % stored; 96 -> 256 5x5 at 27x27, N = 8: 82 and 37).  A tenth ahead, for what two estimates are off.  An emitting call's
+// results are then counted in a pass of their own (4 us).  Not for filters of fewer than 16 stored entries on average: there
+// the rounding of the single products shows (2-norm against 64 bits up to 1.15 times the gather's; from 16 on it was 0.5 times
+// that of what served the call before, over 2112 random layers, and never more).
+bool splits(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int pw, double other, bool emit, ContractPick *pick)
+{
+    const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
+    if (f->nnz < 16LL * f->K || 2 * dense / 350e12 + 3e-6 > other) return false;
+    *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw);
+    return pick->cfg >= 0 && pick->seconds + (emit ? 4e-6 : 0) < 0.9 * other;
+}
+
+// The plan of a contraction (kContractPlan, kSplitPlan) that is to serve an automatic call, NULL where it cannot be made now: no room for
 // the bank as a dense array, or a capture on the stream (building it allocates and waits).  The call then goes to
 // the gather configuration or the direct kernel, which need none of that or fail for reasons of their own.
-fscnn_status_t contract_plan(fscnn_filter_t *f, hipStream_t st, SfPlan **out)
+fscnn_status_t contract_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan **out)
 {
     *out = nullptr;
     {
         std::lock_guard<std::mutex> lock(f->mu);
         for (SfPlan *p : f->plans)
-            if (p->variant == kContractPlan) {
+            if (p->variant == variant) {
                 *out = p;
                 return FSCNN_OK;
             }
     }
     if (capturing(st)) return FSCNN_OK;
-    const fscnn_status_t s = get_plan(f, kContractPlan, st, out);
+    const fscnn_status_t s = get_plan(f, variant, st, out);
     if (s != FSCNN_OK) *out = nullptr;
     return s == FSCNN_ERR_ALLOC ? FSCNN_OK : s;
 }
 
 // How a call is served.  An explicitly selected configuration runs as it is; the automatic choice is
 // remembered for the geometry (evaluating the models takes up to 3 us).  Call with the handle's lock not held.
-fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int in4, int out4, int pool,
+fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int pw, int Ho, int Wo, int in4, int out4, int pool,
                           int variant, bool emit, SfRoute *r)
 {
-    const int key[8] = {N, H, W, sh, sw, Ho, Wo, (in4 ? 1 : 0) | (out4 ? 2 : 0) | (pool ? 4 : 0) | (emit ? 8 : 0)};
+    const int key[9] = {N, H, W, sh, sw, pw, Ho, Wo, (in4 ? 1 : 0) | (out4 ? 2 : 0) | (pool ? 4 : 0) | (emit ? 8 : 0)};
     if (variant == 0) {
         std::lock_guard<std::mutex> lock(f->mu);
         for (const auto &c : f->routes)
@@ -376,6 +397,8 @@ fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw
     if (r->variant > 0)
         r->csplit = sf_choose_csplit(r->variant, N << r->band_shift, f->C, f->K, r->band_h, Wo, density(f), in4, emit, &us);
     r->contract = !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, r->variant, us, &r->pick);
+    if (!in4 && !out4 && !pool)
+        r->split = splits(f, N, H, W, sh, sw, Ho, Wo, pw, r->contract ? r->pick.seconds : 1e-6 * us, emit, &r->spick);
     std::lock_guard<std::mutex> lock(f->mu);
     if (f->routes.size() < 8) {
         f->routes.push_back(*r);
@@ -543,12 +566,14 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (s != FSCNN_OK) return s;
     const int in4 = x_layout == FSCNN_LAYOUT_N4, out4 = y_layout == FSCNN_LAYOUT_N4;
     SfRoute r;
-    s = route_call(f, N, H, W, sh, sw, Ho, Wo, in4, out4, pool, variant, false, &r);
+    s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, in4, out4, pool, variant, false, &r);
     if (s != FSCNN_OK) return s;
     if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
     if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
     SfPlan *p = nullptr;
-    if (r.contract) s = contract_plan(f, (hipStream_t)stream, &p);
+    if (r.split) s = contract_plan(f, kSplitPlan, (hipStream_t)stream, &p);
+    if (s != FSCNN_OK || p) return s;
+    if (r.contract) s = contract_plan(f, kContractPlan, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p) return s;
     s = get_plan(f, r.variant, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p->direct) return s;
@@ -670,10 +695,27 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
     fscnn_status_t s = out_shape(H, W, f->R, f->S, sh, sw, ph, pw, &Ho, &Wo);
     if (s != FSCNN_OK) return s;
     SfRoute r;
-    s = route_call(f, N, H, W, sh, sw, Ho, Wo, 0, 0, 0, 0, false, &r);
+    s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, 0, 0, 0, 0, false, &r);
     if (s != FSCNN_OK) return s;
     *tile_out = r.contract ? r.pick.cfg : -1;
     *panels_out = r.contract ? r.pick.npan : 0;
+    return FSCNN_OK;
+}
+
+fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int ph, int pw,
+                                     int *tile_out, int *panels_out)
+{
+    if (!f || !tile_out || !panels_out) return FSCNN_ERR_NULL;
+    if (!live(f)) return FSCNN_ERR_HANDLE;
+    if (N <= 0) return FSCNN_ERR_SHAPE;
+    int Ho, Wo;
+    fscnn_status_t s = out_shape(H, W, f->R, f->S, sh, sw, ph, pw, &Ho, &Wo);
+    if (s != FSCNN_OK) return s;
+    SfRoute r;
+    s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, 0, 0, 0, 0, false, &r);
+    if (s != FSCNN_OK) return s;
+    *tile_out = r.split ? r.spick.cfg : -1;
+    *panels_out = r.split ? r.spick.npan : 0;
     return FSCNN_OK;
 }
 
@@ -717,7 +759,7 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
         return FSCNN_ERR_UNSUPPORTED;
     if (pool && (Ho < 2 || Wo < 2)) return FSCNN_ERR_SHAPE;   // empty pooled output
     SfRoute r;
-    s = route_call(f, N, H, W, sh, sw, Ho, Wo, in4, out4, pool, variant, emit_cnt != nullptr, &r);
+    s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, in4, out4, pool, variant, emit_cnt != nullptr, &r);
     if (s != FSCNN_OK) return s;
     if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;   // the direct kernel: NCHW, no pool
     if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
@@ -727,7 +769,14 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (dev != f->device) return FSCNN_ERR_MISMATCH;   // the handle's buffers live on another GPU
     hipStream_t st = (hipStream_t)stream;
     SfPlan *p = nullptr;
-    if (r.contract) s = contract_plan(f, st, &p);
+    if (r.split) s = contract_plan(f, kSplitPlan, st, &p);
+    if (s != FSCNN_OK) return s;
+    if (p) {
+        FSCNN_HIP(launch_split_dense(x_dev, p->parts, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, Ho, Wo, sh, sw, ph, pw,
+                                     bias_dev, relu, y_dev, r.spick, st));
+        return FSCNN_OK;
+    }
+    if (r.contract) s = contract_plan(f, kContractPlan, st, &p);
     if (s != FSCNN_OK) return s;
     if (p) {
         // (the tiled gather kernels multiply entries outside the image by zeros as well)

@@ -1,0 +1,542 @@
+// Convolution as a dense contraction on the matrix cores, fp32 operands taken apart into three bfloat16 parts.
+//
+// A float is the exact sum of three bfloat16 numbers (8 + 8 + 8 bits, each part the previous remainder rounded
+// to nearest; exact down to 2^-102, below that the last part loses bits of a subnormal), and a product of two
+// floats is, up to 2^-26 of it, the six products of parts h*h, h*m, m*h, m*m, h*l, l*h.  v_mfma_f32_32x32x16_bf16
+// multiplies at 2.1 PFLOP/s on this chip (registers only), so six of them make 350 TFLOP/s of fp32-like
+// products where v_mfma_f32_16x16x4_f32 (contract.hip) makes 154.  Precision: the matrix unit cuts what it adds
+// two bits below the accumulator's last one, towards zero, which biases a sum that all six products go into (512
+// channels, 3x3: 6.3e-7 of the result in 2-norm, mean -1e-7, against 4.4e-7 of the fp32 unit).  So h*h has an
+// accumulator of its own and the five small products share another one, 2^-8 of its size, added at the end: 1.7e-7.
+//
+// How it is mapped (numbering of pixels, panels and stripes as in contract.hip):
+//   * output channels are the rows of the product, output pixels its columns.  A work-group owns 32*MW channels and
+//     T = 32*NB pixels; of its MW*KS*NW waves (eight), MW lie along the channels (32 rows each), KS take a 16-channel
+//     slice each of every chunk of 16*KS input channels, NW divide the pixel blocks.
+//   * LDS holds the stripe as [octet of channels][pixel][part][8 channels]: 48 bytes per pixel and octet, so that one
+//     ds_read_b128 is the B operand of a part, and consecutive pixels fall on different banks (3 is coprime to 16).
+//     Two buffers, one barrier per chunk: a chunk's stores are spread over the steps of the chunk before, four
+//     pixels of one octet by lane, whose 16-byte loads were issued a chunk earlier.  Pixels outside the image are
+//     cleared once.
+//   * the A operands go from global memory to registers a few taps ahead, packed as the lanes want them:
+//     [32 rows][16 channels][tap][part][lane][8].
+// What bounds it: see the figures at kCost below.
+//
+// Non-finite operands: a value that is Inf, NaN or rounds to an infinite first part has a NaN last part, so every
+// output it is multiplied into (zeros included) is NaN; an output that is not finite is made again entry by
+// entry, from stored entries only (0 * Inf cannot appear).
+#include <type_traits>
+
+#include "internal.h"
+#include "lds_dma.h"
+
+namespace fscnn {
+
+namespace {
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
+
+constexpr int kLdsMax = 160 * 1024 - 512;
+constexpr int kOut = 0x7ffffff0;         // beyond any descriptor's range: the buffer load returns 0
+
+// where an output that is not finite is made again from
+struct SlowArgs {
+    const int *rowptr;                   // filter rows and a dense x, or (NULL)
+    const uint32_t *idx;
+    const float *val;
+    const int *cptr;                     // lists and a dense bank
+    const uint32_t *cidx;
+    const float *xval;
+    int NCP;
+    const float *w;                      // w[k*wk + c*wc + tap*wt]
+    int wk, wc, wt;
+};
+
+struct SpArgs {
+    const float *x;
+    const char *w;
+    const float *bias;
+    float *y;
+    const int *gate;                     // if not NULL and *gate < gate_from, another kernel serves the call
+    int gate_from;
+    int N, C, H, W, K, nslice, nkb, Ho, Wo, sh, sw, ph, pw, act;
+    int SW, tpp, pitch, PL, VR, NKT, QPR, buf_bytes;
+    uint32_t m_qpr, m_vr, m_sw, m_ho;    // reciprocals for div_by()
+    SlowArgs slow;
+};
+
+// x / d for a divisor whose reciprocal ceil(2^31 / d) the host computed; exact while x * d < 2^31
+__device__ inline int div_by(int x, uint32_t m) { return (int)__umulhi((uint32_t)x * 2u, m); }
+inline uint32_t recip_of(int d) { return (uint32_t)(((1LL << 31) + d - 1) / d); }
+
+// the parts of two floats, packed in pairs
+__device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2v));
+    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+    m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{ra, rb}, bf2v));
+    const float la = ra - __uint_as_float(m << 16), lb = rb - __uint_as_float(m & 0xffff0000u);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{la, lb}, bf2v));
+}
+
+template <int MW_, int KS_, int NW_, int NB_, int R_> struct SpCfg {
+    static constexpr int MW = MW_, KS = KS_, NW = NW_, NB = NB_, R = R_, RS = R * R;
+    static constexpr int WAVES = MW * KS * NW, NTH = WAVES * 64;
+    static constexpr int CC = 16 * KS, OCT = 2 * KS;             // channels and octets per chunk
+    static constexpr int T = 32 * NB;
+    static constexpr int NT = (NB + NW - 1) / NW;                // pixel blocks of a wave (the last one may have fewer)
+    static constexpr int SETS = R == 3 ? 3 : 5;                  // taps whose A operands are loaded or in use
+    static constexpr int WPO = WAVES / OCT;                      // waves that stage one octet
+    static constexpr int QMAX = 64 * WPO;                        // items (rows x quads of pixels) of a stripe, at most
+    static constexpr int RED_BYTES = KS > 1 ? WAVES * NT * 64 * 64 : 0;
+    static_assert(WAVES == 8 && WPO * OCT == WAVES && RS % SETS == 0, "layout of the work-group");
+};
+
+template <int I, int N, class F> __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int oy, int ox)
+{
+    constexpr int RS = R * R;
+    const SlowArgs &s = a.slow;
+    float acc = 0.0f;
+    if (s.rowptr) {
+        const float *xn = a.x + (long long)n * a.C * a.H * a.W;
+        for (int i = s.rowptr[k]; i < s.rowptr[k + 1]; ++i) {
+            const uint32_t f = s.idx[i];
+            const int c = (int)(f / RS), rs = (int)(f % RS);
+            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - a.pw + rs % R;
+            if (iy >= 0 && iy < a.H && ix >= 0 && ix < a.W)
+                acc = __builtin_fmaf(s.val[i], xn[((long long)c * a.H + iy) * a.W + ix], acc);
+        }
+    } else {
+        for (int rs = 0; rs < RS; ++rs) {
+            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - a.pw + rs % R;
+            if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W) continue;
+            const long long pix = ((long long)n * a.H + iy) * a.W + ix;
+            for (int i = s.cptr[pix * s.NCP]; i < s.cptr[(pix + 1) * s.NCP]; ++i)
+                acc = __builtin_fmaf(s.xval[i], s.w[(long long)k * s.wk + (long long)s.cidx[i] * s.wc + (long long)rs * s.wt], acc);
+        }
+    }
+    return acc;
+}
+
+// one wave's part: NT blocks of 32 pixels
+template <class G, int NT> __device__ __forceinline__ void split_body(const SpArgs &a, char *ldsb, const int wave, const int lane)
+{
+    const int mw = wave % G::MW, ks = wave / G::MW % G::KS, nw = wave / (G::MW * G::KS);
+    const int j = lane & 31, q = lane >> 5;
+    const int kt = blockIdx.x % a.NKT, tile = blockIdx.x / a.NKT;
+    const int pan = tile / a.tpp;
+    const int p0 = (tile % a.tpp) * G::T;
+    const int ptot = a.N * a.Ho * a.SW;               // pixels of a panel
+    const int plast = p0 + G::T < ptot ? p0 + G::T - 1 : ptot - 1;
+    const int HW = a.H * a.W;
+    auto virt = [&](int v) { return (v / a.Ho) * a.VR + (v % a.Ho) * a.sh; };   // first input row of output row v
+    const int v0 = p0 / a.SW;
+    const int u0 = virt(v0), nrow = virt(plast / a.SW) + G::R - u0;
+    const int n0 = v0 / a.Ho;
+    const int NCH = (a.C + G::CC - 1) / G::CC;
+    if (a.gate && *a.gate < a.gate_from) return;
+
+    // ---- staging: an item is four pixels of a stripe's row (the last ones of a row overlap the ones before), eight channels of each
+    const int oct = wave / G::WPO;
+    int goff = kOut, lpx = -1;                        // byte offset from image n0's first float of the channel; pixel in the stripe
+    {
+        const int e = (wave % G::WPO) * 64 + lane;
+        const int row = div_by(e, a.m_qpr), quad = e - row * a.QPR;
+        const int ul = u0 - n0 * a.VR + row, dn = div_by(ul, a.m_vr);    // image n0 + dn
+        const int iy = ul - dn * a.VR - a.ph, c0 = pan * a.SW * a.sw - a.pw;
+        const int first = c0 > 0 ? c0 : 0, end = c0 + a.pitch < a.W ? c0 + a.pitch : a.W;   // the row's columns in the image: 4 or more
+        const int ix = first + quad * 4 + 4 <= end ? first + quad * 4 : end - 4;
+        if (row < nrow && n0 + dn < a.N && iy >= 0 && iy < a.H) {
+            goff = (dn * a.C * HW + iy * a.W + ix) * 4;
+            lpx = row * a.pitch + ix - c0;
+        }
+    }
+    f4v xr[8];
+    auto load_x = [&](int ci) {
+        const int c0 = ci * G::CC + oct * 8;
+        // from channel c0 of image n0 on; channels past the last one read as zero
+        const float *src = a.x + (c0 < a.C ? ((long long)n0 * a.C + c0) * HW : 0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            // (the condition sits in the descriptor's size: in the offset it becomes a branch)
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src), 0, c0 + t < a.C ? kOut : 0, 0x00020000);
+            xr[t] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rs, goff, t * HW * 4, 0));
+        }
+    };
+    auto store_x = [&](int buf, auto pixel) {         // one of the four pixels
+        constexpr int px = decltype(pixel)::value;
+        u4v h, m, l;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t hh, mm, ll;
+            split2(xr[2 * t][px], xr[2 * t + 1][px], hh, mm, ll);
+            h[t] = hh; m[t] = mm; l[t] = ll;
+        }
+        if (lpx >= 0) {
+            u4v *d = reinterpret_cast<u4v *>(ldsb + buf + (oct * a.PL + lpx + px) * 48);
+            d[0] = h; d[1] = m; d[2] = l;
+        }
+    };
+
+    // a pixel of the tile: row of the panel (from v0 on), column, image and row of the image
+    struct Pos { int ox, dn, oy; };
+    const int x0 = p0 - v0 * a.SW, y0 = v0 - n0 * a.Ho;
+    auto pos_of = [&](int dp) {
+        Pos r;
+        const int dv = div_by(x0 + dp, a.m_sw);
+        r.ox = x0 + dp - dv * a.SW;
+        r.dn = div_by(y0 + dv, a.m_ho);
+        r.oy = y0 + dv - r.dn * a.Ho;
+        return r;
+    };
+    // LDS byte offset of this lane's B operands, per block
+    int boff[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int dp = (nw * G::NT + t) * 32 + j;
+        const Pos r = pos_of(p0 + dp < plast ? dp : plast - p0);
+        boff[t] = (((n0 + r.dn) * a.VR + r.oy * a.sh - u0) * a.pitch + r.ox * a.sw + (ks * 2 + q) * a.PL) * 48;
+    }
+    constexpr int NS = G::RS * NT;                    // steps of a chunk: (tap, block)
+    // blocks whose B operands are requested or in use (a divisor of the steps, so that every step's registers are fixed)
+    constexpr int D = NT >= 4 ? 2 : NS % 3 == 0 ? 3 : NS % 2 == 0 ? 2 : 5;
+    static_assert(NS % D == 0, "ring of B operands");
+    u4v b[D][3];
+    auto read_b = [&](int buf, auto step) {
+        constexpr int st = decltype(step)::value, tap = st / NT;
+        int so = buf + ((tap / G::R) * a.pitch + tap % G::R) * 48;
+        asm volatile("" : "+s"(so));                  // the sum below is made here, not kept in registers from tap to tap
+        const u4v *s = reinterpret_cast<const u4v *>(ldsb + boff[st % NT] + so);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[st % D][p] = s[p];
+    };
+
+    // ---- A operands: this wave's 32 rows, its slice of chunk ci (rows and slices past the last read as zero)
+    const int kb = kt * G::MW + mw;
+    auto weights = [&](int ci) {
+        const bool ok = kb < a.nkb && ci * G::KS + ks < a.nslice;
+        const long long at = ((long long)kb * a.nslice + ci * G::KS + ks) * (G::RS * 3072);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(a.w) + (ok ? at : 0), 0, ok ? G::RS * 3072 : 0, 0x00020000);
+    };
+    u4v av[G::SETS][3];
+    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int tap, u4v (&d)[3]) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) d[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, tap * 3072 + p * 1024, 0);
+    };
+
+    f16v big[NT], small[NT];                          // sums of h*h, and of the five other products
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) big[t][i] = small[t][i] = 0.0f;
+    auto multiply = [&](const u4v (&w)[3], auto step) {
+        constexpr int st = decltype(step)::value, t = st % NT;
+        constexpr int WP[5] = {1, 0, 2, 0, 1}, XP[5] = {1, 2, 0, 1, 0};   // m*m h*l l*h h*m m*h
+#pragma unroll
+        for (int m = 0; m < 5; ++m)
+            small[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8v, w[WP[m]]), __builtin_bit_cast(bf8v, b[st % D][XP[m]]),
+                                                               small[t], 0, 0, 0);
+        big[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8v, w[0]), __builtin_bit_cast(bf8v, b[st % D][0]), big[t], 0, 0, 0);
+    };
+    // (a barrier for LDS alone: __syncthreads() would wait for the A operands in flight as well)
+    auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    {
+        const __amdgpu_buffer_rsrc_t w0 = weights(0);
+#pragma unroll
+        for (int s = 0; s < G::SETS; ++s) load_a(w0, s, av[s]);
+    }
+    load_x(0);
+    for (int e = wave * 64 + lane; e * 16 < 2 * a.buf_bytes; e += G::NTH) reinterpret_cast<u4v *>(ldsb)[e] = u4v{0, 0, 0, 0};
+    lds_barrier();
+    static_for<0, 4>([&](auto px) { store_x(0, px); });
+    lds_barrier();
+    static_for<0, D - 1>([&](auto st) { read_b(0, st); });
+    // the next chunk's pixels are stored at steps LAST-3 .. LAST (several a step where a chunk is short); after LAST
+    // comes the barrier, and then the first reads of the next chunk
+    constexpr int LAST = NS - D, FIRST = LAST >= 3 ? LAST - 3 : 0, PER = (4 + LAST - FIRST) / (LAST + 1 - FIRST);
+    int cur = 0;
+    for (int ci = 0; ci < NCH; ++ci) {
+        const int nxt = a.buf_bytes - cur;
+        // (past the last chunk all loads fall outside their descriptors and read zeros: no branches, behind which
+        // the compiler could not count what is in flight)
+        const __amdgpu_buffer_rsrc_t wcur = weights(ci), wnext = weights(ci + 1);
+        static_for<0, NS>([&](auto step) {
+            constexpr int st = decltype(step)::value, tap = st / NT;
+            if constexpr (st == LAST + 1) lds_barrier();
+            read_b(st + D - 1 < NS ? cur : nxt, std::integral_constant<int, (st + D - 1) % NS>{});
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(av[tap % G::SETS], step);
+            if constexpr (st % NT == NT - 1) {
+                constexpr int up = tap + G::SETS;
+                load_a(up < G::RS ? wcur : wnext, up % G::RS, av[tap % G::SETS]);
+            }
+            if constexpr (st >= FIRST && st <= LAST) {
+                static_for<0, PER>([&](auto i) {
+                    constexpr int px = (st - FIRST) * PER + decltype(i)::value;
+                    if constexpr (px < 4) store_x(nxt, std::integral_constant<int, px>{});
+                });
+            }
+            if constexpr (st == 0) load_x(ci + 1);
+        });
+        cur = nxt;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) big[t] += small[t];
+
+    // ---- the slices' sums, added in order: wave ks finishes registers ks*OWN .. of its blocks
+    constexpr int OWN = 16 / G::KS;
+    float own[NT][OWN];
+    if constexpr (G::KS > 1) {
+        __syncthreads();                              // (the stripe buffers are free)
+        f4v *red = reinterpret_cast<f4v *>(ldsb);
+        auto at = [&](int from, int to, int t, int v) {
+            return ((((nw * G::MW + mw) * G::KS + from) * G::KS + to) * G::NT + t) * (OWN / 4 * 64) + v * 64 + lane;
+        };
+#pragma unroll
+        for (int s = 0; s < G::KS; ++s) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < OWN / 4; ++v) {
+                    const int r = s * OWN + v * 4;
+                    const f4v z = {big[t][r], big[t][r + 1], big[t][r + 2], big[t][r + 3]};
+                    red[at(ks, s, t, v)] = z;
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < OWN / 4; ++v) {
+                f4v sum = red[at(0, ks, t, v)];
+#pragma unroll
+                for (int s = 1; s < G::KS; ++s) sum += red[at(s, ks, t, v)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) own[t][v * 4 + i] = sum[i];
+            }
+    } else {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) own[t][i] = big[t][i];
+    }
+
+    // ---- bias, activation, store: register r of lane (q, j) is row 8*(r/4) + 4*q + r%4 at pixel j
+    const long long plane = (long long)a.Ho * a.Wo;
+    auto row_of = [&](int i) {
+        const int r = ks * OWN + i;
+        return kb * 32 + 8 * (r >> 2) + 4 * q + (r & 3);
+    };
+    bool finite = true;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int dp = (nw * G::NT + t) * 32 + j;
+        const Pos r = pos_of(dp);
+        const int ox = pan * a.SW + r.ox;
+        if (p0 + dp > plast || ox >= a.Wo) continue;
+        float *y = a.y + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wo + ox;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const int k = row_of(i);
+            if (k >= a.K) continue;
+            float v = own[t][i];
+            finite &= __builtin_fabsf(v) < __builtin_inff();
+            if (a.bias) v += a.bias[k];
+            y[(long long)k * plane] = act_apply(v, a.act);
+        }
+    }
+    if (finite) return;
+#pragma nounroll
+    for (int o = 0; o < NT * OWN; ++o) {              // (a lane's own stores: in order)
+        const int t = o / OWN, k = row_of(o % OWN), dp = (nw * G::NT + t) * 32 + j;
+        const Pos r = pos_of(dp);
+        const int ox = pan * a.SW + r.ox;
+        if (p0 + dp > plast || ox >= a.Wo || k >= a.K) continue;
+        float v = slow_output<G::R>(a, n0 + r.dn, k, r.oy, ox);
+        if (a.bias) v += a.bias[k];
+        a.y[((long long)(n0 + r.dn) * a.K + k) * plane + (long long)r.oy * a.Wo + ox] = act_apply(v, a.act);
+    }
+}
+
+template <class G> __global__ void __launch_bounds__(G::NTH, 2) split_kernel(const SpArgs a)
+{
+    extern __shared__ __align__(256) char ldsb[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int LAST_NT = G::NB - (G::NW - 1) * G::NT;
+    if (LAST_NT == G::NT || wave < G::MW * G::KS * (G::NW - 1)) split_body<G, G::NT>(a, ldsb, wave, lane);
+    else split_body<G, LAST_NT>(a, ldsb, wave, lane);
+}
+
+// ---------------------------------------------------------------- packed banks
+
+// zero-filled before
+__global__ void __launch_bounds__(256) split_rows_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
+                                                         const float *__restrict__ val, int RS, int nslice, uint16_t *__restrict__ out)
+{
+    const int k = blockIdx.x;
+    for (int i = rowptr[k] + (int)threadIdx.x; i < rowptr[k + 1]; i += 256) {
+        const int c = (int)(idx[i] / (uint32_t)RS), rs = (int)(idx[i] % (uint32_t)RS);
+        uint32_t h, m, l;
+        split2(val[i], 0.0f, h, m, l);
+        uint16_t *d = out + split_packed_index(k, c, rs, RS, nslice);
+        d[0] = (uint16_t)h; d[512] = (uint16_t)m; d[1024] = (uint16_t)l;
+    }
+}
+__global__ void __launch_bounds__(256) split_clear_kernel(float4 *__restrict__ p, long long n)
+{
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// ---------------------------------------------------------------- launch
+struct Geo { int MW, KS, NW, NB; };
+constexpr Geo kGeo[] = {{2, 2, 2, 7}, {2, 2, 2, 6}, {2, 2, 2, 5}, {2, 2, 2, 4}, {2, 2, 2, 3}, {4, 2, 1, 4}, {4, 2, 1, 3}, {4, 2, 1, 2},
+                        {2, 4, 1, 2}, {2, 4, 1, 1}};
+constexpr int kNGeo = sizeof(kGeo) / sizeof(kGeo[0]);
+
+template <class G> hipError_t launch_cfg(SpArgs a, const ContractPick &p, hipStream_t st)
+{
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&split_kernel<G>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
+    if (attr != hipSuccess) return attr;
+    a.SW = p.SW; a.pitch = p.pitch; a.PL = p.PL; a.buf_bytes = p.buf; a.QPR = p.qpr;
+    a.VR = (a.Ho - 1) * a.sh + G::R;
+    a.m_qpr = recip_of(a.QPR); a.m_vr = recip_of(a.VR); a.m_sw = recip_of(a.SW); a.m_ho = recip_of(a.Ho);
+    a.NKT = (a.K + 32 * G::MW - 1) / (32 * G::MW);
+    const long long P = (long long)a.N * a.Ho * a.SW;
+    a.tpp = (int)((P + G::T - 1) / G::T);
+    const long long nblk = (long long)a.tpp * p.npan * a.NKT;
+    if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * G::NTH > 0xffffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(split_kernel<G>, dim3((unsigned)nblk), dim3(G::NTH), p.lds, st, a);
+    return hipGetLastError();
+}
+
+template <int R> hipError_t launch_any(const SpArgs &a, const ContractPick &p, hipStream_t st)
+{
+    switch (p.cfg) {
+    case 3: return launch_cfg<SpCfg<2, 2, 2, 4, R>>(a, p, st);
+    case 4: return launch_cfg<SpCfg<2, 2, 2, 3, R>>(a, p, st);
+    case 7: return launch_cfg<SpCfg<4, 2, 1, 2, R>>(a, p, st);
+    case 8: return launch_cfg<SpCfg<2, 4, 1, 2, R>>(a, p, st);
+    case 9: return launch_cfg<SpCfg<2, 4, 1, 1, R>>(a, p, st);
+    }
+    if constexpr (R == 3) {   // (for 5x5 the A operands of five taps leave no room for more accumulators)
+        switch (p.cfg) {
+        case 0: return launch_cfg<SpCfg<2, 2, 2, 7, R>>(a, p, st);
+        case 1: return launch_cfg<SpCfg<2, 2, 2, 6, R>>(a, p, st);
+        case 2: return launch_cfg<SpCfg<2, 2, 2, 5, R>>(a, p, st);
+        case 5: return launch_cfg<SpCfg<4, 2, 1, 4, R>>(a, p, st);
+        case 6: return launch_cfg<SpCfg<4, 2, 1, 3, R>>(a, p, st);
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// The configuration of a launch, by a model of its time: rounds of work-groups over the 256 CUs, each taking per
+// chunk its matrix instructions (32 clocks each on four SIMDs), the staging and a fixed part, then a first round
+// trip to memory and its stores; matrix instructions and chunks take longer the fuller the chip is (it runs into its
+// power limit: 2.4 GHz where few CUs work, 1.8 to 2.0 where all do).  Fitted to random geometries of the ranges that
+// the contraction serves: 3x3 at strides 1 and 2, 31091 launches, standard deviation 6 %, its choice 0.8 % slower than
+// the fastest one on average; 5x5, 4632, 5 %, 0.5 %.
+struct SplitCost {
+    double mfma, mfma_fill, stage, chunk, chunk_fill, round, store, launch;
+};
+constexpr SplitCost kSplitCost[] = {{0.916, 0.425, 53.1, 2077, 0.315, 7974, 1197, 2.28},    // 3x3
+                                    {0.876, 0.325, 60.9, 3502, 0.805, 6873, 1215, 2.89}};   // 5x5
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw)
+{
+    ContractPick best;
+    // (rows are loaded four columns at a time)
+    if (R != S || (R != 3 && R != 5) || W < 4) return best;
+    // weights and the images a stripe can touch are addressed with 32-bit byte offsets, pixels of a
+    // panel numbered with ints
+    const long long big = 0x7fffffffLL;
+    if (split_packed_bytes(K, C, R * S) >= big || (long long)N * Ho * (Wo + 64) >= big || (long long)N * H * W >= big ||
+        (long long)N * ((long long)(Ho - 1) * sh + R) >= big || (Ho - 1) * (long long)sh + R > 40000 || Wo > 40000)
+        return best;
+    const SplitCost &m = kSplitCost[R == 3 ? 0 : 1];
+    int last_npan = 0;
+    for (int target : {40000, 64, 48, 32, 24, 16, 12, 8, 6}) {          // widths of a panel
+        const int npan0 = (Wo + target - 1) / target, SW = (Wo + npan0 - 1) / npan0, npan = (Wo + SW - 1) / SW;
+        if (npan == last_npan) continue;
+        last_npan = npan;
+        const int pitch = (SW - 1) * sw + S;
+        // columns of a panel that lie in the image: at least one load's worth, at most qpr
+        int most = 0, least = W;
+        for (int p = 0; p < npan; ++p) {
+            const long long c0 = (long long)p * SW * sw - pw, first = c0 > 0 ? c0 : 0, end = c0 + pitch < W ? c0 + pitch : W;
+            const int have = end > first ? (int)(end - first) : 0;
+            most = have > most ? have : most;
+            least = have < least ? have : least;
+        }
+        if (least < 4) continue;
+        const int qpr = (most + 3) / 4;
+        const long long P = (long long)N * Ho * SW;
+        for (int g = 0; g < kNGeo; ++g) {
+            const Geo &q = kGeo[g];
+            const int T = 32 * q.NB, NT = (q.NB + q.NW - 1) / q.NW;
+            if (R == 5 && NT > 2) continue;
+            const int rows = (T + SW - 2) / SW + 1;             // output rows a tile can touch
+            const int cross = (rows - 1 + Ho - 1) / Ho;         // image boundaries among them
+            const long long nrow = (long long)(rows - 1) * sh + R + (long long)cross * (R > sh ? R - sh : 0);
+            if (nrow * qpr > 64 * 8 / (2 * q.KS)) continue;
+            if ((cross + 2LL) * (C + 8) * H * W * 4 >= big - 64) continue;
+            const long long npx = nrow * pitch;
+            const long long buf = npx * 48 * 2 * q.KS;
+            const long long red = 8LL * NT * 64 * 64;
+            const long long lds = 2 * buf > red ? 2 * buf : red;
+            if (lds > kLdsMax) continue;
+            const long long nwg = (P + T - 1) / T * npan * ((K + 32 * q.MW - 1) / (32 * q.MW));
+            const int nch = (C + 16 * q.KS - 1) / (16 * q.KS);
+            const double rounds = (double)((nwg + 255) / 256), fill = (double)nwg / (256 * rounds);
+            const double mfma = 48.0 * q.MW * q.NB * q.KS * R * S;
+            const double chunk = m.mfma * (1 + m.mfma_fill * fill) * mfma + m.stage * q.KS / 32 * (double)npx + m.chunk * (1 + m.chunk_fill * fill);
+            const double seconds = rounds * (nch * chunk + m.round + m.store * q.MW * q.NB) / 2.4e9 + m.launch * 1e-6;
+            if (best.cfg < 0 || seconds < best.seconds) {
+                best.seconds = seconds;
+                best.cfg = g; best.npan = npan; best.lds = (int)lds; best.qpr = qpr;
+                best.SW = SW; best.pitch = pitch; best.PL = (int)npx; best.buf = (int)buf;
+            }
+        }
+    }
+    return best;
+}
+
+hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS, void *packed, hipStream_t st)
+{
+    const long long n16 = split_packed_bytes(K, C, RS) / 16;
+    hipLaunchKernelGGL(split_clear_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, static_cast<float4 *>(packed), n16);
+    hipLaunchKernelGGL(split_rows_kernel, dim3(K), dim3(256), 0, st, rowptr, idx, val, RS, (C + 15) / 16, static_cast<uint16_t *>(packed));
+    return hipGetLastError();
+}
+
+hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
+                              int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
+                              float *y, const ContractPick &p, hipStream_t st)
+{
+    if (p.cfg < 0) return hipErrorInvalidValue;
+    SpArgs a = {};
+    a.x = x; a.w = static_cast<const char *>(packed); a.bias = bias; a.y = y;
+    a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.nslice = (C + 15) / 16; a.nkb = (K + 31) / 32; a.Ho = Ho; a.Wo = Wo;
+    a.sh = sh; a.sw = sw; a.ph = ph; a.pw = pw; a.act = act;
+    a.slow.rowptr = rowptr; a.slow.idx = idx; a.slow.val = val;
+    return R == 3 ? launch_any<3>(a, p, st) : launch_any<5>(a, p, st);
+}
+
+}  // namespace fscnn

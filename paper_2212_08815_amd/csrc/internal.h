@@ -81,23 +81,28 @@ struct SfPlan {
     // packed array (contract_packed_index), zeros where nothing is stored; behind it an int that is
     // non-zero if a stored value is Inf or NaN (16 bytes).
     float *packed = nullptr;
+    // The plan of the contraction in bfloat16 parts (variant kSplitPlan): the parts (split_packed_index).
+    void *parts = nullptr;
 };
-constexpr int kDirectPlan = -1, kContractPlan = -2;
+constexpr int kDirectPlan = -1, kContractPlan = -2, kSplitPlan = -3;
 
 // How a call of the contraction on the matrix cores would be launched (cfg < 0: it is not served) and an estimate of its time.  Host only.
 struct ContractPick {
     int cfg = -1, npan = 1, lds = 0, SW = 0, pitch = 0, PL = 0, buf = 0;
+    int qpr = 0;                           // in bfloat16 parts: loads of four columns per row of a stripe
     double seconds = 0;
 };
 
 // How a sparse-filter call is served.
 struct SfRoute {
-    int key[8];
+    int key[9];
     int variant = 0;                       // configuration, or kDirectPlan
     int band_shift = 0, band_h = 0;        // sf_choose_bands
     int csplit = 1;                        // sf_choose_csplit
     bool contract = false;                 // by the contraction, as `pick` says, once its plan is there
     ContractPick pick;
+    bool split = false;                    // by the contraction in bfloat16 parts, as `spick` says, once its plan is there
+    ContractPick spick;
 };
 
 struct SiGeom {
@@ -252,6 +257,19 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
                                  const float *val, int N, int C, int H, int W, int K, int R, int S, int Ho, int Wo,
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st);
+// ---- contract_split.hip: the same contraction with the operands taken apart into three bfloat16 parts; 3x3 and 5x5
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw);
+// Packed banks: position of the first part of w[k][c][tap] in 16-bit words (the others 512 and 1024 behind it), and the
+// number of bytes
+__host__ __device__ inline long long split_packed_index(int k, int c, int rs, int RS, int nslice)
+{
+    return (((long long)(k >> 5) * nslice + (c >> 4)) * RS + rs) * 1536 + ((c >> 3) & 1) * 256 + (k & 31) * 8 + (c & 7);
+}
+inline long long split_packed_bytes(int K, int C, int RS) { return (long long)((K + 31) / 32) * ((C + 15) / 16) * RS * 3072; }
+hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS, void *packed, hipStream_t st);
+hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
+                              int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
+                              float *y, const ContractPick &p, hipStream_t st);
 // compressed activation, 3x3 at stride 1; with wflag: w is packed and wflag its non-finite flag,
 // without: w is K x C x 3 x 3.  gate (device, packed banks only) with fewer than gate_from: the launch does nothing; NULL: it runs
 hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,

@@ -35,7 +35,7 @@ EXPORTS = [
     "fscnn_sparse_transpose", "fscnn_sparse_tensor_transpose", "fscnn_sparse_transpose_workspace",
     "fscnn_dense_filter_prepare", "fscnn_dense_filter_destroy", "fscnn_conv2d_sparse_input_prepared",
     "fscnn_si_variant_count", "fscnn_conv2d_sparse_filter_leaky", "fscnn_sparse_transpose_noalloc",
-    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_si_contract_choice", "fscnn_pool_trim",
+    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_sf_split_choice", "fscnn_si_contract_choice", "fscnn_pool_trim",
 ]
 
 NCHW, N4 = 0, 1      # fscnn_layout_t
@@ -158,6 +158,14 @@ def sf_contract_choice(f, N, H, W, stride=(1, 1), pad=(0, 0)):
     t, p = ctypes.c_int(0), ctypes.c_int(0)
     _check(lib().fscnn_sf_contract_choice(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
                                           ctypes.byref(t), ctypes.byref(p)), "fscnn_sf_contract_choice")
+    return t.value, p.value
+
+
+def sf_split_choice(f, N, H, W, stride=(1, 1), pad=(0, 0)):
+    """fscnn_sf_split_choice -> (tile of the contraction in bfloat16 parts that serves an automatic NCHW call, panels); tile -1: it does not."""
+    t, p = ctypes.c_int(), ctypes.c_int()
+    _check(lib().fscnn_sf_split_choice(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
+                                       ctypes.byref(t), ctypes.byref(p)), "fscnn_sf_split_choice")
     return t.value, p.value
 
 
