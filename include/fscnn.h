@@ -187,12 +187,18 @@ fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int
                                      int pad_h, int pad_w, int *tile_out, int *panels_out);
 
 /* The same as fscnn_sf_contract_choice for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
- * values on the contraction serves the call (prepared: fscnn_conv2d_sparse_input_prepared, else
+ * values on the contraction serves the call, where fscnn_si_split_choice below does not say otherwise (prepared: fscnn_conv2d_sparse_input_prepared, else
  * fscnn_conv2d_sparse_input), below a gather kernel; *from_out > N*C*H*W: never (then *tile_out may be
  * -1).  Host-only. */
 fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int pad_h, int pad_w,
                                         int prepared, long long *from_out, int *tile_out,
                                         int *panels_out);
+
+/* The same for the contraction in bfloat16 parts: it serves the call, with tile 0..9, from *from_out stored values on,
+ * whatever fscnn_si_contract_choice says, where the handle keeps the activation's dense form: fscnn_input_compress up to
+ * 256 MB of pairs, fscnn_conv2d_sparse_filter_emit without a y_dev.  Host-only. */
+fscnn_status_t fscnn_si_split_choice(int N, int C, int H, int W, int K, int pad_h, int pad_w, int prepared,
+                                     long long *from_out, int *tile_out, int *panels_out);
 
 /* Sparse-filter convolution (Alg. 6: every output element, all filters; inner product of
  * Alg. 2 over the stored nonzeros only; no kernel flip; padding as index shift):
@@ -272,7 +278,7 @@ fscnn_status_t fscnn_layout_convert(const float *src_dev, int N, int C, int H, i
  * Activation compression (Sec. 3, sparse 3-D tensor in order O_chw: the channel run is the
  * innermost list): one row per pixel in (n, iy, ix) raster order holding the (channel,
  * value) pairs with x != 0.0f, channel ascending.  C up to 8192 (beyond:
- * FSCNN_ERR_UNSUPPORTED).  Allocates the handle's buffers (room for every value up to 256 MB of
+ * FSCNN_ERR_UNSUPPORTED).  Allocates the handle's buffers (room for every value, as pairs and dense, up to 256 MB of
  * pairs, but no more than 1 GB beyond what all live handles store; beyond that, or if there is no such room, for
  * the stored ones) and synchronises `stream` once, for the number of stored
  * values.  The pass that writes the pairs may still be queued on `stream` when the call returns: x_dev must stay valid until
@@ -327,7 +333,10 @@ fscnn_status_t fscnn_conv2d_sparse_filter_emit_into(fscnn_filter_t *f, const flo
  * loops of Alg. 1 with a sparse T_I and dense filters; zero activations are skipped):
  * same result definition as above with w_dev the dense K x C x R x S bank.  The output is
  * written dense (N x K x Ho x Wo).  Every output element has one writer (a gather, no
- * atomics).  Asynchronous on `stream`; allocates nothing. */
+ * atomics).  Asynchronous on `stream`.  Where the contraction in bfloat16 parts serves the call
+ * (fscnn_si_split_choice) the first call of a handle on a stream, and the first with a larger bank, allocates room for
+ * the bank's parts (6 bytes per entry, rounded up to a power of two), which the handle keeps; on a capturing stream
+ * before that, or without that room, the contraction in fp32 serves it.  Allocates nothing otherwise. */
 fscnn_status_t fscnn_conv2d_sparse_input(const fscnn_input_t *in, const float *w_dev, int K,
                                          int R, int S, int stride_h, int stride_w, int pad_h,
                                          int pad_w, const float *bias_dev, int relu,

@@ -426,6 +426,28 @@ long long input_nnz(const fscnn_input_t *in)
     return total;
 }
 
+// Room for a bank in bfloat16 parts on `st`: the buffer this stream used before on the handle if it is large enough, else a
+// new one; NULL where there is none and none can be made (no room, or `st` is capturing).  One per stream: calls that share a
+// handle on different streams never share it.
+void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
+{
+    std::lock_guard<std::mutex> lock(in->mu);
+    for (auto &b : in->banks)
+        if (b.stream == st && b.bytes >= bytes) return b.buf;
+    void *p = nullptr;
+    if (capturing(st)) return nullptr;
+    size_t room = 1 << 20;                            // (powers of two: what outgrown buffers hold is bounded by the largest)
+    while (room < bytes) room *= 2;
+    bytes = room;
+    if (device_alloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    // (a smaller one stays with the handle: launches in flight and graphs captured so far use it)
+    in->banks.push_back({st, p, bytes});
+    return p;
+}
+
 // Orders work on `st` behind the pass that fills a compressed-activation handle (it runs on the
 // stream the handle was made on and may still be in flight).
 hipError_t after_fill(const fscnn_input_t *in, hipStream_t st)
@@ -729,10 +751,27 @@ fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int p
     if (s != FSCNN_OK) return s;
     if (!fits_int((long long)N * C * H * W) || !fits_int((long long)N * K * Ho * Wo) || !fits_int((long long)K * C * 9))
         return FSCNN_ERR_UNSUPPORTED;
-    const SiChoice c = si_choose(N, C, H, W, K, Ho, Wo, prepared != 0);
+    const SiChoice c = si_choose(N, C, H, W, K, Ho, Wo, pw, prepared != 0);
     *from_out = c.from;
     *tile_out = c.pick.cfg;
     *panels_out = c.pick.cfg < 0 ? 0 : c.pick.npan;
+    return FSCNN_OK;
+}
+
+fscnn_status_t fscnn_si_split_choice(int N, int C, int H, int W, int K, int ph, int pw, int prepared, long long *from_out,
+                                     int *tile_out, int *panels_out)
+{
+    if (!from_out || !tile_out || !panels_out) return FSCNN_ERR_NULL;
+    if (N <= 0 || C <= 0 || K <= 0) return FSCNN_ERR_SHAPE;
+    int Ho, Wo;
+    fscnn_status_t s = out_shape(H, W, 3, 3, 1, 1, ph, pw, &Ho, &Wo);
+    if (s != FSCNN_OK) return s;
+    if (!fits_int((long long)N * C * H * W) || !fits_int((long long)N * K * Ho * Wo) || !fits_int((long long)K * C * 9))
+        return FSCNN_ERR_UNSUPPORTED;
+    const SiChoice c = si_choose(N, C, H, W, K, Ho, Wo, pw, prepared != 0);
+    *from_out = c.split_from;
+    *tile_out = c.spick.cfg;
+    *panels_out = c.spick.cfg >= 0 ? c.spick.npan : 0;
     return FSCNN_OK;
 }
 
@@ -875,7 +914,7 @@ fscnn_status_t fscnn_conv2d_sparse_filter(fscnn_filter_t *f, const float *x_dev,
 
 // Dense N x C x H x W activations -> compressed handle.  Synchronises st once, for the number of stored
 // values.  Up to kWholeBytes of indices and values, were every value stored, are allocated with the
-// pointers before anything runs, and the passes follow each other without the host; beyond that the
+// pointers before anything runs (and as much again for the dense form, input_dense_from()), and the passes follow each other without the host; beyond that the
 // number of stored values sizes a second allocation (making and releasing one takes 50 us, more than
 // the passes of a 28x28 layer), and also where the live handles already hold kUnusedBytes more than they store
 // or the allocation fails.  The pass that fills the handle may still be running on st when this
@@ -914,10 +953,11 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     const size_t nodes_at = scratch_at + up(sizeof(int) * (size_t)input_scratch_elems(npix, NCH));
     auto val_at = [&](size_t n) { return up(n * sizeof(uint32_t)); };
     const size_t most = (size_t)(npix * C) + kSiSpare;
-    bool whole = npix * C * 8 <= kWholeBytes && unused_bytes.load() + npix * C * 8 <= kUnusedBytes;
+    const size_t dense_at = up(nodes_at + val_at(most) + most * sizeof(float));
+    bool whole = npix * C * 8 <= kWholeBytes && unused_bytes.load() + npix * C * 12 <= kUnusedBytes;
     hipError_t e = hipErrorOutOfMemory;
     if (whole) {
-        e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at + val_at(most) + most * sizeof(float));
+        e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), dense_at + sizeof(float) * (size_t)(npix * C));
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             whole = false;
@@ -928,7 +968,8 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     auto fill = [&](void *nodes, size_t n) {
         in->cidx = static_cast<uint32_t *>(nodes);
         in->xval = reinterpret_cast<float *>(static_cast<char *>(nodes) + val_at(n));
-        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, st);
+        float *dense = whole ? reinterpret_cast<float *>(static_cast<char *>(in->ptr_block) + dense_at) : nullptr;
+        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, dense, st);
     };
     if (e == hipSuccess) {
         char *base = static_cast<char *>(in->ptr_block);
@@ -944,6 +985,8 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         in->nnz = total;
         if (whole) {
             in->unused = 8 * (npix * C - total);
+            if (total >= input_dense_from(npix, C)) in->dense = reinterpret_cast<float *>(static_cast<char *>(in->ptr_block) + dense_at);
+            else in->unused += 4 * npix * C;
             unused_bytes += in->unused;
         } else {
             const size_t n = (size_t)total + kSiSpare;
@@ -1034,13 +1077,14 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
     hipError_t e = hipSuccess;
     int *scratch = reinterpret_cast<int *>(base + L.sum_at);
     e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, st);
-    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, st);
+    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, nullptr, st);
     if (e == hipSuccess) e = hipEventRecord(in->filled, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
     }
     in->nnz = -1;
+    in->dense = y_dev ? nullptr : y;   // the handle's own result stays as it is until the next fill
     in->made_on = st;
     return FSCNN_OK;
 }
@@ -1164,6 +1208,7 @@ fscnn_status_t fscnn_input_destroy(fscnn_input_t *in)
     (void)hipEventDestroy(in->filled);
     if (in->ptr_block) (void)hipFree(in->ptr_block);
     if (in->node_block) (void)hipFree(in->node_block);
+    for (auto &b : in->banks) (void)hipFree(b.buf);
     unused_bytes -= in->unused;
     delete in;
     return FSCNN_OK;
@@ -1185,9 +1230,17 @@ fscnn_status_t fscnn_conv2d_sparse_input(const fscnn_input_t *in, const float *w
     s = have_device(&dev);
     if (s != FSCNN_OK) return s;
     if (dev != in->device) return FSCNN_ERR_MISMATCH;
-    FSCNN_HIP(after_fill(in, (hipStream_t)stream));
-    FSCNN_HIP(launch_conv_si(in, w_dev, K, R, S, Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev,
-                             (hipStream_t)stream));
+    hipStream_t st = (hipStream_t)stream;
+    SiChoice c;
+    void *bank = nullptr;
+    const bool chosen = si_tiled_supported(K, in->C, R, S, sh, sw);
+    if (chosen) {
+        c = si_choose(in->N, in->C, in->H, in->W, K, Ho, Wo, pw, false);
+        if (in->dense && (in->nnz < 0 ? c.split_from <= (long long)in->N * in->C * in->H * in->W : in->nnz >= c.split_from))
+            bank = bank_scratch(in, st, (size_t)split_packed_bytes(K, in->C, 9));
+    }
+    FSCNN_HIP(after_fill(in, st));
+    FSCNN_HIP(launch_conv_si(in, w_dev, K, R, S, Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, chosen ? &c : nullptr, bank, st));
     return FSCNN_OK;
 }
 
@@ -1210,7 +1263,14 @@ fscnn_status_t fscnn_dense_filter_prepare(const float *w_dev, int K, int C, int 
     const size_t words = (size_t)Kpad * C * R * S;
     bool pack = R == 3 && S == 3;   // what the prepared calls serve
     const size_t packed = pack ? (size_t)Kpad * ((C + 15) / 16 * 16) * 9 : 0;
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&d->wT), sizeof(float) * (words + packed) + 256);
+    const size_t two = (sizeof(float) * (words + packed) + 256 + 255) / 256 * 256;
+    bool parts = pack;
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&d->wT), parts ? two + (size_t)split_packed_bytes(K, C, 9) : two);
+    if (e == hipErrorOutOfMemory && parts) {   // without the third copy
+        (void)hipGetLastError();
+        parts = false;
+        e = device_alloc(reinterpret_cast<void **>(&d->wT), two);
+    }
     if (e == hipErrorOutOfMemory && pack) {   // without the second copy: the gather kernels serve every call
         (void)hipGetLastError();
         pack = false;
@@ -1218,9 +1278,11 @@ fscnn_status_t fscnn_dense_filter_prepare(const float *w_dev, int K, int C, int 
     }
     d->packed = pack ? d->wT + words : nullptr;
     d->flag = pack ? reinterpret_cast<int *>(d->packed + packed) : nullptr;
+    d->parts = parts ? reinterpret_cast<char *>(d->wT) + two : nullptr;
     if (e == hipSuccess)
         e = pack ? launch_pack_dense(w_dev, K, C, Kpad, d->packed, d->wT, d->flag, (hipStream_t)stream)
                  : launch_dense_transpose(w_dev, K, C, R * S, Kpad, d->wT, (hipStream_t)stream);
+    if (e == hipSuccess && parts) e = launch_split_bank(w_dev, K, C, d->parts, (hipStream_t)stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         if (d->wT) (void)hipFree(d->wT);

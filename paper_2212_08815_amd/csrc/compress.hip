@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
                                                             long long npix, int NCH, int PX,
                                                             const int *__restrict__ start, int *__restrict__ cptr,
                                                             uint32_t *__restrict__ cidx, float *__restrict__ xval,
-                                                            int spare)
+                                                            int spare, float *__restrict__ dense, int dense_from)
 {
     constexpr int CC = kSiCC;
     extern __shared__ uint32_t stage[];   // [cap] value bit patterns, then in 16 bits [cap] channels, [PX * NCH] positions
@@ -415,7 +415,9 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
     const int px = threadIdx.x % PX, sj = threadIdx.x / PX, SJ = kBlock / PX;
     const long long p = p0 + px;
     const bool live = p < npix;
-    const float *xp = live ? x + p / HW * C * HW + p % HW : x;
+    const long long first = live ? p / HW * C * HW + p % HW : 0;
+    const float *xp = x + first;
+    float *dp = live && dense && start[gridDim.x] >= dense_from ? dense + first : nullptr;
     auto load = [&](int j, float(&v)[CC]) {
 #pragma unroll
         for (int u = 0; u < CC; ++u) {
@@ -424,6 +426,13 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
         }
     };
     auto count = [&](int j, const float(&v)[CC]) {
+        if (dp) {
+#pragma unroll
+            for (int u = 0; u < CC; ++u) {
+                const int ch = j * CC + u;
+                if (j < NCH && ch < C) dp[(long long)ch * HW] = v[u];
+            }
+        }
         int c = 0;
 #pragma unroll
         for (int u = 0; u < CC; ++u) c += v[u] != 0.0f ? 1 : 0;
@@ -652,13 +661,13 @@ hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H
 }
 
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, hipStream_t st)
+                             uint32_t *cidx, float *xval, int spare, float *dense, hipStream_t st)
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0 || spare >= kBlock) return hipErrorInvalidValue;
     const int PX = input_pixels(NCH);
     hipLaunchKernelGGL(input_fill_kernel, dim3((unsigned)g), dim3(kBlock), (size_t)PX * NCH * kFillBytes, st, x, C,
-                       HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare);
+                       HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, dense ? (int)input_dense_from(npix, C) : 0);
     return hipGetLastError();
 }
 

@@ -58,8 +58,8 @@ struct DcArgs {
     const int *cptr;                     // list source
     const uint32_t *cidx;
     const float *xval;
-    const int *gate;                     // lists, packed bank: if not NULL and *gate < gate_from, another kernel serves the call
-    int gate_from;
+    const int *gate;                     // lists: if not NULL, another kernel serves the call unless gate_from <= *gate < gate_to
+    int gate_from, gate_to;
     const float *w;
     const int *wflag;                    // kWPacked: non-zero if the bank holds an Inf or NaN; NULL: it does not matter
     const int *rowptr;                   // dense source: the stored entries, for the slow way
@@ -161,8 +161,8 @@ __global__ void __launch_bounds__(G::NTH, G::WPE) contract_kernel(const DcArgs a
     const int n0 = v0 / a.Ho;
 
     // (here, where the arguments have arrived: at the top it cost every call one more round trip for them)
-    if constexpr (G::SRC == kSrcLists && G::WSRC == kWPacked)
-        if (a.gate && *a.gate < a.gate_from) return;
+    if constexpr (G::SRC == kSrcLists)
+        if (a.gate && (*a.gate < a.gate_from || *a.gate >= a.gate_to)) return;
 
     // where the stripe's pixels lie: dense source: byte offset from image n0's first float of the
     // channel; lists: byte offset of the pixel's pointers from image n0's; kOut: outside the image
@@ -674,11 +674,11 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
 
 hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,
                                  int Wo, int ph, int pw, const float *bias, int relu, float *y,
-                                 const ContractPick &p, const int *gate, int gate_from, hipStream_t st)
+                                 const ContractPick &p, const int *gate, int gate_from, int gate_to, hipStream_t st)
 {
     if (p.cfg < 0 || in->CC != kSiCC) return hipErrorInvalidValue;
     DcArgs a = {};
-    a.gate = gate; a.gate_from = gate_from; a.cptr = in->cptr; a.cidx = in->cidx; a.xval = in->xval; a.NCP = in->NCH;
+    a.gate = gate; a.gate_from = gate_from; a.gate_to = gate_to; a.cptr = in->cptr; a.cidx = in->cidx; a.xval = in->xval; a.NCP = in->NCH;
     a.w = w; a.nslice = (in->C + 15) / 16; a.wflag = wflag; a.bias = bias; a.y = y;
     a.N = in->N; a.C = in->C; a.H = in->H; a.W = in->W; a.K = K; a.R = 3; a.S = 3; a.Ho = Ho; a.Wo = Wo;
     a.sh = a.sw = 1; a.ph = ph; a.pw = pw; a.act = relu;

@@ -22,6 +22,9 @@
 //     [32 rows][16 channels][tap][part][lane][8].
 // What bounds it: see the figures at kCost below.
 //
+// A compressed activation is served from the dense form its handle keeps (si_choose in conv_si.hip says when), with a
+// dense 3x3 bank taken apart as it is prepared or, where the caller holds it, before the launch.
+//
 // Non-finite operands: a value that is Inf, NaN or rounds to an infinite first part has a NaN last part, so every
 // output it is multiplied into (zeros included) is NaN; an output that is not finite is made again entry by
 // entry, from stored entries only (0 * Inf cannot appear).
@@ -396,6 +399,31 @@ __global__ void __launch_bounds__(256) split_rows_kernel(const int *__restrict__
         d[0] = (uint16_t)h; d[512] = (uint16_t)m; d[1024] = (uint16_t)l;
     }
 }
+// of a dense K x C x 3 x 3 bank: a work-group takes 32 rows and 16 channels through LDS, so that reads and writes are whole lines
+// (512 x 512: 9.4 MB read, 14.2 written in 9 us)
+__global__ void __launch_bounds__(256) split_dense_kernel(const float *__restrict__ w, int K, int C, int nslice, u4v *__restrict__ out)
+{
+    __shared__ float tile[32][145];
+    const int sl = blockIdx.x % nslice, kb = blockIdx.x / nslice;
+    for (int e = threadIdx.x; e < 32 * 144; e += 256) {
+        const int r = e / 144, f = e % 144, k = kb * 32 + r, c = sl * 16 + f / 9;
+        tile[r][f] = k < K && c < C ? w[((long long)k * C + sl * 16) * 9 + f] : 0.0f;
+    }
+    __syncthreads();
+    u4v *dst = out + (long long)blockIdx.x * (9 * 192);
+    for (int e = threadIdx.x; e < 9 * 64; e += 256) {
+        const int tap = e / 64, lane = e % 64;
+        const float *src = &tile[lane & 31][(lane >> 5) * 72 + tap];
+        u4v h, m, l;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t hh, mm, ll;
+            split2(src[t * 18], src[t * 18 + 9], hh, mm, ll);
+            h[t] = hh; m[t] = mm; l[t] = ll;
+        }
+        dst[tap * 192 + lane] = h; dst[tap * 192 + 64 + lane] = m; dst[tap * 192 + 128 + lane] = l;
+    }
+}
 __global__ void __launch_bounds__(256) split_clear_kernel(float4 *__restrict__ p, long long n)
 {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -537,6 +565,29 @@ hipError_t launch_split_dense(const float *x, const void *packed, const int *row
     a.sh = sh; a.sw = sw; a.ph = ph; a.pw = pw; a.act = act;
     a.slow.rowptr = rowptr; a.slow.idx = idx; a.slow.val = val;
     return R == 3 ? launch_any<3>(a, p, st) : launch_any<5>(a, p, st);
+}
+
+hipError_t launch_split_bank(const float *w, int K, int C, void *packed, hipStream_t st)
+{
+    const int nslice = (C + 15) / 16;
+    hipLaunchKernelGGL(split_dense_kernel, dim3((unsigned)((long long)nslice * ((K + 31) / 32))), dim3(256), 0, st, w, K, C, nslice,
+                       static_cast<u4v *>(packed));
+    return hipGetLastError();
+}
+
+hipError_t launch_split_input(const fscnn_input *in, const void *packed, const float *w, int wk, int wc, int wt, int K, int Ho, int Wo,
+                              int ph, int pw, const float *bias, int relu, float *y, const ContractPick &p, const int *gate,
+                              int gate_from, hipStream_t st)
+{
+    if (p.cfg < 0 || !in->dense) return hipErrorInvalidValue;
+    SpArgs a = {};
+    a.gate = gate; a.gate_from = gate_from; a.x = in->dense;
+    a.w = static_cast<const char *>(packed); a.bias = bias; a.y = y;
+    a.N = in->N; a.C = in->C; a.H = in->H; a.W = in->W; a.K = K; a.nslice = (in->C + 15) / 16; a.nkb = (K + 31) / 32; a.Ho = Ho; a.Wo = Wo;
+    a.sh = a.sw = 1; a.ph = ph; a.pw = pw; a.act = relu;
+    a.slow.cptr = in->cptr; a.slow.cidx = in->cidx; a.slow.xval = in->xval; a.slow.NCP = in->NCH;
+    a.slow.w = w; a.slow.wk = wk; a.slow.wc = wc; a.slow.wt = wt;
+    return launch_any<3>(a, p, st);
 }
 
 }  // namespace fscnn

@@ -18,6 +18,8 @@
 // 16-byte LDS read feeds KQ accumulators, and the list bounds and (channel, value) pairs of the
 // patch's 36 input pixels are fetched ahead with vector loads (one lane per pixel) and handed
 // out with readlane, so that the walk over the pixels waits for no memory but LDS.
+#include <algorithm>
+
 #include "internal.h"
 #include "lds_dma.h"
 
@@ -444,7 +446,13 @@ conv_si_direct_kernel(const int *__restrict__ cptr, int NCP, const uint32_t *__r
 // and the stored pairs (fitted to 240 launches of configuration 1 and 110 of configuration 4 over random sizes,
 // standard deviation 11 and 14 %; 512 -> 512 at 28x28, N = 8: 265 us contracted, 157 / 263 / 490 gathered at 3 / 10 / 25 %
 // stored; N = 32: 1090, and 257 / 482 / 920).
-SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepared)
+// The contraction in parts reads the dense form that the handle keeps (the lists themselves, put together while they are
+// staged: 148 us instead of 132, a load instruction touches 64 lines) and goes before the one in fp32 where it is
+// estimated a tenth faster: 512 -> 512 at 28x28, N = 8, 31 % stored: 265 us in fp32, 132 in parts; 256 -> 256: 68 and 43, and 5 for
+// a bank as the caller holds it, which is taken apart first.  Not below a quarter of a value stored per pixel (two or three
+// products per output): there the rounding of the single products shows.  Error against 64 bits over 160 random layers of 2 to
+// 200 products: 0.3 to 1.0 times that of the contraction in fp32, 0.3 to 0.9 times the gather's.
+SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, int pw, bool prepared)
 {
     SiChoice r;
     const int Kpad = (K + 255) / 256 * 256;
@@ -453,6 +461,7 @@ SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepa
     const bool wide = (long long)N * ((Ho + 3) / 4) * ((Wo + 3) / 4) * (Kpad / 256) >= 2048;
     r.variant = wide ? 4 : 1;
     r.pick = contract_pick(prepared ? kContractLists : kContractListsRows, N, C, K, H, W, 3, 3, Ho, Wo, 1, 1);
+    r.spick = split_pick(N, C, K, H, W, 3, 3, Ho, Wo, 1, 1, pw);
     const double all = (double)N * C * H * W, steps = (C + 7) / 8;
     if (r.pick.cfg < 0) {
         r.from = (long long)all + 1;
@@ -469,9 +478,17 @@ SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepa
             rounds = 1.5 * full + (rest > 256 ? 1.5 : rest > 0 ? 1.0 : 0.0);
             stores = 4.46, weights = 1.553, pairs = 22.57;
         }
-        const double share = (((1e6 * r.pick.seconds - 2) / rounds - stores) / steps - weights) / pairs;
-        r.from = share <= 0 ? 0 : share >= 1 ? (long long)all + 1 : (long long)(share * all);
+        auto crossing = [&](double us) {
+            const double share = (((us - 2) / rounds - stores) / steps - weights) / pairs;
+            return share <= 0 ? 0 : share >= 1 ? (long long)all + 1 : (long long)(share * all);
+        };
+        r.from = crossing(1e6 * r.pick.seconds);
+        r.split_from = crossing(1.1e6 * r.spick.seconds);
     }
+    const long long npix = (long long)N * H * W;
+    const double pack = prepared ? 0 : 3e-6 + 90.0 * K * C / 3.6e12;        // (512 -> 512: 9 us)
+    if (r.spick.cfg < 0 || (r.pick.cfg >= 0 && r.spick.seconds + pack > 0.9 * r.pick.seconds)) r.split_from = (long long)all + 1;
+    else r.split_from = std::max({r.split_from, (npix + 3) / 4, input_dense_from(npix, C)});
     return r;
 }
 
@@ -483,12 +500,21 @@ bool si_tiled_supported(int K, int C, int R, int S, int sh, int sw)
 
 hipError_t launch_conv_si(const fscnn_input *in, const float *w, int K, int R, int S, int Ho, int Wo,
                           int sh, int sw, int ph, int pw, const float *bias, int relu, float *y,
-                          hipStream_t st)
+                          const SiChoice *c, void *bank, hipStream_t st)
 {
     const int NKT = (K + 63) / 64;
-    if (si_tiled_supported(K, in->C, R, S, sh, sw)) {
-        const SiChoice c = si_choose(in->N, in->C, in->H, in->W, K, Ho, Wo, false);
-        if (c.from == 0) return launch_contract_lists(in, w, nullptr, K, Ho, Wo, ph, pw, bias, relu, y, c.pick, nullptr, 0, st);
+    if (c) {
+        // (an emitted activation's count may be on the device only: as in launch_conv_si_prepared)
+        const long long npix = (long long)in->N * in->H * in->W, all = npix * in->C;
+        const int *count = in->nnz < 0 ? in->cptr + npix * in->NCH : nullptr;
+        const long long hi = bank && in->dense && (!count || c->from == 0) ? c->split_from : all + 1;
+        if (hi <= all && (count || in->nnz >= hi)) {
+            hipError_t e = launch_split_bank(w, K, in->C, bank, st);
+            if (e == hipSuccess) e = launch_split_input(in, bank, w, in->C * 9, 9, 1, K, Ho, Wo, ph, pw, bias, relu, y, c->spick, count, (int)hi, st);
+            if (!count || e != hipSuccess) return e;
+        }
+        if (c->from == 0)
+            return launch_contract_lists(in, w, nullptr, K, Ho, Wo, ph, pw, bias, relu, y, c->pick, hi <= all ? count : nullptr, 0, (int)hi, st);
     }
     if (si_tiled_supported(K, in->C, R, S, sh, sw) && in->CC == kSiCC) {
         using G = SiCfg<4, 4, 4>;
@@ -549,18 +575,29 @@ hipError_t launch_conv_si_prepared(const fscnn_input *in, const fscnn_dense *d, 
     const int *gate = nullptr;
     int gate_from = 0;
     if (variant == 0) {
-        const SiChoice c = si_choose(in->N, in->C, in->H, in->W, d->K, Ho, Wo, true);
+        const SiChoice c = si_choose(in->N, in->C, in->H, in->W, d->K, Ho, Wo, pw, true);
         const long long all = (long long)in->N * in->C * in->H * in->W;
-        // A handle that a convolution emitted may not have told the host its number of stored values: then both
-        // kernels are launched and the one that does not serve it ends at once (2 us), so that a call's kernel, and
-        // with it the order of its sums, goes by the activation alone.
-        if (d->packed && in->nnz < 0 && c.from > 0 && c.from <= all) {
-            gate = in->cptr + (long long)in->N * in->H * in->W * in->NCH;
-            gate_from = (int)c.from;
+        // A handle that a convolution emitted may not have told the host its number of stored values: then all kernels
+        // that may serve it are launched and those that do not end at once (2 us), so that a call's kernel, and
+        // with it the order of its sums, goes by the activation alone.  The gather serves counts below `lo`, the contraction in
+        // fp32 those from `lo` on and below `hi`, the one in parts the others.
+        const long long hi = d->parts && in->dense ? c.split_from : all + 1;
+        const long long lo = !d->packed || c.from > hi ? hi : c.from;
+        const int *count = in->nnz < 0 ? in->cptr + (long long)in->N * in->H * in->W * in->NCH : nullptr;
+        if (hi <= all && (count || in->nnz >= hi)) {
+            const hipError_t e = launch_split_input(in, d->parts, d->wT, 1, d->Kpad * 9, d->Kpad, d->K, Ho, Wo, ph, pw, bias, relu, y,
+                                                    c.spick, hi > 0 ? count : nullptr, (int)hi, st);
+            if (!count || hi == 0 || e != hipSuccess) return e;
         }
-        if (gate || (d->packed && (in->nnz >= 0 ? in->nnz >= c.from : c.from == 0))) {
-            const hipError_t e = launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, c.pick, gate, gate_from, st);
-            if (!gate || e != hipSuccess) return e;
+        if (lo < hi && (count || in->nnz >= lo)) {
+            const int *gated = lo > 0 || hi <= all ? count : nullptr;
+            const hipError_t e = launch_contract_lists(in, d->packed, d->flag, d->K, Ho, Wo, ph, pw, bias, relu, y, c.pick, gated, (int)lo,
+                                                       hi <= all ? (int)hi : 0x7fffffff, st);
+            if (!count || lo == 0 || e != hipSuccess) return e;
+        }
+        if (count && lo <= all) {
+            gate = count;
+            gate_from = (int)lo;
         }
         variant = c.variant;
     }

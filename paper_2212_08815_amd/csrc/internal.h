@@ -143,6 +143,7 @@ struct fscnn_input {
     float *xval;     // device [nnz]
     int *cptr;       // device [N*H*W*NCH + 1]: cptr[p*NCH + j] = first entry of pixel p with
                      // c >= j*CC; pixel p's row is [cptr[p*NCH], cptr[(p+1)*NCH])
+    const float *dense = nullptr;   // device N x C x H x W: the activation as it was, where the handle keeps it (below)
     // the device allocations behind the arrays: pointers (and the scratch they are made from), then
     // indices and values (null where they are part of the first: small or emitted activations)
     void *ptr_block, *node_block;
@@ -151,6 +152,14 @@ struct fscnn_input {
     // for the worst case, with room for the dense result iff emit_has_y; 0 for other handles
     size_t emit_bytes = 0;
     bool emit_has_y = false;
+    // room for the caller's bank in bfloat16 parts, one buffer per stream that has needed it (bank_scratch in api.hip)
+    struct Bank {
+        hipStream_t stream;
+        void *buf;
+        size_t bytes;
+    };
+    mutable std::mutex mu;
+    mutable std::vector<Bank> banks;
     // the pass that fills the handle runs on `made_on` and may still be in flight when the
     // handle is returned; `filled` is recorded behind it, for users on other streams
     hipStream_t made_on;
@@ -165,6 +174,7 @@ struct fscnn_dense {
     int K, C, R, S, Kpad;
     float *wT;       // device [C*R*S*Kpad]; the arrays below follow it in the same allocation
     float *packed;   // 3x3: the bank in the order of the contraction's A operands; else, or where there was no room for it, NULL
+    void *parts;     // likewise, in bfloat16 parts (split_packed_index)
     int *flag;       // 3x3: non-zero if the bank holds an Inf or NaN
 };
 
@@ -194,8 +204,12 @@ long long input_groups(long long npix, int NCH);
 long long input_scratch_elems(long long npix, int NCH);   // ints
 hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
                              hipStream_t st);
+// dense, if not NULL: receives x as well where input_dense_from() values and more are stored
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, hipStream_t st);
+                             uint32_t *cidx, float *xval, int spare, float *dense, hipStream_t st);
+// An activation that stores a thirty-second of its values is kept dense as well: from there on a contraction may serve it
+// (512 -> 512 at 28x28, N = 8: 132 us contracted, 157 gathered at 3 % stored)
+inline long long input_dense_from(long long npix, int C) { return (npix * C + 31) / 32; }
 hipError_t launch_maxpool2x2(const float *x, int N, int C, int H, int W, float *y, int n4,
                              hipStream_t st);
 hipError_t launch_layout_convert(const float *src, int N, int C, int H, int W, int src_n4, float *dst,
@@ -270,18 +284,25 @@ hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float
 hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
                               int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
                               float *y, const ContractPick &p, hipStream_t st);
+// the same parts of a dense K x C x 3 x 3 bank, and the convolution of a compressed activation with them; w[k*wk + c*wc + tap*wt]: the bank
+// itself.  gate (device) with fewer than gate_from: the launch does nothing; NULL: it runs
+hipError_t launch_split_bank(const float *w, int K, int C, void *packed, hipStream_t st);
+hipError_t launch_split_input(const fscnn_input *in, const void *packed, const float *w, int wk, int wc, int wt, int K, int Ho, int Wo,
+                              int ph, int pw, const float *bias, int relu, float *y, const ContractPick &p, const int *gate,
+                              int gate_from, hipStream_t st);
 // compressed activation, 3x3 at stride 1; with wflag: w is packed and wflag its non-finite flag,
-// without: w is K x C x 3 x 3.  gate (device, packed banks only) with fewer than gate_from: the launch does nothing; NULL: it runs
+// without: w is K x C x 3 x 3.  gate (device) with fewer than gate_from, or gate_to and more: the launch does nothing; NULL: it runs
 hipError_t launch_contract_lists(const fscnn_input *in, const float *w, const int *wflag, int K, int Ho,
                                  int Wo, int ph, int pw, const float *bias, int relu, float *y,
-                                 const ContractPick &p, const int *gate, int gate_from, hipStream_t st);
-// How a sparse-input call (3x3, stride 1) is served: by the contraction from `from` stored values on
+                                 const ContractPick &p, const int *gate, int gate_from, int gate_to, hipStream_t st);
+// How a sparse-input call (3x3, stride 1) is served: by the contraction in bfloat16 parts from split_from stored values
+// on, else by the one in fp32 from `from` on
 struct SiChoice {
-    ContractPick pick;
-    long long from = 0;
+    ContractPick pick, spick;
+    long long from = 0, split_from = 0;
     int variant = 1;   // prepared banks: the gather configuration below
 };
-SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, bool prepared);
+SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, int pw, bool prepared);
 
 // ---- transpose.hip
 long long reorder_workspace_bytes(long long n_buckets, long long nnz);  // -1: too large
@@ -297,8 +318,10 @@ hipError_t launch_reorder(bool tensor, const int *rowptr, const uint32_t *idx, c
 constexpr int kSiCC = 8;   // channels per step of the compressed activation's chunk pointers
 constexpr int kSiSpare = 8;  // entries allocated past the last (channel, value) pair (reader prefetch)
 bool si_tiled_supported(int K, int C, int R, int S, int sh, int sw);
+// c: how the contractions may serve the call (si_choose; NULL: they do not); bank: room for the bank in bfloat16 parts
+// (split_packed_bytes), or NULL
 hipError_t launch_conv_si(const fscnn_input *in, const float *w, int K, int R, int S, int Ho, int Wo,
                           int sh, int sw, int ph, int pw, const float *bias, int relu, float *y,
-                          hipStream_t st);
+                          const SiChoice *c, void *bank, hipStream_t st);
 
 }  // namespace fscnn

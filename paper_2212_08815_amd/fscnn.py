@@ -35,7 +35,7 @@ EXPORTS = [
     "fscnn_sparse_transpose", "fscnn_sparse_tensor_transpose", "fscnn_sparse_transpose_workspace",
     "fscnn_dense_filter_prepare", "fscnn_dense_filter_destroy", "fscnn_conv2d_sparse_input_prepared",
     "fscnn_si_variant_count", "fscnn_conv2d_sparse_filter_leaky", "fscnn_sparse_transpose_noalloc",
-    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_sf_split_choice", "fscnn_si_contract_choice", "fscnn_pool_trim",
+    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_sf_split_choice", "fscnn_si_contract_choice", "fscnn_si_split_choice", "fscnn_pool_trim",
 ]
 
 NCHW, N4 = 0, 1      # fscnn_layout_t
@@ -174,6 +174,14 @@ def si_contract_choice(N, C, H, W, K, pad=(0, 0), prepared=False):
     n, t, p = ctypes.c_longlong(0), ctypes.c_int(0), ctypes.c_int(0)
     _check(lib().fscnn_si_contract_choice(_i(N), _i(C), _i(H), _i(W), _i(K), _i(pad[0]), _i(pad[1]), _i(1 if prepared else 0),
                                           ctypes.byref(n), ctypes.byref(t), ctypes.byref(p)), "fscnn_si_contract_choice")
+    return n.value, t.value, p.value
+
+
+def si_split_choice(N, C, H, W, K, pad=(0, 0), prepared=False):
+    """fscnn_si_split_choice -> (stored values from which the contraction in bfloat16 parts serves the call, its tile, panels)."""
+    n, t, p = ctypes.c_longlong(0), ctypes.c_int(0), ctypes.c_int(0)
+    _check(lib().fscnn_si_split_choice(_i(N), _i(C), _i(H), _i(W), _i(K), _i(pad[0]), _i(pad[1]), _i(1 if prepared else 0),
+                                       ctypes.byref(n), ctypes.byref(t), ctypes.byref(p)), "fscnn_si_split_choice")
     return n.value, t.value, p.value
 
 
