@@ -142,8 +142,8 @@ fscnn_status_t fscnn_filter_plan_export(fscnn_filter_t *f, int N, int H, int W, 
 
 fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f);
 
-/* Scratch of the channel-split mode that destroyed filter handles leave is kept for the next handles, up to
- * 64 MB in all.  This call releases it, for other allocators to use. */
+/* Device memory that destroyed handles leave (allocations of 2 MB and more) is kept for the next handles, up to
+ * 128 MB of filter handles' and up to 512 MB of compressed activations'.  This call releases it, for other allocators to use. */
 fscnn_status_t fscnn_pool_trim(void);
 
 /* Number of selectable kernel configurations of the sparse-filter convolution and a short

@@ -4,6 +4,7 @@
 #include <limits.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <new>
 
@@ -59,45 +60,62 @@ bool live(const fscnn_dense_t *d) { return d && d->magic == kDenseMagic; }
 // Share of a bank's entries that are stored (1 exactly for a bank without zeros).
 double density(const fscnn_filter_t *f) { return (double)f->nnz / ((double)f->K * f->C * f->R * f->S); }
 
-// Buffers of the channel-split mode that destroyed handles leave behind, for the next handles: releasing an
-// allocation of some MB takes the runtime up to 290 us (small ones: 2 us), and a program that compresses
-// its banks for one pass makes a dozen (13-layer stack, N = 1, a load and a pass: at 160x160 2.66 ms
-// with them released, 1.29 kept; at 224x224 2.99 and 1.43).  At most kPoolBytes and kPoolBuffers
-// are held; all of it is given back when an allocation of the library fails, and by fscnn_pool_trim.  A buffer enters after its handle's records
-// were released, which waits for the device, so no launch still uses it; it leaves for one (plan, stream).
-constexpr size_t kPoolBytes = 64u << 20, kPoolBuffers = 64;
-struct SplitPool {
+// Large device blocks that destroyed handles leave behind, for the next handles: releasing an allocation of some MB takes the
+// runtime 20 to 290 us (it waits for the device as well) and making one 10 to 40; smaller ones than kPoolLeast take 1 us and are not
+// kept.  A program that compresses its banks for one pass makes a dozen scratch buffers of the channel split (13-layer stack,
+// N = 1, a load and a pass: at 224x224 2.99 ms with all of them released, 1.42 with 64 MB kept, 1.25 now); one that compresses an
+// activation per pass makes one of 40 MB (512 channels at 28x28, N = 8, with the convolution: 235 us released, 186 kept).  What
+// is held is bounded per pool; a full pool drops what nobody took while kPoolAge blocks came in, or refuses; all of it is given
+// back when an allocation of the library fails, and by fscnn_pool_trim.
+//
+// Nobody waits for a block's last use: a handle whose calls all ran on the default stream gives its blocks back in that
+// stream's order, and only calls on the default stream of the same device take them (that stream lives as long as the
+// process and is never captured, so a later taker's work is behind the earlier one's).  A handle that any other
+// stream has used is released with hipFree; scratch that is given back behind such a wait is idle, and serves any stream.
+constexpr size_t kPoolLeast = 2u << 20, kPoolBuffers = 64, kPoolAge = 256;
+struct DevicePool {
     struct Entry {
         int device;
-        float *buf;
+        void *buf;
         size_t bytes;
+        bool idle;
+        size_t since;                    // `given` when it came
     };
+    const size_t max_bytes;
     std::mutex mu;
-    std::vector<Entry> free;
-    size_t held = 0;
+    std::vector<Entry> free;             // in the order they came
+    size_t held = 0, given = 0;
 
+    explicit DevicePool(size_t bytes) : max_bytes(bytes) {}
     // the smallest that is large enough, up to four times what is needed
-    bool take(int device, size_t bytes, float **buf, size_t *got)
+    bool take(int device, hipStream_t st, size_t bytes, void **buf, size_t *got)
     {
         std::lock_guard<std::mutex> lock(mu);
         size_t best = free.size();
         for (size_t i = 0; i < free.size(); ++i)
-            if (free[i].device == device && free[i].bytes >= bytes && free[i].bytes / 4 <= bytes &&
+            if (free[i].device == device && (free[i].idle || !st) && free[i].bytes >= bytes && free[i].bytes / 4 <= bytes &&
                 (best == free.size() || free[i].bytes < free[best].bytes))
                 best = i;
         if (best == free.size()) return false;
         *buf = free[best].buf;
         *got = free[best].bytes;
         held -= free[best].bytes;
-        free[best] = free.back();
-        free.pop_back();
+        free.erase(free.begin() + best);
         return true;
     }
-    bool give(int device, float *buf, size_t bytes)
+    bool give(int device, void *buf, size_t bytes, bool idle)
     {
+        if (bytes < kPoolLeast || bytes > max_bytes) return false;
         std::lock_guard<std::mutex> lock(mu);
-        if (held + bytes > kPoolBytes || free.size() >= kPoolBuffers) return false;
-        free.push_back({device, buf, bytes});
+        ++given;
+        auto full = [&] { return free.size() >= kPoolBuffers || held + bytes > max_bytes; };
+        while (full() && !free.empty() && given - free.front().since > kPoolAge) {
+            held -= free.front().bytes;
+            (void)hipFree(free.front().buf);
+            free.erase(free.begin());
+        }
+        if (full()) return false;
+        free.push_back({device, buf, bytes, idle, given});
         held += bytes;
         return true;
     }
@@ -109,21 +127,109 @@ struct SplitPool {
         held = 0;
     }
 };
-SplitPool &split_pool()
+// (never destroyed: handles may outlive static objects)
+// banks, plans, and scratch of the channel split; blocks of 8 MB and more have a pool of their own, so that a few of them do not
+// keep the many smaller ones out (the 13-layer stack at N = 1 leaves 50 MB of the former and 47 of the latter)
+DevicePool &filter_pool(size_t bytes)
 {
-    static SplitPool *pool = new SplitPool();   // (never destroyed: handles may outlive static objects)
+    static DevicePool *small = new DevicePool(64u << 20), *large = new DevicePool(64u << 20);
+    return bytes < (8u << 20) ? *small : *large;
+}
+DevicePool &input_pool()    // compressed activations
+{
+    static DevicePool *pool = new DevicePool(512u << 20);
     return *pool;
 }
 
-// hipMalloc that gives the pool back before it fails
+// hipMalloc that gives the pools back before it fails
 hipError_t device_alloc(void **p, size_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
     if (e != hipErrorOutOfMemory) return e;
     (void)hipGetLastError();
-    split_pool().trim();
+    filter_pool(0).trim();
+    filter_pool(~(size_t)0).trim();
+    input_pool().trim();
     return hipMalloc(p, bytes);
 }
+
+// a block for work on `st`; *got: its size
+hipError_t block_alloc(DevicePool &pool, int device, hipStream_t st, void **p, size_t bytes, size_t *got)
+{
+    if (pool.take(device, st, bytes, p, got)) return hipSuccess;
+    *got = bytes;
+    return device_alloc(p, bytes);
+}
+
+// in_order: all its uses are on the default stream.  True if it was released with a wait for the device
+bool block_free(DevicePool &pool, int device, void *p, size_t bytes, bool in_order)
+{
+    if (!p || (in_order && pool.give(device, p, bytes, false))) return false;
+    return hipFree(p) == hipSuccess;
+}
+
+// the same for filter handles
+hipError_t filter_alloc(int device, hipStream_t st, void **p, size_t bytes, size_t *got)
+{
+    return block_alloc(filter_pool(bytes), device, st, p, bytes, got);
+}
+
+bool filter_free(int device, void *p, size_t bytes, bool in_order) { return block_free(filter_pool(bytes), device, p, bytes, in_order); }
+
+// Where a kernel leaves a number for the host: a word of pinned memory (copied from the device to pageable memory the
+// same number takes a launch and 20 us of the host's time more).  NULL where there is none: then it is copied.
+struct HostWord {
+    int *word = nullptr;
+    HostWord()
+    {
+        Words &w = words();
+        std::lock_guard<std::mutex> lock(w.mu);
+        if (!w.made) {
+            w.made = true;
+            int *p = nullptr;
+            if (hipHostMalloc(reinterpret_cast<void **>(&p), kWords * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+                for (int i = 0; i < kWords; ++i) w.free.push_back(p + i * 16);
+            else
+                (void)hipGetLastError();
+        }
+        if (!w.free.empty()) {
+            word = w.free.back();
+            w.free.pop_back();
+        }
+    }
+    ~HostWord()
+    {
+        if (!word) return;
+        Words &w = words();
+        std::lock_guard<std::mutex> lock(w.mu);
+        w.free.push_back(word);
+    }
+    HostWord(const HostWord &) = delete;
+    HostWord &operator=(const HostWord &) = delete;
+    // the number, once the work on `st` is done; from: where the device has it as well.  (After an error the word is not used again: the
+    // kernel may still write it.)
+    hipError_t wait(const int *from, hipStream_t st, int *out)
+    {
+        hipError_t e = word ? hipSuccess : hipMemcpyAsync(out, from, sizeof(int), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) word = nullptr;
+        else if (word) *out = *const_cast<volatile int *>(word);
+        return e;
+    }
+
+private:
+    static constexpr int kWords = 64;    // calls at one time that find a word
+    struct Words {
+        std::mutex mu;
+        bool made = false;
+        std::vector<int *> free;
+    };
+    static Words &words()
+    {
+        static Words *w = new Words();
+        return *w;
+    }
+};
 
 bool capturing(hipStream_t st)
 {
@@ -135,18 +241,20 @@ bool capturing(hipStream_t st)
     return c != hipStreamCaptureStatusNone;
 }
 
-// device: where the plan's buffers live
-void free_plan(SfPlan *p, int device)
+// device: where the plan's buffers live; in_order: all its uses are on the default stream
+void free_plan(SfPlan *p, int device, bool in_order)
 {
     if (!p) return;
-    const bool idle = p->recs && hipFree(p->recs) == hipSuccess;   // with the pointers behind the records; waits for the device
-    if (p->packed) (void)hipFree(p->packed);
-    if (p->parts) (void)hipFree(p->parts);
+    // (the records with the pointers behind them; hipFree waits for the current device)
+    const bool waited = filter_free(device, p->recs, p->recs_bytes, in_order);
+    filter_free(device, p->packed, p->packed_bytes, in_order);
+    filter_free(device, p->parts, p->parts_bytes, in_order);
     int dev = -1;
-    const bool keep = idle && hipGetDevice(&dev) == hipSuccess && dev == device;
+    const bool idle = !in_order && waited && hipGetDevice(&dev) == hipSuccess && dev == device;
     for (auto *list : {&p->split, &p->outgrown})
         for (auto &sc : *list)
-            if (sc.buf && !(keep && split_pool().give(device, sc.buf, sc.bytes))) (void)hipFree(sc.buf);
+            if (!(idle && filter_pool(sc.bytes).give(device, sc.buf, sc.bytes, true)))
+                filter_free(device, sc.buf, sc.bytes, in_order);
     delete p;
 }
 
@@ -175,7 +283,7 @@ fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_
         if (e == hipSuccess) e = hipStreamSynchronize(own);
         if (own) (void)hipStreamDestroy(own);
     } else {
-        if (!split_pool().take(f->device, bytes, &nb, &bytes)) e = device_alloc(reinterpret_cast<void **>(&nb), bytes);
+        e = filter_alloc(f->device, st, reinterpret_cast<void **>(&nb), bytes, &bytes);
         if (e == hipSuccess) e = launch_split_clear(nb, st);
     }
     if (e != hipSuccess) {
@@ -225,16 +333,17 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
         }
         hipError_t e;
         if (variant == kSplitPlan) {
-            e = device_alloc(&p->parts, (size_t)split_packed_bytes(f->K, f->C, f->R * f->S));
+            e = filter_alloc(dev, st, &p->parts, (size_t)split_packed_bytes(f->K, f->C, f->R * f->S), &p->parts_bytes);
             if (e == hipSuccess) e = launch_split_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->parts, st);
         } else {
-            e = device_alloc(reinterpret_cast<void **>(&p->packed), sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4));
+            e = filter_alloc(dev, st, reinterpret_cast<void **>(&p->packed),
+                            sizeof(float) * (size_t)(contract_packed_elems(f->K, f->C, f->R * f->S) + 4), &p->packed_bytes);
             if (e == hipSuccess) e = launch_pack_rows(f->rowptr, f->idx, f->val, f->K, f->C, f->R * f->S, p->packed, st);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(st);   // the plan may be used from other streams
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            free_plan(p, f->device);
+            free_plan(p, f->device, false);
             return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
         }
         f->plans.push_back(p);
@@ -266,14 +375,15 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
     }
     // one allocation: the records, the pointers, and the counts the pointers are scanned from
     const size_t nrecs = (size_t)(cap + kPlanSpare);
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&p->recs), sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)));
+    hipError_t e = filter_alloc(dev, st, reinterpret_cast<void **>(&p->recs),
+                               sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)), &p->recs_bytes);
     int *cnt = nullptr;
     if (e == hipSuccess) {
         p->segptr = reinterpret_cast<int *>(p->recs + nrecs);
         cnt = p->segptr + (nb + 1);
         e = launch_plan_count(f->rowptr, f->idx, f->K, f->R * f->S, g, p->NCH, p->NG, cnt, st);
     }
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, p->segptr, nb, cnt + nb, st);
+    if (e == hipSuccess) e = launch_exclusive_scan(cnt, p->segptr, nb, cnt + nb, nullptr, st);
     if (e == hipSuccess)
         e = g.DENSE ? launch_plan_fill_dense(f->rowptr, f->idx, f->val, f->K, f->C, f->R, f->S, g, p->NCH,
                                              p->NG, cap, p->recs, st)
@@ -283,7 +393,7 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_plan(p, f->device);
+        free_plan(p, f->device, false);
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
     }
     p->nrec = cap;
@@ -435,11 +545,11 @@ void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
     for (auto &b : in->banks)
         if (b.stream == st && b.bytes >= bytes) return b.buf;
     void *p = nullptr;
+    if (st) in->in_order = false;
     if (capturing(st)) return nullptr;
     size_t room = 1 << 20;                            // (powers of two: what outgrown buffers hold is bounded by the largest)
     while (room < bytes) room *= 2;
-    bytes = room;
-    if (device_alloc(&p, bytes) != hipSuccess) {
+    if (block_alloc(input_pool(), in->device, st, &p, room, &bytes) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
@@ -452,6 +562,7 @@ void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
 // stream the handle was made on and may still be in flight).
 hipError_t after_fill(const fscnn_input_t *in, hipStream_t st)
 {
+    if (st) in->in_order = false;
     return st == in->made_on ? hipSuccess : hipStreamWaitEvent(st, in->filled, 0);
 }
 
@@ -516,20 +627,21 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     f->K = K; f->C = C; f->R = R; f->S = S;
     f->nnz = 0;
     f->rowptr = nullptr; f->idx = nullptr; f->val = nullptr;
+    f->in_order = !st;
     int *cnt = nullptr;
     int total = 0;
+    HostWord word;
     // two allocations: the pointers with the counts they are scanned from, and the nodes
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&f->rowptr), sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)));
+    hipError_t e = filter_alloc(dev, st, reinterpret_cast<void **>(&f->rowptr),
+                               sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)), &f->rowptr_bytes);
     if (e == hipSuccess) cnt = f->rowptr + (K + 1);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, st);
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&total, f->rowptr + K, sizeof(int), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, word.word, st);
+    if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total);
     if (e == hipSuccess) {
         f->nnz = total;
         const size_t n = total > 0 ? (size_t)total : 1;
-        e = device_alloc(reinterpret_cast<void **>(&f->idx), (sizeof(uint32_t) + sizeof(float)) * n);
+        e = filter_alloc(dev, st, reinterpret_cast<void **>(&f->idx), (sizeof(uint32_t) + sizeof(float)) * n, &f->idx_bytes);
         if (e == hipSuccess) f->val = reinterpret_cast<float *>(f->idx + n);
     }
     if (e == hipSuccess) e = launch_filter_pack(w_dev, K, row, f->rowptr, f->idx, f->val, st);
@@ -592,6 +704,7 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (s != FSCNN_OK) return s;
     if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
     if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
+    if (stream) f->in_order = false;
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p) return s;
@@ -669,17 +782,20 @@ fscnn_status_t fscnn_filter_destroy(fscnn_filter_t *f)
     if (!f) return FSCNN_ERR_NULL;
     if (!live(f)) return FSCNN_ERR_HANDLE;
     f->magic = 0;
-    for (SfPlan *p : f->plans) free_plan(p, f->device);
+    const bool in_order = f->in_order;
+    for (SfPlan *p : f->plans) free_plan(p, f->device, in_order);
     f->plans.clear();
-    if (f->rowptr) (void)hipFree(f->rowptr);
-    if (f->idx) (void)hipFree(f->idx);
+    filter_free(f->device, f->rowptr, f->rowptr_bytes, in_order);
+    filter_free(f->device, f->idx, f->idx_bytes, in_order);
     delete f;
     return FSCNN_OK;
 }
 
 fscnn_status_t fscnn_pool_trim(void)
 {
-    split_pool().trim();
+    filter_pool(0).trim();
+    filter_pool(~(size_t)0).trim();
+    input_pool().trim();
     return FSCNN_OK;
 }
 
@@ -807,6 +923,7 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (s != FSCNN_OK) return s;
     if (dev != f->device) return FSCNN_ERR_MISMATCH;   // the handle's buffers live on another GPU
     hipStream_t st = (hipStream_t)stream;
+    if (st) f->in_order = false;
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, st, &p);
     if (s != FSCNN_OK) return s;
@@ -942,7 +1059,9 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     in->cidx = nullptr; in->xval = nullptr; in->cptr = nullptr;
     in->ptr_block = nullptr; in->node_block = nullptr;
     in->made_on = st; in->filled = nullptr;
+    in->in_order = !st;
     int total = 0;
+    HostWord word;
     const long long nstep = npix * NCH;   // (pixel, channel step) pairs
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     // first allocation: the pointer array, the scratch of the passes (it stays with the handle, so nothing
@@ -957,13 +1076,13 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
     bool whole = npix * C * 8 <= kWholeBytes && unused_bytes.load() + npix * C * 12 <= kUnusedBytes;
     hipError_t e = hipErrorOutOfMemory;
     if (whole) {
-        e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), dense_at + sizeof(float) * (size_t)(npix * C));
+        e = block_alloc(input_pool(), dev, st, &in->ptr_block, dense_at + sizeof(float) * (size_t)(npix * C), &in->ptr_bytes);
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             whole = false;
         }
     }
-    if (!whole) e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), nodes_at);
+    if (!whole) e = block_alloc(input_pool(), dev, st, &in->ptr_block, nodes_at, &in->ptr_bytes);
     int *scratch = nullptr;
     auto fill = [&](void *nodes, size_t n) {
         in->cidx = static_cast<uint32_t *>(nodes);
@@ -975,12 +1094,10 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         char *base = static_cast<char *>(in->ptr_block);
         in->cptr = reinterpret_cast<int *>(base);
         scratch = reinterpret_cast<int *>(base + scratch_at);
-        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, st);
+        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, word.word, st);
         if (e == hipSuccess && whole) e = fill(base + nodes_at, most);
     }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&total, scratch + input_groups(npix, NCH), sizeof(int), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = word.wait(scratch + input_groups(npix, NCH), st, &total);
     if (e == hipSuccess) {
         in->nnz = total;
         if (whole) {
@@ -990,7 +1107,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
             unused_bytes += in->unused;
         } else {
             const size_t n = (size_t)total + kSiSpare;
-            e = device_alloc(reinterpret_cast<void **>(&in->node_block), val_at(n) + n * sizeof(float));
+            e = block_alloc(input_pool(), dev, st, &in->node_block, val_at(n) + n * sizeof(float), &in->node_bytes);
             if (e == hipSuccess) e = fill(in->node_block, n);
         }
     }
@@ -1065,6 +1182,7 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
                         void *stream, fscnn_input_t *in)
 {
     hipStream_t st = (hipStream_t)stream;
+    if (st) in->in_order = false;
     const int K = f->K, Ho = in->H, Wo = in->W;
     const EmitLayout L = emit_layout((long long)N * Ho * Wo, K, in->NCH);
     char *base = static_cast<char *>(in->ptr_block);
@@ -1076,7 +1194,7 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
     if (s != FSCNN_OK) return s;
     hipError_t e = hipSuccess;
     int *scratch = reinterpret_cast<int *>(base + L.sum_at);
-    e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, st);
+    e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, nullptr, st);
     if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, nullptr, st);
     if (e == hipSuccess) e = hipEventRecord(in->filled, st);
     if (e != hipSuccess) {
@@ -1116,7 +1234,7 @@ fscnn_status_t fscnn_conv2d_sparse_filter_emit(fscnn_filter_t *f, const float *x
     const EmitLayout L = emit_layout((long long)N * Ho * Wo, f->K, NCH);
     in->emit_bytes = L.bytes(y_dev == nullptr);
     in->emit_has_y = y_dev == nullptr;
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&in->ptr_block), in->emit_bytes);
+    hipError_t e = block_alloc(input_pool(), dev, (hipStream_t)stream, &in->ptr_block, in->emit_bytes, &in->ptr_bytes);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&in->filled, hipEventDisableTiming);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -1204,11 +1322,12 @@ fscnn_status_t fscnn_input_destroy(fscnn_input_t *in)
     if (!in) return FSCNN_ERR_NULL;
     if (!live(in)) return FSCNN_ERR_HANDLE;
     in->magic = 0;
-    (void)hipEventSynchronize(in->filled);
+    const bool in_order = in->in_order;
+    if (!in_order) (void)hipEventSynchronize(in->filled);
     (void)hipEventDestroy(in->filled);
-    if (in->ptr_block) (void)hipFree(in->ptr_block);
-    if (in->node_block) (void)hipFree(in->node_block);
-    for (auto &b : in->banks) (void)hipFree(b.buf);
+    block_free(input_pool(), in->device, in->ptr_block, in->ptr_bytes, in_order);
+    block_free(input_pool(), in->device, in->node_block, in->node_bytes, in_order);
+    for (auto &b : in->banks) block_free(input_pool(), in->device, b.buf, b.bytes, in_order);
     unused_bytes -= in->unused;
     delete in;
     return FSCNN_OK;

@@ -53,7 +53,7 @@ __device__ inline int wave_inclusive(int v)
 }
 __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int *__restrict__ in,
                                                                       int *__restrict__ out,
-                                                                      long long n)
+                                                                      long long n, int *__restrict__ host)
 {
     __shared__ int rows[kScanRows + 1];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -95,7 +95,10 @@ __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int 
         carry += rows[kScanRows];
         __syncthreads();   // the next round writes `rows`
     }
-    if (threadIdx.x == 0) out[n] = carry;
+    if (threadIdx.x == 0) {
+        out[n] = carry;
+        if (host) *host = carry;
+    }
 }
 
 // ---- the same for large n, three passes over tiles of kTile elements -------------------
@@ -573,16 +576,16 @@ long long scan_tmp_elems(long long n)
     return n <= 4 * kTile ? 0 : 2 * ((n + kTile - 1) / kTile) + 2;
 }
 
-hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, hipStream_t st)
+hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, hipStream_t st)
 {
     if (n <= 4 * kTile) {
-        hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, in, out, n);
+        hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, in, out, n, host);
         return hipGetLastError();
     }
     const long long nt = (n + kTile - 1) / kTile;
     int *tsum = tmp, *toff = tmp + nt;   // toff has nt + 1 entries
     hipLaunchKernelGGL(scan_tile_sum_kernel, dim3((unsigned)nt), dim3(kTileThreads), 0, st, in, n, tsum);
-    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, tsum, toff, nt);
+    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, tsum, toff, nt, host);
     hipLaunchKernelGGL(scan_tile_kernel, dim3((unsigned)nt), dim3(kTileThreads), 0, st, in, n, toff, out);
     return hipGetLastError();
 }
@@ -650,14 +653,14 @@ long long input_scratch_elems(long long npix, int NCH)
 }
 
 hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
-                             hipStream_t st)
+                             int *host, hipStream_t st)
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(input_sum_kernel, dim3((unsigned)g), dim3(kBlock), 0, st, x, cnt, C, HW, npix, NCH,
                        input_pixels(NCH), scratch + g + 1);
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, st);
+    return e != hipSuccess ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, st);
 }
 
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -77,6 +78,7 @@ struct SfPlan {
         size_t bytes;
     };
     std::vector<SplitScratch> split, outgrown;
+    size_t recs_bytes = 0, packed_bytes = 0, parts_bytes = 0;   // of the allocations
     // The plan of the contraction on the matrix cores (variant kContractPlan): the bank as a dense
     // packed array (contract_packed_index), zeros where nothing is stored; behind it an int that is
     // non-zero if a stored value is Inf or NaN (16 bytes).
@@ -125,6 +127,8 @@ struct fscnn_filter {
     int *rowptr;    // device [K+1]; owns an allocation
     uint32_t *idx;  // device [nnz]; owns an allocation
     float *val;     // device [nnz], behind the indices
+    size_t rowptr_bytes = 0, idx_bytes = 0;   // of the allocations
+    std::atomic<bool> in_order{true};         // no call has used the handle on another stream than the default one
     std::mutex mu;
     std::vector<fscnn::SfPlan *> plans;
     // how automatic calls of a geometry are served (route_call in api.hip): the last few geometries asked for
@@ -147,6 +151,8 @@ struct fscnn_input {
     // the device allocations behind the arrays: pointers (and the scratch they are made from), then
     // indices and values (null where they are part of the first: small or emitted activations)
     void *ptr_block, *node_block;
+    size_t ptr_bytes = 0, node_bytes = 0;
+    mutable std::atomic<bool> in_order{true};   // no call has used the handle on another stream than the default one
     long long unused = 0;   // bytes of indices and values allocated ahead and not stored
     // a handle made by an emitting convolution has ONE allocation (ptr_block) of emit_bytes, sized
     // for the worst case, with room for the dense result iff emit_has_y; 0 for other handles
@@ -182,9 +188,10 @@ namespace fscnn {
 
 // ---- compress.hip
 hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, hipStream_t st);
-// out[0..n] = exclusive scan of in[0..n-1] (out[n] = total); tmp: scan_tmp_elems(n) ints of scratch
+// out[0..n] = exclusive scan of in[0..n-1] (out[n] = total); tmp: scan_tmp_elems(n) ints of scratch; host: receives the total as
+// well (pinned memory), or NULL
 long long scan_tmp_elems(long long n);
-hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, hipStream_t st);
+hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, hipStream_t st);
 hipError_t launch_filter_pack(const float *w, int K, long long row, const int *rowptr,
                               uint32_t *idx, float *val, hipStream_t st);
 hipError_t launch_plan_count(const int *rowptr, const uint32_t *idx, int K, int RS, const SfGeom &g,
@@ -202,8 +209,9 @@ hipError_t launch_plan_fill_dense(const int *rowptr, const uint32_t *idx, const 
 // zeroes the `spare` entries that follow the last stored one.
 long long input_groups(long long npix, int NCH);
 long long input_scratch_elems(long long npix, int NCH);   // ints
+// (host: as above)
 hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
-                             hipStream_t st);
+                             int *host, hipStream_t st);
 // dense, if not NULL: receives x as well where input_dense_from() values and more are stored
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
                              uint32_t *cidx, float *xval, int spare, float *dense, hipStream_t st);

@@ -141,7 +141,7 @@ def conv2d_out_shape(H, W, R, S, stride=(1, 1), pad=(0, 0)):
 
 
 def pool_trim():
-    """fscnn_pool_trim: release the scratch that destroyed filter handles left for the next ones."""
+    """fscnn_pool_trim: release the device memory that destroyed handles left for the next ones."""
     _check(lib().fscnn_pool_trim(), "fscnn_pool_trim")
 
 
