@@ -17,13 +17,20 @@ constexpr int kBlock = 256;
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
 // ---- A1: per output channel, the number of entries with w != 0 ------------------------
+constexpr int kCountPer = 9;   // (13 banks of the stack: 5.4 us each with the compiler's four, 4.8)
 __global__ void __launch_bounds__(kBlock) filter_count_kernel(const float *__restrict__ w,
                                                               long long row, int *__restrict__ cnt)
 {
     __shared__ int part[kBlock / 64];
     const float *wk = w + (long long)blockIdx.x * row;
     int c = 0;
-    for (long long f = threadIdx.x; f < row; f += kBlock) c += (wk[f] != 0.0f) ? 1 : 0;
+    for (long long f = threadIdx.x; f < row; f += kBlock * kCountPer) {   // all loads of a round in flight together
+        float v[kCountPer];
+#pragma unroll
+        for (int u = 0; u < kCountPer; ++u) v[u] = f + u * kBlock < row ? wk[f + u * kBlock] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kCountPer; ++u) c += (v[u] != 0.0f) ? 1 : 0;
+    }
     for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
     if (lane_id() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -353,19 +360,20 @@ __global__ void plan_fill_dense_kernel(const int *__restrict__ rowptr, const uin
 // 8 x 512 x 28 x 28, were four launches and 29 us in front of step 3.)
 
 // with cnt: the counts per (pixel, step) are at hand (sparse output emission) and are only added up
-__global__ void __launch_bounds__(kBlock) input_sum_kernel(const float *__restrict__ x, const int *__restrict__ cnt,
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) input_sum_kernel(const float *__restrict__ x, const int *__restrict__ cnt,
                                                            int C, long long HW, long long npix, int NCH, int PX,
                                                            int *__restrict__ sums)
 {
-    __shared__ int part[kBlock / 64];
+    __shared__ int part[BLOCK / 64];
     const long long p0 = (long long)blockIdx.x * PX, p1 = p0 + PX < npix ? p0 + PX : npix;
     int c = 0;
     if (cnt) {
         const int m = (int)(p1 - p0) * NCH;
-        for (int i = threadIdx.x; i < m; i += kBlock) c += cnt[p0 * NCH + i];
+        for (int i = threadIdx.x; i < m; i += BLOCK) c += cnt[p0 * NCH + i];
     } else {
         const long long p = p0 + threadIdx.x % PX;
-        const int step = kBlock / PX;
+        const int step = BLOCK / PX;
         if (p < npix) {
             const float *xp = x + p / HW * C * HW + p % HW;
             for (int ch = threadIdx.x / PX; ch < C; ch += 16 * step) {   // sixteen loads in flight
@@ -382,17 +390,17 @@ __global__ void __launch_bounds__(kBlock) input_sum_kernel(const float *__restri
     __syncthreads();
     if (threadIdx.x == 0) {
         int t = 0;
-        for (int i = 0; i < kBlock / 64; ++i) t += part[i];
+        for (int i = 0; i < BLOCK / 64; ++i) t += part[i];
         sums[blockIdx.x] = t;
     }
 }
 
 // Thread (pixel px, step lane sj) walks the steps sj, sj + 256/PX, ... of its pixel, so the reads of a
-// channel plane cover PX adjacent floats; the values of its first kKept steps stay in registers between
-// counting and placing.  The (channel, value) pairs meet in an LDS image of the group's output range,
+// channel plane cover PX adjacent floats; the values of its kKept steps stay in registers between
+// counting and placing (PX * NCH <= BLOCK * kKept).  The (channel, value) pairs meet in an LDS image of the group's output range,
 // copied out with fully coalesced stores.
-constexpr int kKept = 4;
-__global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restrict__ x, int C, long long HW,
+template <int BLOCK, int kKept>
+__global__ void __launch_bounds__(BLOCK) input_fill_kernel(const float *__restrict__ x, int C, long long HW,
                                                             long long npix, int NCH, int PX,
                                                             const int *__restrict__ start, int *__restrict__ cptr,
                                                             uint32_t *__restrict__ cidx, float *__restrict__ xval,
@@ -400,7 +408,7 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
 {
     constexpr int CC = kSiCC;
     extern __shared__ uint32_t stage[];   // [cap] value bit patterns, then in 16 bits [cap] channels, [PX * NCH] positions
-    __shared__ int wave_sum[kBlock / 64];
+    __shared__ int wave_sum[BLOCK / 64];
     const int cap = PX * NCH * CC, M = PX * NCH;
     unsigned short *chan = reinterpret_cast<unsigned short *>(stage + cap), *pos = chan + cap;   // (cap is below 10500)
     const int base = start[blockIdx.x];
@@ -415,7 +423,7 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
         }
     }
     const long long p0 = (long long)blockIdx.x * PX;
-    const int px = threadIdx.x % PX, sj = threadIdx.x / PX, SJ = kBlock / PX;
+    const int px = threadIdx.x % PX, sj = threadIdx.x / PX, SJ = BLOCK / PX;
     const long long p = p0 + px;
     const bool live = p < npix;
     const long long first = live ? p / HW * C * HW + p % HW : 0;
@@ -456,14 +464,9 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
     for (int r = 0; r < kKept; ++r) load(sj + r * SJ, kept[r]);
 #pragma unroll
     for (int r = 0; r < kKept; ++r) count(sj + r * SJ, kept[r]);
-    for (int j = sj + kKept * SJ; j < NCH; j += SJ) {
-        float v[CC];
-        load(j, v);
-        count(j, v);
-    }
     __syncthreads();
     // counts -> positions in the group's range: a run of them per thread
-    const int per = (M + kBlock - 1) / kBlock, a = (int)threadIdx.x * per, b = a + per < M ? a + per : M;
+    const int per = (M + BLOCK - 1) / BLOCK, a = (int)threadIdx.x * per, b = a + per < M ? a + per : M;
     int s = 0;
     for (int i = a; i < b; ++i) s += pos[i];
     const int incl = wave_inclusive(s);
@@ -471,7 +474,7 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
     __syncthreads();
     int run = incl - s, total = 0;
 #pragma unroll
-    for (int i = 0; i < kBlock / 64; ++i) {
+    for (int i = 0; i < BLOCK / 64; ++i) {
         if (i < (int)(threadIdx.x >> 6)) run += wave_sum[i];
         total += wave_sum[i];
     }
@@ -482,16 +485,11 @@ __global__ void __launch_bounds__(kBlock) input_fill_kernel(const float *__restr
     }
     __syncthreads();
     const int m = (int)((p0 + PX < npix ? p0 + PX : npix) - p0) * NCH;
-    for (int i = threadIdx.x; i < m; i += kBlock) cptr[p0 * NCH + i] = base + pos[i];
+    for (int i = threadIdx.x; i < m; i += BLOCK) cptr[p0 * NCH + i] = base + pos[i];
 #pragma unroll
     for (int r = 0; r < kKept; ++r) place(sj + r * SJ, kept[r]);
-    for (int j = sj + kKept * SJ; j < NCH; j += SJ) {
-        float v[CC];
-        load(j, v);
-        place(j, v);
-    }
     __syncthreads();
-    for (int t = threadIdx.x; t < total; t += kBlock) {
+    for (int t = threadIdx.x; t < total; t += BLOCK) {
         cidx[base + t] = chan[t];
         xval[base + t] = __uint_as_float(stage[t]);
     }
@@ -657,8 +655,13 @@ hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(input_sum_kernel, dim3((unsigned)g), dim3(kBlock), 0, st, x, cnt, C, HW, npix, NCH,
-                       input_pixels(NCH), scratch + g + 1);
+    const int PX = input_pixels(NCH);
+    // a pass over x is latency and loads in flight: 16 waves per group from four values per thread on (8 x 512 x 28 x 28: 13.5 us with
+    // four waves, 6.5); counts at hand are few
+    if (!cnt && C * PX >= 4096)
+        hipLaunchKernelGGL(input_sum_kernel<1024>, dim3((unsigned)g), dim3(1024), 0, st, x, cnt, C, HW, npix, NCH, PX, scratch + g + 1);
+    else
+        hipLaunchKernelGGL(input_sum_kernel<256>, dim3((unsigned)g), dim3(256), 0, st, x, cnt, C, HW, npix, NCH, PX, scratch + g + 1);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, st);
 }
@@ -669,8 +672,15 @@ hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0 || spare >= kBlock) return hipErrorInvalidValue;
     const int PX = input_pixels(NCH);
-    hipLaunchKernelGGL(input_fill_kernel, dim3((unsigned)g), dim3(kBlock), (size_t)PX * NCH * kFillBytes, st, x, C,
-                       HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, dense ? (int)input_dense_from(npix, C) : 0);
+    const int from = dense ? (int)input_dense_from(npix, C) : 0;
+    const size_t lds = (size_t)PX * NCH * kFillBytes;
+    auto launch = [&](auto kernel, int block) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(block), lds, st, x, C, HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, from);
+    };
+    // Two to three steps per thread, all kept: 512 threads where there are steps for more than 256 (8 x 512 x 28 x 28, dense form
+    // included: 16.0 us with 256 threads that keep four steps and load the others again, 9.6; with 1024: 11)
+    if (PX * NCH > 256) launch(input_fill_kernel<512, 3>, 512);
+    else launch(input_fill_kernel<256, 1>, 256);
     return hipGetLastError();
 }
 
