@@ -182,9 +182,10 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
 
 /* The same for the contraction with its operands taken apart into bfloat16 parts (3x3 and 5x5; products and sums
  * as precise as in fp32): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
- * does.  Host-only. */
+ * does.  *parts_out (may be NULL): the work-groups per tile that the input channels are divided over; more than one need scratch as
+ * the channel-split mode does (fscnn_filter_prepare_ex), and without it one serves the tile.  Host-only. */
 fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h, int stride_w,
-                                     int pad_h, int pad_w, int *tile_out, int *panels_out);
+                                     int pad_h, int pad_w, int *tile_out, int *panels_out, int *parts_out);
 
 /* The same as fscnn_sf_contract_choice for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
  * values on the contraction serves the call, where fscnn_si_split_choice below does not say otherwise (prepared: fscnn_conv2d_sparse_input_prepared, else

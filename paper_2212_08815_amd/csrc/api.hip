@@ -303,6 +303,20 @@ fscnn_status_t split_scratch(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_
     return FSCNN_OK;
 }
 
+// Room for the sums of a divided contraction's parts, behind the counters; NULL where there is none and none can be made now (no
+// room, or `st` is capturing): then one work-group per tile takes all channels.
+float *split_sums(fscnn_filter_t *f, SfPlan *p, hipStream_t st, size_t bytes)
+{
+    bool have = false;
+    if (capturing(st)) {
+        std::lock_guard<std::mutex> lock(f->mu);
+        for (auto &q : p->split) have |= q.stream == st && q.bytes >= bytes;
+        if (!have) return nullptr;
+    }
+    float *buf;
+    return split_scratch(f, p, st, bytes, &buf) == FSCNN_OK ? buf + 256 : nullptr;
+}
+
 // Returns the plan of `variant` (>= 1) for this handle, building it on `st` when absent.
 // kDirectPlan stands for the direct kernel (no device data besides the canonical CSR), kContractPlan
 // for the contraction on the matrix cores (the bank as a dense array).
@@ -459,7 +473,7 @@ bool splits(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho
 {
     const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
     if (f->nnz < 16LL * f->K || 2 * dense / 350e12 + 3e-6 > other) return false;
-    *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw);
+    *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw, true);
     return pick->cfg >= 0 && pick->seconds + (emit ? 4e-6 : 0) < 0.9 * other;
 }
 
@@ -707,6 +721,7 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (stream) f->in_order = false;
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, (hipStream_t)stream, &p);
+    if (p && r.spick.parts > 1) (void)split_sums(f, p, (hipStream_t)stream, split_sums_bytes(r.spick, N, f->K, Ho, Wo));
     if (s != FSCNN_OK || p) return s;
     if (r.contract) s = contract_plan(f, kContractPlan, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p) return s;
@@ -841,7 +856,7 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
 }
 
 fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int ph, int pw,
-                                     int *tile_out, int *panels_out)
+                                     int *tile_out, int *panels_out, int *parts_out)
 {
     if (!f || !tile_out || !panels_out) return FSCNN_ERR_NULL;
     if (!live(f)) return FSCNN_ERR_HANDLE;
@@ -852,6 +867,7 @@ fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int
     SfRoute r;
     s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, 0, 0, 0, 0, false, &r);
     if (s != FSCNN_OK) return s;
+    if (parts_out) *parts_out = r.split ? r.spick.parts : 0;
     *tile_out = r.split ? r.spick.cfg : -1;
     *panels_out = r.split ? r.spick.npan : 0;
     return FSCNN_OK;
@@ -928,8 +944,9 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     if (r.split) s = contract_plan(f, kSplitPlan, st, &p);
     if (s != FSCNN_OK) return s;
     if (p) {
+        float *sums = r.spick.parts > 1 ? split_sums(f, p, st, split_sums_bytes(r.spick, N, f->K, Ho, Wo)) : nullptr;
         FSCNN_HIP(launch_split_dense(x_dev, p->parts, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, Ho, Wo, sh, sw, ph, pw,
-                                     bias_dev, relu, y_dev, r.spick, st));
+                                     bias_dev, relu, y_dev, r.spick, sums, st));
         return FSCNN_OK;
     }
     if (r.contract) s = contract_plan(f, kContractPlan, st, &p);

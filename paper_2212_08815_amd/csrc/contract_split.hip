@@ -18,6 +18,7 @@
 //     Two buffers, one barrier per chunk: a chunk's stores are spread over the steps of the chunk before, four
 //     pixels of one octet by lane, whose 16-byte loads were issued a chunk earlier.  Pixels outside the image are
 //     cleared once.
+//   * where a launch leaves CUs idle the chunks are divided over several work-groups per tile, and a second launch adds up.
 //   * the A operands go from global memory to registers a few taps ahead, packed as the lanes want them:
 //     [32 rows][16 channels][tap][part][lane][8].
 // What bounds it: see the figures at kCost below.
@@ -68,6 +69,8 @@ struct SpArgs {
     int gate_from;
     int N, C, H, W, K, nslice, nkb, Ho, Wo, sh, sw, ph, pw, act;
     int SW, tpp, pitch, PL, VR, NKT, QPR, buf_bytes;
+    int parts, cpp, nblk;                // the chunks are divided over `parts` work-groups per tile, cpp each; tiles
+    float *sums;                         // parts > 1: where they leave their sums, each part in the order of y
     uint32_t m_qpr, m_vr, m_sw, m_ho;    // reciprocals for div_by()
     SlowArgs slow;
 };
@@ -138,7 +141,8 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
 {
     const int mw = wave % G::MW, ks = wave / G::MW % G::KS, nw = wave / (G::MW * G::KS);
     const int j = lane & 31, q = lane >> 5;
-    const int kt = blockIdx.x % a.NKT, tile = blockIdx.x / a.NKT;
+    const int part = a.parts > 1 ? blockIdx.x / a.nblk : 0, blk = blockIdx.x - part * a.nblk;
+    const int kt = blk % a.NKT, tile = blk / a.NKT;
     const int pan = tile / a.tpp;
     const int p0 = (tile % a.tpp) * G::T;
     const int ptot = a.N * a.Ho * a.SW;               // pixels of a panel
@@ -148,7 +152,9 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     const int v0 = p0 / a.SW;
     const int u0 = virt(v0), nrow = virt(plast / a.SW) + G::R - u0;
     const int n0 = v0 / a.Ho;
-    const int NCH = (a.C + G::CC - 1) / G::CC;
+    // this part's chunks; channels from cend on read as zero
+    const int CI0 = part * a.cpp, NCH = (a.C + G::CC - 1) / G::CC < CI0 + a.cpp ? (a.C + G::CC - 1) / G::CC : CI0 + a.cpp;
+    const int cend = a.C < NCH * G::CC ? a.C : NCH * G::CC;
     if (a.gate && *a.gate < a.gate_from) return;
 
     // ---- staging: an item is four pixels of a stripe's row (the last ones of a row overlap the ones before), eight channels of each
@@ -170,11 +176,11 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     auto load_x = [&](int ci) {
         const int c0 = ci * G::CC + oct * 8;
         // from channel c0 of image n0 on; channels past the last one read as zero
-        const float *src = a.x + (c0 < a.C ? ((long long)n0 * a.C + c0) * HW : 0);
+        const float *src = a.x + (c0 < cend ? ((long long)n0 * a.C + c0) * HW : 0);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             // (the condition sits in the descriptor's size: in the offset it becomes a branch)
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src), 0, c0 + t < a.C ? kOut : 0, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src), 0, c0 + t < cend ? kOut : 0, 0x00020000);
             xr[t] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rs, goff, t * HW * 4, 0));
         }
     };
@@ -229,7 +235,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     // ---- A operands: this wave's 32 rows, its slice of chunk ci (rows and slices past the last read as zero)
     const int kb = kt * G::MW + mw;
     auto weights = [&](int ci) {
-        const bool ok = kb < a.nkb && ci * G::KS + ks < a.nslice;
+        const bool ok = kb < a.nkb && (ci * G::KS + ks) * 16 < cend;
         const long long at = ((long long)kb * a.nslice + ci * G::KS + ks) * (G::RS * 3072);
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(a.w) + (ok ? at : 0), 0, ok ? G::RS * 3072 : 0, 0x00020000);
     };
@@ -257,11 +263,11 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     {
-        const __amdgpu_buffer_rsrc_t w0 = weights(0);
+        const __amdgpu_buffer_rsrc_t w0 = weights(CI0);
 #pragma unroll
         for (int s = 0; s < G::SETS; ++s) load_a(w0, s, av[s]);
     }
-    load_x(0);
+    load_x(CI0);
     for (int e = wave * 64 + lane; e * 16 < 2 * a.buf_bytes; e += G::NTH) reinterpret_cast<u4v *>(ldsb)[e] = u4v{0, 0, 0, 0};
     lds_barrier();
     static_for<0, 4>([&](auto px) { store_x(0, px); });
@@ -271,7 +277,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     // comes the barrier, and then the first reads of the next chunk
     constexpr int LAST = NS - D, FIRST = LAST >= 3 ? LAST - 3 : 0, PER = (4 + LAST - FIRST) / (LAST + 1 - FIRST);
     int cur = 0;
-    for (int ci = 0; ci < NCH; ++ci) {
+    for (int ci = CI0; ci < NCH; ++ci) {
         const int nxt = a.buf_bytes - cur;
         // (past the last chunk all loads fall outside their descriptors and read zeros: no branches, behind which
         // the compiler could not count what is in flight)
@@ -343,6 +349,21 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
         const int r = ks * OWN + i;
         return kb * 32 + 8 * (r >> 2) + 4 * q + (r & 3);
     };
+    if (a.parts > 1) {                                // parts_finish_kernel does the rest
+        float *to = a.sums + part * (a.N * a.K * plane);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int dp = (nw * G::NT + t) * 32 + j;
+            const Pos r = pos_of(dp);
+            const int ox = pan * a.SW + r.ox;
+            if (p0 + dp > plast || ox >= a.Wo) continue;
+            float *y = to + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wo + ox;
+#pragma unroll
+            for (int i = 0; i < OWN; ++i)
+                if (row_of(i) < a.K) y[(long long)row_of(i) * plane] = own[t][i];
+        }
+        return;
+    }
     bool finite = true;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -382,6 +403,27 @@ template <class G> __global__ void __launch_bounds__(G::NTH, 2) split_kernel(con
     constexpr int LAST_NT = G::NB - (G::NW - 1) * G::NT;
     if (LAST_NT == G::NT || wave < G::MW * G::KS * (G::NW - 1)) split_body<G, G::NT>(a, ldsb, wave, lane);
     else split_body<G, LAST_NT>(a, ldsb, wave, lane);
+}
+
+// Sums of the parts, in their order.  Bound by the launch and by one round trip to the last-level cache (512 x 14 x 14 in 4 parts: 2 us).
+template <int R> __global__ void __launch_bounds__(256) parts_finish_kernel(const SpArgs a)
+{
+    const long long plane = (long long)a.Ho * a.Wo, total = a.N * a.K * plane, i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const float *s = a.sums + i;
+    float v = 0.0f;
+    for (int p0 = 0; p0 < a.parts; p0 += 8) {          // eight loads in flight
+        float u[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) u[p] = p0 + p < a.parts ? s[(p0 + p) * total] : 0.0f;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) v += u[p];
+    }
+    const long long nk = i / plane;
+    const int k = (int)(nk % a.K), o = (int)(i - nk * plane);
+    if (!(__builtin_fabsf(v) < __builtin_inff())) v = slow_output<R>(a, (int)(nk / a.K), k, o / a.Wo, o % a.Wo);
+    if (a.bias) v += a.bias[k];
+    a.y[i] = act_apply(v, a.act);
 }
 
 // ---------------------------------------------------------------- packed banks
@@ -447,8 +489,14 @@ template <class G> hipError_t launch_cfg(SpArgs a, const ContractPick &p, hipStr
     const long long P = (long long)a.N * a.Ho * a.SW;
     a.tpp = (int)((P + G::T - 1) / G::T);
     const long long nblk = (long long)a.tpp * p.npan * a.NKT;
-    if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * G::NTH > 0xffffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_kernel<G>, dim3((unsigned)nblk), dim3(G::NTH), p.lds, st, a);
+    const int nch = (a.C + G::CC - 1) / G::CC;
+    a.parts = a.sums ? p.parts : 1;
+    a.cpp = (nch + a.parts - 1) / a.parts;
+    if (nblk <= 0 || nblk * a.parts > 0x7fffffffLL || nblk * a.parts * G::NTH > 0xffffffffLL) return hipErrorInvalidValue;
+    a.nblk = (int)nblk;
+    hipLaunchKernelGGL(split_kernel<G>, dim3((unsigned)(nblk * a.parts)), dim3(G::NTH), p.lds, st, a);
+    if (a.parts > 1)
+        hipLaunchKernelGGL(parts_finish_kernel<G::R>, dim3((unsigned)(((long long)a.N * a.K * a.Ho * a.Wo + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -486,7 +534,13 @@ struct SplitCost {
 };
 constexpr SplitCost kSplitCost[] = {{0.916, 0.425, 53.1, 2077, 0.315, 7974, 1197, 2.28},    // 3x3
                                     {0.876, 0.325, 60.9, 3502, 0.805, 6873, 1215, 2.89}};   // 5x5
-ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw)
+// With `divide`, launches that leave CUs idle may divide the input channels over up to kPartsMost work-groups per tile, where all of
+// them still fit one round; the second launch, which adds up, costs 1.5 us and the sums' way (3 TB/s).  10 % stored, us gathered,
+// contracted whole and divided, the estimate of the last: 512 -> 512 at 14x14, N = 1: 19.0, 27.4, 14.4 (15.2); at 7x7: 17.2, 26.4,
+// 11.0 (11.2); 512 -> 128 at 20x20: 17.7, 26.6, 11.9 (11.9); 256 -> 256 at 28x28, where dividing gives little: 15.9, 16.2, 14.5.
+constexpr int kPartsMost = 16;
+constexpr long long kPartsBytes = 64LL << 20;
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide)
 {
     ContractPick best;
     // (rows are loaded four columns at a time)
@@ -531,14 +585,22 @@ ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho,
             if (lds > kLdsMax) continue;
             const long long nwg = (P + T - 1) / T * npan * ((K + 32 * q.MW - 1) / (32 * q.MW));
             const int nch = (C + 16 * q.KS - 1) / (16 * q.KS);
-            const double rounds = (double)((nwg + 255) / 256), fill = (double)nwg / (256 * rounds);
             const double mfma = 48.0 * q.MW * q.NB * q.KS * R * S;
-            const double chunk = m.mfma * (1 + m.mfma_fill * fill) * mfma + m.stage * q.KS / 32 * (double)npx + m.chunk * (1 + m.chunk_fill * fill);
-            const double seconds = rounds * (nch * chunk + m.round + m.store * q.MW * q.NB) / 2.4e9 + m.launch * 1e-6;
-            if (best.cfg < 0 || seconds < best.seconds) {
-                best.seconds = seconds;
-                best.cfg = g; best.npan = npan; best.lds = (int)lds; best.qpr = qpr;
-                best.SW = SW; best.pitch = pitch; best.PL = (int)npx; best.buf = (int)buf;
+            for (int parts = 1; parts <= nch; ++parts) {
+                const int cpp = (nch + parts - 1) / parts;
+                if ((parts - 1) * cpp >= nch) continue;         // (the last one would have none)
+                const double sums = 4.0 * parts * N * K * Ho * Wo;
+                if (parts > 1 && (!divide || parts > kPartsMost || nwg * parts > 256 || sums > kPartsBytes)) break;
+                const double groups = (double)nwg * parts, rounds = (double)((nwg * parts + 255) / 256), fill = groups / (256 * rounds);
+                const double chunk = m.mfma * (1 + m.mfma_fill * fill) * mfma + m.stage * q.KS / 32 * (double)npx + m.chunk * (1 + m.chunk_fill * fill);
+                double seconds = rounds * (cpp * chunk + m.round + m.store * q.MW * q.NB) / 2.4e9 + m.launch * 1e-6;
+                if (parts > 1) seconds += 1.5e-6 + sums / 3e12;
+                if (best.cfg < 0 || seconds < best.seconds) {
+                    best.seconds = seconds;
+                    best.cfg = g; best.npan = npan; best.lds = (int)lds; best.qpr = qpr;
+                    best.SW = SW; best.pitch = pitch; best.PL = (int)npx; best.buf = (int)buf;
+                    best.parts = parts;
+                }
             }
         }
     }
@@ -555,10 +617,11 @@ hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float
 
 hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
                               int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
-                              float *y, const ContractPick &p, hipStream_t st)
+                              float *y, const ContractPick &p, float *sums, hipStream_t st)
 {
     if (p.cfg < 0) return hipErrorInvalidValue;
     SpArgs a = {};
+    a.sums = sums;
     a.x = x; a.w = static_cast<const char *>(packed); a.bias = bias; a.y = y;
     a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.nslice = (C + 15) / 16; a.nkb = (K + 31) / 32; a.Ho = Ho; a.Wo = Wo;
     a.sh = sh; a.sw = sw; a.ph = ph; a.pw = pw; a.act = act;

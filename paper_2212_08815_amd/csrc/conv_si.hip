@@ -461,7 +461,7 @@ SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, int pw, bo
     const bool wide = (long long)N * ((Ho + 3) / 4) * ((Wo + 3) / 4) * (Kpad / 256) >= 2048;
     r.variant = wide ? 4 : 1;
     r.pick = contract_pick(prepared ? kContractLists : kContractListsRows, N, C, K, H, W, 3, 3, Ho, Wo, 1, 1);
-    r.spick = split_pick(N, C, K, H, W, 3, 3, Ho, Wo, 1, 1, pw);
+    r.spick = split_pick(N, C, K, H, W, 3, 3, Ho, Wo, 1, 1, pw, false);
     const double all = (double)N * C * H * W, steps = (C + 7) / 8;
     if (r.pick.cfg < 0) {
         r.from = (long long)all + 1;

@@ -92,6 +92,7 @@ constexpr int kDirectPlan = -1, kContractPlan = -2, kSplitPlan = -3;
 struct ContractPick {
     int cfg = -1, npan = 1, lds = 0, SW = 0, pitch = 0, PL = 0, buf = 0;
     int qpr = 0;                           // in bfloat16 parts: loads of four columns per row of a stripe
+    int parts = 1;                         // likewise: work-groups that the input channels of a tile are divided over
     double seconds = 0;
 };
 
@@ -280,7 +281,7 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st);
 // ---- contract_split.hip: the same contraction with the operands taken apart into three bfloat16 parts; 3x3 and 5x5
-ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw);
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide);
 // Packed banks: position of the first part of w[k][c][tap] in 16-bit words (the others 512 and 1024 behind it), and the
 // number of bytes
 __host__ __device__ inline long long split_packed_index(int k, int c, int rs, int RS, int nslice)
@@ -289,9 +290,11 @@ __host__ __device__ inline long long split_packed_index(int k, int c, int rs, in
 }
 inline long long split_packed_bytes(int K, int C, int RS) { return (long long)((K + 31) / 32) * ((C + 15) / 16) * RS * 3072; }
 hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS, void *packed, hipStream_t st);
+// sums: room for the sums of p.parts parts (split_sums_bytes); NULL: one work-group per tile takes all channels
+inline size_t split_sums_bytes(const ContractPick &p, int N, int K, int Ho, int Wo) { return 1024 + 4 * (size_t)p.parts * N * K * Ho * Wo; }
 hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
                               int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
-                              float *y, const ContractPick &p, hipStream_t st);
+                              float *y, const ContractPick &p, float *sums, hipStream_t st);
 // the same parts of a dense K x C x 3 x 3 bank, and the convolution of a compressed activation with them; w[k*wk + c*wc + tap*wt]: the bank
 // itself.  gate (device) with fewer than gate_from: the launch does nothing; NULL: it runs
 hipError_t launch_split_bank(const float *w, int K, int C, void *packed, hipStream_t st);

@@ -165,8 +165,16 @@ def sf_split_choice(f, N, H, W, stride=(1, 1), pad=(0, 0)):
     """fscnn_sf_split_choice -> (tile of the contraction in bfloat16 parts that serves an automatic NCHW call, panels); tile -1: it does not."""
     t, p = ctypes.c_int(), ctypes.c_int()
     _check(lib().fscnn_sf_split_choice(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
-                                       ctypes.byref(t), ctypes.byref(p)), "fscnn_sf_split_choice")
+                                       ctypes.byref(t), ctypes.byref(p), None), "fscnn_sf_split_choice")
     return t.value, p.value
+
+
+def sf_split_parts(f, N, H, W, stride=(1, 1), pad=(0, 0)):
+    """fscnn_sf_split_choice -> work-groups per tile that the input channels of such a call are divided over (0: not served so)."""
+    t, p, q = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(lib().fscnn_sf_split_choice(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
+                                       ctypes.byref(t), ctypes.byref(p), ctypes.byref(q)), "fscnn_sf_split_choice")
+    return q.value
 
 
 def si_contract_choice(N, C, H, W, K, pad=(0, 0), prepared=False):
