@@ -19,8 +19,9 @@
 // Those passes take up to 8 launches, binary searches over the row pointers per node, global atomics and
 // the rank's loop: at 28 x 28 x 512 with 31 % stored (124 000 nodes, 2.1 MB moved) 83 us, of them 27 + 29
 // in counting and dropping, 21 in ranking.  Where the scratch allows (use_tiles below) three launches over
-// tiles of the dense shape do it in 15, now launch latency mostly (112 x 112 x 512, 50 % stored: 693 -> 73;
-// a 1024 x 8192 matrix, 30 %: 324 -> 77, bound by its 4-byte stores; 64 x 64, 10 %: 26 -> 15):
+// tiles of the dense shape do it in 15, now the host call (112 x 112 x 512, 50 % stored: 693 -> 51, of 73 while a
+// lane's nodes were loaded after the row's ends, values after the indices, and again for the second walk;
+// a 1024 x 8192 matrix, 30 %: 324 -> 75, bound by its 4-byte stores; 64 x 64, 10 %: 26 -> 15):
 //   1. a work-group takes RG (up to 32) consecutive keys and a panel of up to kPanel buckets of one
 //      plane (a matrix is one plane, a tensor has one per h).  Its nodes set bit (key mod RG) of the
 //      bucket's word in LDS; the number of bits is the tile's count for the bucket;
@@ -28,7 +29,7 @@
 //      totals are scanned per block of 256 buckets;
 //   3. the tile's words are built again and every node lands at (start of the bucket) + (offset of
 //      its key group) + (number of set bits below its own).
-#include <type_traits>
+#include <mutex>
 
 #include "internal.h"
 
@@ -144,28 +145,60 @@ __global__ void __launch_bounds__(kBlock) reorder_place_kernel(const int *__rest
 constexpr int kPanel = 4096;        // buckets of a tile at most: 16 KB of words, 16 KB of starts
 constexpr int kMaxSums = 256;       // blocks of 256 buckets whose totals step 3 scans by itself
 
-// f(key mod RG, bucket of the plane relative to the panel, entry) for every node of the tile.  LPR lanes
-// share a row: about as many as an average row has nodes.
-template <class Fn>
-__device__ inline void for_tile_nodes(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx, int H, int C,
-                                      int h, int c0, int RG, int w0, int wn, int LPR, int nnz, Fn f)
+// Nodes of a row that a lane has in flight or in registers: four, LPR apart, from entry e on.  With `values` their values too
+// (where a tile sees the whole row: of several panels each would load them for a few nodes).
+struct Nodes {
+    int e, hi;                          // hi: end of the row
+    uint32_t w[4];
+    float v[4];
+};
+__device__ inline Nodes load_nodes(const uint32_t *__restrict__ idx, const float *__restrict__ val, bool values, int e, int hi, int LPR)
 {
-    for (int r = (int)threadIdx.x / LPR; r < RG && c0 + r < C; r += kBlock / LPR) {
-        const int row = (c0 + r) * H + h;
-        int lo = rowptr[row], hi = rowptr[row + 1];
-        lo = lo < 0 ? 0 : lo;
-        hi = hi > nnz ? nnz : hi;
-        for (int e0 = lo + (int)threadIdx.x % LPR; e0 < hi; e0 += 4 * LPR) {
-            uint32_t w[4];   // four loads in flight
+    Nodes n;
+    n.e = e;
+    n.hi = hi;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) w[u] = hi - e0 > u * LPR ? idx[e0 + u * LPR] : 0xffffffffu;
+    for (int u = 0; u < 4; ++u) n.w[u] = hi - e > u * LPR ? idx[e + u * LPR] : 0xffffffffu;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) n.v[u] = values && hi - e > u * LPR ? val[e + u * LPR] : 0.0f;
+    return n;
+}
+// Lane's first entry and the end of row `key` of plane h; nothing past the last key.
+__device__ inline int2 row_span(const int *__restrict__ rowptr, int H, int C, int h, int key, bool mine, int LPR, int nnz)
+{
+    if (!mine || key >= C) return make_int2(0, 0);
+    const int lo = rowptr[key * H + h], hi = rowptr[key * H + h + 1];
+    return make_int2((lo < 0 ? 0 : lo) + (int)threadIdx.x % LPR, hi > nnz ? nnz : hi);
+}
+__device__ inline Nodes first_nodes(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx, const float *__restrict__ val,
+                                    bool values, int H, int C, int h, int c0, int RG, int LPR, int nnz)
+{
+    const int r = (int)threadIdx.x / LPR;
+    const int2 s = row_span(rowptr, H, C, h, c0 + r, r < RG, LPR, nnz);
+    return load_nodes(idx, val, values, s.x, s.y, LPR);
+}
+
+// f(key mod RG, bucket of the plane relative to the panel, entry, its value if loaded) for every node of the tile.
+// LPR lanes share a row (use_tiles says how many).  `n`: the lane's first nodes, which a caller that walks
+// twice loads once; a row's ends are loaded while the row before is worked on.
+template <class Fn>
+__device__ inline void for_tile_nodes(Nodes n, const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
+                                      const float *__restrict__ val, bool values, int H, int C, int h, int c0, int RG, int w0, int wn,
+                                      int LPR, int nnz, Fn f)
+{
+    const int step = kBlock / LPR;
+    for (int r = (int)threadIdx.x / LPR; r < RG && c0 + r < C; r += step) {
+        const int2 next = row_span(rowptr, H, C, h, c0 + r + step, r + step < RG, LPR, nnz);
+        for (;;) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const uint32_t q = w[u] - (uint32_t)w0;   // (an index outside the panel, or corrupt, wraps past it)
-                if (hi - e0 > u * LPR && q < (uint32_t)wn) f(r, (int)q, e0 + u * LPR);
+                const uint32_t q = n.w[u] - (uint32_t)w0;   // (an index outside the panel, or corrupt, wraps past it)
+                if (n.hi - n.e > u * LPR && q < (uint32_t)wn) f(r, (int)q, n.e + u * LPR, n.v[u]);
             }
-            if (hi - e0 <= 4 * LPR) break;
+            if (n.hi - n.e <= 4 * LPR) break;
+            n = load_nodes(idx, val, values, n.e + 4 * LPR, n.hi, LPR);
         }
+        n = load_nodes(idx, val, values, next.x, next.y, LPR);
     }
 }
 
@@ -191,10 +224,11 @@ __global__ void __launch_bounds__(kBlock) tile_count_kernel(const int *__restric
 {
     extern __shared__ uint32_t word[];
     const Tile t = tile_of(n_cols, H, panels, pw);
+    const Nodes first = first_nodes(rowptr, idx, nullptr, false, H, C, t.h, t.g * RG, RG, LPR, nnz);
     for (int w = threadIdx.x; w < t.wn; w += kBlock) word[w] = 0u;
     __syncthreads();
-    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
-                   [&](int r, int w, int) { atomicOr(&word[w], 1u << r); });
+    for_tile_nodes(first, rowptr, idx, nullptr, false, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
+                   [&](int r, int w, int, float) { atomicOr(&word[w], 1u << r); });
     __syncthreads();
     for (int w = threadIdx.x; w < t.wn; w += kBlock)
         cnt[t.g * n_buckets + (long long)(t.w0 + w) * H + t.h] = (unsigned short)__popc(word[w]);
@@ -202,8 +236,8 @@ __global__ void __launch_bounds__(kBlock) tile_count_kernel(const int *__restric
 
 // cnt -> offsets of the groups inside their bucket (in place); first[b] = start of bucket b inside its
 // block of 256 buckets; sums[block] = nodes of the block.  kParts threads share a bucket, each a run of
-// its groups: it adds them up, then writes their offsets; 16 loads in flight (one thread per bucket took
-// longer than the rest of the transpose where keys are many and buckets few).
+// its groups: it adds them up, then writes their offsets; 16 loads in flight, read once where there are no
+// more (one thread per bucket took longer than the rest of the transpose where keys are many and buckets few).
 constexpr int kParts = 4;
 __global__ void __launch_bounds__(kBlock *kParts) tile_offsets_kernel(unsigned short *__restrict__ cnt, int n_buckets,
                                                                       int G, int *__restrict__ first,
@@ -215,20 +249,18 @@ __global__ void __launch_bounds__(kBlock *kParts) tile_offsets_kernel(unsigned s
     const int per = (G + kParts - 1) / kParts;
     const int ga = part * per, gb = b < n_buckets ? (ga + per < G ? ga + per : G) : 0;
     unsigned short *p = cnt + b;
-    auto walk = [&](int run, auto write) {
-        for (int g0 = ga; g0 < gb; g0 += 16) {
-            int v[16];
+    int v[16];                             // the last 16 that were read
+    auto read = [&](int g0) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = g0 + u < gb ? p[(long long)(g0 + u) * n_buckets] : 0;
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                if (decltype(write)::value && g0 + u < gb) p[(long long)(g0 + u) * n_buckets] = (unsigned short)run;
-                run += v[u];
-            }
-        }
-        return run;
+        for (int u = 0; u < 16; ++u) v[u] = g0 + u < gb ? p[(long long)(g0 + u) * n_buckets] : 0;
     };
-    part_sum[part][t] = walk(0, std::false_type{});
+    int sum = 0;
+    for (int g0 = ga; g0 < gb; g0 += 16) {
+        read(g0);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sum += v[u];
+    }
+    part_sum[part][t] = sum;
     __syncthreads();
     int base = 0, total = 0;
 #pragma unroll
@@ -236,7 +268,14 @@ __global__ void __launch_bounds__(kBlock *kParts) tile_offsets_kernel(unsigned s
         if (q < part) base += part_sum[q][t];
         total += part_sum[q][t];
     }
-    walk(base, std::true_type{});
+    for (int g0 = ga; g0 < gb; g0 += 16) {
+        if (per > 16) read(g0);            // (else they are there)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            if (g0 + u < gb) p[(long long)(g0 + u) * n_buckets] = (unsigned short)base;
+            base += v[u];
+        }
+    }
     int incl = total;
     for (int o = 1; o < 64; o <<= 1) {
         const int v = __shfl_up(incl, o, 64);
@@ -261,6 +300,8 @@ __global__ void __launch_bounds__(kBlock) tile_place_kernel(
     __shared__ int block_start[kMaxSums], wave_sum[kBlock / 64];
     const Tile t = tile_of(n_cols, H, panels, pw);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool values = panels == 1;
+    const Nodes nodes = first_nodes(rowptr, idx, val, values, H, C, t.h, t.g * RG, RG, LPR, nnz);
     for (int w = threadIdx.x; w < t.wn; w += kBlock) word[w] = 0u;
     // starts of the blocks of buckets (kMaxSums == kBlock: one each)
     const int mine = (int)threadIdx.x < nsums ? sums[threadIdx.x] : 0;
@@ -275,8 +316,8 @@ __global__ void __launch_bounds__(kBlock) tile_place_kernel(
     for (int i = 0; i < wave; ++i) before += wave_sum[i];
     block_start[threadIdx.x] = before + incl - mine;
     if (blockIdx.x == 0 && threadIdx.x == kBlock - 1) tptr[n_buckets] = before + incl;
-    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
-                   [&](int r, int w, int) { atomicOr(&word[w], 1u << r); });
+    for_tile_nodes(nodes, rowptr, idx, val, false, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz,
+                   [&](int r, int w, int, float) { atomicOr(&word[w], 1u << r); });
     __syncthreads();
     for (int w = threadIdx.x; w < t.wn; w += kBlock) {
         const int b = (t.w0 + w) * H + t.h;
@@ -285,11 +326,11 @@ __global__ void __launch_bounds__(kBlock) tile_place_kernel(
         start[w] = at + cnt[t.g * n_buckets + b];
     }
     __syncthreads();
-    for_tile_nodes(rowptr, idx, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz, [&](int r, int w, int e) {
+    for_tile_nodes(nodes, rowptr, idx, val, values, H, C, t.h, t.g * RG, RG, t.w0, t.wn, LPR, nnz, [&](int r, int w, int e, float v) {
         const int p = start[w] + __popc(word[w] & ((1u << r) - 1u));
         if (p < nnz) {   // (holds for every node of a valid pointer array)
             tidx[p] = (uint32_t)(t.g * RG + r);
-            tval[p] = val[e];
+            tval[p] = values ? v : val[e];
         }
     });
 }
@@ -342,9 +383,11 @@ TilePlan use_tiles(int n_cols, int H, int C, long long n_buckets, long long nnz)
         t.blocks = blocks;
         if (blocks >= 256 || nnz <= 512 * blocks) break;
     }
+    // Lanes per row: each has four nodes in flight, so a third of a row's average takes most rows in one go; more where a
+    // tile has fewer rows than that makes room for.
     const long long avg = nnz / ((long long)C * H);
     t.LPR = 4;
-    while (t.LPR < 64 && t.LPR < avg) t.LPR *= 2;
+    while (t.LPR < 64 && (3 * t.LPR < avg || t.LPR * t.RG < kBlock)) t.LPR *= 2;
     return t;
 }
 

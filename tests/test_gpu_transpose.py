@@ -157,3 +157,21 @@ def test_tensor_transpose_at_the_edges_of_its_tiles(F, W, H, C, keep):
     ptr, widx, val = csr_of(t.reshape(C * H, W))
     got = F.sparse_tensor_transpose(dev_i32(ptr), dev_i32(widx), torch.from_numpy(val).cuda(), W, H, C)
     same(got, oracle.sparse_tensor_transpose(ptr, widx, val, W, H, C))
+
+
+@pytest.mark.parametrize("rows,cols,avg,longest", [
+    (40, 4096, 1, 33),      # eight lanes a row: one node past the first load
+    (40, 4096, 1, 4096),    # a row that takes many loads beside nearly empty ones
+    (70, 3000, 190, 257),   # 64 lanes a row, 4 rows at a time; one node past the first load
+    (65 * 32, 64, 6, 64),   # 17 counts a thread in the second launch: read twice
+    (64 * 32, 64, 6, 64),   # 16: read once
+    (9, 5000, 100, 5000),   # two panels: values loaded as they are placed
+])
+def test_matrix_transpose_with_one_long_row(F, rows, cols, avg, longest):
+    rng = np.random.default_rng(rows + longest)
+    m = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < avg / cols)).astype(np.float32)
+    m[rows - 2] = 0.0
+    m[rows - 2, rng.permutation(cols)[:longest]] = 1.0 + np.arange(longest, dtype=np.float32)
+    ptr, idx, val = csr_of(m)
+    got = F.sparse_transpose(dev_i32(ptr), dev_i32(idx), torch.from_numpy(val).cuda(), rows, cols)
+    same(got, oracle.sparse_transpose(ptr, idx, val, rows, cols))
