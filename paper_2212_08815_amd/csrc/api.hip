@@ -552,10 +552,10 @@ long long input_nnz(const fscnn_input_t *in)
 
 // Room for a bank in bfloat16 parts on `st`: the buffer this stream used before on the handle if it is large enough, else a
 // new one; NULL where there is none and none can be made (no room, or `st` is capturing).  One per stream: calls that share a
-// handle on different streams never share it.
+// handle on different streams never share it.  Call with in->mu held, and hold it until the launches that write and read the room are
+// made: calls of two threads on one stream share it in stream order, launches of one must not come between the other's.
 void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
 {
-    std::lock_guard<std::mutex> lock(in->mu);
     for (auto &b : in->banks)
         if (b.stream == st && b.bytes >= bytes) return b.buf;
     void *p = nullptr;
@@ -943,7 +943,11 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, st, &p);
     if (s != FSCNN_OK) return s;
+    // from the choice of scratch to the last launch that uses it: threads that share a handle share a stream's scratch in
+    // stream order, and a launch of one must not come between the two of another
+    std::unique_lock<std::mutex> launching(f->launching, std::defer_lock);
     if (p) {
+        if (r.spick.parts > 1) launching.lock();
         float *sums = r.spick.parts > 1 ? split_sums(f, p, st, split_sums_bytes(r.spick, N, f->K, Ho, Wo)) : nullptr;
         FSCNN_HIP(launch_split_dense(x_dev, p->parts, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, Ho, Wo, sh, sw, ph, pw,
                                      bias_dev, relu, y_dev, r.spick, sums, st));
@@ -966,6 +970,7 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     } else {
         float *parts = nullptr;
         if (r.csplit > 1) {
+            launching.lock();
             s = split_scratch(f, p, st, sf_split_bytes(p->g, r.csplit, N << r.band_shift, f->K, r.band_h, Wo), &parts);
             if (s != FSCNN_OK) return s;
         }
@@ -1369,11 +1374,14 @@ fscnn_status_t fscnn_conv2d_sparse_input(const fscnn_input_t *in, const float *w
     hipStream_t st = (hipStream_t)stream;
     SiChoice c;
     void *bank = nullptr;
+    std::unique_lock<std::mutex> launching(in->mu, std::defer_lock);
     const bool chosen = si_tiled_supported(K, in->C, R, S, sh, sw);
     if (chosen) {
         c = si_choose(in->N, in->C, in->H, in->W, K, Ho, Wo, pw, false);
-        if (in->dense && (in->nnz < 0 ? c.split_from <= (long long)in->N * in->C * in->H * in->W : in->nnz >= c.split_from))
+        if (in->dense && (in->nnz < 0 ? c.split_from <= (long long)in->N * in->C * in->H * in->W : in->nnz >= c.split_from)) {
+            launching.lock();
             bank = bank_scratch(in, st, (size_t)split_packed_bytes(K, in->C, 9));
+        }
     }
     FSCNN_HIP(after_fill(in, st));
     FSCNN_HIP(launch_conv_si(in, w_dev, K, R, S, Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, chosen ? &c : nullptr, bank, st));

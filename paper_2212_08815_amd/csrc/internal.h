@@ -131,6 +131,7 @@ struct fscnn_filter {
     size_t rowptr_bytes = 0, idx_bytes = 0;   // of the allocations
     std::atomic<bool> in_order{true};         // no call has used the handle on another stream than the default one
     std::mutex mu;
+    std::mutex launching;                     // held over the launches of a call that share scratch (taken before mu)
     std::vector<fscnn::SfPlan *> plans;
     // how automatic calls of a geometry are served (route_call in api.hip): the last few geometries asked for
     std::vector<fscnn::SfRoute> routes;
@@ -165,7 +166,7 @@ struct fscnn_input {
         void *buf;
         size_t bytes;
     };
-    mutable std::mutex mu;
+    mutable std::mutex mu;   // held over the launches that write and read such room
     mutable std::vector<Bank> banks;
     // the pass that fills the handle runs on `made_on` and may still be in flight when the
     // handle is returned; `filled` is recorded behind it, for users on other streams
