@@ -1110,7 +1110,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         in->cidx = static_cast<uint32_t *>(nodes);
         in->xval = reinterpret_cast<float *>(static_cast<char *>(nodes) + val_at(n));
         float *dense = whole ? reinterpret_cast<float *>(static_cast<char *>(in->ptr_block) + dense_at) : nullptr;
-        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, dense, st);
+        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, dense, input_dense_from(npix, C), st);
     };
     if (e == hipSuccess) {
         char *base = static_cast<char *>(in->ptr_block);
@@ -1209,7 +1209,7 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
     const EmitLayout L = emit_layout((long long)N * Ho * Wo, K, in->NCH);
     char *base = static_cast<char *>(in->ptr_block);
     int *cnt = reinterpret_cast<int *>(base + L.cnt_at);
-    float *y = y_dev ? y_dev : reinterpret_cast<float *>(base + L.y_at);
+    float *own = in->emit_has_y ? reinterpret_cast<float *>(base + L.y_at) : nullptr, *y = y_dev ? y_dev : own;
     bool counted = false;
     fscnn_status_t s = conv_sf_common(f, x_dev, N, C, H, W, sh, sw, ph, pw, bias_dev, relu, y,
                                       FSCNN_LAYOUT_NCHW, FSCNN_LAYOUT_NCHW, 0, 0, stream, cnt, &counted);
@@ -1217,14 +1217,15 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
     hipError_t e = hipSuccess;
     int *scratch = reinterpret_cast<int *>(base + L.sum_at);
     e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, nullptr, st);
-    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, nullptr, st);
+    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare,
+                                               y_dev ? own : nullptr, 0, st);   // (the count may not be looked at: a replay brings another)
     if (e == hipSuccess) e = hipEventRecord(in->filled, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? FSCNN_ERR_ALLOC : FSCNN_ERR_DEVICE;
     }
     in->nnz = -1;
-    in->dense = y_dev ? nullptr : y;   // the handle's own result stays as it is until the next fill
+    in->dense = own;   // stays as it is until the next fill
     in->made_on = st;
     return FSCNN_OK;
 }

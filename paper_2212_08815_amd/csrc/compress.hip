@@ -667,15 +667,14 @@ hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H
 }
 
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, float *dense, hipStream_t st)
+                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, hipStream_t st)
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0 || spare >= kBlock) return hipErrorInvalidValue;
     const int PX = input_pixels(NCH);
-    const int from = dense ? (int)input_dense_from(npix, C) : 0;
     const size_t lds = (size_t)PX * NCH * kFillBytes;
     auto launch = [&](auto kernel, int block) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(block), lds, st, x, C, HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, from);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(block), lds, st, x, C, HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, (int)dense_from);
     };
     // Two to three steps per thread, all kept: 512 threads where there are steps for more than 256 (8 x 512 x 28 x 28, dense form
     // included: 16.0 us with 256 threads that keep four steps and load the others again, 9.6; with 1024: 11)

@@ -149,7 +149,9 @@ struct fscnn_input {
     float *xval;     // device [nnz]
     int *cptr;       // device [N*H*W*NCH + 1]: cptr[p*NCH + j] = first entry of pixel p with
                      // c >= j*CC; pixel p's row is [cptr[p*NCH], cptr[(p+1)*NCH])
-    const float *dense = nullptr;   // device N x C x H x W: the activation as it was, where the handle keeps it (below)
+    // device N x C x H x W: the activation as it was, where the handle keeps it (below).  Every pass that writes the lists renews it as
+    // well, in device order: a captured pass or a captured reader may meet the handle after any other fill
+    const float *dense = nullptr;
     // the device allocations behind the arrays: pointers (and the scratch they are made from), then
     // indices and values (null where they are part of the first: small or emitted activations)
     void *ptr_block, *node_block;
@@ -214,9 +216,9 @@ long long input_scratch_elems(long long npix, int NCH);   // ints
 // (host: as above)
 hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
                              int *host, hipStream_t st);
-// dense, if not NULL: receives x as well where input_dense_from() values and more are stored
+// dense, if not NULL: receives x as well where dense_from values and more are stored
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, float *dense, hipStream_t st);
+                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, hipStream_t st);
 // An activation that stores a thirty-second of its values is kept dense as well: from there on a contraction may serve it
 // (512 -> 512 at 28x28, N = 8: 132 us contracted, 157 gathered at 3 % stored)
 inline long long input_dense_from(long long npix, int C) { return (npix * C + 31) / 32; }

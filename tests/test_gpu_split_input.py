@@ -96,7 +96,7 @@ def test_non_finite_values_meet_stored_values_only(F):
 
 
 def test_refilled_with_the_result_in_a_tensor_of_the_caller(F):
-    """The handle's own dense result is older than its lists then, and is not read."""
+    """The handle's own dense result is renewed then as well."""
     n, c, k, h, w = 8, 64, 256, 28, 28
     x, wt, _ = inputs.random_layer(5, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)
     eye = torch.zeros(c, c, 3, 3, device="cuda")
@@ -108,6 +108,48 @@ def test_refilled_with_the_result_in_a_tensor_of_the_caller(F):
     y.zero_()
     for got in calls(F, s, dev(wt), None, False):
         assert torch.equal(got.cpu(), want)
+
+
+
+@pytest.mark.parametrize("prepared", [True, False])
+def test_fills_and_uses_in_graphs_and_outside_of_them(F, prepared):
+    """A captured convolution reads what the handle holds when it is replayed, wherever the fill left the dense result; and a
+    replayed fill renews what an eager convolution reads."""
+    n, c, k, h, w = 8, 64, 256, 28, 28
+    a, wt, _ = inputs.random_layer(5, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)
+    b = inputs.random_layer(6, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)[0]
+    want = [torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), None, 1, 1) for x in (a, b)]
+    a, b, wd = dev(a), dev(b), dev(wt)
+    eye = torch.zeros(c, c, 3, 3, device="cuda")
+    eye[range(c), range(c), 1, 1] = 1.0
+    f, d, one = F.filter_compress(eye), F.dense_filter_prepare(wd), (1, 1)
+    x, elsewhere, y = a.clone(), torch.empty_like(a), torch.empty(n, k, h, w, device="cuda")
+    conv = lambda **kw: F.conv2d_sparse_input_prepared(s, d, one, one, **kw) if prepared else F.conv2d_sparse_input(s, wd, one, one, **kw)  # noqa: E731
+    s = F.conv2d_sparse_filter_emit(f, x, one, one)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        conv()
+        F.conv2d_sparse_filter_emit(f, x, one, one, dense_out=elsewhere, into=s)
+    torch.cuda.synchronize()
+    use, fill = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    F.conv2d_sparse_filter_emit(f, x, one, one, into=s)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(use, stream=side):
+        conv(out=y)
+    with torch.cuda.graph(fill, stream=side):
+        F.conv2d_sparse_filter_emit(f, x, one, one, dense_out=elsewhere, into=s)
+    for _ in range(3):
+        F.conv2d_sparse_filter_emit(f, b, one, one, dense_out=elsewhere, into=s)
+        use.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.cpu(), want[1])
+        F.conv2d_sparse_filter_emit(f, b, one, one, into=s)
+        fill.replay()
+        assert torch.equal(conv().cpu(), want[0])
+        use.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.cpu(), want[0])
 
 
 def test_captured_with_the_bank_as_the_caller_holds_it(F):
