@@ -1,6 +1,6 @@
 """Device memory that passes from a destroyed handle to the next one: results where the next handle is made, filled and used while
-the earlier one's work is still queued, other sizes on top of it, handles that a second stream has used (their memory does
-not pass), how much is held, and that it is given back."""
+the earlier one's work is still queued, other sizes on top of it, handles that other streams have used (their destruction
+waits), how much is held, and that it is given back."""
 import threading
 
 import numpy as np
@@ -73,6 +73,76 @@ def test_threads_on_the_default_stream(F):
     for t in range(4):
         for i, (*_, w) in enumerate(layers[t:] + layers[:t]):
             assert torch.equal(results[t][2 * i].cpu(), w) and torch.equal(results[t][2 * i + 1].cpu(), w)
+
+
+def kept(F):
+    """Bytes that destroyed handles have left."""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    F.pool_trim()
+    return torch.cuda.mem_get_info()[0] - before
+
+
+def test_handles_of_a_stream_of_the_callers(F):
+    """Their destruction waits for what is queued; the memory then serves any stream."""
+    layers = [layer(40 + i, *s) for i, s in enumerate(SHAPES)]
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    slow = torch.randn(4096, 4096, device="cuda")
+    kept(F)
+    got = []
+    for turn in range(4):
+        with torch.cuda.stream(sides[turn % 2]):
+            got += passes(F, layers)
+    got += passes(F, layers)
+    kept(F)
+    x, wt, b, want = layers[0]
+    with torch.cuda.stream(sides[0]):
+        s, f, done = F.input_compress(x), F.filter_compress(wt), torch.cuda.Event()
+        for _ in range(20):
+            slow @ slow
+        y = F.conv2d_sparse_input(s, wt, (1, 1), (1, 1), b, True)
+        done.record()
+    s.destroy()
+    assert done.query()
+    torch.cuda.synchronize()
+    for g, w in zip(got + [y], [w for *_, w in layers for _ in range(2)] * 5 + [want]):
+        assert torch.equal(g.cpu(), w)
+    f.destroy()
+    assert kept(F) >= 16 << 20                              # the activation
+
+
+def test_destroyed_inside_a_relaxed_capture(F):
+    x, wt, b, want = layer(70, *SHAPES[0])
+    side, y = torch.cuda.Stream(), torch.zeros(want.shape, device="cuda")
+    f = F.filter_compress(wt)
+    F.filter_prepare(f, 8, 36, 33, (1, 1), (1, 1))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        gone = [F.input_compress(x), F.filter_compress(wt)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        for h in gone:
+            h.destroy()
+        F.conv2d_sparse_filter(f, x, (1, 1), (1, 1), b, True, out=y)
+    for _ in range(2):
+        y.zero_()
+        graph.replay()
+        assert torch.equal(y.cpu(), want)
+
+
+def test_a_divided_banks_memory_on_a_stream_of_the_callers(F):
+    x, wt, _, _ = layer(60, 2, 512, 512, 14, 14, 1.0)
+    kept(F)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        f = F.filter_compress(wt)
+        parts = F.sf_split_parts(f, 2, 14, 14, (1, 1), (1, 1))
+        F.conv2d_sparse_filter(f, x, (1, 1), (1, 1))
+        stored = f.nnz
+        f.destroy()
+    sums = 4 * parts * 2 * 512 * 14 * 14
+    assert parts > 1 and sums >= 2 << 20                    # (smaller blocks are not kept)
+    assert kept(F) >= 512 * 512 * 9 * 6 + 8 * stored + sums
 
 
 def test_what_activations_leave_is_bounded_and_given_back(F):
