@@ -121,7 +121,7 @@ def test_destroyed_inside_a_relaxed_capture(F):
         gone = [F.input_compress(x), F.filter_compress(wt)]
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(), capture_error_mode="relaxed"):
         for h in gone:
             h.destroy()
         F.conv2d_sparse_filter(f, x, (1, 1), (1, 1), b, True, out=y)
