@@ -112,7 +112,9 @@ fscnn_status_t fscnn_filter_prepare(fscnn_filter_t *f, int N, int H, int W, int 
  * which the first such call or this one makes and the handle keeps.  Where there is no room for it, or
  * on a capturing stream before it is made, the call is served by the gather kernels as if there were
  * no contraction (with sums in another order).
- * Without this call the first split-mode call of a handle on a stream allocates its scratch. */
+ * Without this call the first split-mode call of a handle on a stream allocates its scratch.
+ * Graphs captured on a stream use the handle's scratch for that stream: replay them in the order of its other calls
+ * on that stream and of each other, not at the same time. */
 fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, int stride_h,
                                        int stride_w, int pad_h, int pad_w, fscnn_layout_t x_layout,
                                        fscnn_layout_t y_layout, int pool, int variant, void *stream);
@@ -337,7 +339,8 @@ fscnn_status_t fscnn_conv2d_sparse_filter_emit_into(fscnn_filter_t *f, const flo
  * atomics).  Asynchronous on `stream`.  Where the contraction in bfloat16 parts serves the call
  * (fscnn_si_split_choice) the first call of a handle on a stream, and the first with a larger bank, allocates room for
  * the bank's parts (6 bytes per entry, rounded up to a power of two), which the handle keeps; on a capturing stream
- * before that, or without that room, the contraction in fp32 serves it.  Allocates nothing otherwise. */
+ * before that, or without that room, the contraction in fp32 serves it.  A capture takes that room for its graph, which may then be
+ * replayed on any stream; the next call on this stream outside of it makes room again.  Allocates nothing otherwise. */
 fscnn_status_t fscnn_conv2d_sparse_input(const fscnn_input_t *in, const float *w_dev, int K,
                                          int R, int S, int stride_h, int stride_w, int pad_h,
                                          int pad_w, const float *bias_dev, int relu,

@@ -257,6 +257,17 @@ bool capturing(hipStream_t st)
     return c != hipStreamCaptureStatusNone;
 }
 
+// 0: st is not capturing; else the number of the capture, which no other has
+unsigned long long capture_id(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (!capturing(st)) return 0;
+    if (hipStreamGetCaptureInfo(st, &c, &id) == hipSuccess && id) return id;
+    (void)hipGetLastError();
+    return ~0ull;
+}
+
 // f(block, bytes) for every device block of a plan (the records' one holds the pointers as well)
 template <class F> void for_blocks(const SfPlan *p, F f)
 {
@@ -569,15 +580,28 @@ long long input_nnz(const fscnn_input_t *in)
 
 // Room for a bank in bfloat16 parts on `st`: the buffer this stream used before on the handle if it is large enough, else a
 // new one; NULL where there is none and none can be made (no room, or `st` is capturing).  One per stream: calls that share a
-// handle on different streams never share it.  Call with in->mu held, and hold it until the launches that write and read the room are
+// handle on different streams never share it.  A capture takes over the stream's buffer: its graph may be replayed on any stream,
+// beside later calls on this one, which make another.  Call with in->mu held, and hold it until the launches that write and read the room are
 // made: calls of two threads on one stream share it in stream order, launches of one must not come between the other's.
 void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
 {
-    for (auto &b : in->banks)
-        if (b.stream == st && b.bytes >= bytes) return b.buf;
-    void *p = nullptr;
+    constexpr int kGraphs = 16;                       // that have a buffer of the handle
+    const unsigned long long graph = capture_id(st);
+    fscnn_input::Bank *own = nullptr;                 // not in a graph
+    int graphs = 0;
+    for (auto &b : in->banks) {
+        graphs += b.graph != 0;
+        if (b.stream != st || b.bytes < bytes) continue;
+        if (b.graph == graph) return b.buf;
+        if (!b.graph) own = &b;
+    }
     if (st) in->in_order = false;
-    if (capturing(st)) return nullptr;
+    if (graph) {
+        if (!own || graphs >= kGraphs) return nullptr;
+        own->graph = graph;
+        return own->buf;
+    }
+    void *p = nullptr;
     size_t room = 1 << 20;                            // (powers of two: what outgrown buffers hold is bounded by the largest)
     while (room < bytes) room *= 2;
     if (block_alloc(input_pool(), in->device, st, &p, room, &bytes) != hipSuccess) {
@@ -585,7 +609,7 @@ void *bank_scratch(const fscnn_input *in, hipStream_t st, size_t bytes)
         return nullptr;
     }
     // (a smaller one stays with the handle: launches in flight and graphs captured so far use it)
-    in->banks.push_back({st, p, bytes});
+    in->banks.push_back({st, p, bytes, 0});
     return p;
 }
 

@@ -162,11 +162,12 @@ struct fscnn_input {
     // for the worst case, with room for the dense result iff emit_has_y; 0 for other handles
     size_t emit_bytes = 0;
     bool emit_has_y = false;
-    // room for the caller's bank in bfloat16 parts, one buffer per stream that has needed it (bank_scratch in api.hip)
+    // room for the caller's bank in bfloat16 parts, one buffer per stream and capture that has needed it (bank_scratch in api.hip)
     struct Bank {
         hipStream_t stream;
         void *buf;
         size_t bytes;
+        unsigned long long graph;   // the capture that has it; 0: none
     };
     mutable std::mutex mu;   // held over the launches that write and read such room
     mutable std::vector<Bank> banks;

@@ -152,6 +152,30 @@ def test_fills_and_uses_in_graphs_and_outside_of_them(F, prepared):
         assert torch.equal(y.cpu(), want[0])
 
 
+def test_a_graph_beside_calls_on_the_stream_that_captured_it(F):
+    n, c, k, h, w = 8, 64, 256, 28, 28
+    x, wt, _ = inputs.random_layer(5, n, c, k, h, w, 3, 3, 1.0, integer=True, x_zero_frac=0.5)
+    banks = [wt, np.ascontiguousarray(wt[::-1]), -wt]
+    want = [torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(b), None, 1, 1).cuda() for b in banks]
+    banks, s = [dev(b) for b in banks], F.input_compress(dev(x))
+    side, y = torch.cuda.Stream(), torch.empty(2, *want[0].shape, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        F.conv2d_sparse_input(s, banks[0], (1, 1), (1, 1))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for i in range(2):
+            F.conv2d_sparse_input(s, banks[i], (1, 1), (1, 1), out=y[i])
+    for _ in range(60):
+        graph.replay()
+        with torch.cuda.stream(side):
+            beside = [F.conv2d_sparse_input(s, banks[2], (1, 1), (1, 1)) for _ in range(3)]
+        torch.cuda.synchronize()
+        assert torch.equal(y[0], want[0]) and torch.equal(y[1], want[1])
+        assert all(torch.equal(b, want[2]) for b in beside)
+
+
 def test_captured_with_the_bank_as_the_caller_holds_it(F):
     """With room for the parts from an eager call on the stream, and without (the contraction in fp32)."""
     n, c, k, h, w = 8, 64, 256, 28, 28
