@@ -1,13 +1,15 @@
 // Convolution as a dense contraction on the matrix cores, fp32 operands taken apart into three bfloat16 parts.
 //
 // A float is the exact sum of three bfloat16 numbers (8 + 8 + 8 bits, each part the previous remainder rounded
-// to nearest; exact down to 2^-102, below that the last part loses bits of a subnormal), and a product of two
+// to nearest; operands are multiplied by 2^16 first, so that subnormal ones have their parts too), and a product of two
 // floats is, up to 2^-26 of it, the six products of parts h*h, h*m, m*h, m*m, h*l, l*h.  v_mfma_f32_32x32x16_bf16
 // multiplies at 2.1 PFLOP/s on this chip (registers only), so six of them make 350 TFLOP/s of fp32-like
 // products where v_mfma_f32_16x16x4_f32 (contract.hip) makes 154.  Precision: the matrix unit cuts what it adds
 // two bits below the accumulator's last one, towards zero, which biases a sum that all six products go into (512
 // channels, 3x3: 6.3e-7 of the result in 2-norm, mean -1e-7, against 4.4e-7 of the fp32 unit).  So h*h has an
 // accumulator of its own and the five small products share another one, 2^-8 of its size, added at the end: 1.7e-7.
+// Sums of one sign are no worse off: 4608 products of magnitudes, 512 -> 512 at 28x28, N = 8: 1.8e-7, mean -7e-10 of the
+// result (the fp32 unit: 3.6e-7); a bank that averages: 1.7e-7 (4.4e-7).
 //
 // How it is mapped (numbering of pixels, panels and stripes as in contract.hip):
 //   * output channels are the rows of the product, output pixels its columns.  A work-group owns 32*MW channels and
@@ -27,9 +29,9 @@
 // A compressed activation is served from the dense form its handle keeps (si_choose in conv_si.hip says when), with a
 // dense 3x3 bank taken apart as it is prepared or, where the caller holds it, before the launch.
 //
-// Non-finite operands: a value that is Inf, NaN or rounds to an infinite first part has a NaN last part, so every
-// output it is multiplied into (zeros included) is NaN; an output that is not finite is made again entry by
-// entry, from stored entries only (0 * Inf cannot appear).
+// Non-finite operands: a value that is Inf, NaN or has an infinite first part (from 2^112 on) has a NaN last part, so every
+// output it is multiplied into (zeros included) is NaN; an output that is not finite (a sum from 2^96 on among them) is made
+// again entry by entry, from stored entries only (0 * Inf cannot appear): 2.4 ms where all of 128 -> 128 at 28x28, N = 8 are.
 #include <type_traits>
 
 #include "internal.h"
@@ -80,9 +82,12 @@ struct SpArgs {
 __device__ inline int div_by(int x, uint32_t m) { return (int)__umulhi((uint32_t)x * 2u, m); }
 inline uint32_t recip_of(int d) { return (uint32_t)(((1LL << 31) + d - 1) / d); }
 
-// the parts of two floats, packed in pairs
+// The parts of two floats times kScale, packed in pairs.  The smallest bfloat16 is 2^-133, the smallest float 2^-149: so no
+// operand loses bits, and a sum is divided by kScale^2 at its end
+constexpr float kScale = 65536.0f, kUnscale = 1.0f / 65536.0f / 65536.0f;
 __device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
 {
+    a *= kScale; b *= kScale;
     h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2v));
     const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
     m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{ra, rb}, bf2v));
@@ -115,7 +120,7 @@ template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int
 {
     constexpr int RS = R * R;
     const SlowArgs &s = a.slow;
-    float acc = 0.0f;
+    double acc = 0.0;                                 // (one chain of thousands of sums)
     if (s.rowptr) {
         const float *xn = a.x + (long long)n * a.C * a.H * a.W;
         for (int i = s.rowptr[k]; i < s.rowptr[k + 1]; ++i) {
@@ -123,7 +128,7 @@ template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int
             const int c = (int)(f / RS), rs = (int)(f % RS);
             const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - a.pw + rs % R;
             if (iy >= 0 && iy < a.H && ix >= 0 && ix < a.W)
-                acc = __builtin_fmaf(s.val[i], xn[((long long)c * a.H + iy) * a.W + ix], acc);
+                acc = __builtin_fma((double)s.val[i], (double)xn[((long long)c * a.H + iy) * a.W + ix], acc);
         }
     } else {
         for (int rs = 0; rs < RS; ++rs) {
@@ -131,10 +136,10 @@ template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int
             if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W) continue;
             const long long pix = ((long long)n * a.H + iy) * a.W + ix;
             for (int i = s.cptr[pix * s.NCP]; i < s.cptr[(pix + 1) * s.NCP]; ++i)
-                acc = __builtin_fmaf(s.xval[i], s.w[(long long)k * s.wk + (long long)s.cidx[i] * s.wc + (long long)rs * s.wt], acc);
+                acc = __builtin_fma((double)s.xval[i], (double)s.w[(long long)k * s.wk + (long long)s.cidx[i] * s.wc + (long long)rs * s.wt], acc);
         }
     }
-    return acc;
+    return (float)acc;
 }
 
 // one wave's part: NT blocks of 32 pixels
@@ -361,7 +366,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
             float *y = to + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wo + ox;
 #pragma unroll
             for (int i = 0; i < OWN; ++i)
-                if (row_of(i) < a.K) y[(long long)row_of(i) * plane] = own[t][i];
+                if (row_of(i) < a.K) y[(long long)row_of(i) * plane] = own[t][i] * kUnscale;
         }
         return;
     }
@@ -377,7 +382,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
         for (int i = 0; i < OWN; ++i) {
             const int k = row_of(i);
             if (k >= a.K) continue;
-            float v = own[t][i];
+            float v = own[t][i] * kUnscale;
             finite &= __builtin_fabsf(v) < __builtin_inff();
             if (a.bias) v += a.bias[k];
             y[(long long)k * plane] = act_apply(v, a.act);

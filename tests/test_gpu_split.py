@@ -1,6 +1,6 @@
 """The contraction in bfloat16 parts: every tile, for both extents, at sizes where it can go wrong (one pixel per row,
 tiles that end inside a row, rows that cross images, panels, rows whose last load of four overlaps the one before,
-channel and filter counts off every multiple), that all parts of both operands count, values of any magnitude, Inf
+channel and filter counts off every multiple), that all parts of both operands count, values of any magnitude and of one sign, Inf
 and NaN, and calls that capture or leave no room for its copy of the bank."""
 import numpy as np
 import pytest
@@ -89,6 +89,28 @@ def test_random_data_stays_within_the_fp32_bound(F, n, c, k, h, w, r, scale):
     want, a = oracle.conv2d_sparse_filter(x, csr, wt.shape, (1, 1), (r // 2, r // 2), b, False, want_abs=True)
     got = F.conv2d_sparse_filter(f, dev(x), (1, 1), (r // 2, r // 2), None if b is None else dev(b), False).cpu().numpy()
     assert_parity(got, want, a, int(np.diff(csr[0]).max()), "parts")
+
+
+# The fp32 unit's error is 2e-7 of the result in 2-norm here (1152 products), this one's 0.5e-7 to 1e-7.  Rounding to nearest leaves no
+# mean over a million results (1e-10 .. 1e-9 of the mean magnitude, 1e-7 over the root of their number); an accumulator of
+# the 72 instructions that cut towards zero would move sums of one sign by some 2^-24 of it.
+@pytest.mark.parametrize("xe,we", [(0, 0), (-110, 60), (-124, 60), (-140, 100), (60, -124), (100, -140), (-60, -60), (110, -110), (120, -120)])
+@pytest.mark.parametrize("sign", [False, True])
+def test_precision_holds_at_any_magnitude_and_for_one_sign(F, xe, we, sign):
+    n, c, k, h, w = 4, 128, 128, 44, 40
+    x, wt, _ = inputs.random_layer(5, n, c, k, h, w, 3, 3, 1.0, bias=False)
+    if sign:
+        x, wt = np.abs(x), np.abs(wt)
+    x = np.ldexp(np.maximum(x, 0).astype(np.float64), xe).astype(np.float32)     # (subnormals keep the bits they have)
+    wt = np.ldexp(wt.astype(np.float64), we).astype(np.float32)
+    want = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(wt).double(), None, 1, 1)
+    f = F.filter_compress(dev(wt))
+    assert F.sf_split_choice(f, n, h, w, (1, 1), (1, 1))[0] >= 0
+    assert F.si_split_choice(n, c, h, w, k, (1, 1))[0] <= np.count_nonzero(x)
+    for got in (F.conv2d_sparse_filter(f, dev(x), (1, 1), (1, 1)), F.conv2d_sparse_input(F.input_compress(dev(x)), dev(wt), (1, 1), (1, 1))):
+        off = got.double().cpu() - want
+        assert off.norm() <= 1.5e-7 * want.norm()
+        assert not sign or abs(off.mean()) <= 1e-8 * want.mean()
 
 
 def test_values_that_are_not_finite_or_round_to_infinity(F):
