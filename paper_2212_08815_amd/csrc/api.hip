@@ -8,6 +8,7 @@
 #include <atomic>
 #include <new>
 
+#include "host_word.h"
 #include "internal.h"
 
 using namespace fscnn;
@@ -191,61 +192,6 @@ hipError_t filter_alloc(int device, hipStream_t st, void **p, size_t bytes, size
 }
 
 void filter_free(int device, void *p, size_t bytes, Left left) { block_free(filter_pool(bytes), device, p, bytes, left); }
-
-// Where a kernel leaves a number for the host: a word of pinned memory (copied from the device to pageable memory the
-// same number takes a launch and 20 us of the host's time more).  NULL where there is none: then it is copied.
-struct HostWord {
-    int *word = nullptr;
-    HostWord()
-    {
-        Words &w = words();
-        std::lock_guard<std::mutex> lock(w.mu);
-        if (!w.made) {
-            w.made = true;
-            int *p = nullptr;
-            if (hipHostMalloc(reinterpret_cast<void **>(&p), kWords * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-                for (int i = 0; i < kWords; ++i) w.free.push_back(p + i * 16);
-            else
-                (void)hipGetLastError();
-        }
-        if (!w.free.empty()) {
-            word = w.free.back();
-            w.free.pop_back();
-        }
-    }
-    ~HostWord()
-    {
-        if (!word) return;
-        Words &w = words();
-        std::lock_guard<std::mutex> lock(w.mu);
-        w.free.push_back(word);
-    }
-    HostWord(const HostWord &) = delete;
-    HostWord &operator=(const HostWord &) = delete;
-    // the number, once the work on `st` is done; from: where the device has it as well.  (After an error the word is not used again: the
-    // kernel may still write it.)
-    hipError_t wait(const int *from, hipStream_t st, int *out)
-    {
-        hipError_t e = word ? hipSuccess : hipMemcpyAsync(out, from, sizeof(int), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) word = nullptr;
-        else if (word) *out = *const_cast<volatile int *>(word);
-        return e;
-    }
-
-private:
-    static constexpr int kWords = 64;    // calls at one time that find a word
-    struct Words {
-        std::mutex mu;
-        bool made = false;
-        std::vector<int *> free;
-    };
-    static Words &words()
-    {
-        static Words *w = new Words();
-        return *w;
-    }
-};
 
 bool capturing(hipStream_t st)
 {
@@ -692,7 +638,7 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
                                sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)), &f->rowptr_bytes);
     if (e == hipSuccess) cnt = f->rowptr + (K + 1);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, st);
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, word.word, st);
+    if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, word.hand_out(), st);
     if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total);
     if (e == hipSuccess) {
         f->nnz = total;
@@ -1161,7 +1107,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         char *base = static_cast<char *>(in->ptr_block);
         in->cptr = reinterpret_cast<int *>(base);
         scratch = reinterpret_cast<int *>(base + scratch_at);
-        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, word.word, st);
+        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, word.hand_out(), st);
         if (e == hipSuccess && whole) e = fill(base + nodes_at, most);
     }
     if (e == hipSuccess) e = word.wait(scratch + input_groups(npix, NCH), st, &total);
