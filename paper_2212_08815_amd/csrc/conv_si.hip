@@ -487,7 +487,8 @@ SiChoice si_choose(int N, int C, int H, int W, int K, int Ho, int Wo, int pw, bo
     }
     const long long npix = (long long)N * H * W;
     const double pack = prepared ? 0 : 3e-6 + 90.0 * K * C / 3.6e12;        // (512 -> 512: 9 us)
-    if (r.spick.cfg < 0 || (r.pick.cfg >= 0 && r.spick.seconds + pack > 0.9 * r.pick.seconds)) r.split_from = (long long)all + 1;
+    // (where the one in fp32 serves no size there is no crossing to go by; no geometry is known that only the one in parts serves)
+    if (r.spick.cfg < 0 || r.pick.cfg < 0 || r.spick.seconds + pack > 0.9 * r.pick.seconds) r.split_from = (long long)all + 1;
     else r.split_from = std::max({r.split_from, (npix + 3) / 4, input_dense_from(npix, C)});
     return r;
 }
@@ -504,10 +505,11 @@ hipError_t launch_conv_si(const fscnn_input *in, const float *w, int K, int R, i
 {
     const int NKT = (K + 63) / 64;
     if (c) {
-        // (an emitted activation's count may be on the device only: as in launch_conv_si_prepared)
+        // (an emitted activation's count may be on the device only: as in launch_conv_si_prepared; where the one in parts may serve,
+        // the one in fp32 serves every smaller count)
         const long long npix = (long long)in->N * in->H * in->W, all = npix * in->C;
         const int *count = in->nnz < 0 ? in->cptr + npix * in->NCH : nullptr;
-        const long long hi = bank && in->dense && (!count || c->from == 0) ? c->split_from : all + 1;
+        const long long hi = bank && in->dense ? c->split_from : all + 1;
         if (hi <= all && (count || in->nnz >= hi)) {
             hipError_t e = launch_split_bank(w, K, in->C, bank, st);
             if (e == hipSuccess) e = launch_split_input(in, bank, w, in->C * 9, 9, 1, K, Ho, Wo, ph, pw, bias, relu, y, c->spick, count, (int)hi, st);
