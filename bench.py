@@ -360,7 +360,7 @@ def other_rows(fscnn, torch, inputs, np, dev_layers):
             xs = fscnn.input_compress(x)
             out["input_compress"] = dict(ms=ms_c, nnz=xs.nnz, density=xs.nnz / x.numel(),
                                          gbs=(x.numel() * 4 + xs.nnz * 8) / ms_c / 1e6,
-                                         note="N=8, C=512, 28x28, ReLU(N(-0.5,1)); incl. allocations and two host syncs")
+                                         note="N=8, C=512, 28x28, ReLU(N(-0.5,1)); incl. the wait for the count; the handle before leaves its memory")
             y2 = fscnn.conv2d_sparse_input(xs, w, (1, 1), (1, 1), b, True)
             ms_s = time_gpu(torch, lambda: fscnn.conv2d_sparse_input(xs, w, (1, 1), (1, 1), b, True, out=y2), 5)
             # effective work: (nonzero input, in-image tap, k) triples
@@ -377,7 +377,7 @@ def other_rows(fscnn, torch, inputs, np, dev_layers):
             out["conv2d_sparse_input_prepared"] = dict(
                 ms=ms_p, effective_tflops=2.0 * triples / ms_p / 1e9,
                 dense_equivalent_tflops=2.0 * w.numel() * h * wd * n / ms_p / 1e9,
-                note="same, filter bank prepared once as a K-contiguous copy (N=8: too few patches to fill the chip)")
+                note="same, filter bank laid out once (fscnn_dense_filter_prepare)")
             # sparse output emission: the sparse-filter convolution of this layer returning its
             # ReLU output compressed (a dense temporary inside), next to the convolution alone
             ms_e = time_gpu(torch, lambda: fscnn.conv2d_sparse_filter_emit(f, x, (1, 1), (1, 1), b, True), 5)
@@ -388,7 +388,7 @@ def other_rows(fscnn, torch, inputs, np, dev_layers):
                 note="same layer at 95 % weight sparsity: convolution + ReLU + compression of the result "
                      "(counted in the convolution's epilogue, one scan, one fill); ms = refilling a handle "
                      "(fscnn_conv2d_sparse_filter_emit_into), ms_with_allocation = a new handle per call "
-                     "(one hipMalloc and the previous handle's hipFree)")
+                     "(in the memory that the previous one leaves)")
             x32 = torch.from_numpy(np.concatenate([c["x"]] * 4, 0)).cuda()
             xs32 = fscnn.input_compress(x32)
             y32 = fscnn.conv2d_sparse_input_prepared(xs32, dw, (1, 1), (1, 1), b, True)

@@ -1,5 +1,6 @@
 // Convolution as a dense contraction on the matrix cores (fp32 MFMA), for the calls whose operand
-// is too dense for a gather of single multiply-adds to pay:
+// is too dense for a gather of single multiply-adds to pay, and which the contraction in bfloat16 parts
+// (contract_split.hip: 3x3 and 5x5) does not serve or is not estimated to serve a tenth faster:
 //   * a compressed filter bank that stores a large share of its entries (or whose extent no gather
 //     configuration serves) applied to a dense NCHW tensor;
 //   * a compressed activation (per-pixel channel lists) with a dense filter bank.
@@ -27,9 +28,9 @@
 //     and tap.  (Read as [c][tap][k] with a power of two of rows, every load of a work-group fell on
 //     the same two of an L2's sixteen channels.)  A lane of a K x C x 3 x 3 bank needs 36 consecutive
 //     floats a chunk, nine 16-byte loads.
-// What bounds it: the matrix unit on full tiles (512 -> 512 at 28x28, N = 8: 253 us back to back, the unit busy 78 % of
-// the clocks from a dense tensor, 69 to 72 from lists; the LDS 20 %, waves waiting 16 to 20 % of their time); where a
-// launch is a round of short work-groups (96 -> 256 5x5 at 27x27, N = 8: busy 54 %) its loads and stores as well.
+// What bounds it: the matrix unit on full tiles (measured where the parts serve now: 512 -> 512 at 28x28, N = 8: 253 us back to
+// back, the unit busy 78 % of the clocks from a dense tensor, 69 to 72 from lists; the LDS 20 %, waves waiting 16 to 20 % of
+// their time); where a launch is a round of short work-groups (96 -> 256 5x5 at 27x27, N = 8: busy 54 %) its loads and stores as well.
 //
 // Non-finite operands: a gather never multiplies an entry that is not stored, so 0 * Inf cannot
 // appear there.  Dense tensors are checked while they are staged (a stripe that holds an Inf or NaN
