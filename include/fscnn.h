@@ -185,7 +185,8 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
 /* The same for the contraction with its operands taken apart into bfloat16 parts (3x3 and 5x5; a product of
  * two floats is held to 2^-26 of it, whatever their magnitudes, and sums are rounded as in fp32): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
  * does.  *parts_out (may be NULL): the work-groups per tile that the input channels are divided over; more than one need scratch as
- * the channel-split mode does (fscnn_filter_prepare_ex), and without it one serves the tile.  Host-only. */
+ * the channel-split mode does (fscnn_filter_prepare_ex), and without it one serves the tile.  Calls that read N4 tensors or pool
+ * are served so by the same rule (3x3; fscnn_sf_variant_choice then names what would serve them otherwise).  Host-only. */
 fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h, int stride_w,
                                      int pad_h, int pad_w, int *tile_out, int *panels_out, int *parts_out);
 

@@ -440,16 +440,20 @@ bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int
 // Whether such a call is served by the contraction in bfloat16 parts, where what it would go to otherwise takes
 // `other` seconds (512 -> 512 at 28x28, N = 8, any share stored: 250 us contracted in fp32, 132 in parts; gathered 126
 // at 10 % stored; 96 -> 256 5x5 at 27x27, N = 8: 82 and 37).  A tenth ahead, for what two estimates are off.  An emitting call's
-// results are then counted in a pass of their own (4 us).  Not for filters of fewer than 16 stored entries on average: there
+// results are then counted in a pass of their own (4 us).  Through N4 tensors and with the merged pool another microsecond ahead:
+// where the gather takes 8 to 10 us its estimate is 1 to 2 above (47 -> 503 at 6x6, N = 3, pooled: 10.5 us, estimated 11.9; 10.9 in
+// parts, estimated 9.2).  NCHW into N4 tensors stays gathered.  Not for filters of fewer than 16 stored entries on average: there
 // the rounding of the single products shows (2-norm against 64 bits up to 1.15 times the gather's; from 16 on it was 0.5 times
 // that of what served the call before, over 2112 random layers of zero-mean weights, and never more; 0.2 to 0.8 times where
 // activations and weights have one sign, over 40 layers).
-bool splits(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int pw, double other, bool emit, ContractPick *pick)
+bool splits(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int pw, bool in4, bool out4, bool pool, double other,
+            bool emit, ContractPick *pick)
 {
+    if (out4 && !in4) return false;
     const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
     if (f->nnz < 16LL * f->K || 2 * dense / 350e12 + 3e-6 > other) return false;
-    *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw, true);
-    return pick->cfg >= 0 && pick->seconds + (emit ? 4e-6 : 0) < 0.9 * other;
+    *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw, true, in4, pool);
+    return pick->cfg >= 0 && pick->seconds + (emit ? 4e-6 : in4 || pool ? 1e-6 : 0) < 0.9 * other;
 }
 
 // The plan of a contraction (kContractPlan, kSplitPlan) that is to serve an automatic call, NULL where it cannot be made now: no room for
@@ -496,8 +500,7 @@ fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw
     if (r->variant > 0)
         r->csplit = sf_choose_csplit(r->variant, N << r->band_shift, f->C, f->K, r->band_h, Wo, density(f), in4, emit, &us);
     r->contract = !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, r->variant, us, &r->pick);
-    if (!in4 && !out4 && !pool)
-        r->split = splits(f, N, H, W, sh, sw, Ho, Wo, pw, r->contract ? r->pick.seconds : 1e-6 * us, emit, &r->spick);
+    r->split = splits(f, N, H, W, sh, sw, Ho, Wo, pw, in4, out4, pool, r->contract ? r->pick.seconds : 1e-6 * us, emit, &r->spick);
     std::lock_guard<std::mutex> lock(f->mu);
     if (f->routes.size() < 8) {
         f->routes.push_back(*r);
@@ -709,7 +712,7 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (stream) f->in_order = false;
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, (hipStream_t)stream, &p);
-    if (p && r.spick.parts > 1) (void)split_sums(f, p, (hipStream_t)stream, split_sums_bytes(r.spick, N, f->K, Ho, Wo));
+    if (p && r.spick.parts > 1) (void)split_sums(f, p, (hipStream_t)stream, split_sums_bytes(r.spick, N, f->K, Ho, Wo, in4));
     if (s != FSCNN_OK || p) return s;
     if (r.contract) s = contract_plan(f, kContractPlan, (hipStream_t)stream, &p);
     if (s != FSCNN_OK || p) return s;
@@ -939,9 +942,9 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
     std::unique_lock<std::mutex> launching(f->launching, std::defer_lock);
     if (p) {
         if (r.spick.parts > 1) launching.lock();
-        float *sums = r.spick.parts > 1 ? split_sums(f, p, st, split_sums_bytes(r.spick, N, f->K, Ho, Wo)) : nullptr;
+        float *sums = r.spick.parts > 1 ? split_sums(f, p, st, split_sums_bytes(r.spick, N, f->K, Ho, Wo, in4)) : nullptr;
         FSCNN_HIP(launch_split_dense(x_dev, p->parts, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, Ho, Wo, sh, sw, ph, pw,
-                                     bias_dev, relu, y_dev, r.spick, sums, st));
+                                     bias_dev, relu, y_dev, in4, out4, pool, r.spick, sums, st));
         return FSCNN_OK;
     }
     if (r.contract) s = contract_plan(f, kContractPlan, st, &p);

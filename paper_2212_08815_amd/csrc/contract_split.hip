@@ -20,6 +20,13 @@
 //     Two buffers, one barrier per chunk: a chunk's stores are spread over the steps of the chunk before, four
 //     pixels of one octet by lane, whose 16-byte loads were issued a chunk earlier.  Pixels outside the image are
 //     cleared once.
+//   * Units.  Groups of four images in an N4 tensor are one image with rows of W x 4 columns, pixel (x, image b of the group) in column
+//     4x + b: a tap to the right is four columns away, everything else is as it was (N4 into NCHW differs in the stores alone).
+//     With the merged pool the pixels are numbered by units of 2x2: a block of 32 is 16 adjacent columns of two rows, 8 units, so
+//     that a unit's maximum is taken over four lanes and reads of B stay as free of bank conflicts as they were.  Without it a unit
+//     is a pixel.  4x4 images, 512 -> 1024, N = 18, 16 % stored, N4: 448 us gathered (a 16x16 tile holds one image), 27 so; 52 layers
+//     on 128x128, N = 18: 3638 -> 1253; 13 layers at 128x128, N = 12, 10 %: 724 -> 558.  250 random layers through N4 tensors or
+//     with the pool, 3 to 50 % stored: 1.29 times as fast as gathered, where the faster of the two each time would make 1.30.
 //   * where a launch leaves CUs idle the chunks are divided over several work-groups per tile, and a second launch adds up.
 //   * the A operands go from global memory to registers a few taps ahead, packed as the lanes want them:
 //     [32 rows][16 channels][tap][part][lane][8].
@@ -70,12 +77,16 @@ struct SpArgs {
     float *y;
     const int *gate;                     // if not NULL and *gate < gate_from, another kernel serves the call
     int gate_from;
-    int N, C, H, W, K, nslice, nkb, Ho, Wo, sh, sw, ph, pw, act;
+    // N, W, pw: groups of images; columns and padding times the images of a group.  Hu, Wu: rows and columns of units (see the top)
+    int N, C, H, W, K, nslice, nkb, Hu, Wu, sh, sw, ph, pw, act;
     int SW, tpp, pitch, PL, VR, NKT, QPR, buf_bytes;
     int parts, cpp, nblk;                // the chunks are divided over `parts` work-groups per tile, cpp each; tiles
     float *sums;                         // parts > 1: where they leave their sums, each part in the order of y
     uint32_t m_qpr, m_vr, m_sw, m_ho;    // reciprocals for div_by()
     SlowArgs slow;
+    // (behind what all launches read: the arguments come a line at a time, from memory)
+    int ystep, rext;                     // input rows from a unit to the one below, and of a unit
+    int il, pool, out4, images;          // log2 of the images of a group; merged pool; y is N4; images in all
 };
 
 // x / d for a divisor whose reciprocal ceil(2^31 / d) the host computed; exact while x * d < 2^31
@@ -95,8 +106,9 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &
     l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{la, lb}, bf2v));
 }
 
-template <int MW_, int KS_, int NW_, int NB_, int R_> struct SpCfg {
+template <int MW_, int KS_, int NW_, int NB_, int R_, bool GEN_> struct SpCfg {
     static constexpr int MW = MW_, KS = KS_, NW = NW_, NB = NB_, R = R_, RS = R * R;
+    static constexpr bool GEN = GEN_;                            // N4 tensors or the merged pool
     static constexpr int WAVES = MW * KS * NW, NTH = WAVES * 64;
     static constexpr int CC = 16 * KS, OCT = 2 * KS;             // channels and octets per chunk
     static constexpr int T = 32 * NB;
@@ -116,30 +128,42 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F &&
     }
 }
 
-template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int oy, int ox)
+// one output, in row oy and column x of output group n (column and image of the group, for N4 tensors)
+template <int R> __device__ float slow_output(const SpArgs &a, int n, int k, int oy, int x)
 {
     constexpr int RS = R * R;
     const SlowArgs &s = a.slow;
+    const int W = a.W >> a.il, pw = a.pw >> a.il, ox = x >> a.il, img = x - (ox << a.il);
     double acc = 0.0;                                 // (one chain of thousands of sums)
     if (s.rowptr) {
-        const float *xn = a.x + (long long)n * a.C * a.H * a.W;
+        const float *xn = a.x + (long long)n * a.C * a.H * a.W + img;
         for (int i = s.rowptr[k]; i < s.rowptr[k + 1]; ++i) {
             const uint32_t f = s.idx[i];
             const int c = (int)(f / RS), rs = (int)(f % RS);
-            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - a.pw + rs % R;
-            if (iy >= 0 && iy < a.H && ix >= 0 && ix < a.W)
-                acc = __builtin_fma((double)s.val[i], (double)xn[((long long)c * a.H + iy) * a.W + ix], acc);
+            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - pw + rs % R;
+            if (iy >= 0 && iy < a.H && ix >= 0 && ix < W)
+                acc = __builtin_fma((double)s.val[i], (double)xn[((long long)c * a.H + iy) * a.W + (ix << a.il)], acc);
         }
     } else {
         for (int rs = 0; rs < RS; ++rs) {
-            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - a.pw + rs % R;
-            if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W) continue;
-            const long long pix = ((long long)n * a.H + iy) * a.W + ix;
+            const int iy = oy * a.sh - a.ph + rs / R, ix = ox * a.sw - pw + rs % R;
+            if (iy < 0 || iy >= a.H || ix < 0 || ix >= W) continue;
+            const long long pix = ((long long)n * a.H + iy) * W + ix;   // (lists: NCHW)
             for (int i = s.cptr[pix * s.NCP]; i < s.cptr[(pix + 1) * s.NCP]; ++i)
                 acc = __builtin_fma((double)s.xval[i], (double)s.w[(long long)k * s.wk + (long long)s.cidx[i] * s.wc + (long long)rs * s.wt], acc);
         }
     }
     return (float)acc;
+}
+
+// 2x2 max-pool over four lanes that hold a unit's results, (0, 0) (0, 1) (1, 0) (1, 1) by dy, dx: rows first, as the gather kernels do
+__device__ __forceinline__ float pool4(float v, int dx, int dy, int dxbit)
+{
+    const float o = __shfl_xor(v, 16, 64);
+    const float r0 = dy ? o : v, r1 = dy ? v : o, m = r1 > r0 ? r1 : r0;
+    const float p = __shfl_xor(m, dxbit, 64);
+    const float c0 = dx ? p : m, c1 = dx ? m : p;
+    return c1 > c0 ? c1 : c0;
 }
 
 // one wave's part: NT blocks of 32 pixels
@@ -150,14 +174,18 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     const int part = a.parts > 1 ? blockIdx.x / a.nblk : 0, blk = blockIdx.x - part * a.nblk;
     const int kt = blk % a.NKT, tile = blk / a.NKT;
     const int pan = tile / a.tpp;
-    const int p0 = (tile % a.tpp) * G::T;
-    const int ptot = a.N * a.Ho * a.SW;               // pixels of a panel
-    const int plast = p0 + G::T < ptot ? p0 + G::T - 1 : ptot - 1;
+    const int il = G::GEN ? a.il : 0;
+    const bool pool = G::GEN && a.pool;
+    const int TU = pool ? G::T / 4 : G::T;            // units of a tile
+    const int p0 = (tile % a.tpp) * TU;
+    const int ptot = a.N * a.Hu * a.SW;               // units of a panel
+    const int plast = p0 + TU < ptot ? p0 + TU - 1 : ptot - 1;
     const int HW = a.H * a.W;
-    auto virt = [&](int v) { return (v / a.Ho) * a.VR + (v % a.Ho) * a.sh; };   // first input row of output row v
+    const int ystep = G::GEN ? a.ystep : a.sh;
+    auto virt = [&](int v) { return (v / a.Hu) * a.VR + (v % a.Hu) * ystep; };   // first input row of row v of units
     const int v0 = p0 / a.SW;
-    const int u0 = virt(v0), nrow = virt(plast / a.SW) + G::R - u0;
-    const int n0 = v0 / a.Ho;
+    const int u0 = virt(v0), nrow = virt(plast / a.SW) + (G::GEN ? a.rext : G::R) - u0;
+    const int n0 = v0 / a.Hu;
     // this part's chunks; channels from cend on read as zero
     const int CI0 = part * a.cpp, NCH = (a.C + G::CC - 1) / G::CC < CI0 + a.cpp ? (a.C + G::CC - 1) / G::CC : CI0 + a.cpp;
     const int cend = a.C < NCH * G::CC ? a.C : NCH * G::CC;
@@ -170,7 +198,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
         const int e = (wave % G::WPO) * 64 + lane;
         const int row = div_by(e, a.m_qpr), quad = e - row * a.QPR;
         const int ul = u0 - n0 * a.VR + row, dn = div_by(ul, a.m_vr);    // image n0 + dn
-        const int iy = ul - dn * a.VR - a.ph, c0 = pan * a.SW * a.sw - a.pw;
+        const int iy = ul - dn * a.VR - a.ph, c0 = pan * a.SW * (pool ? 2 * a.sw : a.sw) - a.pw;
         const int first = c0 > 0 ? c0 : 0, end = c0 + a.pitch < a.W ? c0 + a.pitch : a.W;   // the row's columns in the image: 4 or more
         const int ix = first + quad * 4 + 4 <= end ? first + quad * 4 : end - 4;
         if (row < nrow && n0 + dn < a.N && iy >= 0 && iy < a.H) {
@@ -205,24 +233,34 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
         }
     };
 
-    // a pixel of the tile: row of the panel (from v0 on), column, image and row of the image
+    // a unit of the tile: column, image group (from n0 on) and row of the image
     struct Pos { int ox, dn, oy; };
-    const int x0 = p0 - v0 * a.SW, y0 = v0 - n0 * a.Ho;
+    const int x0 = p0 - v0 * a.SW, y0 = v0 - n0 * a.Hu;
     auto pos_of = [&](int dp) {
         Pos r;
         const int dv = div_by(x0 + dp, a.m_sw);
         r.ox = x0 + dp - dv * a.SW;
         r.dn = div_by(y0 + dv, a.m_ho);
-        r.oy = y0 + dv - r.dn * a.Ho;
+        r.oy = y0 + dv - r.dn * a.Hu;
         return r;
     };
+    // this lane's unit in a block of 32 pixels, and its place in a unit of 2x2: 16 adjacent columns of two rows
+    const int dxbit = il ? 4 : 1, dx = pool && (j & dxbit), dy = pool ? j >> 4 : 0;
+    const int ju = !pool ? j : il ? (j & 3) | (j >> 1 & 4) : j >> 1 & 7;
+    auto unit_of = [&](int t) { return (nw * G::NT + t) * (pool ? 8 : 32) + ju; };
     // LDS byte offset of this lane's B operands, per block
     int boff[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int dp = (nw * G::NT + t) * 32 + j;
-        const Pos r = pos_of(p0 + dp < plast ? dp : plast - p0);
-        boff[t] = (((n0 + r.dn) * a.VR + r.oy * a.sh - u0) * a.pitch + r.ox * a.sw + (ks * 2 + q) * a.PL) * 48;
+        const int du = unit_of(t);
+        const Pos r = pos_of(p0 + du < plast ? du : plast - p0);
+        int row = (n0 + r.dn) * a.VR + r.oy * ystep - u0, col = r.ox * a.sw;
+        if constexpr (G::GEN) {
+            const int ox = r.ox >> il;
+            row += dy * a.sh;
+            col = (((pool ? 2 * ox + dx : ox) * a.sw) << il) + r.ox - (ox << il);
+        }
+        boff[t] = (row * a.pitch + col + (ks * 2 + q) * a.PL) * 48;
     }
     constexpr int NS = G::RS * NT;                    // steps of a chunk: (tap, block)
     // blocks whose B operands are requested or in use (a divisor of the steps, so that every step's registers are fixed)
@@ -231,7 +269,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     u4v b[D][3];
     auto read_b = [&](int buf, auto step) {
         constexpr int st = decltype(step)::value, tap = st / NT;
-        int so = buf + ((tap / G::R) * a.pitch + tap % G::R) * 48;
+        int so = buf + ((tap / G::R) * a.pitch + ((tap % G::R) << il)) * 48;
         asm volatile("" : "+s"(so));                  // the sum below is made here, not kept in registers from tap to tap
         const u4v *s = reinterpret_cast<const u4v *>(ldsb + boff[st % NT] + so);
 #pragma unroll
@@ -350,54 +388,70 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     }
 
     // ---- bias, activation, store: register r of lane (q, j) is row 8*(r/4) + 4*q + r%4 at pixel j
-    const long long plane = (long long)a.Ho * a.Wo;
+    const long long plane = (long long)a.Hu * a.Wu;
     auto row_of = [&](int i) {
         const int r = ks * OWN + i;
         return kb * 32 + 8 * (r >> 2) + 4 * q + (r & 3);
     };
+    // whether the lane's unit of block t is one, and where its results go (row 0 of the product; kp from there to the next).  Groups
+    // of four images go into an NCHW tensor each to its own
+    auto exists = [&](int t, const Pos &r) { return p0 + unit_of(t) <= plast && pan * a.SW + r.ox < a.Wu; };
+    const bool apart = G::GEN && il && !a.out4;
+    const long long kp = apart ? plane >> 2 : plane;
+    auto dest = [&](const Pos &r) {
+        const int xu = pan * a.SW + r.ox;
+        if (apart) return a.y + ((n0 + r.dn) * 4 + (xu & 3)) * (a.K * kp) + (long long)r.oy * (a.Wu >> 2) + (xu >> 2);
+        return a.y + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wu + xu;
+    };
+    // (what images past the last one of an N4 tensor hold is nobody's concern)
+    auto real = [&](const Pos &r) { return !il || (n0 + r.dn) * 4 + ((pan * a.SW + r.ox) & 3) < a.images; };
     if (a.parts > 1) {                                // parts_finish_kernel does the rest
-        float *to = a.sums + part * (a.N * a.K * plane);
+        const int per = pool ? 4 : 1;                 // (a unit's results side by side)
+        float *to = a.sums + part * (a.N * a.K * plane * per);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int dp = (nw * G::NT + t) * 32 + j;
-            const Pos r = pos_of(dp);
-            const int ox = pan * a.SW + r.ox;
-            if (p0 + dp > plast || ox >= a.Wo) continue;
-            float *y = to + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wo + ox;
+            const Pos r = pos_of(unit_of(t));
+            if (!exists(t, r)) continue;
+            float *y = to + ((long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wu + pan * a.SW + r.ox) * per + 2 * dy + dx;
 #pragma unroll
             for (int i = 0; i < OWN; ++i)
-                if (row_of(i) < a.K) y[(long long)row_of(i) * plane] = own[t][i] * kUnscale;
+                if (row_of(i) < a.K) y[row_of(i) * plane * per] = own[t][i] * kUnscale;
         }
         return;
     }
     bool finite = true;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int dp = (nw * G::NT + t) * 32 + j;
-        const Pos r = pos_of(dp);
-        const int ox = pan * a.SW + r.ox;
-        if (p0 + dp > plast || ox >= a.Wo) continue;
-        float *y = a.y + (long long)(n0 + r.dn) * a.K * plane + (long long)r.oy * a.Wo + ox;
+        const Pos r = pos_of(unit_of(t));
+        if (!exists(t, r) || (apart && !real(r))) continue;
+        float *y = dest(r);
 #pragma unroll
         for (int i = 0; i < OWN; ++i) {
             const int k = row_of(i);
             if (k >= a.K) continue;
             float v = own[t][i] * kUnscale;
-            finite &= __builtin_fabsf(v) < __builtin_inff();
+            finite &= __builtin_fabsf(v) < __builtin_inff() || !real(r);
+            if (pool) v = pool4(v, dx, dy, dxbit);
             if (a.bias) v += a.bias[k];
-            y[(long long)k * plane] = act_apply(v, a.act);
+            if (!pool || !(dx | dy)) y[(long long)k * kp] = act_apply(v, a.act);
         }
+    }
+    if (pool) {                                       // a unit's four lanes go on together
+        finite = __shfl_xor((int)finite, 16, 64) && finite;
+        finite = __shfl_xor((int)finite, dxbit, 64) && finite;
     }
     if (finite) return;
 #pragma nounroll
     for (int o = 0; o < NT * OWN; ++o) {              // (a lane's own stores: in order)
-        const int t = o / OWN, k = row_of(o % OWN), dp = (nw * G::NT + t) * 32 + j;
-        const Pos r = pos_of(dp);
-        const int ox = pan * a.SW + r.ox;
-        if (p0 + dp > plast || ox >= a.Wo || k >= a.K) continue;
-        float v = slow_output<G::R>(a, n0 + r.dn, k, r.oy, ox);
+        const int t = o / OWN, k = row_of(o % OWN);
+        const Pos r = pos_of(unit_of(t));
+        if (!exists(t, r) || (apart && !real(r)) || k >= a.K) continue;
+        const int xu = pan * a.SW + r.ox, ox = xu >> il;
+        float v = pool ? slow_output<G::R>(a, n0 + r.dn, k, 2 * r.oy + dy, ((2 * ox + dx) << il) + xu - (ox << il))
+                       : slow_output<G::R>(a, n0 + r.dn, k, r.oy, xu);
+        if (pool) v = pool4(v, dx, dy, dxbit);
         if (a.bias) v += a.bias[k];
-        a.y[((long long)(n0 + r.dn) * a.K + k) * plane + (long long)r.oy * a.Wo + ox] = act_apply(v, a.act);
+        if (!pool || !(dx | dy)) dest(r)[(long long)k * kp] = act_apply(v, a.act);
     }
 }
 
@@ -412,39 +466,85 @@ template <class G> __global__ void __launch_bounds__(G::NTH, 2) split_kernel(con
 }
 
 // Sums of the parts, in their order.  Bound by the launch and by one round trip to the last-level cache (512 x 14 x 14 in 4 parts: 2 us).
-template <int R> __global__ void __launch_bounds__(256) parts_finish_kernel(const SpArgs a)
+template <int R, bool POOL> __global__ void __launch_bounds__(256) parts_finish_kernel(const SpArgs a)
 {
-    const long long plane = (long long)a.Ho * a.Wo, total = a.N * a.K * plane, i = (long long)blockIdx.x * 256 + threadIdx.x;
+    constexpr int PER = POOL ? 4 : 1;                  // results of a unit
+    typedef float vec __attribute__((ext_vector_type(PER)));
+    const long long plane = (long long)a.Hu * a.Wu, total = a.N * a.K * plane, i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total) return;
-    const float *s = a.sums + i;
-    float v = 0.0f;
+    const vec *s = reinterpret_cast<const vec *>(a.sums) + i;
+    float v[PER] = {};
     for (int p0 = 0; p0 < a.parts; p0 += 8) {          // eight loads in flight
-        float u[8];
+        vec u[8];
 #pragma unroll
-        for (int p = 0; p < 8; ++p) u[p] = p0 + p < a.parts ? s[(p0 + p) * total] : 0.0f;
+        for (int p = 0; p < 8; ++p) u[p] = p0 + p < a.parts ? s[(p0 + p) * total] : vec(0.0f);
 #pragma unroll
-        for (int p = 0; p < 8; ++p) v += u[p];
+        for (int p = 0; p < 8; ++p)
+#pragma unroll
+            for (int e = 0; e < PER; ++e) v[e] += u[p][e];
     }
     const long long nk = i / plane;
-    const int k = (int)(nk % a.K), o = (int)(i - nk * plane);
-    if (!(__builtin_fabsf(v) < __builtin_inff())) v = slow_output<R>(a, (int)(nk / a.K), k, o / a.Wo, o % a.Wo);
-    if (a.bias) v += a.bias[k];
-    a.y[i] = act_apply(v, a.act);
+    const int k = (int)(nk % a.K), n = (int)(nk / a.K), o = (int)(i - nk * plane), oy = o / a.Wu, xu = o % a.Wu, ox = xu >> a.il;
+    const int img = a.il ? n * 4 + (xu & 3) : 0;
+    float m = 0.0f;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        if (!(__builtin_fabsf(v[e]) < __builtin_inff()) && img < a.images)
+            v[e] = POOL ? slow_output<R>(a, n, k, 2 * oy + e / 2, ((2 * ox + e % 2) << a.il) + xu - (ox << a.il)) : slow_output<R>(a, n, k, oy, xu);
+    }
+    if constexpr (POOL) {
+        const float c0 = v[2] > v[0] ? v[2] : v[0], c1 = v[3] > v[1] ? v[3] : v[1];
+        m = c1 > c0 ? c1 : c0;
+    } else {
+        m = v[0];
+    }
+    if (a.bias) m += a.bias[k];
+    m = act_apply(m, a.act);
+    if (!a.il || a.out4) a.y[i] = m;
+    else if (img < a.images) a.y[((long long)img * a.K + k) * (plane >> 2) + (long long)oy * (a.Wu >> 2) + ox] = m;
 }
 
 // ---------------------------------------------------------------- packed banks
 
-// zero-filled before
-__global__ void __launch_bounds__(256) split_rows_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
-                                                         const float *__restrict__ val, int RS, int nslice, uint16_t *__restrict__ out)
+// of compressed filters: a work-group puts the entries of 32 rows and 16 channels together in LDS, zeros between them, so that the bank
+// is written once, in whole lines (cleared and scattered before: 512 x 512, 10 % stored, 14.2 MB: 12 to 13 us as two launches, 8.9 so)
+template <int RS> __global__ void __launch_bounds__(512) split_rows_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
+                                                                          const float *__restrict__ val, int K, int nslice, u4v *__restrict__ out)
 {
-    const int k = blockIdx.x;
-    for (int i = rowptr[k] + (int)threadIdx.x; i < rowptr[k + 1]; i += 256) {
-        const int c = (int)(idx[i] / (uint32_t)RS), rs = (int)(idx[i] % (uint32_t)RS);
-        uint32_t h, m, l;
-        split2(val[i], 0.0f, h, m, l);
-        uint16_t *d = out + split_packed_index(k, c, rs, RS, nslice);
-        d[0] = (uint16_t)h; d[512] = (uint16_t)m; d[1024] = (uint16_t)l;
+    constexpr int ROW = 16 * RS + 1;                  // (odd: rows fall on different banks)
+    __shared__ float tile[32 * ROW];
+    const int sl = blockIdx.x % nslice, kb = blockIdx.x / nslice;
+    for (int e = threadIdx.x; e < 32 * ROW; e += 512) tile[e] = 0.0f;
+    __syncthreads();
+    // 16 lanes a row: the first entry of the slice by bisection (entries ascend), then the entries
+    const int r = threadIdx.x / 16, k = kb * 32 + r;
+    if (k < K) {
+        const uint32_t from = (uint32_t)sl * 16 * RS, to = from + 16 * RS;
+        int lo = rowptr[k], hi = rowptr[k + 1];
+        const int end = hi;
+        while (lo < hi) {
+            const int mid = lo + (hi - lo) / 2;
+            if (idx[mid] < from) lo = mid + 1; else hi = mid;
+        }
+        for (int i = lo + (int)(threadIdx.x % 16); i < end; i += 16) {
+            const uint32_t f = idx[i];
+            if (f >= to) break;
+            tile[r * ROW + (int)(f - from)] = val[i];
+        }
+    }
+    __syncthreads();
+    u4v *dst = out + (long long)blockIdx.x * (RS * 192);
+    for (int e = threadIdx.x; e < RS * 64; e += 512) {
+        const int tap = e / 64, lane = e % 64;
+        const float *src = &tile[(lane & 31) * ROW + (lane >> 5) * 8 * RS + tap];
+        u4v h, m, l;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t hh, mm, ll;
+            split2(src[2 * t * RS], src[(2 * t + 1) * RS], hh, mm, ll);
+            h[t] = hh; m[t] = mm; l[t] = ll;
+        }
+        dst[tap * 192 + lane] = h; dst[tap * 192 + 64 + lane] = m; dst[tap * 192 + 128 + lane] = l;
     }
 }
 // of a dense K x C x 3 x 3 bank: a work-group takes 32 rows and 16 channels through LDS, so that reads and writes are whole lines
@@ -471,11 +571,6 @@ __global__ void __launch_bounds__(kBankThreads) split_dense_kernel(const float *
     }
     dst[tap * 192 + lane] = h; dst[tap * 192 + 64 + lane] = m; dst[tap * 192 + 128 + lane] = l;
 }
-__global__ void __launch_bounds__(256) split_clear_kernel(float4 *__restrict__ p, long long n)
-{
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-}
 
 // ---------------------------------------------------------------- launch
 struct Geo { int MW, KS, NW, NB; };
@@ -489,11 +584,12 @@ template <class G> hipError_t launch_cfg(SpArgs a, const ContractPick &p, hipStr
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
     if (attr != hipSuccess) return attr;
     a.SW = p.SW; a.pitch = p.pitch; a.PL = p.PL; a.buf_bytes = p.buf; a.QPR = p.qpr;
-    a.VR = (a.Ho - 1) * a.sh + G::R;
-    a.m_qpr = recip_of(a.QPR); a.m_vr = recip_of(a.VR); a.m_sw = recip_of(a.SW); a.m_ho = recip_of(a.Ho);
+    a.VR = (a.Hu - 1) * a.ystep + a.rext;
+    a.m_qpr = recip_of(a.QPR); a.m_vr = recip_of(a.VR); a.m_sw = recip_of(a.SW); a.m_ho = recip_of(a.Hu);
     a.NKT = (a.K + 32 * G::MW - 1) / (32 * G::MW);
-    const long long P = (long long)a.N * a.Ho * a.SW;
-    a.tpp = (int)((P + G::T - 1) / G::T);
+    const long long P = (long long)a.N * a.Hu * a.SW;
+    const int TU = a.pool ? G::T / 4 : G::T;
+    a.tpp = (int)((P + TU - 1) / TU);
     const long long nblk = (long long)a.tpp * p.npan * a.NKT;
     const int nch = (a.C + G::CC - 1) / G::CC;
     a.parts = a.sums ? p.parts : 1;
@@ -501,27 +597,30 @@ template <class G> hipError_t launch_cfg(SpArgs a, const ContractPick &p, hipStr
     if (nblk <= 0 || nblk * a.parts > 0x7fffffffLL || nblk * a.parts * G::NTH > 0xffffffffLL) return hipErrorInvalidValue;
     a.nblk = (int)nblk;
     hipLaunchKernelGGL(split_kernel<G>, dim3((unsigned)(nblk * a.parts)), dim3(G::NTH), p.lds, st, a);
-    if (a.parts > 1)
-        hipLaunchKernelGGL(parts_finish_kernel<G::R>, dim3((unsigned)(((long long)a.N * a.K * a.Ho * a.Wo + 255) / 256)), dim3(256), 0, st, a);
+    if (a.parts > 1) {
+        const dim3 grid((unsigned)(((long long)a.N * a.K * a.Hu * a.Wu + 255) / 256));
+        if (a.pool) hipLaunchKernelGGL((parts_finish_kernel<G::R, true>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((parts_finish_kernel<G::R, false>), grid, dim3(256), 0, st, a);
+    }
     return hipGetLastError();
 }
 
-template <int R> hipError_t launch_any(const SpArgs &a, const ContractPick &p, hipStream_t st)
+template <int R, bool GEN> hipError_t launch_any(const SpArgs &a, const ContractPick &p, hipStream_t st)
 {
     switch (p.cfg) {
-    case 3: return launch_cfg<SpCfg<2, 2, 2, 4, R>>(a, p, st);
-    case 4: return launch_cfg<SpCfg<2, 2, 2, 3, R>>(a, p, st);
-    case 7: return launch_cfg<SpCfg<4, 2, 1, 2, R>>(a, p, st);
-    case 8: return launch_cfg<SpCfg<2, 4, 1, 2, R>>(a, p, st);
-    case 9: return launch_cfg<SpCfg<2, 4, 1, 1, R>>(a, p, st);
+    case 3: return launch_cfg<SpCfg<2, 2, 2, 4, R, GEN>>(a, p, st);
+    case 4: return launch_cfg<SpCfg<2, 2, 2, 3, R, GEN>>(a, p, st);
+    case 7: return launch_cfg<SpCfg<4, 2, 1, 2, R, GEN>>(a, p, st);
+    case 8: return launch_cfg<SpCfg<2, 4, 1, 2, R, GEN>>(a, p, st);
+    case 9: return launch_cfg<SpCfg<2, 4, 1, 1, R, GEN>>(a, p, st);
     }
     if constexpr (R == 3) {   // (for 5x5 the A operands of five taps leave no room for more accumulators)
         switch (p.cfg) {
-        case 0: return launch_cfg<SpCfg<2, 2, 2, 7, R>>(a, p, st);
-        case 1: return launch_cfg<SpCfg<2, 2, 2, 6, R>>(a, p, st);
-        case 2: return launch_cfg<SpCfg<2, 2, 2, 5, R>>(a, p, st);
-        case 5: return launch_cfg<SpCfg<4, 2, 1, 4, R>>(a, p, st);
-        case 6: return launch_cfg<SpCfg<4, 2, 1, 3, R>>(a, p, st);
+        case 0: return launch_cfg<SpCfg<2, 2, 2, 7, R, GEN>>(a, p, st);
+        case 1: return launch_cfg<SpCfg<2, 2, 2, 6, R, GEN>>(a, p, st);
+        case 2: return launch_cfg<SpCfg<2, 2, 2, 5, R, GEN>>(a, p, st);
+        case 5: return launch_cfg<SpCfg<4, 2, 1, 4, R, GEN>>(a, p, st);
+        case 6: return launch_cfg<SpCfg<4, 2, 1, 3, R, GEN>>(a, p, st);
         }
     }
     return hipErrorInvalidValue;
@@ -546,28 +645,43 @@ constexpr SplitCost kSplitCost[] = {{0.916, 0.425, 53.1, 2077, 0.315, 7974, 1197
 // 11.0 (11.2); 512 -> 128 at 20x20: 17.7, 26.6, 11.9 (11.9); 256 -> 256 at 28x28, where dividing gives little: 15.9, 16.2, 14.5.
 constexpr int kPartsMost = 16;
 constexpr long long kPartsBytes = 64LL << 20;
-ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide)
+// The units of a call (see the top of this file)
+struct Units {
+    int IL, N, W, pw, Hu, Wu, xstep, ystep, rext;
+    Units(int N_, int W_, int R, int Ho, int Wo, int sh, int sw, int pw_, bool in4, bool pool)
+    {
+        IL = in4 ? 4 : 1;
+        N = in4 ? (N_ + 3) / 4 : N_; W = W_ * IL; pw = pw_ * IL;
+        Hu = pool ? Ho / 2 : Ho; Wu = (pool ? Wo / 2 : Wo) * IL;
+        xstep = pool ? 2 * sw : sw; ystep = pool ? 2 * sh : sh; rext = pool ? R + sh : R;
+    }
+};
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide, bool in4, bool pool)
 {
     ContractPick best;
+    if (R != S || (R != 3 && R != 5) || (R == 5 && (in4 || pool)) || (pool && (Ho < 2 || Wo < 2)) || W > 0x10000000) return best;
+    const Units u(N, W, R, Ho, Wo, sh, sw, pw, in4, pool);
+    const int real = Ho * Wo;              // (results per image and channel)
+    N = u.N; W = u.W; pw = u.pw; Ho = u.Hu; Wo = u.Wu;
     // (rows are loaded four columns at a time)
-    if (R != S || (R != 3 && R != 5) || W < 4) return best;
+    if (W < 4) return best;
     // weights and the images a stripe can touch are addressed with 32-bit byte offsets, pixels of a
     // panel numbered with ints
     const long long big = 0x7fffffffLL;
     if (split_packed_bytes(K, C, R * S) >= big || (long long)N * Ho * (Wo + 64) >= big || (long long)N * H * W >= big ||
-        (long long)N * ((long long)(Ho - 1) * sh + R) >= big || (Ho - 1) * (long long)sh + R > 40000 || Wo > 40000)
+        (long long)N * ((long long)(Ho - 1) * u.ystep + u.rext) >= big || (Ho - 1) * (long long)u.ystep + u.rext > 40000 || Wo > 40000)
         return best;
     const SplitCost &m = kSplitCost[R == 3 ? 0 : 1];
     int last_npan = 0;
     for (int target : {40000, 64, 48, 32, 24, 16, 12, 8, 6}) {          // widths of a panel
-        const int npan0 = (Wo + target - 1) / target, SW = (Wo + npan0 - 1) / npan0, npan = (Wo + SW - 1) / SW;
+        const int npan0 = (Wo + target - 1) / target, SW = ((Wo + npan0 - 1) / npan0 + u.IL - 1) / u.IL * u.IL, npan = (Wo + SW - 1) / SW;
         if (npan == last_npan) continue;
         last_npan = npan;
-        const int pitch = (SW - 1) * sw + S;
+        const int pitch = (((pool ? 2 : 1) * SW / u.IL - 1) * sw + S) * u.IL;
         // columns of a panel that lie in the image: at least one load's worth, at most qpr
         int most = 0, least = W;
         for (int p = 0; p < npan; ++p) {
-            const long long c0 = (long long)p * SW * sw - pw, first = c0 > 0 ? c0 : 0, end = c0 + pitch < W ? c0 + pitch : W;
+            const long long c0 = (long long)p * SW * u.xstep - pw, first = c0 > 0 ? c0 : 0, end = c0 + pitch < W ? c0 + pitch : W;
             const int have = end > first ? (int)(end - first) : 0;
             most = have > most ? have : most;
             least = have < least ? have : least;
@@ -577,11 +691,11 @@ ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho,
         const long long P = (long long)N * Ho * SW;
         for (int g = 0; g < kNGeo; ++g) {
             const Geo &q = kGeo[g];
-            const int T = 32 * q.NB, NT = (q.NB + q.NW - 1) / q.NW;
+            const int T = (pool ? 8 : 32) * q.NB, NT = (q.NB + q.NW - 1) / q.NW;
             if (R == 5 && NT > 2) continue;
-            const int rows = (T + SW - 2) / SW + 1;             // output rows a tile can touch
+            const int rows = (T + SW - 2) / SW + 1;             // rows of units a tile can touch
             const int cross = (rows - 1 + Ho - 1) / Ho;         // image boundaries among them
-            const long long nrow = (long long)(rows - 1) * sh + R + (long long)cross * (R > sh ? R - sh : 0);
+            const long long nrow = (long long)(rows - 1) * u.ystep + u.rext + (long long)cross * (R > sh ? R - sh : 0);
             if (nrow * qpr > 64 * 8 / (2 * q.KS)) continue;
             if ((cross + 2LL) * (C + 8) * H * W * 4 >= big - 64) continue;
             const long long npx = nrow * pitch;
@@ -595,7 +709,7 @@ ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho,
             for (int parts = 1; parts <= nch; ++parts) {
                 const int cpp = (nch + parts - 1) / parts;
                 if ((parts - 1) * cpp >= nch) continue;         // (the last one would have none)
-                const double sums = 4.0 * parts * N * K * Ho * Wo;
+                const double sums = 4.0 * parts * N * u.IL * K * real;
                 if (parts > 1 && (!divide || parts > kPartsMost || nwg * parts > 256 || sums > kPartsBytes)) break;
                 const double groups = (double)nwg * parts, rounds = (double)((nwg * parts + 255) / 256), fill = groups / (256 * rounds);
                 const double chunk = m.mfma * (1 + m.mfma_fill * fill) * mfma + m.stage * q.KS / 32 * (double)npx + m.chunk * (1 + m.chunk_fill * fill);
@@ -615,24 +729,30 @@ ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho,
 
 hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS, void *packed, hipStream_t st)
 {
-    const long long n16 = split_packed_bytes(K, C, RS) / 16;
-    hipLaunchKernelGGL(split_clear_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, static_cast<float4 *>(packed), n16);
-    hipLaunchKernelGGL(split_rows_kernel, dim3(K), dim3(256), 0, st, rowptr, idx, val, RS, (C + 15) / 16, static_cast<uint16_t *>(packed));
+    const int nslice = (C + 15) / 16;
+    const dim3 grid((unsigned)((long long)nslice * ((K + 31) / 32)));
+    if (RS == 9) hipLaunchKernelGGL(split_rows_kernel<9>, grid, dim3(512), 0, st, rowptr, idx, val, K, nslice, static_cast<u4v *>(packed));
+    else if (RS == 25) hipLaunchKernelGGL(split_rows_kernel<25>, grid, dim3(512), 0, st, rowptr, idx, val, K, nslice, static_cast<u4v *>(packed));
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
                               int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
-                              float *y, const ContractPick &p, float *sums, hipStream_t st)
+                              float *y, int in4, int out4, int pool, const ContractPick &p, float *sums, hipStream_t st)
 {
-    if (p.cfg < 0) return hipErrorInvalidValue;
+    if (p.cfg < 0 || (out4 && !in4)) return hipErrorInvalidValue;
     SpArgs a = {};
+    const Units u(N, W, R, Ho, Wo, sh, sw, pw, in4 != 0, pool != 0);
     a.sums = sums;
     a.x = x; a.w = static_cast<const char *>(packed); a.bias = bias; a.y = y;
-    a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.nslice = (C + 15) / 16; a.nkb = (K + 31) / 32; a.Ho = Ho; a.Wo = Wo;
-    a.sh = sh; a.sw = sw; a.ph = ph; a.pw = pw; a.act = act;
+    a.N = u.N; a.C = C; a.H = H; a.W = u.W; a.K = K; a.nslice = (C + 15) / 16; a.nkb = (K + 31) / 32;
+    a.sh = sh; a.sw = sw; a.ph = ph; a.pw = u.pw; a.act = act;
+    a.il = in4 ? 2 : 0; a.pool = pool; a.out4 = out4; a.images = N;
+    a.Hu = u.Hu; a.Wu = u.Wu; a.ystep = u.ystep; a.rext = u.rext;
     a.slow.rowptr = rowptr; a.slow.idx = idx; a.slow.val = val;
-    return R == 3 ? launch_any<3>(a, p, st) : launch_any<5>(a, p, st);
+    if (in4 || pool) return R == 3 ? launch_any<3, true>(a, p, st) : hipErrorInvalidValue;
+    return R == 3 ? launch_any<3, false>(a, p, st) : launch_any<5, false>(a, p, st);
 }
 
 hipError_t launch_split_bank(const float *w, int K, int C, void *packed, hipStream_t st)
@@ -651,11 +771,12 @@ hipError_t launch_split_input(const fscnn_input *in, const void *packed, const f
     SpArgs a = {};
     a.gate = gate; a.gate_from = gate_from; a.x = in->dense;
     a.w = static_cast<const char *>(packed); a.bias = bias; a.y = y;
-    a.N = in->N; a.C = in->C; a.H = in->H; a.W = in->W; a.K = K; a.nslice = (in->C + 15) / 16; a.nkb = (K + 31) / 32; a.Ho = Ho; a.Wo = Wo;
+    a.N = a.images = in->N; a.C = in->C; a.H = in->H; a.W = in->W; a.K = K; a.nslice = (in->C + 15) / 16; a.nkb = (K + 31) / 32;
+    a.Hu = Ho; a.Wu = Wo; a.ystep = 1; a.rext = 3;
     a.sh = a.sw = 1; a.ph = ph; a.pw = pw; a.act = relu;
     a.slow.cptr = in->cptr; a.slow.cidx = in->cidx; a.slow.xval = in->xval; a.slow.NCP = in->NCH;
     a.slow.w = w; a.slow.wk = wk; a.slow.wc = wc; a.slow.wt = wt;
-    return launch_any<3>(a, p, st);
+    return launch_any<3, false>(a, p, st);
 }
 
 }  // namespace fscnn

@@ -83,7 +83,7 @@ struct SfPlan {
     // packed array (contract_packed_index), zeros where nothing is stored; behind it an int that is
     // non-zero if a stored value is Inf or NaN (16 bytes).
     float *packed = nullptr;
-    // The plan of the contraction in bfloat16 parts (variant kSplitPlan): the parts (split_packed_index).
+    // The plan of the contraction in bfloat16 parts (variant kSplitPlan): the parts (split_packed_bytes).
     void *parts = nullptr;
 };
 constexpr int kDirectPlan = -1, kContractPlan = -2, kSplitPlan = -3;
@@ -185,7 +185,7 @@ struct fscnn_dense {
     int K, C, R, S, Kpad;
     float *wT;       // device [C*R*S*Kpad]; the arrays below follow it in the same allocation
     float *packed;   // 3x3: the bank in the order of the contraction's A operands; else, or where there was no room for it, NULL
-    void *parts;     // likewise, in bfloat16 parts (split_packed_index)
+    void *parts;     // likewise, in bfloat16 parts (split_packed_bytes)
     int *flag;       // 3x3: non-zero if the bank holds an Inf or NaN
 };
 
@@ -285,20 +285,19 @@ hipError_t launch_contract_dense(const float *x, const float *packed, const int 
                                  int sh, int sw, int ph, int pw, const float *bias, int act, float *y,
                                  const ContractPick &p, hipStream_t st);
 // ---- contract_split.hip: the same contraction with the operands taken apart into three bfloat16 parts; 3x3 and 5x5
-ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide);
-// Packed banks: position of the first part of w[k][c][tap] in 16-bit words (the others 512 and 1024 behind it), and the
-// number of bytes
-__host__ __device__ inline long long split_packed_index(int k, int c, int rs, int RS, int nslice)
-{
-    return (((long long)(k >> 5) * nslice + (c >> 4)) * RS + rs) * 1536 + ((c >> 3) & 1) * 256 + (k & 31) * 8 + (c & 7);
-}
+ContractPick split_pick(int N, int C, int K, int H, int W, int R, int S, int Ho, int Wo, int sh, int sw, int pw, bool divide, bool in4 = false,
+                        bool pool = false);
+// Packed banks, 16-bit words: [32 rows][16 channels][tap][part][octet of channels][row][channel]; the number of bytes
 inline long long split_packed_bytes(int K, int C, int RS) { return (long long)((K + 31) / 32) * ((C + 15) / 16) * RS * 3072; }
 hipError_t launch_split_rows(const int *rowptr, const uint32_t *idx, const float *val, int K, int C, int RS, void *packed, hipStream_t st);
 // sums: room for the sums of p.parts parts (split_sums_bytes); NULL: one work-group per tile takes all channels
-inline size_t split_sums_bytes(const ContractPick &p, int N, int K, int Ho, int Wo) { return 1024 + 4 * (size_t)p.parts * N * K * Ho * Wo; }
+inline size_t split_sums_bytes(const ContractPick &p, int N, int K, int Ho, int Wo, bool in4)
+{
+    return 1024 + 4 * (size_t)p.parts * (in4 ? (N + 3) / 4 * 4 : N) * K * Ho * Wo;
+}
 hipError_t launch_split_dense(const float *x, const void *packed, const int *rowptr, const uint32_t *idx, const float *val, int N, int C,
                               int H, int W, int K, int R, int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias, int act,
-                              float *y, const ContractPick &p, float *sums, hipStream_t st);
+                              float *y, int in4, int out4, int pool, const ContractPick &p, float *sums, hipStream_t st);
 // the same parts of a dense K x C x 3 x 3 bank, and the convolution of a compressed activation with them; w[k*wk + c*wc + tap*wt]: the bank
 // itself.  gate (device) with fewer than gate_from: the launch does nothing; NULL: it runs
 hipError_t launch_split_bank(const float *w, int K, int C, void *packed, hipStream_t st);
