@@ -284,8 +284,8 @@ fscnn_status_t fscnn_layout_convert(const float *src_dev, int N, int C, int H, i
  * value) pairs with x != 0.0f, channel ascending.  C up to 8192 (beyond:
  * FSCNN_ERR_UNSUPPORTED).  Allocates the handle's buffers (room for every value, as pairs and dense, up to 256 MB of
  * pairs, but no more than 1 GB beyond what all live handles store; beyond that, or if there is no such room, for
- * the stored ones) and synchronises `stream` once, for the number of stored
- * values.  The pass that writes the pairs may still be queued on `stream` when the call returns: x_dev must stay valid until
+ * the stored ones) and waits once, for the number of stored
+ * values, which comes behind all earlier work on `stream`.  The pass that writes the pairs may still be queued on `stream` when the call returns: x_dev must stay valid until
  * the work queued on `stream` so far has run (stream order suffices), and the library
  * orders every later use of the handle, on any stream, behind that pass. */
 fscnn_status_t fscnn_input_compress(const float *x_dev, int N, int C, int H, int W,

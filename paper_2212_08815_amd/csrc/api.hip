@@ -361,24 +361,21 @@ fscnn_status_t get_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan *
         delete p;
         return ds;
     }
-    // one allocation: the records, the pointers, and the counts the pointers are scanned from
+    // one allocation: the records, the pointers, and scratch of the launch that writes them
     const size_t nrecs = (size_t)(cap + kPlanSpare);
     hipError_t e = filter_alloc(dev, st, reinterpret_cast<void **>(&p->recs),
-                               sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + nb + scan_tmp_elems(nb)), &p->recs_bytes);
-    int *cnt = nullptr;
+                               sizeof(Rec) * nrecs + sizeof(int) * (size_t)(nb + 1 + plan_scratch_elems(g, p->NCH, p->NG)), &p->recs_bytes);
+    HostWord word;
     if (e == hipSuccess) {
         p->segptr = reinterpret_cast<int *>(p->recs + nrecs);
-        cnt = p->segptr + (nb + 1);
-        e = launch_plan_count(f->rowptr, f->idx, f->K, f->R * f->S, g, p->NCH, p->NG, cnt, st);
+        e = launch_plan(f->rowptr, f->idx, f->val, f->K, f->R, f->S, g, p->NCH, p->NG, p->segptr + (nb + 1), p->segptr,
+                        g.DENSE ? nullptr : p->recs, g.DENSE ? -1 : word.slot(), g.DENSE ? nullptr : word.hand_out(), st);
     }
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, p->segptr, nb, cnt + nb, nullptr, st);
-    if (e == hipSuccess)
-        e = g.DENSE ? launch_plan_fill_dense(f->rowptr, f->idx, f->val, f->K, f->C, f->R, f->S, g, p->NCH,
-                                             p->NG, cap, p->recs, st)
-                    : launch_plan_fill(f->rowptr, f->idx, f->val, f->K, f->R, f->S, g, p->NCH, p->NG, f->nnz,
-                                       p->segptr, p->recs, st);
+    if (e == hipSuccess && g.DENSE)
+        e = launch_plan_fill_dense(f->rowptr, f->idx, f->val, f->K, f->C, f->R, f->S, g, p->NCH, p->NG, cap, p->recs, st);
     // The plan may be used from other streams: wait for the build.
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    int built = 0;
+    if (e == hipSuccess) e = g.DENSE ? hipStreamSynchronize(st) : word.wait(nullptr, st, &built);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_plan(p, f->device, Left::kUnknown);
@@ -635,13 +632,12 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     f->in_order = !st;
     int *cnt = nullptr;
     int total = 0;
-    HostWord word;
+    HostWord word, packed;
     // two allocations: the pointers with the counts they are scanned from, and the nodes
     hipError_t e = filter_alloc(dev, st, reinterpret_cast<void **>(&f->rowptr),
                                sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)), &f->rowptr_bytes);
     if (e == hipSuccess) cnt = f->rowptr + (K + 1);
-    if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, st);
-    if (e == hipSuccess) e = launch_exclusive_scan(cnt, f->rowptr, K, cnt + K, word.hand_out(), st);
+    if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, f->rowptr, word.slot(), word.hand_out(), st);
     if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total);
     if (e == hipSuccess) {
         f->nnz = total;
@@ -649,8 +645,8 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
         e = filter_alloc(dev, st, reinterpret_cast<void **>(&f->idx), (sizeof(uint32_t) + sizeof(float)) * n, &f->idx_bytes);
         if (e == hipSuccess) f->val = reinterpret_cast<float *>(f->idx + n);
     }
-    if (e == hipSuccess) e = launch_filter_pack(w_dev, K, row, f->rowptr, f->idx, f->val, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = launch_filter_pack(w_dev, K, row, f->rowptr, f->idx, f->val, packed.slot(), packed.hand_out(), st);
+    if (e == hipSuccess) e = packed.wait(nullptr, st, &total);   // (w may be another's from here on, and any stream use the handle)
     if (e != hipSuccess) {
         (void)hipGetLastError();
         if (f->rowptr) (void)hipFree(f->rowptr);
@@ -1099,18 +1095,21 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         }
     }
     if (!whole) e = block_alloc(input_pool(), dev, st, &in->ptr_block, nodes_at, &in->ptr_bytes);
-    int *scratch = nullptr;
+    int *scratch = nullptr, *host = nullptr;
+    const bool scanned = !whole || input_scans(npix, NCH);   // (the number sizes the second allocation)
     auto fill = [&](void *nodes, size_t n) {
         in->cidx = static_cast<uint32_t *>(nodes);
         in->xval = reinterpret_cast<float *>(static_cast<char *>(nodes) + val_at(n));
         float *dense = whole ? reinterpret_cast<float *>(static_cast<char *>(in->ptr_block) + dense_at) : nullptr;
-        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare, dense, input_dense_from(npix, C), st);
+        return launch_input_fill(x_dev, N, C, H, W, NCH, scratch, scanned, in->cptr, in->cidx, in->xval, kSiSpare, dense, input_dense_from(npix, C),
+                                 scanned ? nullptr : host, st);
     };
     if (e == hipSuccess) {
         char *base = static_cast<char *>(in->ptr_block);
         in->cptr = reinterpret_cast<int *>(base);
         scratch = reinterpret_cast<int *>(base + scratch_at);
-        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, word.hand_out(), st);
+        host = word.hand_out();
+        e = launch_input_sums(x_dev, nullptr, N, C, H, W, NCH, scratch, scanned, scanned ? host : nullptr, st);
         if (e == hipSuccess && whole) e = fill(base + nodes_at, most);
     }
     if (e == hipSuccess) e = word.wait(scratch + input_groups(npix, NCH), st, &total);
@@ -1210,9 +1209,10 @@ fscnn_status_t emit_run(fscnn_filter_t *f, const float *x_dev, int N, int C, int
     if (s != FSCNN_OK) return s;
     hipError_t e = hipSuccess;
     int *scratch = reinterpret_cast<int *>(base + L.sum_at);
-    e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, nullptr, st);
-    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, in->cptr, in->cidx, in->xval, kSiSpare,
-                                               y_dev ? own : nullptr, 0, st);   // (the count may not be looked at: a replay brings another)
+    const bool scanned = input_scans((long long)N * Ho * Wo, in->NCH);
+    e = launch_input_sums(y, counted ? cnt : nullptr, N, K, Ho, Wo, in->NCH, scratch, scanned, nullptr, st);
+    if (e == hipSuccess) e = launch_input_fill(y, N, K, Ho, Wo, in->NCH, scratch, scanned, in->cptr, in->cidx, in->xval, kSiSpare,
+                                               y_dev ? own : nullptr, 0, nullptr, st);   // (the count may not be looked at: a replay brings another)
     if (e == hipSuccess) e = hipEventRecord(in->filled, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();

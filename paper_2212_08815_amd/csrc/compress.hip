@@ -6,7 +6,11 @@
 // counts that start with 0, one row per filter.  The construction used here is
 // count -> exclusive scan -> order-preserving compaction, which makes the result unique
 // (ascending flat index inside each row) and independent of thread scheduling.
+#include <stddef.h>
+
+#include "host_word.h"
 #include "internal.h"
+#include "lds_dma.h"
 
 namespace fscnn {
 
@@ -16,29 +20,34 @@ constexpr int kBlock = 256;
 
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
-// ---- A1: per output channel, the number of entries with w != 0 ------------------------
-constexpr int kCountPer = 9;   // (13 banks of the stack: 5.4 us each with the compiler's four, 4.8)
-__global__ void __launch_bounds__(kBlock) filter_count_kernel(const float *__restrict__ w,
-                                                              long long row, int *__restrict__ cnt)
+// Stores that reach the memory that the XCDs' caches do not keep apart, and the last of a launch's work-groups to have made its own telling the
+// host so: every stream finds them from there on.  (A wait for the stream is over 4 to 8 us later.)  The counter is left at zero.
+template <class T> __device__ inline void store_through(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// (Arrivals at one address are counted one after the other, 8 ns each: 4 us of 512 work-groups.  So they meet in sixteen counters
+// a line apart, the last ones of which meet in one.)
+constexpr int kArriveWays = 16, kCounterInts = (kArriveWays + 1) * 32;
+__device__ inline bool arrive(int *counter)   // one thread, behind a barrier that all stores were waited for in front of
 {
-    __shared__ int part[kBlock / 64];
-    const float *wk = w + (long long)blockIdx.x * row;
-    int c = 0;
-    for (long long f = threadIdx.x; f < row; f += kBlock * kCountPer) {   // all loads of a round in flight together
-        float v[kCountPer];
-#pragma unroll
-        for (int u = 0; u < kCountPer; ++u) v[u] = f + u * kBlock < row ? wk[f + u * kBlock] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < kCountPer; ++u) c += (v[u] != 0.0f) ? 1 : 0;
-    }
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-    if (lane_id() == 0) part[threadIdx.x >> 6] = c;
+    auto count = [](int *c, int all) {
+        if (__hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != all - 1) return false;
+        __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    };
+    const int groups = (int)gridDim.x, way = (int)blockIdx.x % kArriveWays;
+    if (!count(counter + (way + 1) * 32, (groups - way + kArriveWays - 1) / kArriveWays) ||
+        !count(counter, groups < kArriveWays ? groups : kArriveWays)) return false;
+    wait_vmcnt<0>();   // (the host may hand the slot on as soon as it is told)
+    return true;
+}
+// a number for the host that waits for it
+__device__ inline void store_host(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// the end of a kernel whose stores are all store_through(); counter NULL: nothing is told
+__device__ inline void tell_host(int *counter, int *host)
+{
+    if (!counter) return;
+    wait_vmcnt<0>();
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-        for (int i = 0; i < kBlock / 64; ++i) t += part[i];
-        cnt[blockIdx.x] = t;
-    }
+    if (threadIdx.x == 0 && arrive(counter)) store_host(host, 0);
 }
 
 // ---- exclusive scan of n ints into out[0..n] (out[n] = total); one work-group ---------
@@ -104,7 +113,7 @@ __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int 
     }
     if (threadIdx.x == 0) {
         out[n] = carry;
-        if (host) *host = carry;
+        if (host) store_host(host, carry);
     }
 }
 
@@ -179,23 +188,79 @@ __global__ void __launch_bounds__(kTileThreads) scan_tile_kernel(const int *__re
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kTileThreads - 1) out[n] = toff[gridDim.x];
 }
 
+__device__ int g_count_slots[HostWord::kWords * kCounterInts];
+constexpr int kCountScan = 4096;   // rows that one work-group scans
+
+// ---- A1: per output channel, the number of entries with w != 0 ------------------------
+// With a counter the work-group that finishes last scans the counts as well (rowptr, and the total for the host): the scan as a launch of
+// its own was 3.4 us and the gap in front of it.
+// (a 512 x 3 x 3 row is one round: the bank's 9.4 MB, counted and scanned, take 13.9 us in two rounds of 256 threads with one counter, 8.6 so)
+constexpr int kCountThreads = 512, kCountPer = 9;
+__global__ void __launch_bounds__(kCountThreads) filter_count_kernel(const float *__restrict__ w, long long row, int *__restrict__ cnt,
+                                                              int *__restrict__ rowptr, int *__restrict__ counter, int *__restrict__ host)
+{
+    __shared__ int part[kCountThreads / 64], last;
+    const float *wk = w + (long long)blockIdx.x * row;
+    int c = 0;
+    for (long long f = threadIdx.x; f < row; f += kCountThreads * kCountPer) {   // all loads of a round in flight together
+        float v[kCountPer];
+#pragma unroll
+        for (int u = 0; u < kCountPer; ++u) v[u] = f + u * kCountThreads < row ? wk[f + u * kCountThreads] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kCountPer; ++u) c += (v[u] != 0.0f) ? 1 : 0;
+    }
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
+    if (lane_id() == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int i = 0; i < kCountThreads / 64; ++i) t += part[i];
+        store_through(cnt + blockIdx.x, t);
+        wait_vmcnt<0>();
+        last = counter && arrive(counter);
+    }
+    __syncthreads();
+    if (!last) return;
+    const int K = (int)gridDim.x, wave = threadIdx.x >> 6;
+    int carry = 0;
+    for (int k0 = 0; k0 < K; k0 += kCountThreads) {
+        const int k = k0 + (int)threadIdx.x;
+        const int v = k < K ? __hip_atomic_load(cnt + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        const int incl = wave_inclusive(v);
+        if (lane_id() == 63) part[wave] = incl;
+        __syncthreads();
+        int before = carry;
+#pragma unroll
+        for (int i = 0; i < kCountThreads / 64; ++i) {
+            if (i < wave) before += part[i];
+            carry += part[i];
+        }
+        if (k < K) rowptr[k] = before + incl - v;
+        __syncthreads();   // the next round writes `part`
+    }
+    if (threadIdx.x == 0) {
+        rowptr[K] = carry;
+        if (host) store_host(host, carry);
+    }
+}
+
 // ---- A2: ordered pack of row k into idx/val at rowptr[k] ------------------------------
 // A round takes kPackPer elements per thread, a wave 64 * kPackPer consecutive ones: all loads in flight
 // together, positions by ballots, one exchange of the wave totals (one element per thread and round, two
 // barriers each, spent its time in the 18 rounds of a 512 x 3 x 3 row).
-constexpr int kPackPer = 8;
-__global__ void __launch_bounds__(kBlock) filter_pack_kernel(const float *__restrict__ w,
+constexpr int kPackThreads = 512, kPackPer = 9;   // (again one round for 512 x 3 x 3)
+__global__ void __launch_bounds__(kPackThreads) filter_pack_kernel(const float *__restrict__ w,
                                                              long long row,
                                                              const int *__restrict__ rowptr,
                                                              uint32_t *__restrict__ idx,
-                                                             float *__restrict__ val)
+                                                             float *__restrict__ val, int *__restrict__ counter, int *__restrict__ host)
 {
-    __shared__ int wave_tot[2][kBlock / 64];
+    __shared__ int wave_tot[2][kPackThreads / 64];
     const int k = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
     const float *wk = w + (long long)k * row;
     long long base = rowptr[k];
     int side = 0;
-    for (long long f0 = 0; f0 < row; f0 += kBlock * kPackPer) {
+    for (long long f0 = 0; f0 < row; f0 += kPackThreads * kPackPer) {
         const long long first = f0 + wave * (64 * kPackPer) + lane;
         float v[kPackPer];
 #pragma unroll
@@ -211,7 +276,7 @@ __global__ void __launch_bounds__(kBlock) filter_pack_kernel(const float *__rest
         __syncthreads();
         long long at = base;
 #pragma unroll
-        for (int i = 0; i < kBlock / 64; ++i) {
+        for (int i = 0; i < kPackThreads / 64; ++i) {
             const int t = wave_tot[side][i];
             if (i < wave) at += t;
             base += t;
@@ -220,10 +285,11 @@ __global__ void __launch_bounds__(kBlock) filter_pack_kernel(const float *__rest
 #pragma unroll
         for (int u = 0; u < kPackPer; ++u)
             if (v[u] != 0.0f) {
-                idx[at + pos[u]] = (uint32_t)(first + u * 64);
-                val[at + pos[u]] = v[u];
+                store_through(idx + at + pos[u], (uint32_t)(first + u * 64));
+                store_through(val + at + pos[u], v[u]);
             }
     }
+    tell_host(counter, host);
 }
 
 // ---- A3: regroup into (group g, chunk ci, channel-in-group kk) buckets -----------------
@@ -238,81 +304,84 @@ __device__ inline int lower_bound_u32(const uint32_t *a, int lo, int hi, uint32_
     return lo;
 }
 
-// Bucket b <-> (group g, wave w, chunk ci, slot j), slot fastest: the records of one wave form
-// one contiguous stream ordered by (chunk, slot); its output channel is k = g*KG + w*SLOTS + j.
-struct Bucket {
-    int k, ci;
-};
-__device__ inline Bucket decode_bucket(long long b, int SLOTS, int WAVES, int NCH)
+// Bucket (group g, wave w, chunk ci, slot j), slot fastest: the records of one wave form one contiguous stream ordered by (chunk,
+// slot); its output channel is k = g*KG + w*SLOTS + j.  A wave's channels are SLOTS adjacent rows, so its stream starts where the
+// first of them does and nothing has to be counted across waves: a work-group builds a wave's stream whole.  It reads the rows' entries
+// twice, all loads coalesced: first for where the chunks begin (an entry whose chunk is not the one of the entry before), then,
+// after a scan over the buckets, to write the records.  Three launches before (count by bisection, scan, fill): 5.5 + 3.4 + 5.4 us and the
+// gaps between them on average over the stack's layers, one of 6.9 us now, of which 1.3 are for
+// stores and arrivals that end the host's wait early.
+// mem: where the chunks' first entries go if they do not fit the LDS (lds_ints); recs may be NULL (only the pointers are wanted)
+__global__ void __launch_bounds__(kBlock) plan_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
+                                                      const float *__restrict__ val, int K, int R, int S, int CC, int SLOTS, int NCH,
+                                                      int IN_ROWS, int PITCH, int BV, int STRIDE, int nwaves, int lds_ints,
+                                                      int *__restrict__ mem, int *__restrict__ segptr, Rec *__restrict__ recs,
+                                                      int *__restrict__ counter, int *__restrict__ host)
 {
-    Bucket r;
-    const int j = (int)(b % SLOTS);
-    r.ci = (int)((b / SLOTS) % NCH);
-    const int w = (int)((b / ((long long)SLOTS * NCH)) % WAVES);
-    const int g = (int)(b / ((long long)SLOTS * NCH * WAVES));
-    r.k = (g * WAVES + w) * SLOTS + j;
-    return r;
-}
-
-__global__ void plan_count_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
-                                  int K, int RS, int CC, int SLOTS, int WAVES, int NCH, int NG,
-                                  int *__restrict__ cnt)
-{
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long nb = (long long)NG * NCH * SLOTS * WAVES;
-    if (b >= nb) return;
-    const Bucket q = decode_bucket(b, SLOTS, WAVES, NCH);
-    int c = 0;
-    if (q.k < K) {
-        const int lo = rowptr[q.k], hi = rowptr[q.k + 1];
-        const int a = lower_bound_u32(idx, lo, hi, (uint32_t)q.ci * CC * RS);
-        const int e = lower_bound_u32(idx, lo, hi, (uint32_t)(q.ci + 1) * CC * RS);
-        c = e - a;
+    extern __shared__ int plan_lds[];
+    __shared__ int part[kBlock / 64];
+    const int gw = blockIdx.x, RS = R * S, wave = threadIdx.x >> 6, B = NCH * SLOTS;
+    const uint32_t per = (uint32_t)(CC * RS);
+    // first entry of chunk c of row j: at[j * (NCH + 1) + c], the row's end at c = NCH; then every bucket's first record
+    const bool fits = 2 * B + SLOTS <= lds_ints;
+    int *at = fits ? plan_lds : mem + (long long)gw * (2 * B + SLOTS), *seg = at + SLOTS * (NCH + 1);
+    const int k0 = gw * SLOTS;
+    auto row = [&](int k) { return rowptr[k < K ? k : K]; };
+    const int base = row(k0);
+    for (int j = 0; j < SLOTS; ++j) {
+        int *a = at + j * (NCH + 1);
+        const int lo = row(k0 + j), hi = row(k0 + j + 1);
+        for (int i = lo + (int)threadIdx.x; i <= hi; i += kBlock) {      // (hi: behind the last entry)
+            const int c = i < hi ? (int)(idx[i] / per) : NCH, p = i > lo ? (int)(idx[i - 1] / per) : -1;
+            for (int q = p + 1; q <= c; ++q) a[q] = i;
+        }
     }
-    cnt[b] = c;
-}
-
-// LPB lanes (a power of two, 64 at most) share a bucket, about as many as it has entries: a thread per
-// bucket walked a dozen dependent loads and stores one by one (18 us a layer of the 13-layer stack).
-__global__ void plan_fill_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
-                                 const float *__restrict__ val, int K, int R, int S, int CC,
-                                 int SLOTS, int WAVES, int NCH, int NG, int IN_ROWS, int PITCH,
-                                 int BV, int STRIDE, int LPB, const int *__restrict__ segptr,
-                                 Rec *__restrict__ recs)
-{
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long b = t / LPB;
-    const int sub = (int)(t % LPB);
-    const long long nb = (long long)NG * NCH * SLOTS * WAVES;
-    if (t < kPlanSpare) {  // spare records a prefetching reader may touch past the end
-        const int last = segptr[nb];
-        Rec z;
-        z.off = 0u;
-        z.val = 0.0f;
-        recs[last + t] = z;
+    __syncthreads();
+    int *out = segptr + (long long)gw * B;
+    int carry = base;
+    for (int b0 = 0; b0 < B; b0 += kBlock) {
+        const int b = b0 + (int)threadIdx.x;
+        int v = 0;
+        if (b < B) {
+            const int *a = at + (b % SLOTS) * (NCH + 1) + b / SLOTS;
+            v = a[1] - a[0];
+        }
+        const int incl = wave_inclusive(v);
+        if (lane_id() == 63) part[wave] = incl;
+        __syncthreads();
+        int before = carry;
+#pragma unroll
+        for (int i = 0; i < kBlock / 64; ++i) {
+            if (i < wave) before += part[i];
+            carry += part[i];
+        }
+        if (b < B) store_through(out + b, seg[b] = before + incl - v);
+        __syncthreads();   // the next round writes `part`
     }
-    if (b >= nb) return;
-    const Bucket q = decode_bucket(b, SLOTS, WAVES, NCH);
-    if (q.k >= K) return;
-    const int RS = R * S;
-    const int lo = rowptr[q.k], hi = rowptr[q.k + 1];
-    const int o0 = segptr[b], count = segptr[b + 1] - o0;
-    if (count == 0) return;
-    const int a = lower_bound_u32(idx, lo, hi, (uint32_t)q.ci * CC * RS);
-    for (int d = sub; d < count; d += LPB) {
-        const int i = a + d, o = o0 + d;
-        const uint32_t f = idx[i];
-        const int c = (int)(f / RS) - q.ci * CC;
-        const int rs = (int)(f % RS);
-        const int r = rs / S, s = rs % S;
-        Rec rec;
-        // stride 2: tap (r, s) lies in plane (r mod 2, s mod 2) of the channel at (r/2, s/2)
-        const int plane = (r % STRIDE) * STRIDE + (s % STRIDE);
-        rec.off = (uint32_t)(((((c * STRIDE * STRIDE + plane) * IN_ROWS) + r / STRIDE) * PITCH + s / STRIDE) * BV * 4);
-        rec.val = val[i];
-        recs[o] = rec;
+    if (gw == nwaves - 1 && threadIdx.x == 0) store_through(out + B, carry);
+    if (!recs) return;                                // (another launch follows)
+    // a record is one 64-bit number
+    auto put = [&](long long at, uint32_t off, float val) {
+        store_through(reinterpret_cast<unsigned long long *>(recs) + at, (unsigned long long)__float_as_uint(val) << 32 | off);
+    };
+    if (gw == nwaves - 1 && (int)threadIdx.x < kPlanSpare) put(carry + (int)threadIdx.x, 0u, 0.0f);   // spare records that a prefetching reader may touch past the end
+    for (int j = 0; j < SLOTS; ++j) {
+        const int *a = at + j * (NCH + 1);
+        const int lo = row(k0 + j), hi = row(k0 + j + 1);
+        for (int i = lo + (int)threadIdx.x; i < hi; i += kBlock) {
+            const uint32_t f = idx[i];
+            const int ci = (int)(f / per), c = (int)(f / RS) - ci * CC;
+            const int rs = (int)(f % RS);
+            const int r = rs / S, s = rs % S;
+            // stride 2: tap (r, s) lies in plane (r mod 2, s mod 2) of the channel at (r/2, s/2)
+            const int plane = (r % STRIDE) * STRIDE + (s % STRIDE);
+            put(seg[ci * SLOTS + j] + i - a[ci],
+                (uint32_t)(((((c * STRIDE * STRIDE + plane) * IN_ROWS) + r / STRIDE) * PITCH + s / STRIDE) * BV * 4), val[i]);
+        }
     }
+    tell_host(counter, host);
 }
+static_assert(sizeof(Rec) == 8 && offsetof(Rec, off) == 0, "written as one number");
 
 // The plan of the taps-outer form: for every (group, wave, chunk), CC*R*S groups of SLOTS records
 // {LDS byte offset of tap (c mod CC, r, s), weight of output channel (group*WAVES + wave)*SLOTS + j
@@ -402,33 +471,22 @@ __global__ void __launch_bounds__(BLOCK) input_sum_kernel(const float *__restric
 template <int BLOCK, int kKept>
 __global__ void __launch_bounds__(BLOCK) input_fill_kernel(const float *__restrict__ x, int C, long long HW,
                                                             long long npix, int NCH, int PX,
-                                                            const int *__restrict__ start, int *__restrict__ cptr,
+                                                            int *__restrict__ start, const int *__restrict__ sums,
+                                                            int *__restrict__ cptr,
                                                             uint32_t *__restrict__ cidx, float *__restrict__ xval,
-                                                            int spare, float *__restrict__ dense, int dense_from)
+                                                            int spare, float *__restrict__ dense, int dense_from, int *__restrict__ host)
 {
     constexpr int CC = kSiCC;
     extern __shared__ uint32_t stage[];   // [cap] value bit patterns, then in 16 bits [cap] channels, [PX * NCH] positions
-    __shared__ int wave_sum[BLOCK / 64];
+    __shared__ int wave_sum[BLOCK / 64], wave_all[BLOCK / 64];
     const int cap = PX * NCH * CC, M = PX * NCH;
     unsigned short *chan = reinterpret_cast<unsigned short *>(stage + cap), *pos = chan + cap;   // (cap is below 10500)
-    const int base = start[blockIdx.x];
-    // the entries past the last stored one (readers fetch a few positions ahead) and the last pointer
-    if (blockIdx.x == 0 && (int)threadIdx.x <= spare) {
-        const int total = start[gridDim.x];
-        if ((int)threadIdx.x == spare) {
-            cptr[npix * NCH] = total;
-        } else {
-            cidx[total + threadIdx.x] = 0u;
-            xval[total + threadIdx.x] = 0.0f;
-        }
-    }
     const long long p0 = (long long)blockIdx.x * PX;
     const int px = threadIdx.x % PX, sj = threadIdx.x / PX, SJ = BLOCK / PX;
     const long long p = p0 + px;
     const bool live = p < npix;
     const long long first = live ? p / HW * C * HW + p % HW : 0;
     const float *xp = x + first;
-    float *dp = live && dense && start[gridDim.x] >= dense_from ? dense + first : nullptr;
     auto load = [&](int j, float(&v)[CC]) {
 #pragma unroll
         for (int u = 0; u < CC; ++u) {
@@ -436,6 +494,52 @@ __global__ void __launch_bounds__(BLOCK) input_fill_kernel(const float *__restri
             v[u] = live && j < NCH && ch < C ? xp[(long long)ch * HW] : 0.0f;
         }
     };
+    float kept[kKept][CC];
+#pragma unroll
+    for (int r = 0; r < kKept; ++r) load(sj + r * SJ, kept[r]);
+    // where the lists start and how many values there are in all: as scanned, or (sums) added up here
+    int base, all;
+    if (!sums) {
+        base = start[blockIdx.x];
+        all = start[gridDim.x];
+    } else {
+        int before = 0, every = 0;
+        for (int i = threadIdx.x; i < (int)gridDim.x; i += BLOCK) {
+            const int v = sums[i];
+            every += v;
+            before += i < (int)blockIdx.x ? v : 0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            before += __shfl_down(before, o, 64);
+            every += __shfl_down(every, o, 64);
+        }
+        if (lane_id() == 0) {
+            wave_sum[threadIdx.x >> 6] = before;
+            wave_all[threadIdx.x >> 6] = every;
+        }
+        __syncthreads();
+        base = all = 0;
+#pragma unroll
+        for (int i = 0; i < BLOCK / 64; ++i) {
+            base += wave_sum[i];
+            all += wave_all[i];
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            start[gridDim.x] = all;
+            if (host) store_host(host, all);
+        }
+    }
+    // the entries past the last stored one (readers fetch a few positions ahead) and the last pointer
+    if (blockIdx.x == 0 && (int)threadIdx.x <= spare) {
+        if ((int)threadIdx.x == spare) {
+            cptr[npix * NCH] = all;
+        } else {
+            cidx[all + threadIdx.x] = 0u;
+            xval[all + threadIdx.x] = 0.0f;
+        }
+    }
+    float *dp = live && dense && all >= dense_from ? dense + first : nullptr;
     auto count = [&](int j, const float(&v)[CC]) {
         if (dp) {
 #pragma unroll
@@ -459,9 +563,6 @@ __global__ void __launch_bounds__(BLOCK) input_fill_kernel(const float *__restri
                 ++o;
             }
     };
-    float kept[kKept][CC];
-#pragma unroll
-    for (int r = 0; r < kKept; ++r) load(sj + r * SJ, kept[r]);
 #pragma unroll
     for (int r = 0; r < kKept; ++r) count(sj + r * SJ, kept[r]);
     __syncthreads();
@@ -563,10 +664,23 @@ inline unsigned blocks_for(long long n, int per) { return (unsigned)((n + per - 
 
 }  // namespace
 
-hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, hipStream_t st)
+// The counter, on the current device, of a launch that writes the host's word of this slot; none (NULL) for slot -1
+static hipError_t count_slot(int slot, int **p)
 {
-    hipLaunchKernelGGL(filter_count_kernel, dim3(K), dim3(kBlock), 0, st, w, row, cnt);
-    return hipGetLastError();
+    *p = nullptr;
+    if (slot < 0) return hipSuccess;
+    constexpr int kDevices = 64;
+    static std::atomic<int *> known[kDevices];
+    int dev;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    int *q = dev < kDevices ? known[dev].load() : nullptr;
+    if (!q) {
+        e = hipGetSymbolAddress(reinterpret_cast<void **>(&q), HIP_SYMBOL(g_count_slots));
+        if (e == hipSuccess && dev < kDevices) known[dev] = q;
+    }
+    *p = q + slot * kCounterInts;
+    return e;
 }
 
 long long scan_tmp_elems(long long n)
@@ -588,33 +702,43 @@ hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp,
     return hipGetLastError();
 }
 
+hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, int *rowptr, int slot, int *host, hipStream_t st)
+{
+    int *counter = nullptr;
+    const hipError_t ce = count_slot(K <= kCountScan ? slot : -1, &counter);
+    if (ce != hipSuccess) return ce;
+    hipLaunchKernelGGL(filter_count_kernel, dim3(K), dim3(kCountThreads), 0, st, w, row, cnt, rowptr, counter, host);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || counter ? e : launch_exclusive_scan(cnt, rowptr, K, cnt + K, host, st);
+}
+
 hipError_t launch_filter_pack(const float *w, int K, long long row, const int *rowptr,
-                              uint32_t *idx, float *val, hipStream_t st)
+                              uint32_t *idx, float *val, int slot, int *host, hipStream_t st)
 {
-    hipLaunchKernelGGL(filter_pack_kernel, dim3(K), dim3(kBlock), 0, st, w, row, rowptr, idx, val);
+    int *counter = nullptr;
+    const hipError_t e = count_slot(slot, &counter);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(filter_pack_kernel, dim3(K), dim3(kPackThreads), 0, st, w, row, rowptr, idx, val, counter, host);
     return hipGetLastError();
 }
 
-hipError_t launch_plan_count(const int *rowptr, const uint32_t *idx, int K, int RS, const SfGeom &g,
-                             int NCH, int NG, int *cnt, hipStream_t st)
+constexpr int kPlanLds = 12288;   // ints
+long long plan_scratch_elems(const SfGeom &g, int NCH, int NG)
 {
-    const long long nb = (long long)NG * NCH * g.KG;
-    hipLaunchKernelGGL(plan_count_kernel, dim3(blocks_for(nb, kBlock)), dim3(kBlock), 0, st, rowptr,
-                       idx, K, RS, g.CC, g.SLOTS, g.WAVES, NCH, NG, cnt);
-    return hipGetLastError();
+    const long long per = 2LL * NCH * g.SLOTS + g.SLOTS;
+    return per <= kPlanLds ? 0 : per * NG * g.WAVES;
 }
 
-hipError_t launch_plan_fill(const int *rowptr, const uint32_t *idx, const float *val, int K, int R,
-                            int S, const SfGeom &g, int NCH, int NG, long long nnz, const int *segptr, Rec *recs,
-                            hipStream_t st)
+hipError_t launch_plan(const int *rowptr, const uint32_t *idx, const float *val, int K, int R, int S, const SfGeom &g, int NCH, int NG,
+                       int *scratch, int *segptr, Rec *recs, int slot, int *host, hipStream_t st)
 {
-    const long long nb = (long long)NG * NCH * g.KG;
-    int LPB = 1;
-    while (LPB < 64 && LPB * nb < nnz && 2 * LPB * nb < (1LL << 31)) LPB *= 2;
-    const long long threads = nb * LPB > kPlanSpare ? nb * LPB : kPlanSpare;
-    hipLaunchKernelGGL(plan_fill_kernel, dim3(blocks_for(threads, kBlock)), dim3(kBlock), 0, st, rowptr,
-                       idx, val, K, R, S, g.CC, g.SLOTS, g.WAVES, NCH, NG, g.IN_ROWS, g.PITCH, g.BV, g.STRIDE,
-                       LPB, segptr, recs);
+    int *counter = nullptr;
+    const hipError_t e = count_slot(slot, &counter);
+    if (e != hipSuccess) return e;
+    const long long waves = (long long)NG * g.WAVES, per = 2LL * NCH * g.SLOTS + g.SLOTS;
+    const size_t lds = per <= kPlanLds ? sizeof(int) * (size_t)per : 0;
+    hipLaunchKernelGGL(plan_kernel, dim3((unsigned)waves), dim3(kBlock), lds, st, rowptr, idx, val, K, R, S, g.CC, g.SLOTS, NCH, g.IN_ROWS,
+                       g.PITCH, g.BV, g.STRIDE, (int)waves, lds ? kPlanLds : 0, scratch, segptr, recs, counter, host);
     return hipGetLastError();
 }
 
@@ -644,13 +768,19 @@ long long input_groups(long long npix, int NCH)
     return PX ? (npix + PX - 1) / PX : 0;
 }
 
+// Up to as many groups every work-group of the fill pass adds up the groups before its own (a few loads per thread, behind those of x)
+// instead of a scan between the passes (8 x 512 x 28 x 28, 784 groups: 0.9 us here, 3.6 and the gap as a launch; 2 x 87 x 31 x 38 compressed
+// and convolved: 46.0 us with the scan, 42.0)
+constexpr long long kFillSums = 2048;
+bool input_scans(long long npix, int NCH) { return input_groups(npix, NCH) > kFillSums; }
+
 long long input_scratch_elems(long long npix, int NCH)
 {
     const long long g = input_groups(npix, NCH);
     return 2 * g + 1 + scan_tmp_elems(g);
 }
 
-hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
+hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch, bool scan,
                              int *host, hipStream_t st)
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
@@ -663,18 +793,19 @@ hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H
     else
         hipLaunchKernelGGL(input_sum_kernel<256>, dim3((unsigned)g), dim3(256), 0, st, x, cnt, C, HW, npix, NCH, PX, scratch + g + 1);
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, st);
+    return e != hipSuccess || !scan ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, st);
 }
 
-hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, hipStream_t st)
+hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, int *scratch, bool scanned, int *cptr,
+                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, int *host, hipStream_t st)
 {
     const long long HW = (long long)H * W, npix = (long long)N * HW, g = input_groups(npix, NCH);
     if (g == 0 || spare >= kBlock) return hipErrorInvalidValue;
     const int PX = input_pixels(NCH);
     const size_t lds = (size_t)PX * NCH * kFillBytes;
     auto launch = [&](auto kernel, int block) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(block), lds, st, x, C, HW, npix, NCH, PX, scratch, cptr, cidx, xval, spare, dense, (int)dense_from);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(block), lds, st, x, C, HW, npix, NCH, PX, scratch, scanned ? nullptr : scratch + g + 1, cptr, cidx,
+                           xval, spare, dense, (int)dense_from, host);
     };
     // Two to three steps per thread, all kept: 512 threads where there are steps for more than 256 (8 x 512 x 28 x 28, dense form
     // included: 16.0 us with 256 threads that keep four steps and load the others again, 9.6; with 1024: 11)

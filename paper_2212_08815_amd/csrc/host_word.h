@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <vector>
 
@@ -19,7 +21,7 @@ public:
             w.made = true;
             void *p = nullptr;
             if (hipHostMalloc(&p, kWords * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-                for (int i = 0; i < kWords; ++i) w.free.push_back(static_cast<int *>(p) + i * 16);
+                for (int i = 0; i < kWords; ++i) w.free.push_back((w.first = static_cast<int *>(p)) + i * 16);
             else
                 (void)hipGetLastError();
         }
@@ -41,12 +43,33 @@ public:
     int *hand_out()
     {
         in_flight = true;
+        if (word) *const_cast<volatile int *>(word) = kNone;
         return word;
     }
-    // the number, once the work on `st` is done; from: where the device has it as well
+    // a number below kWords that no other word in use has, -1: there is no word
+    int slot() const { return word ? (int)((word - words().first) / 16) : -1; }
+    static constexpr int kWords = 64;    // calls at one time that find a word
+    // the number, which is not negative, as soon as a kernel on `st` has written it (store_host): what follows that kernel on the stream
+    // need not be done, and the wait is over 4 to 8 us before a wait for the stream would be.  Where the stream has more than a
+    // millisecond to do first, and where there is no word, the stream is waited for; from: where the device has the number as well (NULL: it
+    // is not wanted)
     hipError_t wait(const int *from, hipStream_t st, int *out)
     {
-        hipError_t e = word ? hipSuccess : hipMemcpyAsync(out, from, sizeof(int), hipMemcpyDeviceToHost, st);
+        if (word) {
+            const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+            for (int i = 1; (*out = *const_cast<volatile int *>(word)) == kNone; ++i) {
+                if (i % 64 == 0 && std::chrono::steady_clock::now() > until) break;
+#if defined(__x86_64__)
+                __builtin_ia32_pause();
+#endif
+            }
+            if (*out != kNone) {
+                std::atomic_thread_fence(std::memory_order_acquire);
+                in_flight = false;
+                return hipSuccess;
+            }
+        }
+        hipError_t e = word || !from ? hipSuccess : hipMemcpyAsync(out, from, sizeof(int), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
         in_flight = false;
@@ -55,12 +78,13 @@ public:
     }
 
 private:
-    static constexpr int kWords = 64;    // calls at one time that find a word
+    static constexpr int kNone = -1;     // (what no kernel writes)
     int *word = nullptr;
     bool in_flight = false;
     struct Words {
         std::mutex mu;
         bool made = false;
+        int *first = nullptr;
         std::vector<int *> free;
     };
     static Words &words()

@@ -192,34 +192,35 @@ struct fscnn_dense {
 namespace fscnn {
 
 // ---- compress.hip
-hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, hipStream_t st);
+// cnt: K + scan_tmp_elems(K) ints; rowptr: K + 1.  slot: HostWord::slot() of the word `host`, which receives the number of stored values
+hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, int *rowptr, int slot, int *host, hipStream_t st);
 // out[0..n] = exclusive scan of in[0..n-1] (out[n] = total); tmp: scan_tmp_elems(n) ints of scratch; host: receives the total as
 // well (pinned memory), or NULL
 long long scan_tmp_elems(long long n);
 hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, hipStream_t st);
+// slot, host: of a word that receives 0 when idx and val are there for every stream; -1: none does
 hipError_t launch_filter_pack(const float *w, int K, long long row, const int *rowptr,
-                              uint32_t *idx, float *val, hipStream_t st);
-hipError_t launch_plan_count(const int *rowptr, const uint32_t *idx, int K, int RS, const SfGeom &g,
-                             int NCH, int NG, int *cnt, hipStream_t st);
-hipError_t launch_plan_fill(const int *rowptr, const uint32_t *idx, const float *val, int K, int R,
-                            int S, const SfGeom &g, int NCH, int NG, long long nnz, const int *segptr, Rec *recs,
-                            hipStream_t st);
+                              uint32_t *idx, float *val, int slot, int *host, hipStream_t st);
+// pointers and records; recs NULL: the pointers alone, and no word.  scratch: plan_scratch_elems() ints; slot, host: as above
+long long plan_scratch_elems(const SfGeom &g, int NCH, int NG);
+hipError_t launch_plan(const int *rowptr, const uint32_t *idx, const float *val, int K, int R, int S, const SfGeom &g, int NCH, int NG,
+                       int *scratch, int *segptr, Rec *recs, int slot, int *host, hipStream_t st);
 // the taps-outer plan (SfGeom::DENSE): nrec = NG*WAVES*NCH*CC*R*S*SLOTS records plus the spare ones
 hipError_t launch_plan_fill_dense(const int *rowptr, const uint32_t *idx, const float *val, int K, int C,
                                   int R, int S, const SfGeom &g, int NCH, int NG, long long nrec, Rec *recs,
                                   hipStream_t st);
-// Activation compression: launch_input_sums leaves where the lists of every group of input_pixels(NCH)
-// pixels start in scratch[0 .. input_groups] (the last one is the number of stored values); with cnt, the
-// counts per (pixel, step) are added up instead of x.  launch_input_fill then writes pointers and lists, and
-// zeroes the `spare` entries that follow the last stored one.
+// Activation compression: launch_input_sums adds up the stored values of every group of input_pixels(NCH) pixels, with cnt the counts
+// per (pixel, step) instead of x; launch_input_fill then writes pointers and lists, and zeroes the `spare` entries that follow the last
+// stored one.  scan: launch_input_sums scans the sums as well, which it has to where input_scans().  The number of stored values is then
+// in scratch[input_groups] and in *host (pinned memory, or NULL) behind it, else behind launch_input_fill.
+bool input_scans(long long npix, int NCH);
 long long input_groups(long long npix, int NCH);
 long long input_scratch_elems(long long npix, int NCH);   // ints
-// (host: as above)
-hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch,
+hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H, int W, int NCH, int *scratch, bool scan,
                              int *host, hipStream_t st);
 // dense, if not NULL: receives x as well where dense_from values and more are stored
-hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, const int *scratch, int *cptr,
-                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, hipStream_t st);
+hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, int *scratch, bool scanned, int *cptr,
+                             uint32_t *cidx, float *xval, int spare, float *dense, long long dense_from, int *host, hipStream_t st);
 // An activation that stores a thirty-second of its values is kept dense as well: from there on a contraction may serve it
 // (512 -> 512 at 28x28, N = 8: 132 us contracted, 157 gathered at 3 % stored)
 inline long long input_dense_from(long long npix, int C) { return (npix * C + 31) / 32; }
