@@ -303,8 +303,6 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
                                                                small[t], 0, 0, 0);
         big[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8v, w[0]), __builtin_bit_cast(bf8v, b[st % D][0]), big[t], 0, 0, 0);
     };
-    // (a barrier for LDS alone: __syncthreads() would wait for the A operands in flight as well)
-    auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     {
         const __amdgpu_buffer_rsrc_t w0 = weights(CI0);
@@ -313,9 +311,9 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
     }
     load_x(CI0);
     for (int e = wave * 64 + lane; e * 16 < 2 * a.buf_bytes; e += G::NTH) reinterpret_cast<u4v *>(ldsb)[e] = u4v{0, 0, 0, 0};
-    lds_barrier();
+    lds_only_barrier();
     static_for<0, 4>([&](auto px) { store_x(0, px); });
-    lds_barrier();
+    lds_only_barrier();
     static_for<0, D - 1>([&](auto st) { read_b(0, st); });
     // the next chunk's pixels are stored at steps LAST-3 .. LAST (several a step where a chunk is short); after LAST
     // comes the barrier, and then the first reads of the next chunk
@@ -328,7 +326,7 @@ template <class G, int NT> __device__ __forceinline__ void split_body(const SpAr
         const __amdgpu_buffer_rsrc_t wcur = weights(ci), wnext = weights(ci + 1);
         static_for<0, NS>([&](auto step) {
             constexpr int st = decltype(step)::value, tap = st / NT;
-            if constexpr (st == LAST + 1) lds_barrier();
+            if constexpr (st == LAST + 1) lds_only_barrier();
             read_b(st + D - 1 < NS ? cur : nxt, std::integral_constant<int, (st + D - 1) % NS>{});
             __builtin_amdgcn_sched_barrier(0);
             multiply(av[tap % G::SETS], step);
