@@ -32,6 +32,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          # packed-fp32 forms are switched off for every device function of the library
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a kernel's first arguments are in registers when it starts instead of being loaded by it: 0.7 % on average over
+         # calls of 7 to 900 us, 1 to 2.5 % on the 13-layer stack at N = 1
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-command-line-argument",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
