@@ -22,7 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libfscnn.so")
-SOURCES = ["api.hip", "compress.hip", "conv_sf.hip", "conv_si.hip", "contract.hip", "contract_split.hip", "transpose.hip"]
+SOURCES = ["api.hip", "compress.hip", "conv_sf.hip", "conv_si.hip", "contract.hip", "contract_split.hip", "pointwise.hip", "transpose.hip"]
 PROBE_LIB = os.path.join(HERE, "libfscnn_bench_probe.so")
 PROBE_SRC = os.path.join(CSRC, "bench_probe.hip")
 CALL_LIB = os.path.join(HERE, "_fscnn_call.so")

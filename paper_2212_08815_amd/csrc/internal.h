@@ -106,6 +106,7 @@ struct SfRoute {
     ContractPick pick;
     bool split = false;                    // by the contraction in bfloat16 parts, as `spick` says, once its plan is there
     ContractPick spick;
+    bool pointwise = false;                // by the kernel for 1x1 filters
 };
 
 struct SiGeom {
@@ -262,6 +263,11 @@ hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const f
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,
                                  int relu, float *y, hipStream_t st);
 
+// ---- pointwise.hip: 1x1 filters at stride 1 without padding, both tensors NCHW or both N4; no plan
+bool pointwise_serves(int N, int C, int H, int W, int K, bool n4);
+double pointwise_us(int N, int C, int H, int W, int K, bool n4, long long nnz);   // estimated time
+hipError_t launch_pointwise(const int *rowptr, const uint32_t *idx, const float *val, const float *x, int N, int C, int H, int W, int K,
+                            bool n4, const float *bias, int act, float *y, hipStream_t st);
 // ---- contract.hip: convolution as a dense contraction on the matrix cores
 // (sources and banks: dense tensor; lists with a packed bank; lists with a K x C x 3 x 3 bank)
 enum ContractForm { kContractDense, kContractLists, kContractListsRows };
