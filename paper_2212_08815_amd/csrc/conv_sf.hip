@@ -889,40 +889,57 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
     }
 }
 
-// Fallback for any stride / filter extent: one thread per output element walks its filter's
-// canonical CSR(C) row and reads the taps from global memory.  Lanes run along x.
-__global__ void __launch_bounds__(256)
+// Fallback for any stride / filter extent: the filters' canonical CSR(C) rows, taps from global memory.  Lanes run along x, a thread makes
+// PER rows of up to kDirectRows output channels one after the other: with PER = 4 an entry's place in the filter is worked out on the scalar unit
+// for 256 outputs, and their loads are in flight together.  Every output is one chain in the order of the entries.  5 -> 82 5x5 at 215x140,
+// N = 26, 4 % stored: 803 us with one output per thread (345 000 work-groups), 288 so; 10 -> 504 at 128x128, N = 1, 6 %: 193, 95.  Where there
+// are few outputs, one a thread is the faster (64 -> 64 at 7x7, N = 1: 8.7 us, 10.9 with four).
+constexpr int kDirectRows = 8;
+template <int PER> __global__ void __launch_bounds__(256)
 conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
                       const float *__restrict__ val, const float *__restrict__ x, int N, int C,
                       int H, int W, int K, int R, int S, int Ho, int Wo, int sh, int sw, int ph,
-                      int pw, const float *__restrict__ bias, int relu, float *__restrict__ y)
+                      int pw, const float *__restrict__ bias, int relu, float *__restrict__ y, int kper)
 {
-    const int bx = (Wo + 63) / 64, by = (Ho + 3) / 4;
-    long long b = blockIdx.x;
-    const int ox = (int)(b % bx) * 64 + (threadIdx.x & 63);
+    const int bx = (Wo + 63) / 64, by = (Ho + 4 * PER - 1) / (4 * PER), bk = (K + kper - 1) / kper;
+    int b = blockIdx.x;
+    const int ox = b % bx * 64 + (threadIdx.x & 63);
     b /= bx;
-    const int oy = (int)(b % by) * 4 + (threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), oy0 = (b % by * 4 + wave) * PER;
     b /= by;
-    const int k = (int)(b % K);
-    const int n = (int)(b / K);
-    if (ox >= Wo || oy >= Ho) return;
+    const int k0 = b % bk * kper, n = b / bk;
     const float *xn = x + (long long)n * C * H * W;
-    const int RS = R * S;
-    float acc = 0.0f;
-    const int lo = rowptr[k], hi = rowptr[k + 1];
-    for (int i = lo; i < hi; ++i) {
-        const uint32_t f = idx[i];
-        const int c = (int)(f / RS);
-        const int rs = (int)(f % RS);
-        const int r = rs / S, s = rs % S;
-        const int iy = oy * sh - ph + r;
-        const int ix = ox * sw - pw + s;
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-            acc = __builtin_fmaf(val[i], xn[((long long)c * H + iy) * W + ix], acc);
+    const uint32_t RS = (uint32_t)(R * S);
+    for (int k = k0; k < k0 + kper && k < K; ++k) {
+        float acc[PER] = {};
+        const int lo = rowptr[k], hi = rowptr[k + 1];
+        for (int i = lo; i < hi; ++i) {
+            const uint32_t f = idx[i], c = f / RS, rs = f % RS;
+            const float w = val[i];
+            const int ix = ox * sw - pw + (int)(rs % (uint32_t)S), iy0 = oy0 * sh - ph + (int)(rs / (uint32_t)S);
+            const float *xc = xn + (long long)c * H * W;
+            const bool in_x = ix >= 0 && ix < W;
+            float v[PER];
+            bool ok[PER];
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int iy = iy0 + q * sh;
+                ok[q] = in_x && iy >= 0 && iy < H;
+                // (a tap outside the image is read somewhere inside it and not taken)
+                v[q] = xc[ok[q] ? (long long)iy * W + ix : 0];
+            }
+#pragma unroll
+            for (int q = 0; q < PER; ++q) acc[q] = ok[q] ? __builtin_fmaf(w, v[q], acc[q]) : acc[q];
+        }
+        const float bk0 = bias ? bias[k] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (ox < Wo && oy0 + q < Ho) {
+                float r = acc[q];
+                if (bias) r += bk0;
+                y[(((long long)n * K + k) * Ho + oy0 + q) * Wo + ox] = act_apply(r, relu);
+            }
     }
-    if (bias) acc += bias[k];
-    acc = act_apply(acc, relu);
-    y[(((long long)n * K + k) * Ho + oy) * Wo + ox] = acc;
 }
 
 // The sums of a channel split where a launch of its own is the faster way (split_by_launch): a wave adds up, in
@@ -1501,10 +1518,21 @@ hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const f
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,
                                  int relu, float *y, hipStream_t st)
 {
-    const long long nblk = (long long)((Wo + 63) / 64) * ((Ho + 3) / 4) * N * K;
+    // four rows a thread from 4096 waves of one on, where the rows are not mostly padding; then output channels a work-group: as many
+    // as leave 16 work-groups a CU
+    const long long columns = (long long)((Wo + 63) / 64) * N;
+    const int per = Ho > 8 && columns * K * ((Ho + 3) / 4) * 4 >= 4096 ? 4 : 1;
+    const long long tiles = columns * ((Ho + 4 * per - 1) / (4 * per));
+    int kper = 1;
+    while (per > 1 && kper < kDirectRows && tiles * ((K + 2 * kper - 1) / (2 * kper)) >= 4096) kper *= 2;
+    const long long nblk = tiles * ((K + kper - 1) / kper);
     if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * 256 > 0xffffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(conv_sf_direct_kernel, dim3((unsigned)nblk), dim3(256), 0, st, rowptr, idx,
-                       val, x, N, C, H, W, K, R, S, Ho, Wo, sh, sw, ph, pw, bias, relu, y);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(256), 0, st, rowptr, idx, val, x, N, C, H, W, K, R, S, Ho, Wo, sh, sw, ph, pw,
+                           bias, relu, y, kper);
+    };
+    if (per == 4) launch(conv_sf_direct_kernel<4>);
+    else launch(conv_sf_direct_kernel<1>);
     return hipGetLastError();
 }
 
