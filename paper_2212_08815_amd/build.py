@@ -79,7 +79,7 @@ def build_host_sanitized(verbose=True):
 
 def build(force=False, extra_flags=(), verbose=True):
     os.makedirs(OBJDIR, exist_ok=True)
-    headers = [os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "host_word.h"), os.path.join(CSRC, "lds_dma.h"),
+    headers = [os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "arrival.h"), os.path.join(CSRC, "host_word.h"), os.path.join(CSRC, "lds_dma.h"),
                os.path.join(ROOT, "include", "fscnn.h"),
                os.path.abspath(__file__)]
     jobs, objs = [], []

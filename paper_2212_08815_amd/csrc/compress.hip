@@ -8,9 +8,9 @@
 // (ascending flat index inside each row) and independent of thread scheduling.
 #include <stddef.h>
 
+#include "arrival.h"
 #include "host_word.h"
 #include "internal.h"
-#include "lds_dma.h"
 
 namespace fscnn {
 
@@ -23,31 +23,23 @@ __device__ inline int lane_id() { return threadIdx.x & 63; }
 // Stores that reach the memory that the XCDs' caches do not keep apart, and the last of a launch's work-groups to have made its own telling the
 // host so: every stream finds them from there on.  (A wait for the stream is over 4 to 8 us later.)  The counter is left at zero.
 template <class T> __device__ inline void store_through(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// (Arrivals at one address are counted one after the other, 8 ns each: 4 us of 512 work-groups.  So they meet in sixteen counters
-// a line apart, the last ones of which meet in one.)
-constexpr int kArriveWays = 16, kCounterInts = (kArriveWays + 1) * 32;
-__device__ inline bool arrive(int *counter)   // one thread, behind a barrier that all stores were waited for in front of
-{
-    auto count = [](int *c, int all) {
-        if (__hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != all - 1) return false;
-        __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return true;
-    };
-    const int groups = (int)gridDim.x, way = (int)blockIdx.x % kArriveWays;
-    if (!count(counter + (way + 1) * 32, (groups - way + kArriveWays - 1) / kArriveWays) ||
-        !count(counter, groups < kArriveWays ? groups : kArriveWays)) return false;
-    wait_vmcnt<0>();   // (the host may hand the slot on as soon as it is told)
-    return true;
-}
+// a wait for this wave's stores that the compiler moves nothing across either
+__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+struct DeviceMem {
+    __device__ int add(int *p) const { return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ void clear(int *p) const { store_through(p, 0); }
+    __device__ void wait() const { wait_stores(); }
+};
+__device__ inline bool arrived_last(int *counter) { return arrive(DeviceMem(), counter, (int)gridDim.x, (int)blockIdx.x); }
 // a number for the host that waits for it
 __device__ inline void store_host(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 // the end of a kernel whose stores are all store_through(); counter NULL: nothing is told
 __device__ inline void tell_host(int *counter, int *host)
 {
     if (!counter) return;
-    wait_vmcnt<0>();
+    wait_stores();
     __syncthreads();
-    if (threadIdx.x == 0 && arrive(counter)) store_host(host, 0);
+    if (threadIdx.x == 0 && arrived_last(counter)) store_host(host, 0);
 }
 
 // ---- exclusive scan of n ints into out[0..n] (out[n] = total); one work-group ---------
@@ -216,8 +208,8 @@ __global__ void __launch_bounds__(kCountThreads) filter_count_kernel(const float
         int t = 0;
         for (int i = 0; i < kCountThreads / 64; ++i) t += part[i];
         store_through(cnt + blockIdx.x, t);
-        wait_vmcnt<0>();
-        last = counter && arrive(counter);
+        wait_stores();
+        last = counter && arrived_last(counter);
     }
     __syncthreads();
     if (!last) return;
