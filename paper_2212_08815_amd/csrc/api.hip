@@ -651,6 +651,7 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     if (e == hipSuccess) cnt = f->rowptr + (K + 1);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, f->rowptr, word.slot(), word.hand_out(), st);
     if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total);
+    if (e == hipSuccess && total < 0) e = hipErrorUnknown;
     if (e == hipSuccess) {
         f->nnz = total;
         const size_t n = total > 0 ? (size_t)total : 1;
@@ -1131,6 +1132,7 @@ static fscnn_status_t compress_activations(const float *x_dev, int N, int C, int
         if (e == hipSuccess && whole) e = fill(base + nodes_at, most);
     }
     if (e == hipSuccess) e = word.wait(scratch + input_groups(npix, NCH), st, &total);
+    if (e == hipSuccess && total < 0) e = hipErrorUnknown;
     if (e == hipSuccess) {
         in->nnz = total;
         if (whole) {

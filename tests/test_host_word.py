@@ -50,3 +50,23 @@ def test_words_that_may_be_written_are_not_reused(tmp_path, refuse):
                     "-I", os.path.join(ROOT, "paper_2212_08815_amd", "csrc"), str(src), "-o", str(exe), "-lpthread"], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+UNWRITTEN = PROGRAM[:PROGRAM.index("int main()")] + r"""
+int main()
+{
+    int out = 0, on_device = 7, *p = nullptr;
+    { HostWord w; p = w.hand_out(); CHECK(w.wait(&on_device, nullptr, &out) == hipSuccess && out < 0); }     // the stream ended, nothing was written
+    { HostWord w; CHECK(w.hand_out() != p); *w.hand_out() = 3; CHECK(w.wait(&on_device, nullptr, &out) == hipSuccess && out == 3); }
+    return 0;
+}
+"""
+
+
+def test_a_word_that_nothing_wrote_is_no_number_and_not_reused(tmp_path):
+    src, exe = tmp_path / "unwritten.cpp", tmp_path / "unwritten"
+    src.write_text(UNWRITTEN.replace("REFUSE", "false"))
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    "-I", os.path.join(ROOT, "paper_2212_08815_amd", "csrc"), str(src), "-o", str(exe), "-lpthread"], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
