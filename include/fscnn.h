@@ -176,8 +176,8 @@ fscnn_status_t fscnn_sf_band_choice(int variant, int N, int Ho, int n4, int pool
 
 /* How the automatic choice (variant 0, NCHW tensors, no pool) serves a call by the dense contraction on
  * the matrix cores, where fscnn_sf_split_choice below says -1: *tile_out receives the number (0..7) of its tile, or -1 where the
- * configuration of fscnn_sf_variant_choice (or the direct kernel) serves the call, *panels_out the panels the image's
- * columns are divided into.  Host-only: launches nothing and needs no device. */
+ * configuration of fscnn_sf_variant_choice (or the direct kernel, or the one for 1x1 filters: fscnn_sf_serves) serves the call,
+ * *panels_out the panels the image's columns are divided into.  Host-only: launches nothing and needs no device. */
 fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h,
                                         int stride_w, int pad_h, int pad_w, int *tile_out,
                                         int *panels_out);
@@ -186,9 +186,23 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
  * two floats is held to 2^-26 of it, whatever their magnitudes, and sums are rounded as in fp32): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
  * does.  *parts_out (may be NULL): the work-groups per tile that the input channels are divided over; more than one need scratch as
  * the channel-split mode does (fscnn_filter_prepare_ex), and without it one serves the tile.  Calls that read N4 tensors or pool
- * are served so by the same rule (3x3; fscnn_sf_variant_choice then names what would serve them otherwise).  Host-only. */
+ * are served so by the same rule (3x3; fscnn_sf_serves says where, fscnn_sf_variant_choice what would serve them otherwise).  Host-only. */
 fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int stride_h, int stride_w,
                                      int pad_h, int pad_w, int *tile_out, int *panels_out, int *parts_out);
+
+/* Which kernel serves an automatic call (variant 0) with these layouts and this pool flag: the direct one, the configuration of
+ * fscnn_sf_variant_choice, the contraction in fp32 or in bfloat16 parts (once its dense copy of the bank is there, see
+ * fscnn_filter_prepare_ex), or the one for 1x1 filters at stride 1 without padding, which needs no plan.  An emitting call is
+ * never served by the last one.  FSCNN_ERR_UNSUPPORTED where such a call is refused.  Host-only. */
+enum {
+    FSCNN_SERVES_DIRECT = 0,
+    FSCNN_SERVES_GATHER = 1,
+    FSCNN_SERVES_CONTRACT = 2,
+    FSCNN_SERVES_SPLIT = 3,
+    FSCNN_SERVES_POINTWISE = 4
+};
+fscnn_status_t fscnn_sf_serves(fscnn_filter_t *f, int N, int H, int W, int stride_h, int stride_w, int pad_h, int pad_w,
+                               fscnn_layout_t x_layout, fscnn_layout_t y_layout, int pool, int *serves_out);
 
 /* The same as fscnn_sf_contract_choice for a compressed N x C x H x W activation and K filters of 3x3 at stride 1: from *from_out stored
  * values on the contraction serves the call, where fscnn_si_split_choice below does not say otherwise (prepared: fscnn_conv2d_sparse_input_prepared, else

@@ -878,6 +878,29 @@ fscnn_status_t fscnn_sf_split_choice(fscnn_filter_t *f, int N, int H, int W, int
     return FSCNN_OK;
 }
 
+fscnn_status_t fscnn_sf_serves(fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int ph, int pw, fscnn_layout_t x_layout,
+                               fscnn_layout_t y_layout, int pool, int *serves_out)
+{
+    if (!f || !serves_out) return FSCNN_ERR_NULL;
+    if (!live(f)) return FSCNN_ERR_HANDLE;
+    if (N <= 0) return FSCNN_ERR_SHAPE;
+    if ((x_layout != FSCNN_LAYOUT_NCHW && x_layout != FSCNN_LAYOUT_N4) || (y_layout != FSCNN_LAYOUT_NCHW && y_layout != FSCNN_LAYOUT_N4))
+        return FSCNN_ERR_UNSUPPORTED;
+    int Ho, Wo;
+    fscnn_status_t s = out_shape(H, W, f->R, f->S, sh, sw, ph, pw, &Ho, &Wo);
+    if (s != FSCNN_OK) return s;
+    if (pool && (Ho < 2 || Wo < 2)) return FSCNN_ERR_SHAPE;
+    const int in4 = x_layout == FSCNN_LAYOUT_N4, out4 = y_layout == FSCNN_LAYOUT_N4;
+    SfRoute r;
+    s = route_call(f, N, H, W, sh, sw, pw, Ho, Wo, in4, out4, pool, 0, false, &r);
+    if (s != FSCNN_OK) return s;
+    if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
+    if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
+    *serves_out = r.pointwise ? FSCNN_SERVES_POINTWISE : r.split ? FSCNN_SERVES_SPLIT : r.contract ? FSCNN_SERVES_CONTRACT
+                  : r.variant > 0 ? FSCNN_SERVES_GATHER : FSCNN_SERVES_DIRECT;
+    return FSCNN_OK;
+}
+
 fscnn_status_t fscnn_si_contract_choice(int N, int C, int H, int W, int K, int ph, int pw, int prepared, long long *from_out,
                                         int *tile_out, int *panels_out)
 {

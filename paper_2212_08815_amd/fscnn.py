@@ -35,7 +35,7 @@ EXPORTS = [
     "fscnn_sparse_transpose", "fscnn_sparse_tensor_transpose", "fscnn_sparse_transpose_workspace",
     "fscnn_dense_filter_prepare", "fscnn_dense_filter_destroy", "fscnn_conv2d_sparse_input_prepared",
     "fscnn_si_variant_count", "fscnn_conv2d_sparse_filter_leaky", "fscnn_sparse_transpose_noalloc",
-    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_sf_split_choice", "fscnn_si_contract_choice", "fscnn_si_split_choice", "fscnn_pool_trim",
+    "fscnn_filter_prepare_ex", "fscnn_sf_band_choice", "fscnn_sf_contract_choice", "fscnn_sf_split_choice", "fscnn_sf_serves", "fscnn_si_contract_choice", "fscnn_si_split_choice", "fscnn_pool_trim",
 ]
 
 NCHW, N4 = 0, 1      # fscnn_layout_t
@@ -175,6 +175,17 @@ def sf_split_parts(f, N, H, W, stride=(1, 1), pad=(0, 0)):
     _check(lib().fscnn_sf_split_choice(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]),
                                        ctypes.byref(t), ctypes.byref(p), ctypes.byref(q)), "fscnn_sf_split_choice")
     return q.value
+
+
+DIRECT, GATHER, CONTRACT, SPLIT, POINTWISE = range(5)      # FSCNN_SERVES_*
+
+
+def sf_serves(f, N, H, W, stride=(1, 1), pad=(0, 0), x_layout=NCHW, y_layout=NCHW, pool=False):
+    """fscnn_sf_serves -> DIRECT, GATHER, CONTRACT, SPLIT or POINTWISE: the kernel that serves such a call with variant 0."""
+    s = ctypes.c_int()
+    _check(lib().fscnn_sf_serves(f.handle, _i(N), _i(H), _i(W), _i(stride[0]), _i(stride[1]), _i(pad[0]), _i(pad[1]), _i(x_layout), _i(y_layout),
+                                 _i(1 if pool else 0), ctypes.byref(s)), "fscnn_sf_serves")
+    return s.value
 
 
 def si_contract_choice(N, C, H, W, K, pad=(0, 0), prepared=False):

@@ -27,11 +27,13 @@ def test_rows(F, n, c, k, h, w, r, s, pad):
     dev = lambda a: torch.from_numpy(a).cuda()
     want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), s, pad)
     f = F.filter_compress(dev(wt))
-    assert F.sf_split_choice(f, n, h, w, (s, s), (pad, pad))[0] == F.sf_contract_choice(f, n, h, w, (s, s), (pad, pad))[0] == -1
+    assert F.sf_serves(f, n, h, w, (s, s), (pad, pad)) == F.DIRECT
     assert torch.equal(F.conv2d_sparse_filter(f, dev(x), (s, s), (pad, pad), dev(b), True).cpu(), want.relu())
     if pad:
         wt[3] = 0.0
         wt[3, 0, 0, 0] = np.inf                    # meets x at (oy*s - pad, ox*s - pad)
-        got = F.conv2d_sparse_filter(F.filter_compress(dev(wt)), dev(x), (s, s), (pad, pad)).cpu()[:, 3]
+        f = F.filter_compress(dev(wt))
+        assert F.sf_serves(f, n, h, w, (s, s), (pad, pad)) == F.DIRECT
+        got = F.conv2d_sparse_filter(f, dev(x), (s, s), (pad, pad)).cpu()[:, 3]
         first = -(-pad // s)
         assert (got[:, :first] == 0).all() and (got[:, :, :first] == 0).all() and torch.isinf(got[:, first:, first:]).all()

@@ -30,6 +30,11 @@ def call(F, f, x, n4, bias=None, relu=False, leaky=None):
     return F.layout_convert(y, F.N4, n=x.shape[0])
 
 
+def served(F, f, n, h, w, n4):
+    lay = F.N4 if n4 else F.NCHW
+    return F.sf_serves(f, n, h, w, x_layout=lay, y_layout=lay) == F.POINTWISE
+
+
 def bank(k, c, integer, seed=0):
     """Filters of 0, 1, 2, ... entries."""
     rng = np.random.default_rng(seed + k + c)
@@ -48,6 +53,8 @@ def test_sizes(F, n, c, k, h, w, n4):
     b = np.arange(k, dtype=np.float32) % 5 - 2
     wt = bank(k, c, True)
     f, xd, bd = F.filter_compress(dev(wt)), dev(x), dev(b)
+    # (fewer than four pixels are not its own; the largest through N4 tensors is gathered)
+    assert served(F, f, n, h, w, n4) == (h * w * (4 if n4 else 1) >= 4 and not (n4 and h == 31))
     want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt))
     assert torch.equal(call(F, f, xd, n4).cpu(), want)
     want = want + torch.from_numpy(b).view(1, k, 1, 1)
@@ -60,7 +67,9 @@ def test_precision(F):
     n, c, k, h, w = 2, 120, 70, 20, 21
     x, wt = np.abs(inputs.random_layer(1, n, c, k, h, w, 1, 1, 1.0)[0]), np.abs(bank(k, c, False))
     want = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(wt).double())
-    got = call(F, F.filter_compress(dev(wt)), dev(x), False).cpu().double()
+    f = F.filter_compress(dev(wt))
+    assert served(F, f, n, h, w, False)
+    got = call(F, f, dev(x), False).cpu().double()
     bound = torch.from_numpy((np.count_nonzero(wt, axis=(1, 2, 3)) + 3) * 2.0 ** -24).view(1, k, 1, 1)
     assert ((got - want).abs() <= bound * want).all()
 
@@ -71,7 +80,9 @@ def test_values_that_are_not_finite(F):
     wt = bank(64, 64, True)
     want = np.einsum("kc,chw->khw", wt[:, :, 0, 0], np.where(np.isfinite(x[0]), x[0], 0))
     met = np.einsum("kc,chw->khw", wt[:, :, 0, 0] != 0, ~np.isfinite(x[0])) > 0
-    got = call(F, F.filter_compress(dev(wt)), dev(x), False)[0].cpu().numpy()
+    f = F.filter_compress(dev(wt))
+    assert served(F, f, 1, 12, 12, False)
+    got = call(F, f, dev(x), False)[0].cpu().numpy()
     assert np.array_equal(np.isfinite(got), ~met) and np.array_equal(got[~met], want[~met]) and met.any()
 
 
@@ -82,7 +93,7 @@ def test_captured_without_a_plan(F, n4):
     wt = bank(128, 256, True)
     want = torch.nn.functional.conv2d(x.cpu(), torch.from_numpy(wt))
     f, xx, lay = F.filter_compress(dev(wt)), F.layout_convert(x, F.NCHW) if n4 else x, F.N4 if n4 else F.NCHW
-    assert F.sf_variant_choice(f, 4, 22, 22, n4=n4) > 0 and F.sf_contract_choice(f, 4, 22, 22)[0] == -1
+    assert F.sf_variant_choice(f, 4, 22, 22, n4=n4) > 0 and served(F, f, 4, 22, 22, n4)
     y = torch.zeros(F.n4_shape(4, 128, 22, 22) if n4 else want.shape, device="cuda")
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()

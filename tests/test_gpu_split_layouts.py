@@ -38,6 +38,11 @@ def gathered(F, f, x, n4, pool, s):
     return F.sf_variant_choice(f, x.shape[0], x.shape[2], x.shape[3], (s, s), n4, pool)
 
 
+def parts(F, f, x, n4, out4, pool, s):
+    n, _, h, w = x.shape
+    return F.sf_serves(f, n, h, w, (s, s), (1, 1), F.N4 if n4 else F.NCHW, F.N4 if out4 else F.NCHW, pool) == F.SPLIT
+
+
 CASES = [   # n, c, k, h, w, stride, N4 in, N4 out, pool
     (18, 512, 1024, 4, 4, 1, True, True, False), (5, 256, 130, 8, 8, 1, True, True, False), (8, 128, 96, 28, 28, 1, True, True, False),
     (6, 130, 70, 17, 19, 1, True, True, False), (9, 100, 65, 30, 3, 1, True, False, False), (4, 512, 96, 7, 1, 1, True, True, False),
@@ -57,6 +62,7 @@ def test_layouts_and_pool(F, n, c, k, h, w, s, n4, out4, pool):
     want = torch.nn.functional.conv2d(torch.from_numpy(x), torch.from_numpy(wt), torch.from_numpy(b), s, 1)
     want = (torch.nn.functional.max_pool2d(want, 2) if pool else want).relu_()
     f = F.filter_compress(dev(wt))
+    assert parts(F, f, x, n4, out4, pool, s)
     assert torch.equal(call(F, f, dev(x), n4, out4, pool, s, dev(b), True).cpu(), want)
     # values of any size: not the gather kernel's sums, and within fp32's bound of the exact ones
     x, wt, b = inputs.random_layer(n + c + k, n, c, k, h, w, 3, 3, 1.0)
@@ -83,7 +89,9 @@ def test_values_that_are_not_finite(F, n4, pool, n, c, k, h, w):
     if pool:
         want, met = torch.nn.functional.max_pool2d(want, 2), torch.nn.functional.max_pool2d(met, 2)
     met = met > 0
-    got = call(F, F.filter_compress(dev(wt)), dev(x), n4, n4, pool, 1, dev(b)).cpu()
+    f = F.filter_compress(dev(wt))
+    assert parts(F, f, x, n4, n4, pool, 1)
+    got = call(F, f, dev(x), n4, n4, pool, 1, dev(b)).cpu()
     assert torch.equal(got[~met], want[~met]) and 0 < met.sum() < met.numel()
     if not pool:                       # (a maximum over a unit with -Inf or NaN may be one of the others)
         assert torch.equal(torch.isfinite(got), ~met)
@@ -96,6 +104,7 @@ def test_images_past_the_last_one(F):
     f, x4 = F.filter_compress(dev(wt)), F.layout_convert(dev(x), F.NCHW)
     x4[1, :, :, :, 2:] = float("nan")
     for out4 in (True, False):
+        assert parts(F, f, x, True, out4, False, 1)
         y = F.conv2d_sparse_filter(f, x4, (1, 1), (1, 1), dev(b), False, x_layout=F.N4, y_layout=F.N4 if out4 else F.NCHW, n=6)
         assert torch.equal((F.layout_convert(y, F.N4, n=6) if out4 else y).cpu(), want)
 
@@ -110,6 +119,7 @@ def test_captured_with_and_without_its_plan(F, n4, pool):
     xd, bd = F.layout_convert(dev(x), F.NCHW) if n4 else dev(x), dev(b)
     for prepared in (True, False):
         f = F.filter_compress(dev(wt))
+        assert parts(F, f, x, n4, n4, pool, 1)
         v = 0 if prepared else F.sf_variant_choice(f, n, h, w, n4=n4, pool=pool)
         F.filter_prepare(f, n, h, w, (1, 1), (1, 1), v, lay, lay, pool)
         run = lambda out=None: F.conv2d_sparse_filter(f, xd, (1, 1), (1, 1), bd, x_layout=lay, y_layout=lay, n=n, pool=pool, out=out)

@@ -101,6 +101,8 @@ def test_argument_checks_come_before_device_work(L):
     assert L.fscnn_sf_variant_choice(None, 1, 4, 4, 1, 1, 0, 0, ctypes.byref(v)) == 1
     assert L.fscnn_sf_variant_choice(ctypes.byref(junk), 1, 4, 4, 1, 1, 0, 0, None) == 1
     assert L.fscnn_sf_variant_choice(ctypes.byref(junk), 1, 4, 4, 1, 1, 0, 0, ctypes.byref(v)) == 7
+    assert L.fscnn_sf_serves(None, 1, 4, 4, 1, 1, 0, 0, 0, 0, 0, ctypes.byref(v)) == L.fscnn_sf_serves(ctypes.byref(junk), 1, 4, 4, 1, 1, 0, 0, 0, 0, 0, None) == 1
+    assert L.fscnn_sf_serves(ctypes.byref(junk), 1, 4, 4, 1, 1, 0, 0, 0, 0, 0, ctypes.byref(v)) == 7
 
 
 def test_argument_checks_of_the_remaining_entry_points(L):
