@@ -893,9 +893,11 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
 // PER rows of up to kDirectRows output channels one after the other: with PER = 4 an entry's place in the filter is worked out on the scalar unit
 // for 256 outputs, and their loads are in flight together.  Every output is one chain in the order of the entries.  5 -> 82 5x5 at 215x140,
 // N = 26, 4 % stored: 803 us with one output per thread (345 000 work-groups), 288 so; 10 -> 504 at 128x128, N = 1, 6 %: 193, 95.  Where there
-// are few outputs, one a thread is the faster (64 -> 64 at 7x7, N = 1: 8.7 us, 10.9 with four).
+// are few outputs, one a thread is the faster (64 -> 64 at 7x7, N = 1: 7.7 us, 10.9 with four).  SKIP: one output a thread, and a lane whose
+// tap lies outside the image skips it: the faster way where many waves of few rows fill the CUs (200 -> 512 at 7x7, N = 2: 19.7 us, 18.8 so;
+// 31 -> 136 at 13x11, stride 2, N = 24: 20.4, 18.3) and the slower one where a wave's chain of entries is all there is (64 -> 64: 8.7).
 constexpr int kDirectRows = 8;
-template <int PER> __global__ void __launch_bounds__(256)
+template <int PER, bool SKIP> __global__ void __launch_bounds__(256)
 conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
                       const float *__restrict__ val, const float *__restrict__ x, int N, int C,
                       int H, int W, int K, int R, int S, int Ho, int Wo, int sh, int sw, int ph,
@@ -905,11 +907,25 @@ conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict
     int b = blockIdx.x;
     const int ox = b % bx * 64 + (threadIdx.x & 63);
     b /= bx;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), oy0 = (b % by * 4 + wave) * PER;
+    const int first = b % by * 4, oy0 = (first + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * PER;
     b /= by;
     const int k0 = b % bk * kper, n = b / bk;
     const float *xn = x + (long long)n * C * H * W;
     const uint32_t RS = (uint32_t)(R * S);
+    if constexpr (SKIP) {
+        const int oy = first + (int)(threadIdx.x >> 6);
+        if (ox >= Wo || oy >= Ho) return;
+        float acc = 0.0f;
+        const int lo = rowptr[k0], hi = rowptr[k0 + 1];
+        for (int i = lo; i < hi; ++i) {
+            const uint32_t f = idx[i];
+            const int c = (int)(f / RS), rs = (int)(f % RS), iy = oy * sh - ph + rs / S, ix = ox * sw - pw + rs % S;
+            if (iy >= 0 && iy < H && ix >= 0 && ix < W) acc = __builtin_fmaf(val[i], xn[((long long)c * H + iy) * W + ix], acc);
+        }
+        if (bias) acc += bias[k0];
+        y[(((long long)n * K + k0) * Ho + oy) * Wo + ox] = act_apply(acc, relu);
+        return;
+    }
     for (int k = k0; k < k0 + kper && k < K; ++k) {
         float acc[PER] = {};
         const int lo = rowptr[k], hi = rowptr[k + 1];
@@ -1505,6 +1521,24 @@ int sf_choose_csplit(int variant, int N, int C, int K, int Ho, int Wo, double de
     return s;
 }
 
+// The direct kernel's work: four rows a thread from 4096 waves of one on, where the rows are not mostly padding; then output channels a
+// work-group: as many as leave 16 work-groups a CU
+struct DirectShape {
+    int per, kper = 1;
+    bool skip;                       // (of one row a thread)
+    long long groups;
+    DirectShape(int N, int K, int Ho, int Wo)
+    {
+        const long long columns = (long long)((Wo + 63) / 64) * N;
+        const bool many = columns * K * ((Ho + 3) / 4) * 4 >= 4096;
+        per = Ho > 8 && many ? 4 : 1;
+        skip = per == 1 && many;
+        const long long tiles = columns * ((Ho + 4 * per - 1) / (4 * per));
+        while (per > 1 && kper < kDirectRows && tiles * ((K + 2 * kper - 1) / (2 * kper)) >= 4096) kper *= 2;
+        groups = tiles * ((K + kper - 1) / kper);
+    }
+};
+
 // A thread of the direct kernel walks its filter's entries, a wave 64 columns of a row: measured over 65 layers of 5x5
 // and 7x7 filters, 41 us to 10 ms, within 7 %.
 double sf_direct_us(int N, int K, int Ho, int Wo, long long nnz)
@@ -1518,21 +1552,16 @@ hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const f
                                  int Ho, int Wo, int sh, int sw, int ph, int pw, const float *bias,
                                  int relu, float *y, hipStream_t st)
 {
-    // four rows a thread from 4096 waves of one on, where the rows are not mostly padding; then output channels a work-group: as many
-    // as leave 16 work-groups a CU
-    const long long columns = (long long)((Wo + 63) / 64) * N;
-    const int per = Ho > 8 && columns * K * ((Ho + 3) / 4) * 4 >= 4096 ? 4 : 1;
-    const long long tiles = columns * ((Ho + 4 * per - 1) / (4 * per));
-    int kper = 1;
-    while (per > 1 && kper < kDirectRows && tiles * ((K + 2 * kper - 1) / (2 * kper)) >= 4096) kper *= 2;
-    const long long nblk = tiles * ((K + kper - 1) / kper);
+    const DirectShape d(N, K, Ho, Wo);
+    const long long nblk = d.groups;
     if (nblk <= 0 || nblk > 0x7fffffffLL || nblk * 256 > 0xffffffffLL) return hipErrorInvalidValue;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(256), 0, st, rowptr, idx, val, x, N, C, H, W, K, R, S, Ho, Wo, sh, sw, ph, pw,
-                           bias, relu, y, kper);
+                           bias, relu, y, d.kper);
     };
-    if (per == 4) launch(conv_sf_direct_kernel<4>);
-    else launch(conv_sf_direct_kernel<1>);
+    if (d.per == 4) launch(conv_sf_direct_kernel<4, false>);
+    else if (d.skip) launch(conv_sf_direct_kernel<1, true>);
+    else launch(conv_sf_direct_kernel<1, false>);
     return hipGetLastError();
 }
 
