@@ -420,6 +420,19 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
     return FSCNN_OK;
 }
 
+// What the direct kernel takes, for the choice between it and the contractions.  Up to 12 entries a filter, and below 16 where up to 8 channels
+// leave the contraction in fp32 one chain as well, its sums are as exact as that one's (2-norm against 64 bits 0.95 to 1.02 times, the mean of
+// each of a dozen groups of 105 random layers of 3x3 to 7x7) and its time decides (1 -> 300 at 14x9, stride 3, N = 2: 9.2 us contracted, 6.8
+// direct; 40 -> 300 5x5 at 16x16, N = 1, 1 % stored: 13.8, 10.1).  Beyond, its chains of roundings show (1.05 to 1.9 times the error of the contraction in
+// fp32, 2 to 4 times that of the one in parts): there the contractions serve what was faster so than with one row a thread, though four
+// rows a thread take about half of that (21 -> 38 5x5 at 184x189, N = 30, 3 %: estimated 500 us, 640 in parts).
+double direct_us(const fscnn_filter_t *f, int N, int Ho, int Wo)
+{
+    if (f->R * f->S >= 9 && f->nnz <= (f->C <= 8 ? 16LL * f->K - 1 : 12LL * f->K)) return sf_direct_us(N, f->K, Ho, Wo, f->nnz);
+    const double waves = (double)N * f->K * ((Wo + 63) / 64) * ((Ho + 3) / 4) * 4;
+    return 9.7 + (double)f->nnz / f->K * (0.132 + 7.48e-5 * waves);
+}
+
 // Whether an automatic call is served by the contraction on the matrix cores instead of the resolved
 // gather configuration (or the direct kernel), which takes gather_us: by their estimated times (512 -> 512 at
 // 28x28, N = 8, measured: 126 / 217 / 320 / 500 us at 10 / 20 / 30 / 50 % stored against 250 us contracted).
@@ -503,7 +516,7 @@ fscnn_status_t route_call(fscnn_filter_t *f, int N, int H, int W, int sh, int sw
     sf_choose_bands(r->variant, N, Ho, in4 || out4, pool != 0, &r->band_shift, &r->band_h);
     if (variant != 0) return FSCNN_OK;
     memcpy(r->key, key, sizeof key);
-    double us = sf_direct_us(N, f->K, Ho, Wo, f->nnz);
+    double us = direct_us(f, N, Ho, Wo);
     if (r->variant > 0)
         r->csplit = sf_choose_csplit(r->variant, N << r->band_shift, f->C, f->K, r->band_h, Wo, density(f), in4, emit, &us);
     r->contract = !in4 && !out4 && !pool && contracts(f, N, H, W, sh, sw, Ho, Wo, r->variant, us, &r->pick);

@@ -1539,12 +1539,14 @@ struct DirectShape {
     }
 };
 
-// A thread of the direct kernel walks its filter's entries, a wave 64 columns of a row: measured over 65 layers of 5x5
-// and 7x7 filters, 41 us to 10 ms, within 7 %.
+// A launch, a wave's chain of entries, the entries of all waves, what a wave starts and stores: over 650 layers of 5x5, 7x7 and 3x3 filters, strides
+// 1 to 3, 4 us to 13 ms, within 9 to 11 % (standard deviation) in each of the three forms.
 double sf_direct_us(int N, int K, int Ho, int Wo, long long nnz)
 {
-    const double waves = (double)N * K * ((Wo + 63) / 64) * ((Ho + 3) / 4) * 4;
-    return 9.7 + (double)nnz / K * (0.132 + 7.48e-5 * waves);
+    const DirectShape d(N, K, Ho, Wo);
+    const double entries = (double)nnz / K, waves = 4.0 * d.groups;
+    if (d.per == 4) return 3.9 + d.kper * (entries * (0.30 + 1.4e-4 * waves) + 2.9e-4 * waves);
+    return d.skip ? 2.9 + entries * (0.143 + 7.8e-5 * waves) + 2.6e-4 * waves : 4.0 + entries * (0.164 + 7e-5 * waves) + 4e-5 * waves;
 }
 
 hipError_t launch_conv_sf_direct(const int *rowptr, const uint32_t *idx, const float *val,
