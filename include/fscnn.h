@@ -183,7 +183,8 @@ fscnn_status_t fscnn_sf_contract_choice(fscnn_filter_t *f, int N, int H, int W, 
                                         int *panels_out);
 
 /* The same for the contraction with its operands taken apart into bfloat16 parts (3x3 and 5x5; a product of
- * two floats is held to 2^-26 of it, whatever their magnitudes, and sums are rounded as in fp32): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
+ * two floats is held to 2^-24 of it, whatever their magnitudes, root mean square 2^-27.4, and sums are rounded as in fp32 or less; banks that store
+ * 16 entries a filter on average and no filter of one to three): it serves the call with tile 0..9, or -1: it does not, and fscnn_sf_contract_choice says what
  * does.  *parts_out (may be NULL): the work-groups per tile that the input channels are divided over; more than one need scratch as
  * the channel-split mode does (fscnn_filter_prepare_ex), and without it one serves the tile.  Calls that read N4 tensors or pool
  * are served so by the same rule (3x3; fscnn_sf_serves says where, fscnn_sf_variant_choice what would serve them otherwise).  Host-only. */

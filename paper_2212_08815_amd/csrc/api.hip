@@ -455,13 +455,15 @@ bool contracts(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int
 // parts, estimated 9.2).  NCHW into N4 tensors stays gathered.  Not for filters of fewer than 16 stored entries on average: there
 // the rounding of the single products shows (2-norm against 64 bits up to 1.15 times the gather's; from 16 on it was 0.5 times
 // that of what served the call before, over 2112 random layers of zero-mean weights, and never more; 0.2 to 0.8 times where
-// activations and weights have one sign, over 40 layers).
+// activations and weights have one sign, over 40 layers).  Nor where one filter stores fewer than 4: a product of six parts is off by
+// up to 2^-24 before it is rounded, and the results of such a filter are the less exact ones (rows of 1, 2, 3, 4, 5, 8, 16 entries in banks of
+// 150 on average, 2-norm as multiples of the gather's: 1.03, 1.05, 1.01, 0.97, 0.95, 0.88, 0.7; largest error of a single entry 1.5 times).
 bool splits(const fscnn_filter_t *f, int N, int H, int W, int sh, int sw, int Ho, int Wo, int pw, bool in4, bool out4, bool pool, double other,
             bool emit, ContractPick *pick)
 {
     if (out4 && !in4) return false;
     const double dense = (double)f->K * f->C * f->R * f->S * Ho * Wo * N;
-    if (f->nnz < 16LL * f->K || 2 * dense / 350e12 + 3e-6 > other) return false;
+    if (f->nnz < 16LL * f->K || f->fewest < 4 || 2 * dense / 350e12 + 3e-6 > other) return false;
     *pick = split_pick(N, f->C, f->K, H, W, f->R, f->S, Ho, Wo, sh, sw, pw, true, in4, pool);
     return pick->cfg >= 0 && pick->seconds + (emit ? 4e-6 : in4 || pool ? 1e-6 : 0) < 0.9 * other;
 }
@@ -660,10 +662,10 @@ fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, in
     HostWord word, packed;
     // two allocations: the pointers with the counts they are scanned from, and the nodes
     hipError_t e = filter_alloc(dev, st, reinterpret_cast<void **>(&f->rowptr),
-                               sizeof(int) * (size_t)(K + 1 + K + scan_tmp_elems(K)), &f->rowptr_bytes);
-    if (e == hipSuccess) cnt = f->rowptr + (K + 1);
+                               sizeof(int) * (size_t)(K + 2 + K + scan_tmp_elems(K)), &f->rowptr_bytes);
+    if (e == hipSuccess) cnt = f->rowptr + (K + 2);
     if (e == hipSuccess) e = launch_filter_count(w_dev, K, row, cnt, f->rowptr, word.slot(), word.hand_out(), st);
-    if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total);
+    if (e == hipSuccess) e = word.wait(f->rowptr + K, st, &total, &f->fewest);
     if (e == hipSuccess && total < 0) e = hipErrorUnknown;
     if (e == hipSuccess) {
         f->nnz = total;

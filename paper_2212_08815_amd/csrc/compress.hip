@@ -33,6 +33,12 @@ struct DeviceMem {
 __device__ inline bool arrived_last(int *counter) { return arrive(DeviceMem(), counter, (int)gridDim.x, (int)blockIdx.x); }
 // a number for the host that waits for it
 __device__ inline void store_host(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// the same with the one behind it, at once: one store
+__device__ inline void store_host(int *p, int v, int second)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)(uint32_t)second << 32 | (uint32_t)v, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // the end of a kernel whose stores are all store_through(); counter NULL: nothing is told
 __device__ inline void tell_host(int *counter, int *host)
 {
@@ -48,6 +54,21 @@ __device__ inline void tell_host(int *counter, int *host)
 // (u, wave) row of 64 is scanned with lane shuffles, the 256 row totals by the first wave, two barriers
 // in all.  (A run of consecutive elements per thread and a scan of the 1024 sums with 20 barriers:
 // 6.8 us on average over the 26 scans of loading the 13-layer stack.)
+constexpr int kNoRow = 0x7fffffff;   // no row stores anything
+// the smallest over a work-group, for all of it; part: an int per wave
+template <int THREADS> __device__ inline int group_min(int v, int *part)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const int t = __shfl_xor(v, o, 64);
+        v = t < v ? t : v;
+    }
+    if (lane_id() == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < THREADS / 64; ++i) v = part[i] < v ? part[i] : v;
+    return v;
+}
 constexpr int kScanThreads = 1024, kScanPer = 16, kScanRows = kScanThreads / 64 * kScanPer;
 __device__ inline int wave_inclusive(int v)
 {
@@ -61,11 +82,11 @@ __device__ inline int wave_inclusive(int v)
 }
 __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int *__restrict__ in,
                                                                       int *__restrict__ out,
-                                                                      long long n, int *__restrict__ host)
+                                                                      long long n, int *__restrict__ host, int fewest)
 {
     __shared__ int rows[kScanRows + 1];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    int carry = 0;
+    int carry = 0, few = kNoRow;
     for (long long n0 = 0; n0 < n; n0 += kScanThreads * kScanPer) {
         int v[kScanPer], incl[kScanPer];
         const long long left = n - n0;
@@ -74,6 +95,8 @@ __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int 
             const int i = u * kScanThreads + (int)threadIdx.x;
             v[u] = i < left ? in[n0 + i] : 0;
         }
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) few = v[u] > 0 && v[u] < few ? v[u] : few;
 #pragma unroll
         for (int u = 0; u < kScanPer; ++u) {
             incl[u] = 0;
@@ -103,9 +126,31 @@ __global__ void __launch_bounds__(kScanThreads) exclusive_scan_kernel(const int 
         carry += rows[kScanRows];
         __syncthreads();   // the next round writes `rows`
     }
+    if (fewest) few = group_min<kScanThreads>(few, rows);
     if (threadIdx.x == 0) {
         out[n] = carry;
-        if (host) store_host(host, carry);
+        if (fewest) out[n + 1] = few;
+        if (host && fewest) store_host(host, carry, few);
+        else if (host) store_host(host, carry);
+    }
+}
+
+// the smallest of in[] above 0, where no work-group that scans sees all of it
+__global__ void __launch_bounds__(kScanThreads) scan_fewest_kernel(const int *__restrict__ in, long long n, int *__restrict__ out, int *__restrict__ host)
+{
+    __shared__ int part[kScanThreads / 64];
+    int few = kNoRow;
+    for (long long n0 = threadIdx.x; n0 < n; n0 += kScanThreads * kScanPer) {
+        int v[kScanPer];
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) v[u] = n0 + u * kScanThreads < n ? in[n0 + u * kScanThreads] : 0;
+#pragma unroll
+        for (int u = 0; u < kScanPer; ++u) few = v[u] > 0 && v[u] < few ? v[u] : few;
+    }
+    few = group_min<kScanThreads>(few, part);
+    if (threadIdx.x == 0) {
+        *out = few;
+        if (host) store_host(host, few);
     }
 }
 
@@ -184,7 +229,7 @@ __device__ int g_count_slots[HostWord::kWords * kCounterInts];
 constexpr int kCountScan = 4096;   // rows that one work-group scans
 
 // ---- A1: per output channel, the number of entries with w != 0 ------------------------
-// With a counter the work-group that finishes last scans the counts as well (rowptr, and the total for the host): the scan as a launch of
+// With a counter the work-group that finishes last scans the counts as well (rowptr, and the total and the fewest for the host): the scan as a launch of
 // its own was 3.4 us and the gap in front of it.
 // (a 512 x 3 x 3 row is one round: the bank's 9.4 MB, counted and scanned, take 13.9 us in two rounds of 256 threads with one counter, 8.6 so)
 constexpr int kCountThreads = 512, kCountPer = 9;
@@ -214,10 +259,11 @@ __global__ void __launch_bounds__(kCountThreads) filter_count_kernel(const float
     __syncthreads();
     if (!last) return;
     const int K = (int)gridDim.x, wave = threadIdx.x >> 6;
-    int carry = 0;
+    int carry = 0, few = kNoRow;
     for (int k0 = 0; k0 < K; k0 += kCountThreads) {
         const int k = k0 + (int)threadIdx.x;
         const int v = k < K ? __hip_atomic_load(cnt + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        few = v > 0 && v < few ? v : few;
         const int incl = wave_inclusive(v);
         if (lane_id() == 63) part[wave] = incl;
         __syncthreads();
@@ -230,9 +276,11 @@ __global__ void __launch_bounds__(kCountThreads) filter_count_kernel(const float
         if (k < K) rowptr[k] = before + incl - v;
         __syncthreads();   // the next round writes `part`
     }
+    few = group_min<kCountThreads>(few, part);
     if (threadIdx.x == 0) {
         rowptr[K] = carry;
-        if (host) store_host(host, carry);
+        rowptr[K + 1] = few;
+        if (host) store_host(host, carry, few);
     }
 }
 
@@ -680,16 +728,17 @@ long long scan_tmp_elems(long long n)
     return n <= 4 * kTile ? 0 : 2 * ((n + kTile - 1) / kTile) + 2;
 }
 
-hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, hipStream_t st)
+hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, bool fewest, hipStream_t st)
 {
     if (n <= 4 * kTile) {
-        hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, in, out, n, host);
+        hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, in, out, n, host, fewest ? 1 : 0);
         return hipGetLastError();
     }
     const long long nt = (n + kTile - 1) / kTile;
     int *tsum = tmp, *toff = tmp + nt;   // toff has nt + 1 entries
     hipLaunchKernelGGL(scan_tile_sum_kernel, dim3((unsigned)nt), dim3(kTileThreads), 0, st, in, n, tsum);
-    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, tsum, toff, nt, host);
+    if (fewest) hipLaunchKernelGGL(scan_fewest_kernel, dim3(1), dim3(kScanThreads), 0, st, in, n, out + n + 1, host ? host + 1 : nullptr);
+    hipLaunchKernelGGL(exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, tsum, toff, nt, host, 0);
     hipLaunchKernelGGL(scan_tile_kernel, dim3((unsigned)nt), dim3(kTileThreads), 0, st, in, n, toff, out);
     return hipGetLastError();
 }
@@ -701,7 +750,7 @@ hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, i
     if (ce != hipSuccess) return ce;
     hipLaunchKernelGGL(filter_count_kernel, dim3(K), dim3(kCountThreads), 0, st, w, row, cnt, rowptr, counter, host);
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess || counter ? e : launch_exclusive_scan(cnt, rowptr, K, cnt + K, host, st);
+    return e != hipSuccess || counter ? e : launch_exclusive_scan(cnt, rowptr, K, cnt + K, host, true, st);
 }
 
 hipError_t launch_filter_pack(const float *w, int K, long long row, const int *rowptr,
@@ -785,7 +834,7 @@ hipError_t launch_input_sums(const float *x, const int *cnt, int N, int C, int H
     else
         hipLaunchKernelGGL(input_sum_kernel<256>, dim3((unsigned)g), dim3(256), 0, st, x, cnt, C, HW, npix, NCH, PX, scratch + g + 1);
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess || !scan ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, st);
+    return e != hipSuccess || !scan ? e : launch_exclusive_scan(scratch + g + 1, scratch, g, scratch + 2 * g + 1, host, false, st);
 }
 
 hipError_t launch_input_fill(const float *x, int N, int C, int H, int W, int NCH, int *scratch, bool scanned, int *cptr,

@@ -2,14 +2,15 @@
 //
 // A float is the exact sum of three bfloat16 numbers (8 + 8 + 8 bits, each part the previous remainder rounded
 // to nearest; operands are multiplied by 2^16 first, so that subnormal ones have their parts too), and a product of two
-// floats is, up to 2^-26 of it, the six products of parts h*h, h*m, m*h, m*m, h*l, l*h.  v_mfma_f32_32x32x16_bf16
+// floats is, up to 2^-24 of it (root mean square 2^-27.4), the six products of parts h*h, h*m, m*h, m*m, h*l, l*h.  v_mfma_f32_32x32x16_bf16
 // multiplies at 2.1 PFLOP/s on this chip (registers only), so six of them make 350 TFLOP/s of fp32-like
 // products where v_mfma_f32_16x16x4_f32 (contract.hip) makes 154.  Precision: the matrix unit cuts what it adds
 // two bits below the accumulator's last one, towards zero, which biases a sum that all six products go into (512
 // channels, 3x3: 6.3e-7 of the result in 2-norm, mean -1e-7, against 4.4e-7 of the fp32 unit).  So h*h has an
 // accumulator of its own and the five small products share another one, 2^-8 of its size, added at the end: 1.7e-7.
 // Sums of one sign are no worse off: 4608 products of magnitudes, 512 -> 512 at 28x28, N = 8: 1.8e-7, mean -7e-10 of the
-// result (the fp32 unit: 3.6e-7); a bank that averages: 1.7e-7 (4.4e-7).
+// result (the fp32 unit: 3.6e-7); a bank that averages: 1.7e-7 (4.4e-7).  Sums of one to three products are the less exact ones here (up to 1.05
+// times the 2-norm error of one rounding each, a single product up to 1.5 times the largest): splits() in api.hip keeps such filters out.
 //
 // How it is mapped (numbering of pixels, panels and stripes as in contract.hip):
 //   * output channels are the rows of the product, output pixels its columns.  A work-group owns 32*MW channels and

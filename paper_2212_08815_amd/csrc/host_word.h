@@ -52,8 +52,9 @@ public:
     // the number, which is not negative, as soon as a kernel on `st` has written it (store_host): what follows that kernel on the stream
     // need not be done, and the wait is over 4 to 8 us before a wait for the stream would be.  Where the stream has more than a
     // millisecond to do first, and where there is no word, the stream is waited for; from: where the device has the number as well (NULL: it
-    // is not wanted).  A negative number: the stream's work is done and there is none
-    hipError_t wait(const int *from, hipStream_t st, int *out)
+    // is not wanted).  A negative number: the stream's work is done and there is none.  second: receives the int behind the number, which is
+    // written with it or before it
+    hipError_t wait(const int *from, hipStream_t st, int *out, int *second = nullptr)
     {
         if (word) {
             const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
@@ -66,13 +67,16 @@ public:
             if (*out != kNone) {
                 std::atomic_thread_fence(std::memory_order_acquire);
                 in_flight = false;
+                if (second) *second = const_cast<volatile int *>(word)[1];
                 return hipSuccess;
             }
         }
         hipError_t e = word || !from ? hipSuccess : hipMemcpyAsync(out, from, sizeof(int), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess && !word && from && second) e = hipMemcpyAsync(second, from + 1, sizeof(int), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
         if (word) *out = *const_cast<volatile int *>(word);
+        if (word && second) *second = const_cast<volatile int *>(word)[1];
         // (the stream is done and no kernel has written it: none of its launches counted to their end.  Neither the word nor the counters
         // of its slot serve another call, and the caller finds a negative number)
         in_flight = word && *out == kNone;

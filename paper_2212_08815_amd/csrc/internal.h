@@ -126,9 +126,10 @@ struct fscnn_filter {
     int device;
     int K, C, R, S;
     long long nnz;
-    int *rowptr;    // device [K+1]; owns an allocation
+    int *rowptr;    // device [K+1], `fewest` behind them; owns an allocation
     uint32_t *idx;  // device [nnz]; owns an allocation
     float *val;     // device [nnz], behind the indices
+    int fewest = 0;                           // stored values of the filter that stores the fewest, of those that store any
     size_t rowptr_bytes = 0, idx_bytes = 0;   // of the allocations
     std::atomic<bool> in_order{true};         // no call has used the handle on another stream than the default one
     std::mutex mu;
@@ -193,12 +194,13 @@ struct fscnn_dense {
 namespace fscnn {
 
 // ---- compress.hip
-// cnt: K + scan_tmp_elems(K) ints; rowptr: K + 1.  slot: HostWord::slot() of the word `host`, which receives the number of stored values
+// cnt: K + scan_tmp_elems(K) ints; rowptr: K + 2, the last one for the stored values of the filter that stores the fewest, of those that store
+// any (INT_MAX: none does).  slot: HostWord::slot() of the word `host`, which receives the number of stored values, and that one behind it
 hipError_t launch_filter_count(const float *w, int K, long long row, int *cnt, int *rowptr, int slot, int *host, hipStream_t st);
 // out[0..n] = exclusive scan of in[0..n-1] (out[n] = total); tmp: scan_tmp_elems(n) ints of scratch; host: receives the total as
-// well (pinned memory), or NULL
+// well (pinned memory), or NULL.  fewest: out[n + 1] and the int behind *host receive the smallest of in[] above 0 (INT_MAX: none is)
 long long scan_tmp_elems(long long n);
-hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, hipStream_t st);
+hipError_t launch_exclusive_scan(const int *in, int *out, long long n, int *tmp, int *host, bool fewest, hipStream_t st);
 // slot, host: of a word that receives 0 when idx and val are there for every stream; -1: none does
 hipError_t launch_filter_pack(const float *w, int K, long long row, const int *rowptr,
                               uint32_t *idx, float *val, int slot, int *host, hipStream_t st);

@@ -461,7 +461,7 @@ hipError_t launch_reorder(bool tensor, const int *rowptr, const uint32_t *idx, c
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_exclusive_scan(cnt, tptr, n_buckets, ws + l.scan, nullptr, st);
+    e = launch_exclusive_scan(cnt, tptr, n_buckets, ws + l.scan, nullptr, false, st);
     if (e != hipSuccess || nnz == 0) return e;
     hipLaunchKernelGGL(reorder_cursor_kernel, dim3(blocks_for(n_buckets)), dim3(kBlock), 0, st, tptr,
                        n_buckets, cursor);
