@@ -14,19 +14,13 @@ namespace fscnn {
 constexpr int kArriveWays = 16, kCounterInts = (kArriveWays + 1) * 32;
 
 // One thread of work-group `group` of `groups`, behind a barrier that all its stores were waited for in front of; true for the last one, and
-// then all counters are zero for whoever has them next.  mem.add() counts and returns what was there, mem.clear() stores a zero that
-// may take its time, mem.wait() returns when this thread's stores are done.
+// then all counters are zero for whoever has them next: mem.count(c, most) adds one to *c, or makes it zero where it is `most`, and
+// returns what was there, all in one operation.  (A zero stored by the last one of a way has to be waited for before it counts in
+// front: 1 us of a bank's three launches.)
 template <class Mem> FSCNN_DEVICE inline bool arrive(const Mem &mem, int *counter, int groups, int group)
 {
-    auto count = [&](int *c, int all) {
-        if (mem.add(c) != all - 1) return false;
-        mem.clear(c);
-        mem.wait();   // (of all these last ones, before the one behind them can be told: another launch may count here next)
-        return true;
-    };
-    const int way = group % kArriveWays;
-    return count(counter + (way + 1) * 32, (groups - way + kArriveWays - 1) / kArriveWays) &&
-           count(counter, groups < kArriveWays ? groups : kArriveWays);
+    const int way = group % kArriveWays, of_way = (groups - way + kArriveWays - 1) / kArriveWays, ways = groups < kArriveWays ? groups : kArriveWays;
+    return mem.count(counter + (way + 1) * 32, of_way - 1) == of_way - 1 && mem.count(counter, ways - 1) == ways - 1;
 }
 
 }  // namespace fscnn

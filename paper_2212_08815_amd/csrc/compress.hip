@@ -21,14 +21,12 @@ constexpr int kBlock = 256;
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
 // Stores that reach the memory that the XCDs' caches do not keep apart, and the last of a launch's work-groups to have made its own telling the
-// host so: every stream finds them from there on.  (A wait for the stream is over 4 to 8 us later.)  The counter is left at zero.
+// host so: every stream finds them from there on.  (A wait for the stream is over 4 to 8 us later.)
 template <class T> __device__ inline void store_through(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // a wait for this wave's stores that the compiler moves nothing across either
 __device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 struct DeviceMem {
-    __device__ int add(int *p) const { return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    __device__ void clear(int *p) const { store_through(p, 0); }
-    __device__ void wait() const { wait_stores(); }
+    __device__ int count(int *p, int most) const { return (int)atomicInc(reinterpret_cast<unsigned *>(p), (unsigned)most); }
 };
 __device__ inline bool arrived_last(int *counter) { return arrive(DeviceMem(), counter, (int)gridDim.x, (int)blockIdx.x); }
 // a number for the host that waits for it

@@ -1,5 +1,6 @@
-"""The counters by which the last work-group of a launch tells the host that everything is there (csrc/arrival.h), on the CPU with a memory
-whose plain stores take effect as late as they may: whoever hears of it may hand the counters to another launch."""
+"""The counters by which the last work-group of a launch tells the host that everything is there (csrc/arrival.h), on the CPU: the last one
+alone is told, and the counters are zero by then without a store that could still be on its way, for whoever hears of it may hand them
+to another launch."""
 import os
 import subprocess
 
@@ -13,11 +14,8 @@ PROGRAM = r"""
 #include <vector>
 using namespace fscnn;
 static int counters[kCounterInts];
-struct Late {                                // a work-group's stores, done when it waits or when its launch ends
-    mutable std::vector<int *> pending;
-    int add(int *p) const { return (*p)++; }
-    void clear(int *p) const { pending.push_back(p); }
-    void wait() const { for (int *p : pending) *p = 0; pending.clear(); }
+struct Mem {
+    int count(int *p, int most) const { const int was = *p; *p = was >= most ? 0 : was + 1; return was; }
 };
 int main()
 {
@@ -27,10 +25,9 @@ int main()
             std::vector<int> order(groups);
             for (int i = 0; i < groups; ++i) order[i] = i;
             std::shuffle(order.begin(), order.end(), rng);
-            std::vector<Late> of(groups);
             int told = 0;
             for (int i = 0; i < groups; ++i)
-                if (arrive(of[i], counters, groups, order[i])) {
+                if (arrive(Mem(), counters, groups, order[i])) {
                     ++told;
                     if (i != groups - 1) { std::printf("%d groups: told after %d\n", groups, i + 1); return 1; }
                 }
