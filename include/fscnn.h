@@ -92,7 +92,8 @@ fscnn_status_t fscnn_filter_export(const fscnn_filter_t *f, int *rowptr_host,
  * Allocates device memory, launches on `stream` and synchronises it once.  Optional:
  * fscnn_conv2d_sparse_filter builds the plan on first use; after that (or after this
  * call) convolution calls served by the same kernel configuration allocate nothing and do
- * not synchronise.  `variant` selects a kernel configuration (0 = automatic choice; see
+ * not synchronise.  Calls that the kernel for 1x1 filters serves (fscnn_sf_serves) need no plan, and none is made;
+ * emitting calls, which it does not serve, make theirs on first use.  `variant` selects a kernel configuration (0 = automatic choice; see
  * fscnn_sf_variant_count).  The automatic choice depends on the tensor layouts and on the merged
  * pool: this call prepares for NCHW tensors without pooling, fscnn_filter_prepare_ex for the call
  * it is told about. */

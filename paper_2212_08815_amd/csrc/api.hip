@@ -478,20 +478,22 @@ bool pointwise(const fscnn_filter_t *f, int N, int H, int W, bool n4, bool contr
            pointwise_us(N, f->C, H, W, f->K, n4, f->nnz) < 0.9 * other_us;
 }
 
+// The plan of `variant` if it is there
+SfPlan *made_plan(fscnn_filter_t *f, int variant)
+{
+    std::lock_guard<std::mutex> lock(f->mu);
+    for (SfPlan *p : f->plans)
+        if (p->variant == variant) return p;
+    return nullptr;
+}
+
 // The plan of a contraction (kContractPlan, kSplitPlan) that is to serve an automatic call, NULL where it cannot be made now: no room for
 // the bank as a dense array, or a capture on the stream (building it allocates and waits).  The call then goes to
 // the gather configuration or the direct kernel, which need none of that or fail for reasons of their own.
 fscnn_status_t contract_plan(fscnn_filter_t *f, int variant, hipStream_t st, SfPlan **out)
 {
-    *out = nullptr;
-    {
-        std::lock_guard<std::mutex> lock(f->mu);
-        for (SfPlan *p : f->plans)
-            if (p->variant == variant) {
-                *out = p;
-                return FSCNN_OK;
-            }
-    }
+    *out = made_plan(f, variant);
+    if (*out) return FSCNN_OK;
     if (capturing(st)) return FSCNN_OK;
     const fscnn_status_t s = get_plan(f, variant, st, out);
     if (s != FSCNN_OK) *out = nullptr;
@@ -733,7 +735,11 @@ fscnn_status_t fscnn_filter_prepare_ex(fscnn_filter_t *f, int N, int H, int W, i
     if (s != FSCNN_OK) return s;
     if ((in4 || out4 || pool) && r.variant < 0) return FSCNN_ERR_UNSUPPORTED;
     if (r.variant > 0 && !sf_variant_has_layout(r.variant, in4, out4, pool)) return FSCNN_ERR_UNSUPPORTED;
-    if (r.pointwise) return FSCNN_OK;
+    if (r.pointwise) {
+        int dev;
+        s = have_device(&dev);
+        return s == FSCNN_OK && dev != f->device ? FSCNN_ERR_MISMATCH : s;
+    }
     if (stream) f->in_order = false;
     SfPlan *p = nullptr;
     if (r.split) s = contract_plan(f, kSplitPlan, (hipStream_t)stream, &p);
@@ -1007,6 +1013,12 @@ static fscnn_status_t conv_sf_common(fscnn_filter_t *f, const float *x_dev, int 
         const int *wflag = r.variant < 0 ? reinterpret_cast<const int *>(p->packed + contract_packed_elems(f->K, f->C, f->R * f->S)) : nullptr;
         FSCNN_HIP(launch_contract_dense(x_dev, p->packed, wflag, f->rowptr, f->idx, f->val, N, C, H, W, f->K, f->R, f->S,
                                         Ho, Wo, sh, sw, ph, pw, bias_dev, relu, y_dev, r.pick, st));
+        return FSCNN_OK;
+    }
+    // (the 1x1 kernel is what prepares nothing for the geometry, so an emitting call may find no plan in a capture, which cannot make one)
+    if (emit_cnt && f->R == 1 && f->S == 1 && sh == 1 && sw == 1 && Ho == H && Wo == W && pointwise_serves(N, C, H, W, f->K, false) &&
+        !made_plan(f, r.variant) && capturing(st)) {
+        FSCNN_HIP(launch_pointwise(f->rowptr, f->idx, f->val, x_dev, N, C, H, W, f->K, false, bias_dev, relu, y_dev, st));
         return FSCNN_OK;
     }
     s = get_plan(f, r.variant, st, &p);

@@ -86,6 +86,31 @@ def test_values_that_are_not_finite(F):
     assert np.array_equal(np.isfinite(got), ~met) and np.array_equal(got[~met], want[~met]) and met.any()
 
 
+def test_emitting_call_captured_after_prepare(F):
+    """(The 1x1 kernel prepares no plan, and it does not serve emitting calls that can make one.)"""
+    n, c, k, h, w = 2, 256, 128, 22, 21
+    x = dev(np.random.default_rng(4).integers(-3, 4, (n, c, h, w)).astype(np.float32))
+    f1, wt = F.filter_compress(dev(bank(k, c, True, 1))), bank(k, c, True)
+    want = torch.nn.functional.conv2d(x.cpu(), torch.from_numpy(wt)).relu()
+    into, f = F.conv2d_sparse_filter_emit(f1, x, relu=True), F.filter_compress(dev(wt))
+    assert served(F, f, n, h, w, False)
+    F.filter_prepare(f, n, h, w)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        F.conv2d_sparse_filter_emit(f, x, relu=True, into=into)
+    for _ in range(3):
+        F.conv2d_sparse_filter_emit(f1, x, relu=True, into=into)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        into._nnz = None
+        prow, cidx, val = F.input_export(into)
+        got = np.zeros((n * h * w, k), np.float32)
+        got[np.repeat(np.arange(n * h * w), np.diff(prow)), cidx] = val
+        assert np.array_equal(got.reshape(n, h, w, k).transpose(0, 3, 1, 2), want.numpy())
+
+
 @pytest.mark.parametrize("n4", [False, True])
 def test_captured_without_a_plan(F, n4):
     """(What would serve these calls otherwise builds a plan, which a capture refuses.)"""
