@@ -72,7 +72,9 @@ fscnn_status_t fscnn_conv2d_out_shape(int H, int W, int R, int S, int stride_h, 
  * w_dev: dense K x C x R x S fp32.  The handle holds, per output channel k, the entries
  * with w != 0.0f (-0.0 dropped, NaN/denormals kept, values copied bit for bit) in ascending
  * flat index (c*R + r)*S + s, i.e. sorted by input channel first.  Runs its kernels on
- * `stream` and synchronises it once (the nonzero count sizes the buffers).
+ * `stream` and waits for what they write, not for the stream: for the nonzero count, which sizes the buffers, and for
+ * the entries.  When it returns w_dev may be overwritten or freed and the handle used on any stream; the last launch's
+ * end may still be on `stream`, which need not be idle.
  * K*C*R*S must be < 2^31.  *out is set only on FSCNN_OK. */
 fscnn_status_t fscnn_filter_compress(const float *w_dev, int K, int C, int R, int S,
                                      void *stream, fscnn_filter_t **out);
@@ -89,7 +91,8 @@ fscnn_status_t fscnn_filter_export(const fscnn_filter_t *f, int *rowptr_host,
 /* Builds (once) the device-side plan the convolution kernel streams for this geometry:
  * the nonzeros regrouped by (output-channel group, wave, input-channel chunk, channel slot)
  * with each (c,r,s) packed into the byte offset of that tap inside the LDS input tile.
- * Allocates device memory, launches on `stream` and synchronises it once.  Optional:
+ * Allocates device memory, launches on `stream` and waits until the plan is written (as fscnn_filter_compress does:
+ * any stream may use it then, `stream` need not be idle).  Optional:
  * fscnn_conv2d_sparse_filter builds the plan on first use; after that (or after this
  * call) convolution calls served by the same kernel configuration allocate nothing and do
  * not synchronise.  Calls that the kernel for 1x1 filters serves (fscnn_sf_serves) need no plan, and none is made;

@@ -1110,7 +1110,7 @@ fscnn_status_t fscnn_conv2d_sparse_filter(fscnn_filter_t *f, const float *x_dev,
                                         0, stream);
 }
 
-// Dense N x C x H x W activations -> compressed handle.  Synchronises st once, for the number of stored
+// Dense N x C x H x W activations -> compressed handle.  Waits once, for the number of stored
 // values.  Up to kWholeBytes of indices and values, were every value stored, are allocated with the
 // pointers before anything runs (and as much again for the dense form, input_dense_from()), and the passes follow each other without the host; beyond that the
 // number of stored values sizes a second allocation (making and releasing one takes 50 us, more than

@@ -7,7 +7,8 @@
 // loads, eight at a time, so that eight loads are in flight.  Four partial sums per output, added at the end: shorter chains of roundings
 // than one sum in the order of the entries.  Work-groups of one pixel block run next to each other on one XCD and find its planes in the L2.
 // What bounds it: few images, two round trips to memory behind a launch; many, the 64 bytes a clock that a CU takes from its
-// L1 (4 bytes per multiply-add) or the tensors' way from memory.  Nothing is kept for it: no plan.
+// L1 (4 bytes per multiply-add; 35 of them reached by 512 -> 256 at 26x26, N = 8, 5 % stored, N4, 11.2 us) or the tensors' way from and to
+// memory (225 -> 741 at 79x146, N = 9, 1 %, N4: 535 MB in 221 us, 17 bytes a clock from the L1).  Nothing is kept for it: no plan.
 // 5 % stored, us before (contracted in fp32 or gathered) and so: 256 -> 128 at 44x44, N = 1: 11.4, 5.4; 1024 -> 512 at 11x11, N = 1: 20.2, 6.7;
 // 512 -> 256 at 8x8, N = 18, 16 % stored, N4: 17.9, 10.8; 225 -> 741 at 79x146, N = 9, 1 %, N4: 471, 236.  At 52x52 and N = 32 the planes' way
 // through the L1 makes it the slower one (256 -> 128: 33 gathered, 60): pointwise() in api.hip draws the line.

@@ -70,3 +70,25 @@ def test_a_word_that_nothing_wrote_is_no_number_and_not_reused(tmp_path):
                     "-I", os.path.join(ROOT, "paper_2212_08815_amd", "csrc"), str(src), "-o", str(exe), "-lpthread"], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+SECOND = PROGRAM[:PROGRAM.index("int main()")] + r"""
+int main()
+{
+    int out = 0, few = 0, on_device[2] = {7, 3};
+    HostWord w;
+    if (int *p = w.hand_out()) { p[0] = 41; p[1] = 5; }
+    CHECK(w.wait(on_device, nullptr, &out, &few) == hipSuccess && out == (refuse ? 7 : 41) && few == (refuse ? 3 : 5) && copies == (refuse ? 2 : 0));
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("refuse", [False, True])
+def test_the_number_behind_the_word(tmp_path, refuse):
+    src, exe = tmp_path / "second.cpp", tmp_path / "second"
+    src.write_text(SECOND.replace("REFUSE", "true" if refuse else "false"))
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    "-I", os.path.join(ROOT, "paper_2212_08815_amd", "csrc"), str(src), "-o", str(exe), "-lpthread"], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
