@@ -423,14 +423,15 @@ fscnn_status_t resolve_variant(const fscnn_filter_t *f, int N, int H, int W, int
 // What the direct kernel takes, for the choice between it and the contractions.  Up to 12 entries a filter, and below 16 where up to 8 channels
 // leave the contraction in fp32 one chain as well, its sums are as exact as that one's (2-norm against 64 bits 0.95 to 1.02 times, the mean of
 // each of a dozen groups of 105 random layers of 3x3 to 7x7) and its time decides (1 -> 300 at 14x9, stride 3, N = 2: 9.2 us contracted, 6.8
-// direct; 40 -> 300 5x5 at 16x16, N = 1, 1 % stored: 13.8, 10.1).  Beyond, its chains of roundings show (1.05 to 1.9 times the error of the contraction in
+// direct; 40 -> 300 5x5 at 16x16, N = 1, 1 % stored: 13.8, 10.1), a quarter ahead for what the estimate is off (12 -> 192 5x5 at 12x12, N = 24,
+// 1.5 % stored: estimated 22 us, 30 measured, 22.8 contracted).  Beyond, its chains of roundings show (1.05 to 1.9 times the error of the contraction in
 // fp32, 2 to 4 times that of the one in parts): there the contractions serve what was faster so than with one row a thread, though four
 // rows a thread take about half of that (21 -> 38 5x5 at 184x189, N = 30, 3 %: estimated 500 us, 640 in parts).
 double direct_us(const fscnn_filter_t *f, int N, int Ho, int Wo)
 {
-    if (f->R * f->S >= 9 && f->nnz <= (f->C <= 8 ? 16LL * f->K - 1 : 12LL * f->K)) return sf_direct_us(N, f->K, Ho, Wo, f->nnz);
-    const double waves = (double)N * f->K * ((Wo + 63) / 64) * ((Ho + 3) / 4) * 4;
-    return 9.7 + (double)f->nnz / f->K * (0.132 + 7.48e-5 * waves);
+    const double waves = (double)N * f->K * ((Wo + 63) / 64) * ((Ho + 3) / 4) * 4, one_row = 9.7 + (double)f->nnz / f->K * (0.132 + 7.48e-5 * waves);
+    const bool exact = f->R * f->S >= 9 && f->nnz <= (f->C <= 8 ? 16LL * f->K - 1 : 12LL * f->K);
+    return exact ? std::min(1.25 * sf_direct_us(N, f->K, Ho, Wo, f->nnz), one_row) : one_row;
 }
 
 // Whether an automatic call is served by the contraction on the matrix cores instead of the resolved

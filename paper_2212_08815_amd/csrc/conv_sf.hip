@@ -894,8 +894,9 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
 // for 256 outputs, and their loads are in flight together.  Every output is one chain in the order of the entries.  5 -> 82 5x5 at 215x140,
 // N = 26, 4 % stored: 803 us with one output per thread (345 000 work-groups), 288 so; 10 -> 504 at 128x128, N = 1, 6 %: 193, 95.  Where there
 // are few outputs, one a thread is the faster (64 -> 64 at 7x7, N = 1: 7.7 us, 10.9 with four).  SKIP: one output a thread, and a lane whose
-// tap lies outside the image skips it: the faster way where many waves of few rows fill the CUs (200 -> 512 at 7x7, N = 2: 19.7 us, 18.8 so;
-// 31 -> 136 at 13x11, stride 2, N = 24: 20.4, 18.3) and the slower one where a wave's chain of entries is all there is (64 -> 64: 8.7).
+// tap lies outside the image skips it: the faster way from 8192 waves of few rows on, which fill the CUs (200 -> 512 at 7x7, N = 2: 19.7 us, 19.3 so;
+// 31 -> 136 at 13x11, stride 2, N = 24: 20.4, 18.3), and the slower one where a wave's chain of entries is all there is (64 -> 64: 8.7; 6 -> 261 at
+// 8x8, N = 2, 4176 waves: 6.8, 7.1).
 constexpr int kDirectRows = 8;
 template <int PER, bool SKIP> __global__ void __launch_bounds__(256)
 conv_sf_direct_kernel(const int *__restrict__ rowptr, const uint32_t *__restrict__ idx,
@@ -1530,9 +1531,9 @@ struct DirectShape {
     DirectShape(int N, int K, int Ho, int Wo)
     {
         const long long columns = (long long)((Wo + 63) / 64) * N;
-        const bool many = columns * K * ((Ho + 3) / 4) * 4 >= 4096;
-        per = Ho > 8 && many ? 4 : 1;
-        skip = per == 1 && many;
+        const long long rows = columns * K * ((Ho + 3) / 4) * 4;   // waves of one row a thread
+        per = Ho > 8 && rows >= 4096 ? 4 : 1;
+        skip = per == 1 && rows >= 8192;
         const long long tiles = columns * ((Ho + 4 * per - 1) / (4 * per));
         while (per > 1 && kper < kDirectRows && tiles * ((K + 2 * kper - 1) / (2 * kper)) >= 4096) kper *= 2;
         groups = tiles * ((K + kper - 1) / kper);
