@@ -894,8 +894,9 @@ conv_sf_tiled_kernel(const float *__restrict__ x, float *__restrict__ y,
 // for 256 outputs, and their loads are in flight together.  Every output is one chain in the order of the entries.  5 -> 82 5x5 at 215x140,
 // N = 26, 4 % stored: 803 us with one output per thread (345 000 work-groups), 288 so; 10 -> 504 at 128x128, N = 1, 6 %: 193, 95.  Where there
 // are few outputs, one a thread is the faster (64 -> 64 at 7x7, N = 1: 7.7 us, 10.9 with four).  SKIP: one output a thread, and a lane whose
-// tap lies outside the image skips it: the faster way from 8192 waves of few rows on, which fill the CUs (200 -> 512 at 7x7, N = 2: 19.7 us, 19.3 so;
-// 31 -> 136 at 13x11, stride 2, N = 24: 20.4, 18.3), and the slower one where a wave's chain of entries is all there is (64 -> 64: 8.7; 6 -> 261 at
+// tap lies outside the image skips it: the faster way from 8192 waves of few rows on, which fill the CUs (2 -> 326 at 10x19, stride 2, N = 30:
+// 42.0 us, 36.1 so; 31 -> 136 at 13x11, stride 2, N = 24: 20.4, 18.4; 200 -> 512 at 7x7, N = 2: 19.7, and 18.8 to 19.7 by where its code
+// lies), and the slower one where a wave's chain of entries is all there is (64 -> 64: 8.7; 6 -> 261 at
 // 8x8, N = 2, 4176 waves: 6.8, 7.1).
 constexpr int kDirectRows = 8;
 template <int PER, bool SKIP> __global__ void __launch_bounds__(256)
